@@ -182,12 +182,25 @@ BwdLayout bwd_layout(const LayerDims& L, modse_dtype dt) {
   return w;
 }
 
-int64_t tiles_bound(const LayerDims& L, int64_t rows_max, const TileShape& t, bool n_is_f) {
-  int64_t s = 0;
-  for (int e = 0; e < L.N; ++e) {
-    const int64_t nt = ((n_is_f ? L.f[e] : L.d) + t.bn - 1) / t.bn;
-    s += ((rows_max + t.bm - 1) / t.bm) * nt;
+// Upper bound of the number of tiles of a GEMM whose rows are the experts' token rows (top_k * T in all, at most T of
+// one expert) and whose columns are the hidden width (n_is_f) or d.  The row blocks number at most
+// floor(rows / bm) + 1 per expert together, and the bound gives as many of them as can be to the widest experts.
+int64_t tiles_bound(const LayerDims& L, const TileShape& t, bool n_is_f) {
+  int64_t s = 0, full = (int64_t)L.T * L.k / t.bm;
+  for (int i = 0; i < L.N; ++i) {
+    const int64_t nt = ((n_is_f ? L.f[L.order[i]] : L.d) + t.bn - 1) / t.bn;
+    const int64_t mine = std::min<int64_t>(full, (L.T + t.bm - 1) / t.bm - 1);
+    full -= mine;
+    s += (mine + 1) * nt;
   }
+  return s;
+}
+// tiles of the weight-gradient launch (their number does not depend on the routing)
+int64_t wgrad_tiles(const LayerDims& L, const TileShape& t) {
+  int64_t s = 0;
+  for (int e = 0; e < L.N; ++e)
+    s += 2 * (int64_t)((L.f[e] + t.bm - 1) / t.bm) * ((L.d + t.bn - 1) / t.bn) +
+         (int64_t)((L.d + t.bm - 1) / t.bm) * ((L.f[e] + t.bn - 1) / t.bn);
   return s;
 }
 
@@ -415,8 +428,8 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   }
   pa.up = reinterpret_cast<GemmPlan*>(wsb + w.plan_up);
   pa.down = reinterpret_cast<GemmPlan*>(wsb + w.plan_down);
-  pa.up_tile = gemm_tile_shape(dt, EPI_SWIGLU, T);
-  pa.down_tile = gemm_tile_shape(dt, EPI_STORE, T);
+  pa.up_tile = gemm_tile_shape(L, dt, EPI_SWIGLU);
+  pa.down_tile = gemm_tile_shape(L, dt, EPI_STORE);
   // inference on a decode-sized batch: split-K down-projection (the backward pass wants O itself)
   const int kchunk = saved ? 0 : splitk_chunk(L);
   pa.kchunk = kchunk;
@@ -426,21 +439,19 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   HIP_TRY(launch_permute(L, dt, x, R, RB, Xp, ext ? &G : nullptr, &pa, s));
   stamp.mark(MODSE_STAGE_PERMUTE);
 
-  const int skinny = T <= MODSE_SKINNY_TOKENS;
-  HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU, pa.up, 0, saved != nullptr, tiles_bound(L, T, pa.up_tile, true), s, -1,
-                              skinny));
+  HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU, pa.up_tile, pa.up, 0, saved != nullptr, tiles_bound(L, pa.up_tile, true), s));
   stamp.mark(MODSE_STAGE_UP);
   if (kchunk) {
     int64_t nprob = 0;
     for (int e = 0; e < L.N; ++e) nprob += (L.f[e] + kchunk - 1) / kchunk;
     const int64_t bound = nprob * ((T + pa.down_tile.bm - 1) / pa.down_tile.bm) * ((L.d + pa.down_tile.bn - 1) / pa.down_tile.bn);
-    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.down, 0, 0, bound, s, LAYOUT_TN, skinny));
+    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.down_tile, pa.down, 0, 0, bound, s, LAYOUT_TN));
     stamp.mark(MODSE_STAGE_DOWN);
     HIP_TRY(launch_combine_split(L, dt, pa.Opart, kchunk, R, y, s));
     stamp.mark(MODSE_STAGE_COMBINE);
     return MODSE_OK;
   }
-  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE, pa.down, 0, 0, tiles_bound(L, T, pa.down_tile, false), s, -1, skinny));
+  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE, pa.down_tile, pa.down, 0, 0, tiles_bound(L, pa.down_tile, false), s));
   stamp.mark(MODSE_STAGE_DOWN);
   HIP_TRY(launch_combine(L, dt, pa.O, R, y, s));
   stamp.mark(MODSE_STAGE_COMBINE);
@@ -494,20 +505,17 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   pa.dh = reinterpret_cast<GemmPlan*>(wsb + w.plan[0]);
   pa.dx = reinterpret_cast<GemmPlan*>(wsb + w.plan[1]);
   pa.wg = reinterpret_cast<GemmPlan*>(wsb + w.plan[2]);
-  pa.dh_tile = gemm_tile_shape(dt, EPI_SWIGLU_BWD, T);
-  pa.dx_tile = gemm_tile_shape(dt, EPI_STORE_DUALK, T);
-  pa.wg_tile = gemm_tile_shape(dt, EPI_STORE_F32, T);
+  pa.dh_tile = gemm_tile_shape(L, dt, EPI_SWIGLU_BWD);
+  pa.dx_tile = gemm_tile_shape(L, dt, EPI_STORE_DUALK);
+  pa.wg_tile = gemm_tile_shape(L, dt, EPI_STORE_F32);
   HIP_TRY(launch_plan_bwd(L, dt, R.counts, R.offsets, pa, s));
   stamp.mark(MODSE_STAGE_BWD_PREP);
 
-  HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU_BWD, pa.dh, 0, 0, tiles_bound(L, T, pa.dh_tile, true), s));
-  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx, 0, 0, tiles_bound(L, T, pa.dx_tile, false), s));
+  HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU_BWD, pa.dh_tile, pa.dh, 0, 0, tiles_bound(L, pa.dh_tile, true), s));
+  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, 0, 0, tiles_bound(L, pa.dx_tile, false), s));
   stamp.mark(MODSE_STAGE_BWD_DGRAD);
 
-  int64_t fmax = L.f[L.order[0]];
-  const int64_t wg13 = tiles_bound(L, fmax, pa.wg_tile, false);
-  const int64_t wg2 = tiles_bound(L, L.d, pa.wg_tile, true);
-  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg, accumulate, 0, 2 * wg13 + wg2, s));
+  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, accumulate, 0, wgrad_tiles(L, pa.wg_tile), s));
   stamp.mark(MODSE_STAGE_BWD_WGRAD);
 
   const BwdRouterBufs rb = {reinterpret_cast<float*>(wsb + w.dl), reinterpret_cast<float*>(wsb + w.du),

@@ -187,11 +187,11 @@ hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, 
 struct TileShape {
   int32_t bm, bn;
 };
-TileShape gemm_tile_shape(modse_dtype dt, int epilogue, int64_t T);
-// layout < 0: the layout that goes with the epilogue (see gemm.hip); skinny: the plan was made with the
-// decode-sized tile shapes of gemm_tile_shape (every problem has M <= MODSE_SKINNY_TOKENS)
-hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, const GemmPlan* plan, int accumulate, int save_pre,
-                               int64_t max_tiles, hipStream_t s, int layout = -1, int skinny = 0);
+TileShape gemm_tile_shape(const LayerDims& L, modse_dtype dt, int epilogue);
+// t: the tile shape that the plan was made with.  max_tiles: upper bound of the number of tiles.  layout < 0: the
+// layout that goes with the epilogue (see gemm.hip).
+hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int accumulate,
+                               int save_pre, int64_t max_tiles, hipStream_t s, int layout = -1);
 
 struct FwdPlanArgs {
   const void *Xp, *W1, *W3, *W2;

@@ -6,93 +6,17 @@
 // Operand layouts (GemmLayout): every tensor of the layer is used as it lies in memory.  The forward
 // GEMMs have both operands K-contiguous; the data-gradient GEMMs read the weights as [K, N]; the
 // weight-gradient GEMMs contract over tokens and read both activations as [K, M] and [K, N].
+#include <algorithm>
+
 #include "common.h"
 #include "gemm_bf16.h"
 #include "gemm_bf16_skinny.h"
+#include "gemm_block.h"
 #include "gemm_plan.h"
 #include "gemm_tiles.h"
 
 namespace {
 using namespace modse_gemm;
-
-// ------------------------------------------------------------------------------------------------
-// float32 path: plain FMA tiles (parity configuration; no throughput claim)
-// ------------------------------------------------------------------------------------------------
-template <int EPI, int LAYOUT>
-__global__ __launch_bounds__(256) void gg_f32_kernel(const GemmPlan* __restrict__ plan, int accumulate,
-                                                     int save_pre) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  constexpr int NB = (EPI == EPI_SWIGLU) ? 2 : 1;
-  constexpr bool A_T = (LAYOUT & 1) != 0, B_T = (LAYOUT & 2) != 0;
-  static_assert(!(B_T && NB == 2), "the two-matrix up-projection reads K-contiguous weights");
-  __shared__ float As[BK][BM + 4];
-  __shared__ float Bs[NB][BK][BN + 4];
-  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-  // K-contiguous operand: thread loads 4 consecutive k of row tid/4; [K, X] operand: 4 consecutive x of K row tid/16
-  const int lrow = tid / 4, lk = (tid % 4) * 4;
-  const int tk = tid / 16, tx4 = (tid % 16) * 4;
-  const int total = plan->tile_start[plan->n_prob];
-  for (int tile = first_tile_of_block(); tile < total; tile += gridDim.x) {
-    TileCoord tc;
-    if (!decode_tile(plan, tile, tc)) break;
-    const GemmProblem P = plan->prob[tc.p];
-    const int m0 = tc.mt * BM, n0 = tc.nt * BN;
-    float acc[NB][4][4];
-#pragma unroll
-    for (int q = 0; q < NB; ++q)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[q][i][j] = 0.f;
-    const int arow = min(m0 + lrow, P.M - 1), brow = min(n0 + lrow, P.N - 1);
-    const int acol = min(m0 + tx4, P.M - 4), bcol = min(n0 + tx4, P.N - 4);  // M, N are multiples of 4
-    const int npass = (EPI == EPI_STORE_DUALK) ? 2 : 1;
-    for (int pass = 0; pass < npass; ++pass) {
-      const float* A = static_cast<const float*>(pass ? P.A2 : P.A);
-      const float* B = static_cast<const float*>(pass ? P.B2 : P.B);
-      const float* B2 = static_cast<const float*>(P.B2);
-      for (int k0 = 0; k0 < P.K; k0 += BK) {
-        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-        f32x4 av, bv, b2v = zero;
-        if (A_T) av = k0 + tk < P.K ? *reinterpret_cast<const f32x4*>(A + (size_t)(k0 + tk) * P.lda + acol) : zero;
-        else av = *reinterpret_cast<const f32x4*>(A + (size_t)arow * P.lda + k0 + lk);  // K % 16 == 0 here
-        if (B_T) bv = k0 + tk < P.K ? *reinterpret_cast<const f32x4*>(B + (size_t)(k0 + tk) * P.ldb + bcol) : zero;
-        else bv = *reinterpret_cast<const f32x4*>(B + (size_t)brow * P.ldb + k0 + lk);
-        if (NB == 2) b2v = *reinterpret_cast<const f32x4*>(B2 + (size_t)brow * P.ldb + k0 + lk);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          if (A_T) As[tk][tx4 + i] = av[i];
-          else As[lk + i][lrow] = av[i];
-          if (B_T) Bs[0][tk][tx4 + i] = bv[i];
-          else Bs[0][lk + i][lrow] = bv[i];
-          if (NB == 2) Bs[NB - 1][lk + i][lrow] = b2v[i];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < BK; ++k) {
-          float a[4], b[NB][4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
-#pragma unroll
-          for (int q = 0; q < NB; ++q)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[q][j] = Bs[q][k][tx * 4 + j];
-#pragma unroll
-          for (int q = 0; q < NB; ++q)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-              for (int j = 0; j < 4; ++j) acc[q][i][j] = fmaf(a[i], b[q][j], acc[q][i][j]);
-        }
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      epilogue4<float, EPI>(P, m0 + ty * 4 + i, n0 + tx * 4, acc[0][i], acc[NB - 1][i], accumulate, save_pre);
-  }
-}
 
 // ------------------------------------------------------------------------------------------------
 // plan kernel of the backward GEMMs (single block): device-side counts -> problem tables.  (The forward plans
@@ -192,55 +116,89 @@ hipError_t run_bf16(const GemmPlan* plan, int accumulate, int save_pre, int64_t 
   return hipGetLastError();
 }
 
-template <int EPI, int LAYOUT>
-hipError_t run_f32(const GemmPlan* plan, int accumulate, int save_pre, int64_t max_tiles, hipStream_t s) {
-  int64_t grid = (int64_t)num_cus() * 8;
-  if (max_tiles < grid) grid = max_tiles;
-  if (grid < 1) grid = 1;
-  hipLaunchKernelGGL((gg_f32_kernel<EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan, accumulate, save_pre);
+// max_tiles: an upper bound of the tile list's length; one workgroup per tile
+template <typename T, int BM, int BN, int EPI, int LAYOUT>
+hipError_t run_block(const GemmPlan* plan, int accumulate, int save_pre, int64_t max_tiles, hipStream_t s) {
+  constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
+  const int64_t grid = (int64_t)align_up((size_t)std::max<int64_t>(max_tiles, 1), NUM_XCD * TILE_RUN);
+  if constexpr (std::is_same_v<T, float>)
+    hipLaunchKernelGGL((gg_f32_kernel<BM, BN, NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan, accumulate,
+                       save_pre);
+  else
+    hipLaunchKernelGGL((gg_bf16_block_kernel<BM, BN, NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan,
+                       accumulate, save_pre);
   return hipGetLastError();
+}
+
+// EPI_SWIGLU: `bn` columns of each of the two matrices
+template <typename T, int EPI, int LAYOUT>
+hipError_t run_block_tile(TileShape t, const GemmPlan* plan, int accumulate, int save_pre, int64_t max_tiles, hipStream_t s) {
+  if (t.bm == 128) return run_block<T, 128, EPI == EPI_SWIGLU ? 64 : 128, EPI, LAYOUT>(plan, accumulate, save_pre, max_tiles, s);
+  return run_block<T, 64, 64, EPI, LAYOUT>(plan, accumulate, save_pre, max_tiles, s);
 }
 
 }  // namespace
 
+namespace {
+// tiles of an average batch: every expert has T * k / N rows (of C, or of the contraction for weight gradients)
+int64_t expected_tiles(const LayerDims& L, int epilogue, int bm, int bn) {
+  const int64_t rows = ((int64_t)L.T * L.k + L.N - 1) / L.N, mt = (rows + bm - 1) / bm, nt_d = (L.d + bn - 1) / bn;
+  int64_t n = 0;
+  for (int e = 0; e < L.N; ++e) {
+    const int64_t nt_f = (L.f[e] + bn - 1) / bn;
+    switch (epilogue) {
+      case EPI_SWIGLU:
+      case EPI_SWIGLU_BWD: n += mt * nt_f; break;
+      case EPI_STORE_F32: n += 2 * ((L.f[e] + bm - 1) / bm) * nt_d + ((L.d + bm - 1) / bm) * nt_f; break;
+      default: n += mt * nt_d;
+    }
+  }
+  return n;
+}
+}  // namespace
+
 // Forward GEMMs of a decode-sized batch (no expert can have more than MODSE_SKINNY_TOKENS rows) use tiles
 // 64 rows high and 8 waves wide: 8/9 of what a stage loads is weights instead of half.
-TileShape gemm_tile_shape(modse_dtype dt, int epilogue, int64_t T) {
-  if (dt == MODSE_F32) return {64, 64};
-  const bool skinny = T <= MODSE_SKINNY_TOKENS && (epilogue == EPI_SWIGLU || epilogue == EPI_STORE);
+// float32: 128 x 128 tiles (a wave then needs four LDS reads per sixteen matrix instructions) unless they are too few to
+// give every CU two, where 64 x 64 tiles spread the work.
+TileShape gemm_tile_shape(const LayerDims& L, modse_dtype dt, int epilogue) {
+  if (dt == MODSE_F32) {
+    const TileShape t = epilogue == EPI_SWIGLU ? TileShape{128, 64} : TileShape{128, 128};
+    return expected_tiles(L, epilogue, t.bm, t.bn) >= 2 * num_cus() ? t : TileShape{64, 64};
+  }
+  const bool skinny = L.T <= MODSE_SKINNY_TOKENS && (epilogue == EPI_SWIGLU || epilogue == EPI_STORE);
   if (epilogue == EPI_SWIGLU) return skinny ? TileShape{64, 256} : TileShape{256, 128};
   return skinny ? TileShape{64, 512} : TileShape{256, 256};
 }
 
 // The epilogue fixes the operand layout: forward GEMMs are K-contiguous on both sides, data gradients read
-// the weights as [K, N], weight gradients read both activations token-major.
-hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, const GemmPlan* plan, int accumulate, int save_pre,
-                               int64_t max_tiles, hipStream_t s, int layout, int skinny) {
-  if (epilogue == EPI_STORE_F32 && layout == LAYOUT_TN) {  // split-K partial sums of a forward GEMM
-    if (dt == MODSE_F32) return run_f32<EPI_STORE_F32, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
-    if (skinny) return run_bf16<64, 512, 1, 1, 8, EPI_STORE_F32, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
-    return run_bf16<256, 256, 1, 4, 2, EPI_STORE_F32, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
-  }
-  if (dt == MODSE_BF16 && skinny) {
-    if (epilogue == EPI_SWIGLU)
-      return run_bf16<64, 256, 2, 1, 8, EPI_SWIGLU, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
-    if (epilogue == EPI_STORE)
-      return run_bf16<64, 512, 1, 1, 8, EPI_STORE, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
-  }
+// the weights as [K, N], weight gradients read both activations token-major; split-K partial sums of a forward GEMM
+// (EPI_STORE_F32 with LAYOUT_TN) are the one exception.
+hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int accumulate,
+                               int save_pre, int64_t max_tiles, hipStream_t s, int layout) {
+  const bool split_k = epilogue == EPI_STORE_F32 && layout == LAYOUT_TN;
   if (dt == MODSE_F32) {
+    if (split_k) return run_block_tile<float, EPI_STORE_F32, LAYOUT_TN>(t, plan, accumulate, save_pre, max_tiles, s);
     switch (epilogue) {
-      case EPI_STORE: return run_f32<EPI_STORE, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
-      case EPI_SWIGLU: return run_f32<EPI_SWIGLU, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
-      case EPI_SWIGLU_BWD: return run_f32<EPI_SWIGLU_BWD, LAYOUT_B_KN>(plan, accumulate, save_pre, max_tiles, s);
-      case EPI_STORE_DUALK: return run_f32<EPI_STORE_DUALK, LAYOUT_B_KN>(plan, accumulate, save_pre, max_tiles, s);
-      case EPI_STORE_F32: return run_f32<EPI_STORE_F32, LAYOUT_AB_K>(plan, accumulate, save_pre, max_tiles, s);
+      case EPI_STORE: return run_block_tile<float, EPI_STORE, LAYOUT_TN>(t, plan, accumulate, save_pre, max_tiles, s);
+      case EPI_SWIGLU: return run_block_tile<float, EPI_SWIGLU, LAYOUT_TN>(t, plan, accumulate, save_pre, max_tiles, s);
+      case EPI_SWIGLU_BWD: return run_block_tile<float, EPI_SWIGLU_BWD, LAYOUT_B_KN>(t, plan, accumulate, save_pre, max_tiles, s);
+      case EPI_STORE_DUALK: return run_block_tile<float, EPI_STORE_DUALK, LAYOUT_B_KN>(t, plan, accumulate, save_pre, max_tiles, s);
+      case EPI_STORE_F32: return run_block_tile<float, EPI_STORE_F32, LAYOUT_AB_K>(t, plan, accumulate, save_pre, max_tiles, s);
     }
     return hipErrorInvalidValue;
   }
+  const bool skinny = t.bm == 64;
+  if (split_k) {
+    if (skinny) return run_bf16<64, 512, 1, 1, 8, EPI_STORE_F32, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
+    return run_bf16<256, 256, 1, 4, 2, EPI_STORE_F32, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
+  }
   switch (epilogue) {
     case EPI_STORE:
+      if (skinny) return run_bf16<64, 512, 1, 1, 8, EPI_STORE, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
       return run_bf16<256, 256, 1, 4, 2, EPI_STORE, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
     case EPI_SWIGLU:
+      if (skinny) return run_bf16<64, 256, 2, 1, 8, EPI_SWIGLU, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
       return run_bf16<256, 128, 2, 4, 2, EPI_SWIGLU, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
     case EPI_SWIGLU_BWD:
       return run_bf16<256, 256, 1, 4, 2, EPI_SWIGLU_BWD, LAYOUT_B_KN>(plan, accumulate, save_pre, max_tiles, s);

@@ -1,0 +1,361 @@
+// Grouped GEMM with small tiles for gfx950: 128 x 128 or 64 x 64 tiles, one per workgroup of four waves, float32 and
+// bf16, every layout and epilogue of the layer.
+//
+// Where the 256 x 256 kernel of gemm_bf16.h wants tall problems (one workgroup per CU, a ring of five panels), this one
+// serves problems that do not fill such tiles: the workgroup is small enough (two LDS stages, 64 KiB for a 128 x 128
+// tile) that two of them share a CU, so one multiplies while the other waits at its barrier or stores its result, and
+// the tiles are numerous enough to go round.  The grid has one workgroup per tile; workgroups beyond the tile list
+// (its length is known on the device only) leave at once.
+//
+// An LDS row of a K-contiguous operand is 128 bytes whatever the element type: 64 bf16 or 32 float32 along K, which is
+// one K step.  The 16-byte chunk index of a row is XOR-ed with ((row >> 1) & 7), so that the lanes a 128-bit LDS read
+// serves together fall into different banks.  A lane of the upper half takes the odd chunk of a pair, one of the lower
+// half the even one.  For bf16 that is the operand layout of v_mfma_f32_32x32x16_bf16; for float32 the four values of
+// the chunk feed four v_mfma_f32_32x32x2_f32 (K index s of the even chunk with K index s of the odd one: the order of
+// the contraction is free as long as both operands agree).
+// An operand stored [K, X] keeps its memory order in LDS; bf16 fragments are read with ds_read_b64_tr_b16 (16-byte chunk
+// index XOR-ed so that the four K rows a read covers start in different banks), float32 ones with 32-bit reads: the
+// float32 matrix instruction takes 64 cycles, so LDS has time to spare.
+//
+// float32 is bound by the matrix pipe (157 TFLOP/s; a library product of 8192^3 reaches 153).  Measured in place of
+// vector-FMA tiles of 64 x 64 x 16: the five GEMMs of a training step at d = 1024, 4096 tokens, 8 experts of mean width
+// 2816 take 3.9 ms instead of 7.0 (60 -> 109 TFLOP/s); at d = 256, 512 tokens 66 us instead of 174.
+#pragma once
+#include "gemm_bf16.h"
+
+namespace modse_gemm {
+
+// Consecutive workgroups go to the 8 XCDs in turn.  Runs of TILE_RUN tiles (row blocks of the same weight columns come
+// first in the list) stay on one XCD, so that they read the weights through the same L2, and the runs are dealt out to
+// the XCDs in turn: the list is sorted by falling cost, and contiguous eighths of it would leave the last XCDs idle.
+constexpr int TILE_RUN = 8;
+__device__ inline int tile_of_workgroup(int b) {
+  const int i = b / NUM_XCD;
+  return ((i / TILE_RUN) * NUM_XCD + b % NUM_XCD) * TILE_RUN + i % TILE_RUN;
+}
+
+// BN: columns of C per tile.  NB = 2: two B matrices that share A (the up-projection's W1 and W3), BN columns of each.
+template <typename T, int BM, int BN, int NB, int EPI, int LAYOUT>
+__device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int accumulate, int save_pre) {
+  constexpr int ES = sizeof(T), CE = 16 / ES, BK = 128 / ES;
+  constexpr bool A_T = (LAYOUT & 1) != 0, B_T = (LAYOUT & 2) != 0, F32 = ES == 4;
+  constexpr int BR = NB * BN;               // B rows of a stage
+  constexpr int STAGE = (BM + BR) * 128;
+  constexpr int UA = BM / 32, UB = BR / 32; // 1 KiB load units per wave and step
+  constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 32, NI = WN / 32;
+  static_assert(BM % 64 == 0 && BN % 64 == 0, "2 x 2 waves, wave tiles of 32 x 32 blocks");
+  static_assert(!(B_T && NB != 1), "a [K, N] operand is a single matrix");
+  static_assert(STAGE / 4 >= 4096, "epilogue: 4 KiB of a stage per wave");
+  __shared__ __attribute__((aligned(1024))) char stages[2 * STAGE];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int tile = tile_of_workgroup(blockIdx.x);
+  // the tile's problem: the last one that starts at or before it (every lane looks at one entry of the list)
+  const int n_prob = plan->n_prob;
+  if (tile >= plan->tile_start[n_prob]) return;
+  int p = -1;
+  for (int i0 = 0; i0 < n_prob; i0 += 64)
+    p += __popcll(__ballot(i0 + lane < n_prob && plan->tile_start[min(i0 + lane, n_prob)] <= tile));
+  p = uniform_int(p);
+  ProblemRegs P;
+  P.load(plan->prob + p);
+  const int M = P.M(), N = P.N(), K = P.K();
+  int m0, n0;
+  {
+    int mt, nt;
+    decode_local(tile - uniform_int(plan->tile_start[p]), P.mtiles(), P.ntiles(), P.magic_group(), P.magic_tail(), mt, nt);
+    m0 = mt * BM;
+    n0 = nt * BN;
+  }
+  const int nk = (K + BK - 1) / BK;
+  const int nsteps = (EPI == EPI_STORE_DUALK) ? 2 * nk : nk;
+  const uint32_t lds_base = __builtin_amdgcn_readfirstlane(lds_address(stages));
+
+  // ---- loads.  Which 16-byte chunk a lane fetches is chosen so that the data lands swizzled: unit u of a K-contiguous
+  // panel is rows 8u .. 8u+7; of a [K, X] panel 1024 / (X * ES) rows of K.
+  auto tr_swz = [](int k, int row_bytes) { return F32 ? 0 : row_bytes >= 256 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); };
+  // offset (bytes) of this lane's chunk of unit u from the tile's first element of the operand, and its K index
+  typedef std::conditional_t<F32, int64_t, uint32_t> off_t_;  // (bf16 matrices stay below 2^32 bytes, float32 ones need not)
+  auto chunk_offset = [&](bool tr, int X, int u, int x0, int rows, int ld, int& kfirst) -> off_t_ {
+    if (tr) {
+      const int rb = X * ES, byte = lane * 16;
+      const int k = u * (1024 / rb) + byte / rb;
+      const int c = ((byte % rb) >> 4) ^ tr_swz(k, rb);
+      kfirst = k;
+      return ((off_t_)k * ld + (min(x0 + c * CE, rows - CE) - x0)) * ES;  // columns past the end repeat the last chunk
+    }
+    const int r = u * 8 + (lane >> 3);
+    const int c = (lane & 7) ^ ((r >> 1) & 7);
+    kfirst = c * CE;
+    return ((off_t_)(min(x0 + r % X, rows - 1) - x0) * ld + c * CE) * ES;
+  };
+  off_t_ offa[UA], offb[UB];
+  int ka[UA], kb[UB];
+#pragma unroll
+  for (int i = 0; i < UA; ++i) offa[i] = chunk_offset(A_T, BM, wave * UA + i, m0, M, P.lda(), ka[i]);
+#pragma unroll
+  for (int i = 0; i < UB; ++i) offb[i] = chunk_offset(B_T, BN, wave * UB + i, n0, N, P.ldb(), kb[i]);
+  const size_t a_org = (A_T ? (size_t)m0 : (size_t)m0 * P.lda()) * ES;
+  const size_t b_org = (B_T ? (size_t)n0 : (size_t)n0 * P.ldb()) * ES;
+  const size_t a_step = A_T ? (size_t)128 * P.lda() : 128, b_step = B_T ? (size_t)128 * P.ldb() : 128;
+  const bool second = NB == 2 && wave * UB * 8 >= BN;  // this wave's B units belong to the second matrix
+  const char* sa = static_cast<const char*>(uniform_ptr(P.A() + a_org));
+  const char* sb = static_cast<const char*>(uniform_ptr((second ? P.B2() : P.B()) + b_org));
+  int kstep = 0, pass = 0;
+  auto issue = [&](int buf) {
+    const uint32_t da = lds_base + buf * STAGE + wave * UA * 1024, db = lds_base + buf * STAGE + BM * 128 + wave * UB * 1024;
+    auto fetch = [&](const char* s, off_t_ off, uint32_t dst) {
+      if constexpr (F32) dma_b128(s + off, dst);
+      else dma_b128_s(s, off, dst);
+    };
+    if ((kstep + 1) * BK <= K) {
+#pragma unroll
+      for (int i = 0; i < UA; ++i) fetch(sa, offa[i], da + i * 1024);
+#pragma unroll
+      for (int i = 0; i < UB; ++i) fetch(sb, offb[i], db + i * 1024);
+    } else {  // the last step of a pass: what lies beyond K reads zeros
+      const char* zero = reinterpret_cast<const char*>(g_zero_chunk);
+#pragma unroll
+      for (int i = 0; i < UA; ++i) dma_b128(kstep * BK + ka[i] < K ? sa + offa[i] : zero, da + i * 1024);
+#pragma unroll
+      for (int i = 0; i < UB; ++i) dma_b128(kstep * BK + kb[i] < K ? sb + offb[i] : zero, db + i * 1024);
+    }
+    sa += a_step;
+    sb += b_step;
+    if (EPI == EPI_STORE_DUALK && ++kstep == nk && pass == 0) {
+      pass = 1;
+      kstep = 0;
+      sa = static_cast<const char*>(uniform_ptr(P.A2() + a_org));
+      sb = static_cast<const char*>(uniform_ptr(P.B2() + b_org));
+    } else if (EPI != EPI_STORE_DUALK) {
+      ++kstep;
+    }
+  };
+
+  // ---- fragments: K slice kk (two chunks of every row)
+  typedef std::conditional_t<F32, f32x4, bf16x8> frag_t;
+  const int khalf = lane >> 5, lsw = (lane >> 1) & 7;
+  const int blk = lane >> 4, sl = lane & 15, kq = sl >> 2;
+  auto load_frag = [&](bool tr, const char* panel, int X, int row, int kk) -> frag_t {  // row: first of the 32 (or, [K, X], column)
+    if (!tr) return *reinterpret_cast<const frag_t*>(panel + (row + (lane & 31)) * 128 + (((kk * 2 + khalf) ^ lsw) << 4));
+    const int rb = X * ES;
+    if constexpr (F32) {
+      frag_t v;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) v[s] = *reinterpret_cast<const float*>(panel + (kk * 8 + khalf * 4 + s) * rb + (row + (lane & 31)) * 4);
+      return v;
+    } else {
+      // lane 16 blk + sl reads 8 bytes at K row kk*16 + (blk >> 1)*8 + h*4 + (sl >> 2), column row + (blk & 1)*16 +
+      // 4 (sl & 3) and receives four consecutive K of column row + (blk & 1)*16 + sl
+      typedef short s16x4 __attribute__((ext_vector_type(4)));
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
+      const int c16 = (row + (blk & 1) * 16) / 8 + ((sl & 3) >> 1);
+      const char* q = panel + (kk * 16 + (blk >> 1) * 8 + kq) * rb + ((c16 ^ tr_swz(kq, rb)) << 4) + (sl & 1) * 8;
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(q));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(q + 4 * rb));
+      const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      return __builtin_bit_cast(frag_t, v);
+    }
+  };
+  frag_t af[2][MI], bf[2][NB][NI];
+  auto load_frags = [&](const char* st, int kk, int set) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) af[set][i] = load_frag(A_T, st, BM, wm * WM + i * 32, kk);
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) bf[set][q][j] = load_frag(B_T, st + BM * 128, BN, q * BN + wn * WN + j * 32, kk);
+  };
+  f32x16 acc[NB][MI][NI];
+#pragma unroll
+  for (int q = 0; q < NB; ++q)
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[q][i][j][r] = 0.f;
+  // (the B fragment is the instruction's first operand: a lane's accumulator then holds four consecutive columns of C)
+  auto mfma_slice = [&](int set) {
+    if constexpr (F32) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+#pragma unroll
+          for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+              acc[q][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[set][q][j][s], af[set][i][s], acc[q][i][j], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+            acc[q][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[set][q][j], af[set][i], acc[q][i][j], 0, 0, 0);
+    }
+  };
+
+  if (nsteps > 0) issue(0);
+#pragma unroll 1
+  for (int g = 0; g < nsteps; ++g) {
+    // my loads of step g have landed and my LDS reads of step g-1 have returned; then everybody meets: the stage of
+    // step g may be read and the other one refilled
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    const char* st = stages + (g & 1) * STAGE;
+    load_frags(st, 0, 0);
+    if (g + 1 < nsteps) issue((g + 1) & 1);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      if (kk < 3) load_frags(st, kk + 1, (kk + 1) & 1);
+      mfma_slice(kk & 1);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- epilogue.  For register group r of block (i, j) the lane holds columns 8 r + 4 khalf .. + 3 of row lane & 31.
+  // A wave stages units of 32 rows x 128 bytes (64 for a 32-column bf16 tile) through LDS, so that global memory sees
+  // whole lines: written in accumulator order, read back row-wise.  The staging area is this wave's quarter of the
+  // stage that step nsteps - 1 did not use: nobody reads it any more.
+  typedef std::conditional_t<F32 || EPI == EPI_STORE_F32, float, bf16_t> out_t;
+  constexpr int OS = sizeof(out_t), UC = OS == 4 ? 32 : (WN < 64 ? WN : 64);  // columns of a unit
+  constexpr int CPR = UC * OS / 16, ITS = 32 * CPR / 64, NJU = WN / UC, JPU = UC / 32;
+  typedef std::conditional_t<OS == 4, f32x4, bf16x8> chunk_t;
+  char* const slot = stages + (nsteps & 1) * STAGE + wave * (STAGE / 4);
+  const int er = lane & 31, esw = (er >> 1) & 7;
+  const int ldc = P.ldc();
+  auto stage = [&](auto value) {  // value(jj, idx): element idx of the accumulator of the unit's block jj
+#pragma unroll
+    for (int jj = 0; jj < JPU; ++jj)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if constexpr (OS == 4) {
+          const f32x4 v = {value(jj, 4 * r), value(jj, 4 * r + 1), value(jj, 4 * r + 2), value(jj, 4 * r + 3)};
+          *reinterpret_cast<f32x4*>(slot + er * 128 + (((2 * r + khalf) ^ esw) << 4)) = v;
+        } else {
+          bf16x4 v;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = (bf16_t)value(jj, 4 * r + q);
+          *reinterpret_cast<bf16x4*>(slot + er * 128 + (((jj * 4 + r) ^ esw) << 4) + khalf * 8) = v;
+        }
+      }
+  };
+  auto row_of = [&](int it) { return it * (64 / CPR) + lane / CPR; };
+  auto chunk = [&](int it) -> chunk_t* {
+    const int rr = row_of(it);
+    return reinterpret_cast<chunk_t*>(slot + rr * 128 + (((lane % CPR) ^ ((rr >> 1) & 7)) << 4));
+  };
+  typedef __attribute__((address_space(1))) chunk_t global_chunk_t;
+  // element offset of this lane's chunk `it` of unit (i, ju) in C, or -1 outside the matrix
+  auto offset = [&](int i, int ju, int it) -> long {
+    const int m = m0 + wm * WM + i * 32 + row_of(it), n = n0 + wn * WN + ju * UC + (lane % CPR) * (16 / OS);
+    return (m < M && n < N) ? (long)m * ldc + n : -1;
+  };
+  auto at = [&](const void* base, long o) { return (global_chunk_t*)(uintptr_t)(static_cast<const out_t*>(base) + o); };
+  auto store_unit = [&](int i, int ju, void* C) {
+#pragma unroll
+    for (int it = 0; it < ITS; ++it) {
+      const chunk_t v = *chunk(it);
+      const long o = offset(i, ju, it);
+      if (o >= 0) *at(C, o) = v;
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    if (m0 + wm * WM + i * 32 >= M) break;
+#pragma unroll
+    for (int ju = 0; ju < NJU; ++ju) {
+      const int j0 = ju * JPU;
+      if constexpr (EPI == EPI_SWIGLU) {
+        stage([&](int jj, int x) {
+          const float a = acc[0][i][j0 + jj][x], b = acc[NB - 1][i][j0 + jj][x];
+          float h, pd, qd;
+          swiglu_terms(a, b, F32 ? 1.f / (1.f + __expf(-a)) : sigmoid_fast(a), h, pd, qd);
+          acc[0][i][j0 + jj][x] = pd;
+          acc[NB - 1][i][j0 + jj][x] = qd;
+          return h;
+        });
+        store_unit(i, ju, P.C());
+        if (save_pre) {
+          stage([&](int jj, int x) { return acc[0][i][j0 + jj][x]; });
+          store_unit(i, ju, P.C2());
+          stage([&](int jj, int x) { return acc[NB - 1][i][j0 + jj][x]; });
+          store_unit(i, ju, P.C3());
+        }
+      } else {
+        if constexpr (EPI == EPI_SWIGLU_BWD) {
+          // the saved terms dh/da and dh/db come in row-wise, are multiplied by dh in accumulator order where they lie
+          // in LDS, and leave row-wise
+          chunk_t e[2][ITS];
+#pragma unroll
+          for (int w = 0; w < 2; ++w)
+#pragma unroll
+            for (int it = 0; it < ITS; ++it) {
+              const long o = offset(i, ju, it);
+              e[w][it] = o >= 0 ? *at(w ? P.E2() : P.E1(), o) : chunk_t{};
+            }
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {
+#pragma unroll
+            for (int it = 0; it < ITS; ++it) *chunk(it) = e[w][it];
+#pragma unroll
+            for (int jj = 0; jj < JPU; ++jj)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                typedef std::conditional_t<OS == 4, f32x4, bf16x4> quad_t;
+                quad_t& v = *reinterpret_cast<quad_t*>(OS == 4 ? slot + er * 128 + (((2 * r + khalf) ^ esw) << 4)
+                                                               : slot + er * 128 + (((jj * 4 + r) ^ esw) << 4) + khalf * 8);
+                quad_t o = v;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) o[q] = (out_t)(acc[0][i][j0 + jj][4 * r + q] * (float)o[q]);
+                v = o;
+              }
+            store_unit(i, ju, w ? P.C2() : P.C());
+          }
+          continue;
+        }
+        stage([&](int jj, int x) { return acc[0][i][j0 + jj][x]; });
+        if constexpr (EPI == EPI_STORE_F32) {
+          if (accumulate) {
+            chunk_t old[ITS];
+#pragma unroll
+            for (int it = 0; it < ITS; ++it) {
+              const long o = offset(i, ju, it);
+              old[it] = o >= 0 ? *at(P.C(), o) : chunk_t{};
+            }
+#pragma unroll
+            for (int it = 0; it < ITS; ++it) {
+              const chunk_t v = *chunk(it) + old[it];
+              const long o = offset(i, ju, it);
+              if (o >= 0) *at(P.C(), o) = v;
+            }
+            continue;
+          }
+        }
+        store_unit(i, ju, P.C());
+      }
+    }
+  }
+}
+
+template <int BM, int BN, int NB, int EPI, int LAYOUT>
+__global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GemmPlan* __restrict__ plan, int accumulate, int save_pre) {
+  gg_block<float, BM, BN, NB, EPI, LAYOUT>(plan, accumulate, save_pre);
+}
+template <int BM, int BN, int NB, int EPI, int LAYOUT>
+__global__ __launch_bounds__(256, 2) void gg_bf16_block_kernel(const GemmPlan* __restrict__ plan, int accumulate,
+                                                              int save_pre) {
+  gg_block<bf16_t, BM, BN, NB, EPI, LAYOUT>(plan, accumulate, save_pre);
+}
+
+}  // namespace modse_gemm
