@@ -6,6 +6,7 @@
 // does not depend on summation order beyond the last bit.
 #include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "common.h"
 #include "gemm_plan.h"
@@ -192,57 +193,6 @@ struct LdsRows {
   }
 };
 
-// acc[tt * EC + e] += sum over this lane's columns c of row[tt][c] * W[c][e0 + e], in float64
-template <typename T, int TOK, int EC, typename Rows>
-__device__ inline void lane_dots(const T* const (&row)[TOK], int d, int lane, const Rows& rows,
-                                 double (&acc)[TOK * EC]) {
-  const int nstep = (d + 511) >> 9;
-  Raw8<T> cur[TOK], nxt[TOK];
-  {
-    const int c = min(lane * 8, d - 8);
-#pragma unroll
-    for (int tt = 0; tt < TOK; ++tt) cur[tt].load(row[tt] + c);
-  }
-  for (int st = 0; st < nstep; ++st) {
-    const int c = st * 512 + lane * 8;
-    const bool more = st + 1 < nstep;
-    if (more) {
-      const int cn = min(c + 512, d - 8);
-#pragma unroll
-      for (int tt = 0; tt < TOK; ++tt) nxt[tt].load(row[tt] + cn);
-    }
-    if (c < d) {
-      float wf[EC];
-      rows.fetch(c, wf);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float wn[EC];
-        if (i < 7) rows.fetch(c + i + 1, wn);  // the next matrix row is on its way during this row's arithmetic
-        double wd[EC];
-#pragma unroll
-        for (int e = 0; e < EC; ++e) wd[e] = (double)wf[e];
-#pragma unroll
-        for (int tt = 0; tt < TOK; ++tt) {
-          const double xd = (double)cur[tt].get(i);
-#pragma unroll
-          for (int e = 0; e < EC; ++e) acc[tt * EC + e] = fma(xd, wd[e], acc[tt * EC + e]);
-        }
-        if (i < 7) {
-#pragma unroll
-          for (int e = 0; e < EC; ++e) wf[e] = wn[e];
-        }
-        // keeps the scheduler from fetching and converting all eight rows ahead of the arithmetic, which
-        // costs more registers than there are
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    if (more) {
-#pragma unroll
-      for (int tt = 0; tt < TOK; ++tt) cur[tt] = nxt[tt];
-    }
-  }
-}
-
 // tokens x expert columns that a wave sums at a time
 template <int NE>
 struct RouterShape {
@@ -250,97 +200,6 @@ struct RouterShape {
   static constexpr int TOK = 32 / EC < 4 ? 32 / EC : 4;  // (more tokens: their row registers no longer fit)
   static constexpr int V = TOK * EC;
 };
-
-// One wave's TOK tokens against all NE expert columns of one matrix: sums[tt][e] (an LDS array of the wave)
-template <typename T, int NE, typename MakeRows>
-__device__ inline void wave_logits(const T* const (&row)[RouterShape<NE>::TOK], int d, int lane, MakeRows make_rows,
-                                   double (*sums)[NE]) {
-  using S = RouterShape<NE>;
-  constexpr int EC = S::EC, TOK = S::TOK, V = S::V;
-#pragma unroll 1
-  for (int e0 = 0; e0 < NE; e0 += EC) {
-    double acc[V];
-#pragma unroll
-    for (int i = 0; i < V; ++i) acc[i] = 0.0;
-    lane_dots<T, TOK, EC>(row, d, lane, make_rows(e0), acc);
-    wave_sum_values<V>(acc, lane);
-    if (lane < V) {
-      const int v = bitrev<Log2<V>::value>(lane);
-      sums[v / EC][e0 + v % EC] = acc[0];
-    }
-  }
-}
-
-// One block routes TPB consecutive tokens, eight per wave.  blockhist[b][0..N-1] = this block's per-expert
-// assignment counts, blockhist[b][N] = its near-tie token count.  Reads the router matrices from memory (through
-// the caches) for every TOK tokens: the form for layers whose W_gate does not fit router_stream_kernel's LDS
-// area, for small batches with many experts, and for the optional parts of the gate (EXT): the noise term
-// RMSNorm(Softplus(x W_n)) of H(x) (Sec. 2 Eq. 4-5; G.W_noise != null), which takes a second pass over the
-// token rows with W_n in place of W_gate, and the full-softmax probabilities p(x) that the auxiliary loss needs
-// (Sec. 3.2 Eq. 11; G.probs != null).
-template <typename T, int NE, bool EXT>
-__global__ __launch_bounds__(ROUTE_THREADS, 2) void router_kernel(const T* __restrict__ x, const T* __restrict__ Wg,
-                                                              const float* __restrict__ bias, int ntok, int d, int N,
-                                                              int top_k, int32_t* __restrict__ topk_idx,
-                                                              float* __restrict__ topk_w,
-                                                              int32_t* __restrict__ blockhist, GateExtPtrs G) {
-  constexpr int TOK = RouterShape<NE>::TOK, EC = RouterShape<NE>::EC;
-  constexpr int WAVES = ROUTE_THREADS / 64;
-  __shared__ double s_logit[WAVES][TOK][NE];
-  __shared__ double s_u[EXT ? WAVES : 1][EXT ? TOK : 1][EXT ? NE : 1];
-  __shared__ int s_hist[MODSE_MAX_EXPERTS + 1];
-  const T* Wn = EXT ? static_cast<const T*>(G.W_noise) : nullptr;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int tok0 = blockIdx.x * TPB + wave * TOK_PER_WAVE;
-  if (tid <= N) s_hist[tid] = 0;
-  __syncthreads();
-
-  for (int pass = 0; pass < TOK_PER_WAVE / TOK; ++pass) {
-    const int tbase = tok0 + pass * TOK;
-    const T* row[TOK];
-#pragma unroll
-    for (int tt = 0; tt < TOK; ++tt)  // rows past the end repeat the last token; never written
-      row[tt] = x + (size_t)min(tbase + tt, ntok - 1) * d;
-    wave_logits<T, NE>(row, d, lane, [&](int e0) { return GlobalRows<T, EC>{Wg, NE, e0}; }, s_logit[wave]);
-    if constexpr (EXT) {
-      if (Wn) wave_logits<T, NE>(row, d, lane, [&](int e0) { return GlobalRows<T, EC>{Wn, NE, e0}; }, s_u[wave]);
-    }
-    __syncthreads();
-    if (lane < TOK && tbase + lane < ntok) {
-      const int t = tbase + lane;
-      if (bias)
-        for (int e = 0; e < N; ++e) s_logit[wave][lane][e] += (double)bias[e];
-      if constexpr (EXT) {
-        if (Wn) {  // H(x)_e += gamma s_e / sqrt(mean_i s_i^2 + eps),  s = softplus(x W_n)
-          double ss = 0.0;
-          for (int e = 0; e < N; ++e) {
-            const double u = s_u[wave][lane][e];
-            G.noise_pre[(size_t)t * N + e] = (float)u;
-            const double sp = softplus_f64(u);
-            s_u[wave][lane][e] = sp;
-            ss += sp * sp;
-          }
-          const double scale = (double)G.gamma[0] / sqrt(ss / N + (double)G.eps);
-          for (int e = 0; e < N; ++e) s_logit[wave][lane][e] += scale * s_u[wave][lane][e];
-        }
-      }
-      const TopPick p = pick_top(s_logit[wave][lane], N);
-      const bool near = write_gate(p, t, N, top_k, topk_idx, topk_w);
-      atomicAdd(&s_hist[p.i1], 1);
-      if (top_k == 2) atomicAdd(&s_hist[p.i2], 1);
-      if (near) atomicAdd(&s_hist[N], 1);
-      if constexpr (EXT) {
-        if (G.probs) {  // p(x) = softmax over all N logits
-          double den = 0.0;
-          for (int e = 0; e < N; ++e) den += exp(s_logit[wave][lane][e] - p.m1);
-          for (int e = 0; e < N; ++e) G.probs[(size_t)t * N + e] = (float)(exp(s_logit[wave][lane][e] - p.m1) / den);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (tid <= N) blockhist[(size_t)blockIdx.x * (N + 1) + tid] = s_hist[tid];
-}
 
 // Router for large batches without the optional gate parts.  One 512-thread block per CU copies W_gate into LDS
 // once (as float64 when that fits RS_W_BYTES, else as float: both exact) and then walks over groups of 64 tokens
@@ -629,6 +488,241 @@ __global__ __launch_bounds__(RM_THREADS) void router_mfma_kernel(const T* __rest
   }
 }
 
+// EPL consecutive elements of a router matrix row as loaded, and element i of them as float
+template <typename T, int EPL>
+struct RawRow;
+template <int EPL>
+struct RawRow<bf16_t, EPL> {
+  typedef std::conditional_t<EPL == 1, uint16_t, std::conditional_t<EPL == 2, uint32_t, uint64_t>> word_t;
+  word_t v;
+  __device__ void load(const bf16_t* p) { v = *reinterpret_cast<const word_t*>(p); }
+  __device__ float get(int i) const { return __uint_as_float((uint32_t)(uint16_t)(v >> (16 * i)) << 16); }
+};
+template <int EPL>
+struct RawRow<float, EPL> {
+  typedef float vec_t __attribute__((ext_vector_type(EPL)));
+  vec_t v;
+  __device__ void load(const float* p) { v = *reinterpret_cast<const vec_t*>(p); }
+  __device__ float get(int i) const { return v[i]; }
+};
+template <>
+struct RawRow<float, 1> {
+  float v;
+  __device__ void load(const float* p) { v = *p; }
+  __device__ float get(int) const { return v; }
+};
+
+// Top-k of two sets of experts, every expert of a before every expert of b: equal values stay with a.
+__device__ inline TopPick merge_top(const TopPick& a, const TopPick& b) {
+  TopPick r;
+  if (b.m1 > a.m1) {
+    r.m1 = b.m1; r.i1 = b.i1;
+    if (b.m2 > a.m1) { r.m2 = b.m2; r.i2 = b.i2; r.m3 = fmax(a.m1, b.m3); }
+    else { r.m2 = a.m1; r.i2 = a.i1; r.m3 = fmax(a.m2, b.m2); }
+  } else {
+    r.m1 = a.m1; r.i1 = a.i1;
+    if (b.m1 > a.m2) { r.m2 = b.m1; r.i2 = b.i1; r.m3 = fmax(a.m2, b.m2); }
+    else { r.m2 = a.m2; r.i2 = a.i2; r.m3 = fmax(a.m3, b.m1); }
+  }
+  return r;
+}
+
+// Logits -> routing of 16 lanes' token (lanes t16 = 0..15 of an aligned group; `on`: the token exists): each lane holds
+// PER consecutive logits l[], experts t16 * PER .., and, with the noise term, their x W_n in u[].  All lanes return the
+// pick; lane 0 has written topk_idx / topk_w.  Sums over experts run over a fixed tree.
+template <int PER, bool NOISE>
+__device__ inline TopPick route_token16(double (&l)[PER], double (&u)[PER], int t16, int t, bool on, int N, int top_k,
+                                        const GateExtPtrs& G, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
+                                        bool& near) {
+  const int e0 = t16 * PER;
+  if constexpr (NOISE) {  // H(x)_e += gamma s_e / sqrt(mean_i s_i^2 + eps),  s = softplus(x W_n)
+    double ss = 0.0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (e0 + i < N) {
+        if (on) G.noise_pre[(size_t)t * N + e0 + i] = (float)u[i];
+        u[i] = softplus_f64(u[i]);
+        ss += u[i] * u[i];
+      }
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) ss += shfl_xor_f64(ss, m);
+    const double scale = (double)G.gamma[0] / sqrt(ss / N + (double)G.eps);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) l[i] += scale * u[i];
+  }
+  TopPick p = {-INFINITY, -INFINITY, -INFINITY, -1, -1};
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const double v = e0 + i < N ? l[i] : -INFINITY;
+    if (v > p.m1) {
+      p.m3 = p.m2; p.m2 = p.m1; p.i2 = p.i1; p.m1 = v; p.i1 = e0 + i;
+    } else if (v > p.m2) {
+      p.m3 = p.m2; p.m2 = v; p.i2 = e0 + i;
+    } else if (v > p.m3) {
+      p.m3 = v;
+    }
+  }
+#pragma unroll
+  for (int m = 1; m < 16; m <<= 1) {
+    TopPick o;
+    o.m1 = shfl_xor_f64(p.m1, m); o.m2 = shfl_xor_f64(p.m2, m); o.m3 = shfl_xor_f64(p.m3, m);
+    o.i1 = __shfl_xor(p.i1, m, 64); o.i2 = __shfl_xor(p.i2, m, 64);
+    p = (t16 & m) ? merge_top(o, p) : merge_top(p, o);
+  }
+  if (p.i1 < 0) p.i1 = 0;                                     // every logit is -inf
+  if (p.i2 < 0 || p.i2 == p.i1) p.i2 = p.i1 == 0 ? 1 : 0;     // no second one above -inf (see pick_top)
+  near = false;
+  if (on && t16 == 0) near = write_gate(p, t, N, top_k, topk_idx, topk_w);
+  if (G.probs) {  // p(x) = softmax over all N logits (Sec. 3.2 Eq. 11)
+    double ex[PER], den = 0.0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      ex[i] = e0 + i < N ? exp(l[i] - p.m1) : 0.0;
+      den += ex[i];
+    }
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) den += shfl_xor_f64(den, m);
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (on && e0 + i < N) G.probs[(size_t)t * N + e0 + i] = (float)(ex[i] / den);
+  }
+  return p;
+}
+
+// Router for more than 16 experts and for the optional gate parts (noise term: NOISE; probabilities: G.probs), on
+// v_mfma_f64_16x16x4_f64.  Operand lane 16 k + i holds A[i][k] (or B[k][i]); result lane 16 q + j, register r holds
+// D[4 r + q][j] (checked with a one-hot probe).  Rows are 16 tokens, columns 16 experts (or, up to 8 experts with the
+// noise term, 8 experts and their noise columns); the order of the contraction is free, so lane 16 q + i takes the eight
+// columns 8q .. 8q+7 of a 32-column step of its token row (one 16-byte load) and the matrix rows that go with them.  A
+// lane reads EPL neighbouring experts of a matrix row at once: column j of group g is expert EPL j + g.
+// A block of eight waves takes 32 tokens; wave w takes the column steps w, w + 8, ...; the matrices come from L2 (32
+// tokens share a read) straight into operand order, and the eight partial sums meet in LDS in a fixed order.
+// Bound by the float64 matrix pipe: 73 TFLOP/s of a probe, 29 us for 8192 tokens, d = 2048, 64 experts, where the launch
+// takes 42 us; the vector-FMA form before it, which fetched every matrix row for two tokens, took 178.
+constexpr int RW_THREADS = 512, RW_WAVES = RW_THREADS / 64, RW_TOKENS = 32;
+static_assert(RW_TOKENS == TPB && RW_TOKENS * 16 == RW_THREADS, "one histogram block per group; 16 threads per token");
+template <typename T, int NE, bool NOISE>
+__global__ __launch_bounds__(RW_THREADS) void router_kernel(const T* __restrict__ x, const T* __restrict__ Wg,
+                                                           const float* __restrict__ bias, int ntok, int d, int N,
+                                                           int top_k, int32_t* __restrict__ topk_idx,
+                                                           float* __restrict__ topk_w, int32_t* __restrict__ blockhist,
+                                                           GateExtPtrs G) {
+  constexpr int EPL = NE <= 16 ? 1 : NE / 16, PER = EPL;
+  constexpr bool SHARE = NOISE && NE <= 8;       // gate and noise columns share one group of 16
+  constexpr int NM = NOISE && !SHARE ? 2 : 1;    // passes over the token rows: W_gate, W_noise (both at once do not fit the registers)
+  constexpr int NG = EPL;                        // column groups per pass over the token rows
+  constexpr int CP = 16 * NM * NG + 1;           // (+1: the rows of a column read start in different banks)
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  __shared__ double s_part[RW_WAVES / 2][RW_TOKENS][CP];
+  __shared__ int s_hist[MODSE_MAX_EXPERTS + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane >> 4, j = lane & 15;
+  const int ngroups = (ntok + RW_TOKENS - 1) / RW_TOKENS;
+  const int nstep = (d / 32 - wave + RW_WAVES - 1) / RW_WAVES;  // this wave's column steps
+  const T* Wn = static_cast<const T*>(G.W_noise);
+  // this lane's columns of the matrix rows (lanes without a column repeat one; their results are not used)
+  const T* wsrc[NM];
+  if constexpr (SHARE) wsrc[0] = j < 8 ? Wg + min(j, NE - 1) : Wn + min(j - 8, NE - 1);
+  else {
+    wsrc[0] = Wg + min(j * EPL, NE - EPL);
+    if constexpr (NM == 2) wsrc[1] = Wn + min(j * EPL, NE - EPL);
+  }
+  struct Step {
+    Raw8<T> x[2];
+    RawRow<T, EPL> w[8];
+  };
+  Step cur, nxt;
+  int l_grp = blockIdx.x, l_pass = 0, l_st = 0;
+  auto load_next = [&](Step& s) {  // one step ahead of the arithmetic, across groups
+    if (l_grp >= ngroups || nstep <= 0) return;
+    const int c = (wave + l_st * RW_WAVES) * 32 + q * 8;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)  // rows past the end repeat the last token; never written
+      s.x[h].load(x + (size_t)min(l_grp * RW_TOKENS + h * 16 + j, ntok - 1) * d + c);
+    const T* w = NM == 2 && l_pass ? wsrc[NM - 1] : wsrc[0];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) s.w[m].load(w + (size_t)(c + m) * NE);
+    if (++l_st == nstep) {
+      l_st = 0;
+      if (++l_pass == NM) {
+        l_pass = 0;
+        l_grp += gridDim.x;
+      }
+    }
+  };
+  load_next(cur);
+  if (tid <= MODSE_MAX_EXPERTS) s_hist[tid] = 0;
+
+  for (int grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
+#pragma unroll 1
+    for (int pass = 0; pass < NM; ++pass) {
+      f64x4 acc[2][NG];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int g = 0; g < NG; ++g) acc[h][g] = f64x4{0.0, 0.0, 0.0, 0.0};
+      for (int st = 0; st < nstep; ++st) {
+        load_next(nxt);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+          const double a0 = (double)cur.x[0].get(m), a1 = (double)cur.x[1].get(m);
+#pragma unroll
+          for (int g = 0; g < NG; ++g) {
+            const double b = (double)cur.w[m].get(g);
+            acc[0][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b, acc[0][g], 0, 0, 0);
+            acc[1][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b, acc[1][g], 0, 0, 0);
+          }
+        }
+        cur = nxt;
+      }
+      // waves 4-7 hand their sums to waves 0-3, which add their own and leave four partial sums per value
+      auto part = [&](int w, int h, int g, int r) -> double& {
+        return s_part[w][h * 16 + 4 * r + q][(pass * NG + g) * 16 + j];
+      };
+      if (wave >= RW_WAVES / 2) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part(wave - RW_WAVES / 2, h, g, r) = acc[h][g][r];
+      }
+      __syncthreads();
+      if (wave < RW_WAVES / 2) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part(wave, h, g, r) = acc[h][g][r] + part(wave, h, g, r);
+      }
+    }
+    __syncthreads();
+    // sixteen threads per token
+    const int t16 = tid & 15, tl = tid >> 4, t = grp * RW_TOKENS + tl;
+    double l[PER], u[PER];
+    auto total = [&](int c) { return (s_part[0][tl][c] + s_part[1][tl][c]) + (s_part[2][tl][c] + s_part[3][tl][c]); };
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {  // expert t16 * EPL + i: column t16 of group i
+      const int e = t16 * PER + i;
+      l[i] = total(i * 16 + t16) + ((bias && e < N) ? (double)bias[e] : 0.0);
+      u[i] = NOISE ? total(SHARE ? 8 + (t16 & 7) : (EPL * (NM - 1) + i) * 16 + t16) : 0.0;
+    }
+    bool near;
+    const TopPick p = route_token16<PER, NOISE>(l, u, t16, t, t < ntok, N, top_k, G, topk_idx, topk_w, near);
+    if (t16 == 0 && t < ntok) {
+      atomicAdd(&s_hist[p.i1], 1);
+      if (top_k == 2) atomicAdd(&s_hist[p.i2], 1);
+      if (near) atomicAdd(&s_hist[N], 1);
+    }
+    __syncthreads();
+    if (tid <= N) {  // the thread that writes a counter out also clears it for the next group
+      blockhist[(size_t)grp * (N + 1) + tid] = s_hist[tid];
+      s_hist[tid] = 0;
+    }
+  }
+}
+
 // Router without the optional gate parts: one block per G tokens, the 256 threads split the d columns, so
 // a token row and the router matrix are read once with 16-byte loads and the whole dot product is one or
 // two rounds of memory latency.  Every thread leaves its G x N float64 partial sums in LDS; they are added
@@ -699,6 +793,70 @@ __global__ __launch_bounds__(ROUTE_THREADS, 2) void router_token_kernel(const T*
     const int t = t0 + tid;
     const TopPick p = pick_top(s_logit[tid], N);
     near_flag[t] = write_gate(p, t, N, top_k, topk_idx, topk_w) ? 1 : 0;
+  }
+}
+
+// The one-block-per-token(s) router for more than 16 experts: sixteen threads share a matrix row (EPL = NE / 16
+// neighbouring experts each), the block's sixteen such groups share the columns of d, eight consecutive ones at a time.
+// A matrix row read serves the block's G tokens.  Sums are added in a fixed order: four groups of a wave by shuffles,
+// then the four waves through LDS.
+template <typename T, int NE, int G>
+__global__ __launch_bounds__(ROUTE_THREADS) void router_token_wide_kernel(const T* __restrict__ x, const T* __restrict__ Wg,
+                                                                         const float* __restrict__ bias, int ntok, int d,
+                                                                         int N, int top_k, int32_t* __restrict__ topk_idx,
+                                                                         float* __restrict__ topk_w,
+                                                                         int32_t* __restrict__ near_flag) {
+  constexpr int EPL = NE / 16;
+  static_assert(G * 16 <= ROUTE_THREADS, "sixteen threads per token in the last step");
+  __shared__ double s_part[ROUTE_THREADS / 64][G][NE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, t16 = tid & 15, t0 = blockIdx.x * G;
+  double acc[G][EPL];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[g][e] = 0.0;
+  const T* row[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) row[g] = x + (size_t)min(t0 + g, ntok - 1) * d;  // (clamped rows: never written)
+#pragma unroll 2
+  for (int c = (tid >> 4) * 8; c < d; c += ROUTE_THREADS / 16 * 8) {
+    RawRow<T, EPL> w[8];
+    Raw8<T> xv[G];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) w[m].load(Wg + (size_t)(c + m) * NE + t16 * EPL);
+#pragma unroll
+    for (int g = 0; g < G; ++g) xv[g].load(row[g] + c);
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        const double wd = (double)w[m].get(e);
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc[g][e] = fma((double)xv[g].get(m), wd, acc[g][e]);
+      }
+  }
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      double v = acc[g][e];
+      v += shfl_xor_f64(v, 16);
+      v += shfl_xor_f64(v, 32);
+      if (lane < 16) s_part[wave][g][t16 * EPL + e] = v;
+    }
+  __syncthreads();
+  const int g = tid >> 4, t = t0 + g;
+  if (g < G) {
+    double l[EPL], u[EPL];
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      const int e = t16 * EPL + i;
+      l[i] = (s_part[0][g][e] + s_part[1][g][e]) + (s_part[2][g][e] + s_part[3][g][e]) + ((bias && e < N) ? (double)bias[e] : 0.0);
+      u[i] = 0.0;
+    }
+    bool near;
+    route_token16<EPL, false>(l, u, t16, t, t < ntok, N, top_k, GateExtPtrs{}, topk_idx, topk_w, near);
+    if (t16 == 0 && t < ntok) near_flag[t] = near ? 1 : 0;
   }
 }
 
@@ -1329,25 +1487,26 @@ __global__ __launch_bounds__(256) void pad_rows_kernel(const T* __restrict__ W, 
 template <typename T, int NE>
 hipError_t run_router(const LayerDims& L, const T* x, const T* Wg, const float* bias, const RoutingPtrs& R,
                       int32_t* blockhist, const GateExtPtrs* G, hipStream_t s) {
-  const int nb = (L.T + TPB - 1) / TPB;
-  if (G)
-    hipLaunchKernelGGL((router_kernel<T, NE, true>), dim3(nb), dim3(ROUTE_THREADS), 0, s, x, Wg, bias, L.T, L.d, L.N,
-                       L.k, R.topk_idx, R.topk_w, blockhist, *G);
+  const dim3 grid(std::min((L.T + RW_TOKENS - 1) / RW_TOKENS, 256)), blk(RW_THREADS);
+  if (G && G->W_noise)
+    hipLaunchKernelGGL((router_kernel<T, NE, true>), grid, blk, 0, s, x, Wg, bias, L.T, L.d, L.N, L.k, R.topk_idx,
+                       R.topk_w, blockhist, *G);
   else
-    hipLaunchKernelGGL((router_kernel<T, NE, false>), dim3(nb), dim3(ROUTE_THREADS), 0, s, x, Wg, bias, L.T, L.d, L.N,
-                       L.k, R.topk_idx, R.topk_w, blockhist, GateExtPtrs{});
+    hipLaunchKernelGGL((router_kernel<T, NE, false>), grid, blk, 0, s, x, Wg, bias, L.T, L.d, L.N, L.k, R.topk_idx,
+                       R.topk_w, blockhist, G ? *G : GateExtPtrs{});
   return hipGetLastError();
 }
 
-// Which router a layer takes.  Plain gate, small and medium batches: one block per token keeps the chip busy
-// where 32-token blocks would leave most CUs idle (measured at d = 2048..4096: 0.04 ms instead of 0.11 ms for 64
-// tokens).  Larger plain batches: router_stream_kernel when W_gate fits its LDS area.  Otherwise, and with the
-// optional gate parts, router_kernel.
+// Which router a layer takes.  Plain gate, small and medium batches: one block per token (or four) keeps the chip busy
+// where 32-token blocks would leave most CUs idle.  Larger plain batches of up to 16 experts: router_stream_kernel (or
+// its matrix-instruction form) when W_gate fits its LDS area.  Otherwise, and with the optional gate parts,
+// router_kernel.  At d = 2048 the routing call takes 15 / 56 / 81 us for 64 / 1024 / 4096 tokens with 64 experts on
+// the token router, where router_kernel takes 46 / 78 / 79.
 enum RouterKind { ROUTER_TOKEN, ROUTER_STREAM, ROUTER_BLOCK };
 RouterKind router_kind(const LayerDims& L, const GateExtPtrs* G) {
   if (G) return ROUTER_BLOCK;
-  if (L.N <= 16 && L.T <= ROUTER_TOKEN_MAX_T) return ROUTER_TOKEN;
-  if ((size_t)(L.d / 8) * rs_group_bytes(padded_experts(L.N), 4) <= (size_t)RS_W_BYTES && L.T >= 1024) return ROUTER_STREAM;
+  if (L.T <= ROUTER_TOKEN_MAX_T) return ROUTER_TOKEN;
+  if (L.N <= 16 && (size_t)(L.d / 8) * rs_group_bytes(padded_experts(L.N), 4) <= (size_t)RS_W_BYTES) return ROUTER_STREAM;
   return ROUTER_BLOCK;
 }
 
@@ -1390,7 +1549,18 @@ hipError_t router_typed(const LayerDims& L, const void* xv, const void* Wgv, con
     if (NE == 2) MODSE_LAUNCH_TOKEN_ROUTER(2);
     else if (NE == 4) MODSE_LAUNCH_TOKEN_ROUTER(4);
     else if (NE == 8) MODSE_LAUNCH_TOKEN_ROUTER(8);
-    else MODSE_LAUNCH_TOKEN_ROUTER(16);
+    else if (NE == 16) MODSE_LAUNCH_TOKEN_ROUTER(16);
+#define MODSE_LAUNCH_TOKEN_WIDE(NE_, G_)                                                                             \
+  hipLaunchKernelGGL((router_token_wide_kernel<T, NE_, G_>), dim3((L.T + G_ - 1) / G_), blk, 0, s, x, Wg, bias, L.T, \
+                     L.d, L.N, L.k, R.topk_idx, R.topk_w, B.near_flag)
+    else if (L.T <= 512) {  // one token per block until they fill the chip twice
+      if (NE == 32) MODSE_LAUNCH_TOKEN_WIDE(32, 1);
+      else MODSE_LAUNCH_TOKEN_WIDE(64, 1);
+    } else {
+      if (NE == 32) MODSE_LAUNCH_TOKEN_WIDE(32, 4);
+      else MODSE_LAUNCH_TOKEN_WIDE(64, 4);
+    }
+#undef MODSE_LAUNCH_TOKEN_WIDE
 #undef MODSE_LAUNCH_TOKEN_ROUTER
     e = hipGetLastError();
   } else if (kind == ROUTER_STREAM && router_on_mfma(L)) {
@@ -1420,9 +1590,7 @@ hipError_t router_typed(const LayerDims& L, const void* xv, const void* Wgv, con
       case 2: MODSE_LAUNCH_STREAM_ROUTER(2); break;
       case 4: MODSE_LAUNCH_STREAM_ROUTER(4); break;
       case 8: MODSE_LAUNCH_STREAM_ROUTER(8); break;
-      case 16: MODSE_LAUNCH_STREAM_ROUTER(16); break;
-      case 32: MODSE_LAUNCH_STREAM_ROUTER(32); break;
-      default: MODSE_LAUNCH_STREAM_ROUTER(64); break;
+      default: MODSE_LAUNCH_STREAM_ROUTER(16); break;
     }
 #undef MODSE_LAUNCH_STREAM_ROUTER
     e = hipGetLastError();
