@@ -291,7 +291,7 @@ def main():
         # decode-sized batch: the layer streams every expert's weights once; judged against HBM bandwidth
         wbytes = 3.0 * d * sum(cfg.d_ff) * (2 if cfg.dtype == "bf16" else 4)
         gbs = wbytes / ((st["up"] + st["down"]) * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "kernel": "gg_bf16_skinny_kernel 64-row tiles (up-projection + split-K "
+        roofline = {"bound": "hbm", "kernel": "gg_bf16_skinny_kernel 64- and 32-row tiles (up-projection + split-K "
                                               "down-projection)",
                     "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(gbs / PEAK_HBM_GBS, 4),
                     "traffic": None, "bytes_per_launch": wbytes, "avg_launch_ms": round(st["up"] + st["down"], 4),

@@ -90,26 +90,10 @@ RouteBufs route_bufs(char* base, const RouteScratch& r) {
 
 struct FwdLayout {
   RouteScratch route;
-  size_t topk_idx, topk_w, counts, offsets, row_of, src_of, near_tie, plan_up, plan_down, Xp, H, O, Opart, total;
+  size_t topk_idx, topk_w, counts, offsets, row_of, src_of, near_tie, plan_up, plan_down, Xp, H, O, Opart, unsplit, total;
+  GemmChoice down;
 };
 
-// Decode-sized batches stream the expert weights once; the down-projection then has too few output tiles
-// to occupy the chip (d / 256 per expert) and very long K loops, so its K is cut into chunks that become
-// problems of their own.  Returns the chunk length (a multiple of 64), or 0 when K is not split.
-constexpr int64_t SPLITK_MAX_TOKENS = MODSE_SKINNY_TOKENS;
-int splitk_chunk(const LayerDims& L) {
-  if (L.T > SPLITK_MAX_TOKENS) return 0;
-  int64_t F = 0;
-  for (int e = 0; e < L.N; ++e) F += L.f[e];
-  const int64_t ntiles_n = (L.d + 511) / 512;
-  // two tiles per CU: fewer, longer chunks mean fewer float32 slabs to write and to add up again (measured at the
-  // decode configuration of the benchmark: 1024 tiles 0.187 + 0.016 ms for down-projection + combine, 512 tiles
-  // 0.176 + 0.012 ms, 256 tiles 0.261 + 0.009 ms; counts that are no multiple of the CU count lose a round)
-  int64_t want = std::max<int64_t>(L.N, 512 / ntiles_n);
-  want = std::min<int64_t>(want, MODSE_MAX_PROBLEMS - L.N);          // sum_e ceil(f_e / chunk) <= want + N
-  const int64_t chunk = align_up((size_t)((F + want - 1) / want), 64);
-  return (int)std::max<int64_t>(chunk, 512);
-}
 int splitk_max_chunks(const LayerDims& L, int kchunk) {
   int m = 0;
   for (int e = 0; e < L.N; ++e) m = std::max(m, (L.f[e] + kchunk - 1) / kchunk);
@@ -135,8 +119,9 @@ FwdLayout fwd_layout(const LayerDims& L, modse_dtype dt, bool with_saved) {
   w.Xp = c.take(with_saved ? 0 : Tk * L.d * es);
   w.H = c.take(with_saved ? 0 : hidden_elems_max(L) * es);
   w.O = c.take(with_saved ? 0 : Tk * L.d * es);
-  const int kchunk = with_saved ? 0 : splitk_chunk(L);
-  w.Opart = c.take(kchunk ? (size_t)splitk_max_chunks(L, kchunk) * Tk * L.d * 4 : 0);
+  w.down = gemm_choice(L, dt, EPI_STORE);
+  w.unsplit = c.off;
+  w.Opart = c.take(w.down.kchunk ? (size_t)splitk_max_chunks(L, w.down.kchunk) * Tk * L.d * 4 : 0);
   w.total = c.off;
   return w;
 }
@@ -159,7 +144,8 @@ SavedLayout saved_layout(const LayerDims& L, modse_dtype dt) {
 }
 
 struct BwdLayout {
-  size_t plan[3], dO, dA, dB, dXp, dg, dl, du, dgamma_part, dWg_partial, total;
+  size_t plan[3], dO, dA, dB, dXp, dg, dl, du, dgamma_part, dWg_partial, dXpart, unsplit, total;
+  GemmChoice dx;
 };
 
 BwdLayout bwd_layout(const LayerDims& L, modse_dtype dt) {
@@ -178,6 +164,9 @@ BwdLayout bwd_layout(const LayerDims& L, modse_dtype dt) {
   w.du = c.take((size_t)L.T * L.N * 4);
   w.dgamma_part = c.take((((size_t)L.T + 255) / 256) * 4);
   w.dWg_partial = c.take(nb * L.d * L.N * 4);
+  w.dx = gemm_choice(L, dt, EPI_STORE_DUALK);
+  w.unsplit = c.off;
+  w.dXpart = c.take(w.dx.kchunk ? (size_t)2 * splitk_max_chunks(L, w.dx.kchunk) * Tk * L.d * 4 : 0);
   w.total = c.off;
   return w;
 }
@@ -192,6 +181,17 @@ int64_t tiles_bound(const LayerDims& L, const TileShape& t, bool n_is_f) {
     const int64_t mine = std::min<int64_t>(full, (L.T + t.bm - 1) / t.bm - 1);
     full -= mine;
     s += (mine + 1) * nt;
+  }
+  return s;
+}
+// the same for a product with d columns whose K = f_e is cut into chunks
+int64_t split_tiles_bound(const LayerDims& L, const TileShape& t, int kchunk, int passes) {
+  const int64_t nt = (L.d + t.bn - 1) / t.bn;
+  int64_t s = 0, full = (int64_t)L.T * L.k / t.bm;
+  for (int i = 0; i < L.N; ++i) {
+    const int64_t mine = std::min<int64_t>(full, (L.T + t.bm - 1) / t.bm - 1);
+    full -= mine;
+    s += (mine + 1) * nt * passes * ((L.f[L.order[i]] + kchunk - 1) / kchunk);
   }
   return s;
 }
@@ -403,8 +403,11 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   if (routing_out && !routing_complete(routing_out)) return MODSE_ERR_INVALID_ARG;
   const modse_dtype dt = desc->dtype;
   const LayerDims L = make_dims(desc, T);
-  const FwdLayout w = fwd_layout(L, dt, saved != nullptr);
-  if (ws_bytes < w.total) return MODSE_ERR_WORKSPACE;
+  FwdLayout w = fwd_layout(L, dt, saved != nullptr);
+  // a workspace made for more tokens may be too small for the partial sums that this batch would use: it then does
+  // without them
+  if (ws_bytes < w.total) w.down.kchunk = 0;
+  if (ws_bytes < w.unsplit) return MODSE_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   char* wsb = static_cast<char*>(ws);
   const RoutingPtrs R = routing_from(routing_out, wsb, w);
@@ -428,10 +431,9 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   }
   pa.up = reinterpret_cast<GemmPlan*>(wsb + w.plan_up);
   pa.down = reinterpret_cast<GemmPlan*>(wsb + w.plan_down);
-  pa.up_tile = gemm_tile_shape(L, dt, EPI_SWIGLU);
-  pa.down_tile = gemm_tile_shape(L, dt, EPI_STORE);
-  // inference on a decode-sized batch: split-K down-projection (the backward pass wants O itself)
-  const int kchunk = saved ? 0 : splitk_chunk(L);
+  pa.up_tile = gemm_choice(L, dt, EPI_SWIGLU).tile;
+  pa.down_tile = w.down.tile;
+  const int kchunk = w.down.kchunk;
   pa.kchunk = kchunk;
   pa.Opart = reinterpret_cast<float*>(wsb + w.Opart);
   // histogram, scan (which also writes the tile plans), stable scatter: one launch for all of it on decode-sized
@@ -442,12 +444,10 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU, pa.up_tile, pa.up, 0, saved != nullptr, tiles_bound(L, pa.up_tile, true), s));
   stamp.mark(MODSE_STAGE_UP);
   if (kchunk) {
-    int64_t nprob = 0;
-    for (int e = 0; e < L.N; ++e) nprob += (L.f[e] + kchunk - 1) / kchunk;
-    const int64_t bound = nprob * ((T + pa.down_tile.bm - 1) / pa.down_tile.bm) * ((L.d + pa.down_tile.bn - 1) / pa.down_tile.bn);
+    const int64_t bound = split_tiles_bound(L, pa.down_tile, kchunk, 1);
     HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.down_tile, pa.down, 0, 0, bound, s, LAYOUT_TN));
     stamp.mark(MODSE_STAGE_DOWN);
-    HIP_TRY(launch_combine_split(L, dt, pa.Opart, kchunk, R, y, s));
+    HIP_TRY(launch_combine_split(L, dt, pa.Opart, kchunk, R, saved ? pa.O : nullptr, y, s));
     stamp.mark(MODSE_STAGE_COMBINE);
     return MODSE_OK;
   }
@@ -482,8 +482,9 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   if (!routing_complete(routing)) return MODSE_ERR_INVALID_ARG;
   const modse_dtype dt = desc->dtype;
   const LayerDims L = make_dims(desc, T);
-  const BwdLayout w = bwd_layout(L, dt);
-  if (ws_bytes < w.total) return MODSE_ERR_WORKSPACE;
+  BwdLayout w = bwd_layout(L, dt);
+  if (ws_bytes < w.total) w.dx.kchunk = 0;  // (as in the forward pass)
+  if (ws_bytes < w.unsplit) return MODSE_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   char* wsb = static_cast<char*>(ws);
   const SavedLayout sl = saved_layout(L, dt);
@@ -502,17 +503,25 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   pa.W1 = W1; pa.W3 = W3; pa.W2 = W2;
   pa.dA = wsb + w.dA; pa.dB = wsb + w.dB; pa.dXp = wsb + w.dXp;
   pa.dW1 = dW1; pa.dW3 = dW3; pa.dW2 = dW2;
+  pa.dXpart = reinterpret_cast<float*>(wsb + w.dXpart);
+  pa.dx_kchunk = w.dx.kchunk;
   pa.dh = reinterpret_cast<GemmPlan*>(wsb + w.plan[0]);
   pa.dx = reinterpret_cast<GemmPlan*>(wsb + w.plan[1]);
   pa.wg = reinterpret_cast<GemmPlan*>(wsb + w.plan[2]);
-  pa.dh_tile = gemm_tile_shape(L, dt, EPI_SWIGLU_BWD);
-  pa.dx_tile = gemm_tile_shape(L, dt, EPI_STORE_DUALK);
-  pa.wg_tile = gemm_tile_shape(L, dt, EPI_STORE_F32);
+  pa.dh_tile = gemm_choice(L, dt, EPI_SWIGLU_BWD).tile;
+  pa.dx_tile = w.dx.tile;
+  pa.wg_tile = gemm_choice(L, dt, EPI_STORE_F32).tile;
   HIP_TRY(launch_plan_bwd(L, dt, R.counts, R.offsets, pa, s));
   stamp.mark(MODSE_STAGE_BWD_PREP);
 
   HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU_BWD, pa.dh_tile, pa.dh, 0, 0, tiles_bound(L, pa.dh_tile, true), s));
-  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, 0, 0, tiles_bound(L, pa.dx_tile, false), s));
+  if (pa.dx_kchunk) {
+    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.dx_tile, pa.dx, 0, 0, split_tiles_bound(L, pa.dx_tile, pa.dx_kchunk, 2),
+                                s, LAYOUT_B_KN));
+    HIP_TRY(launch_sum_slabs(L, dt, pa.dXpart, pa.dx_kchunk, 2, R, pa.dXp, s));
+  } else {
+    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, 0, 0, tiles_bound(L, pa.dx_tile, false), s));
+  }
   stamp.mark(MODSE_STAGE_BWD_DGRAD);
 
   HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, accumulate, 0, wgrad_tiles(L, pa.wg_tile), s));

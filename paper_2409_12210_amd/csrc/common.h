@@ -7,7 +7,6 @@
 
 #define MODSE_MAX_EXPERTS 64
 #define MODSE_MAX_PROBLEMS (3 * MODSE_MAX_EXPERTS)  // the three weight-gradient GEMMs share one launch
-#define MODSE_SKINNY_TOKENS 64           // batches up to this size take the decode-shaped forward GEMMs
 #define MODSE_PERMUTE_SMALL_MAX_T 64      // batches up to this size take the fused permute + plan launch
 #define MODSE_ROUTE_TOKENS_PER_BLOCK 32  // tokens handled by one block of the router / scatter kernels
 
@@ -168,8 +167,12 @@ hipError_t launch_routing_stats(const LayerDims& L, const int32_t* topk_idx, int
                                 hipStream_t s);
 hipError_t launch_combine(const LayerDims& L, modse_dtype dt, const void* O, const RoutingPtrs& R, void* y,
                           hipStream_t s);
+// O (may be null): the summed rows, for a backward pass to come
 hipError_t launch_combine_split(const LayerDims& L, modse_dtype dt, const float* Opart, int kchunk, const RoutingPtrs& R,
-                                void* y, hipStream_t s);
+                                void* O, void* y, hipStream_t s);
+// out[r] = sum over the slabs of row r's expert, passes * ceil(f_e / kchunk) of them, in ascending order
+hipError_t launch_sum_slabs(const LayerDims& L, modse_dtype dt, const float* slabs, int kchunk, int passes,
+                            const RoutingPtrs& R, void* out, hipStream_t s);
 hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, const void* O, const RoutingPtrs& R,
                            void* dO, float* dg, hipStream_t s);
 struct BwdRouterBufs {  // workspace of the router's backward pass
@@ -187,7 +190,12 @@ hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, 
 struct TileShape {
   int32_t bm, bn;
 };
-TileShape gemm_tile_shape(const LayerDims& L, modse_dtype dt, int epilogue);
+struct GemmChoice {
+  TileShape tile;
+  int32_t kchunk;  // the product's K = f_e is cut into ceil(f_e / kchunk) chunks (per operand pair); 0 = not split
+};
+// tiles (and split) of the GEMM with this epilogue; a pure function of its arguments
+GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue);
 // t: the tile shape that the plan was made with.  max_tiles: upper bound of the number of tiles.  layout < 0: the
 // layout that goes with the epilogue (see gemm.hip).
 hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int accumulate,
@@ -196,7 +204,7 @@ hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const 
 struct FwdPlanArgs {
   const void *Xp, *W1, *W3, *W2;
   void *H, *dHdA, *dHdB, *O;  // dHdA/dHdB (derivatives of h by the two pre-activations) may be null
-  // split-K down-projection for decode-sized batches: expert e's K = f_e is cut into chunks of `kchunk`
+  // split-K down-projection for batches with few tiles: expert e's K = f_e is cut into chunks of `kchunk`
   // columns; chunk c writes float32 partial sums to Opart[c] ([T*k, d] each), which the combine step adds up.
   float* Opart;
   int32_t kchunk;  // 0 = no split
@@ -209,6 +217,10 @@ struct BwdPlanArgs {
   const void *W1, *W3, *W2;
   void *dA, *dB, *dXp;
   float *dW1, *dW3, *dW2;
+  // split dX product (batches with few tiles): K = f_e of either operand pair is cut into chunks of `dx_kchunk`; slab
+  // p * ceil(f_e / dx_kchunk) + c of dXpart holds chunk c of pair p, to be added up by launch_sum_slabs
+  float* dXpart;
+  int32_t dx_kchunk;  // 0 = one product over both pairs
   GemmPlan *dh, *dx, *wg;  // wg: dW1, dW3 and dW2 of every expert in one problem list
   TileShape dh_tile, dx_tile, wg_tile;
 };

@@ -7,10 +7,10 @@
 // GEMMs have both operands K-contiguous; the data-gradient GEMMs read the weights as [K, N]; the
 // weight-gradient GEMMs contract over tokens and read both activations as [K, M] and [K, N].
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "gemm_bf16.h"
-#include "gemm_bf16_skinny.h"
 #include "gemm_block.h"
 #include "gemm_plan.h"
 #include "gemm_tiles.h"
@@ -48,6 +48,30 @@ __global__ __launch_bounds__(64) void plan_bwd_kernel(LayerDims L, int esize, co
     a.dh->prob[i] = P;
   }
   finish_plan(a.dh, i, L.N, s_tiles);
+  if (a.dx_kchunk > 0) {  // split: one problem per (expert, operand pair, chunk of K), float32 partial sums
+    int first = 0, total = 0;
+    for (int q = 0; q < L.N; ++q) {
+      const int n = 2 * ((L.f[L.order[q]] + a.dx_kchunk - 1) / a.dx_kchunk);
+      if (q < i) first += n;
+      total += n;
+    }
+    if (on) {
+      const int nchunk = (f + a.dx_kchunk - 1) / a.dx_kchunk;
+      const int len = balanced_chunk(f, nchunk);
+      for (int c = 0; c < 2 * nchunk; ++c) {
+        const int k0 = min((c % nchunk) * len, f);
+        GemmProblem P = {};
+        P.A = cadd(c < nchunk ? a.dA : a.dB, (hoff + k0) * es);
+        P.B = cadd(c < nchunk ? a.W1 : a.W3, (woff + (size_t)k0 * d) * es);
+        P.C = a.dXpart + ((size_t)c * L.T * L.k + offsets[e]) * d;
+        P.M = n_e; P.N = d; P.K = min(len, f - k0);
+        P.lda = f; P.ldb = d; P.ldc = d;
+        s_tiles[first + c] = set_tiles(P, a.dx_tile.bm, a.dx_tile.bn);
+        a.dx->prob[first + c] = P;
+      }
+    }
+    finish_plan(a.dx, i, total, s_tiles);
+  } else {
   if (on) {  // dXp = dA W1 + dB W3 (W1_e, W3_e are [f, d]: [K, N] operands)
     GemmProblem P = {};
     P.A = cadd(a.dA, hoff * es);
@@ -61,6 +85,7 @@ __global__ __launch_bounds__(64) void plan_bwd_kernel(LayerDims L, int esize, co
     a.dx->prob[i] = P;
   }
   finish_plan(a.dx, i, L.N, s_tiles);
+  }
   // Weight gradients contract over the expert's tokens, so a tile costs n_e K-steps whatever its expert's
   // width: the three GEMMs of one expert are listed together, experts by falling token count.
   if (on) {
@@ -106,27 +131,25 @@ hipError_t run_bf16(const GemmPlan* plan, int accumulate, int save_pre, int64_t 
   int64_t grid = num_cus();  // the LDS panels fill a CU: one persistent workgroup per CU
   if (max_tiles < grid) grid = max_tiles;
   if (grid < 1) grid = 1;
-  if constexpr (BM == 64) {  // decode-sized batches
-    hipLaunchKernelGGL((gg_bf16_skinny_kernel<BM, BN, NB, WAVES_M, WAVES_N, EPI, LAYOUT>), dim3((unsigned)grid), dim3(NT), 0,
-                       s, plan, accumulate, save_pre);
-  } else {
-    hipLaunchKernelGGL((gg_bf16_kernel<BM, BN, NB, WAVES_M, WAVES_N, EPI, LAYOUT>), dim3((unsigned)grid), dim3(NT), 0, s,
-                       plan, accumulate, save_pre);
-  }
+  hipLaunchKernelGGL((gg_bf16_kernel<BM, BN, NB, WAVES_M, WAVES_N, EPI, LAYOUT>), dim3((unsigned)grid), dim3(NT), 0, s,
+                     plan, accumulate, save_pre);
   return hipGetLastError();
 }
 
 // max_tiles: an upper bound of the tile list's length; one workgroup per tile
-template <typename T, int BM, int BN, int EPI, int LAYOUT>
+template <typename T, int BM, int BN, int EPI, int LAYOUT, int WAVES_M = 2, int WAVES_N = 2>
 hipError_t run_block(const GemmPlan* plan, int accumulate, int save_pre, int64_t max_tiles, hipStream_t s) {
   constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
   const int64_t grid = (int64_t)align_up((size_t)std::max<int64_t>(max_tiles, 1), NUM_XCD * TILE_RUN);
   if constexpr (std::is_same_v<T, float>)
     hipLaunchKernelGGL((gg_f32_kernel<BM, BN, NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan, accumulate,
                        save_pre);
+  else if constexpr (BM < 128)
+    hipLaunchKernelGGL((gg_bf16_skinny_kernel<BM, BN, NB, WAVES_M, WAVES_N, EPI, LAYOUT>), dim3((unsigned)grid),
+                       dim3(WAVES_M * WAVES_N * 64), 0, s, plan, accumulate, save_pre);
   else
-    hipLaunchKernelGGL((gg_bf16_block_kernel<BM, BN, NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan,
-                       accumulate, save_pre);
+    hipLaunchKernelGGL((gg_bf16_block_kernel<BM, BN, NB, WAVES_M, WAVES_N, EPI, LAYOUT>), dim3((unsigned)grid),
+                       dim3(WAVES_M * WAVES_N * 64), 0, s, plan, accumulate, save_pre);
   return hipGetLastError();
 }
 
@@ -134,71 +157,180 @@ hipError_t run_block(const GemmPlan* plan, int accumulate, int save_pre, int64_t
 template <typename T, int EPI, int LAYOUT>
 hipError_t run_block_tile(TileShape t, const GemmPlan* plan, int accumulate, int save_pre, int64_t max_tiles, hipStream_t s) {
   if (t.bm == 128) return run_block<T, 128, EPI == EPI_SWIGLU ? 64 : 128, EPI, LAYOUT>(plan, accumulate, save_pre, max_tiles, s);
-  return run_block<T, 64, 64, EPI, LAYOUT>(plan, accumulate, save_pre, max_tiles, s);
+  constexpr int BN = std::is_same_v<T, float> || EPI == EPI_SWIGLU ? 64 : 128;
+  if constexpr (!std::is_same_v<T, float> && LAYOUT == LAYOUT_TN && EPI != EPI_SWIGLU)
+    if (t.bm == 32) return run_block<T, 32, BN, EPI, LAYOUT, 1, 4>(plan, accumulate, save_pre, max_tiles, s);
+  return run_block<T, 64, BN, EPI, LAYOUT>(plan, accumulate, save_pre, max_tiles, s);
 }
 
 }  // namespace
 
 namespace {
-// tiles of an average batch: every expert has T * k / N rows (of C, or of the contraction for weight gradients)
-int64_t expected_tiles(const LayerDims& L, int epilogue, int bm, int bn) {
-  const int64_t rows = ((int64_t)L.T * L.k + L.N - 1) / L.N, mt = (rows + bm - 1) / bm, nt_d = (L.d + bn - 1) / bn;
-  int64_t n = 0;
+// ---- Which tiles a GEMM of the layer takes, and whether its K is split.  The realised token counts are known on the
+// device only, so the choice goes by the mean number of rows r = T k / N of an expert, with loads spread evenly over
+// 0.85 r .. 1.15 r.
+
+// expected number of row blocks of an expert
+double row_blocks(double r, int bm) {
+  double n = 1;
+  for (int j = 1; 1.15 * r > (double)j * bm; ++j) n += std::min(1.0, (1.15 * r - (double)j * bm) / (0.3 * r));
+  return n;
+}
+
+// One product with output tiles of all experts: `tiles` of them with K steps of 64 each
+struct Work {
+  double tiles = 0, steps = 0;  // totals (steps: over all tiles)
+  double longest = 0;           // K steps of the longest tile
+  void add(double t, double k) {
+    tiles += t;
+    steps += t * k;
+    longest = std::max(longest, k);
+  }
+};
+Work gemm_work(const LayerDims& L, int epilogue, TileShape t) {
+  const double r = (double)L.T * L.k / L.N, mb = row_blocks(r, t.bm);
+  auto blocks = [](int n, int b) { return (double)((n + b - 1) / b); };
+  Work w;
   for (int e = 0; e < L.N; ++e) {
-    const int64_t nt_f = (L.f[e] + bn - 1) / bn;
+    const int f = L.f[e], d = L.d;
     switch (epilogue) {
       case EPI_SWIGLU:
-      case EPI_SWIGLU_BWD: n += mt * nt_f; break;
-      case EPI_STORE_F32: n += 2 * ((L.f[e] + bm - 1) / bm) * nt_d + ((L.d + bm - 1) / bm) * nt_f; break;
-      default: n += mt * nt_d;
+      case EPI_SWIGLU_BWD: w.add(mb * blocks(f, t.bn), blocks(d, 64)); break;
+      case EPI_STORE: w.add(mb * blocks(d, t.bn), blocks(f, 64)); break;
+      case EPI_STORE_DUALK: w.add(mb * blocks(d, t.bn), 2 * blocks(f, 64)); break;
+      case EPI_STORE_F32:
+        w.add(2 * blocks(f, t.bm) * blocks(d, t.bn) + blocks(d, t.bm) * blocks(f, t.bn), row_blocks(r, 64));
+        break;
     }
   }
-  return n;
+  return w;
+}
+
+// Estimated time in us of a bf16 product (chunk: K steps of a split product's problems, 0 = not split), fitted to the
+// measured times of all five GEMMs at d = 1024 ... 4096, 4 ... 64 experts and 16 ... 8192 tokens.  A step of a tile takes
+// 1.67 us in the 256 x 256 kernel (one workgroup per CU), 1.1 us (weight gradients: 1.85) with 128-row tiles and 0.8 us (dH: 1.0) with 64-row ones
+// (two workgroups per CU); a tile pays for its opening and its epilogue with `fix` further steps, and the float32 slabs of
+// a split product are written and read at 4 TB/s.
+double gemm_cost(const LayerDims& L, int epilogue, TileShape t, int chunk) {
+  const double cus = num_cus();
+  Work w = gemm_work(L, epilogue, t);
+  if (w.tiles < 1) return 0;
+  const bool wgrad = epilogue == EPI_STORE_F32;
+  const bool same = wgrad || epilogue == EPI_SWIGLU || epilogue == EPI_SWIGLU_BWD;  // tiles of one length
+  if (t.bm == 256) {
+    const double fix = same && !wgrad ? 4 : 7;
+    const double mean = w.steps / w.tiles + fix;
+    if (same) return (std::ceil(w.tiles / cus) + (wgrad ? 0.3 : 0)) * mean * 1.67;  // whole rounds
+    // (a lone workgroup's steps are shorter when other CUs stand idle)
+    return std::max(w.tiles * mean / cus, (0.75 + 0.25 * std::min(1.0, w.tiles / cus)) * (w.longest + fix)) * 1.67;
+  }
+  const double fix = 2.5, us = wgrad ? 1.85 : t.bm == 128 ? 1.1 : epilogue == EPI_SWIGLU_BWD ? 1.0 : 0.8, slots = 2 * cus;
+  double mean = w.steps / w.tiles + fix, chain = w.longest + fix, slabs = 0;
+  if (chunk) {
+    const double n = std::max(1.0, w.steps / w.tiles / chunk);
+    slabs = 2 + n * L.T * L.k * L.d * (8 / 4e6);
+    w.tiles *= n;
+    mean = chain = chunk + fix;
+  }
+  // a workgroup that has its CU for itself runs faster
+  const double alone = 0.62 + 0.38 * std::min(1.0, std::max(0.0, (w.tiles - cus) / cus));
+  return std::max((w.tiles / slots + (wgrad ? 0 : same ? 0.6 : 0.35)) * mean, chain * alone) * us + slabs;
+}
+
+// Chunk length of a split K = f_e (a multiple of 64), or 0.  A batch with few rows has too few output tiles (d / bn per
+// expert and row block) to fill the chip, and K loops of up to f_e / 64 (dX: twice that) steps in a row; cut into chunks
+// that become problems of their own it fills the workgroup slots.  Each chunk costs a float32 slab of rows x d, written
+// and read once, so chunks are not made shorter than 640 columns.
+// Decode-sized batches, whose slabs are small, take more and shorter chunks: they are bound by the weight stream, which
+// runs better the more loads are in flight (d = 4096, 64 tokens: 512 / 1024 / 1536 tiles 180 / 183 / 178 us; 16 tokens
+// 177 / 173 / 164).
+int split_chunk(const LayerDims& L, modse_dtype dt, TileShape t, int passes) {
+  const int64_t rows = ((int64_t)L.T * L.k + L.N - 1) / L.N;
+  const int64_t tiles = ((rows + t.bm - 1) / t.bm) * ((L.d + t.bn - 1) / t.bn);  // of one expert
+  const int64_t cus = num_cus(), target = dt == MODSE_F32 ? (t.bm == 64 ? 4 : 2) * cus
+                                          : t.bm == 32    ? 6 * cus
+                                          : t.bm == 64 && passes == 1 ? 4 * cus : 2 * cus;
+  if (t.bm > 128 || t.bn > 128 || tiles == 0 || 4 * L.N * tiles > 3 * target) return 0;
+  int64_t F = 0, fmax = 0;
+  for (int e = 0; e < L.N; ++e) {
+    F += passes * (int64_t)L.f[e];
+    fmax = std::max<int64_t>(fmax, L.f[e]);
+  }
+  const int64_t want = (target + tiles - 1) / tiles, most = MODSE_MAX_PROBLEMS - passes * L.N;
+  // passes * sum_e ceil(f_e / chunk) <= F / chunk + passes * N, which has to be at most MODSE_MAX_PROBLEMS
+  int64_t chunk = std::min<int64_t>(std::max<int64_t>((F + want - 1) / want, 640), 4096);
+  chunk = (int64_t)align_up((size_t)std::max<int64_t>(chunk, (F + most - 1) / most), 64);
+  return fmax > 2 * chunk ? (int)chunk : 0;
 }
 }  // namespace
 
-// Forward GEMMs of a decode-sized batch (no expert can have more than MODSE_SKINNY_TOKENS rows) use tiles
-// 64 rows high and 8 waves wide: 8/9 of what a stage loads is weights instead of half.
-// float32: 128 x 128 tiles (a wave then needs four LDS reads per sixteen matrix instructions) unless they are too few to
-// give every CU two, where 64 x 64 tiles spread the work.
-TileShape gemm_tile_shape(const LayerDims& L, modse_dtype dt, int epilogue) {
+GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue) {
+  const int passes = epilogue == EPI_STORE ? 1 : epilogue == EPI_STORE_DUALK ? 2 : 0;  // 0: never split
+  auto with_chunk = [&](TileShape t) {
+    GemmChoice c = {t, passes ? split_chunk(L, dt, t, passes) : 0};
+    if (c.kchunk && dt == MODSE_BF16 && t.bm > 32 && gemm_cost(L, epilogue, t, c.kchunk / 64) > gemm_cost(L, epilogue, t, 0))
+      c.kchunk = 0;
+    return c;
+  };
+  const double r = (double)L.T * L.k / L.N;
+  const bool swiglu = epilogue == EPI_SWIGLU;  // `bn` columns of each of the two matrices
   if (dt == MODSE_F32) {
-    const TileShape t = epilogue == EPI_SWIGLU ? TileShape{128, 64} : TileShape{128, 128};
-    return expected_tiles(L, epilogue, t.bm, t.bn) >= 2 * num_cus() ? t : TileShape{64, 64};
+    // 128 x 128 tiles (a wave then needs four LDS reads per sixteen matrix instructions) unless they are too few to give
+    // every CU two, where 64 x 64 tiles spread the work
+    const TileShape t = swiglu ? TileShape{128, 64} : TileShape{128, 128};
+    return with_chunk(gemm_work(L, epilogue, t).tiles >= 2 * num_cus() ? t : TileShape{64, 64});
   }
-  const bool skinny = L.T <= MODSE_SKINNY_TOKENS && (epilogue == EPI_SWIGLU || epilogue == EPI_STORE);
-  if (epilogue == EPI_SWIGLU) return skinny ? TileShape{64, 256} : TileShape{256, 128};
-  return skinny ? TileShape{64, 512} : TileShape{256, 256};
+  // The products with d columns: 32-row tiles for decode-sized batches (20 KiB a K step, four of them in flight), 64-row
+  // tiles as long as they hold an expert's rows.  d = 2048, eight experts: 32 rows (T = 130) 32 against 64 rows 54 / 56
+  // us with 64 / 128-row tiles, 97 rows 74 / 71.
+  if (passes) {
+    if (passes == 1 && r <= 28) return with_chunk(TileShape{32, 128});
+    if (r <= 52) return with_chunk(TileShape{64, 128});
+  }
+  GemmChoice best = {swiglu ? TileShape{256, 128} : TileShape{256, 256}, 0};
+  // (loads less even than assumed cost the large tiles more, hence the 10 %)
+  double cost = 1.1 * gemm_cost(L, epilogue, best.tile, 0);
+  for (int bm = 128; bm >= 64; bm -= 64) {
+    if (bm == 64 && (passes || epilogue == EPI_STORE_F32)) break;
+    const GemmChoice c = with_chunk(swiglu ? TileShape{bm, 64} : TileShape{bm, 128});
+    const double mine = gemm_cost(L, epilogue, c.tile, c.kchunk / 64);
+    if (mine < cost) {
+      cost = mine;
+      best = c;
+    }
+  }
+  return best;
 }
 
+namespace {
 // The epilogue fixes the operand layout: forward GEMMs are K-contiguous on both sides, data gradients read
 // the weights as [K, N], weight gradients read both activations token-major; split-K partial sums of a forward GEMM
 // (EPI_STORE_F32 with LAYOUT_TN) are the one exception.
+template <typename T>
+hipError_t launch_block(int epilogue, int layout, TileShape t, const GemmPlan* plan, int accumulate, int save_pre,
+                        int64_t max_tiles, hipStream_t s) {
+  switch (epilogue) {
+    case EPI_STORE: return run_block_tile<T, EPI_STORE, LAYOUT_TN>(t, plan, accumulate, save_pre, max_tiles, s);
+    case EPI_SWIGLU: return run_block_tile<T, EPI_SWIGLU, LAYOUT_TN>(t, plan, accumulate, save_pre, max_tiles, s);
+    case EPI_SWIGLU_BWD: return run_block_tile<T, EPI_SWIGLU_BWD, LAYOUT_B_KN>(t, plan, accumulate, save_pre, max_tiles, s);
+    case EPI_STORE_DUALK: return run_block_tile<T, EPI_STORE_DUALK, LAYOUT_B_KN>(t, plan, accumulate, save_pre, max_tiles, s);
+    case EPI_STORE_F32:
+      if (layout == LAYOUT_B_KN) return run_block_tile<T, EPI_STORE_F32, LAYOUT_B_KN>(t, plan, accumulate, save_pre, max_tiles, s);
+      if (layout == LAYOUT_TN) return run_block_tile<T, EPI_STORE_F32, LAYOUT_TN>(t, plan, accumulate, save_pre, max_tiles, s);
+      return run_block_tile<T, EPI_STORE_F32, LAYOUT_AB_K>(t, plan, accumulate, save_pre, max_tiles, s);
+  }
+  return hipErrorInvalidValue;
+}
+}  // namespace
+
 hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int accumulate,
                                int save_pre, int64_t max_tiles, hipStream_t s, int layout) {
-  const bool split_k = epilogue == EPI_STORE_F32 && layout == LAYOUT_TN;
-  if (dt == MODSE_F32) {
-    if (split_k) return run_block_tile<float, EPI_STORE_F32, LAYOUT_TN>(t, plan, accumulate, save_pre, max_tiles, s);
-    switch (epilogue) {
-      case EPI_STORE: return run_block_tile<float, EPI_STORE, LAYOUT_TN>(t, plan, accumulate, save_pre, max_tiles, s);
-      case EPI_SWIGLU: return run_block_tile<float, EPI_SWIGLU, LAYOUT_TN>(t, plan, accumulate, save_pre, max_tiles, s);
-      case EPI_SWIGLU_BWD: return run_block_tile<float, EPI_SWIGLU_BWD, LAYOUT_B_KN>(t, plan, accumulate, save_pre, max_tiles, s);
-      case EPI_STORE_DUALK: return run_block_tile<float, EPI_STORE_DUALK, LAYOUT_B_KN>(t, plan, accumulate, save_pre, max_tiles, s);
-      case EPI_STORE_F32: return run_block_tile<float, EPI_STORE_F32, LAYOUT_AB_K>(t, plan, accumulate, save_pre, max_tiles, s);
-    }
-    return hipErrorInvalidValue;
-  }
-  const bool skinny = t.bm == 64;
-  if (split_k) {
-    if (skinny) return run_bf16<64, 512, 1, 1, 8, EPI_STORE_F32, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
-    return run_bf16<256, 256, 1, 4, 2, EPI_STORE_F32, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
-  }
+  if (dt == MODSE_F32) return launch_block<float>(epilogue, layout, t, plan, accumulate, save_pre, max_tiles, s);
+  if (t.bm <= 128 && t.bn <= 128) return launch_block<bf16_t>(epilogue, layout, t, plan, accumulate, save_pre, max_tiles, s);
   switch (epilogue) {
     case EPI_STORE:
-      if (skinny) return run_bf16<64, 512, 1, 1, 8, EPI_STORE, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
       return run_bf16<256, 256, 1, 4, 2, EPI_STORE, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
     case EPI_SWIGLU:
-      if (skinny) return run_bf16<64, 256, 2, 1, 8, EPI_SWIGLU, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
       return run_bf16<256, 128, 2, 4, 2, EPI_SWIGLU, LAYOUT_TN>(plan, accumulate, save_pre, max_tiles, s);
     case EPI_SWIGLU_BWD:
       return run_bf16<256, 256, 1, 4, 2, EPI_SWIGLU_BWD, LAYOUT_B_KN>(plan, accumulate, save_pre, max_tiles, s);

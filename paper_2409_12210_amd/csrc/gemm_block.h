@@ -1,10 +1,10 @@
-// Grouped GEMM with small tiles for gfx950: 128 x 128 or 64 x 64 tiles, one per workgroup of four waves, float32 and
-// bf16, every layout and epilogue of the layer.
+// Grouped GEMM with small tiles for gfx950: 128 x 128 down to 32 x 128 tiles, one per workgroup of four waves, float32
+// and bf16, every layout and epilogue of the layer.
 //
 // Where the 256 x 256 kernel of gemm_bf16.h wants tall problems (one workgroup per CU, a ring of five panels), this one
-// serves problems that do not fill such tiles: the workgroup is small enough (two LDS stages, 64 KiB for a 128 x 128
-// tile) that two of them share a CU, so one multiplies while the other waits at its barrier or stores its result, and
-// the tiles are numerous enough to go round.  The grid has one workgroup per tile; workgroups beyond the tile list
+// serves problems that do not fill such tiles: the workgroup is small enough (80 KiB of LDS) that two of them share a
+// CU, so one multiplies while the other waits at its barrier or stores its result, and the tiles are numerous enough to
+// go round.  The grid has one workgroup per tile; workgroups beyond the tile list
 // (its length is known on the device only) leave at once.
 //
 // An LDS row of a K-contiguous operand is 128 bytes whatever the element type: 64 bf16 or 32 float32 along K, which is
@@ -16,6 +16,16 @@
 // An operand stored [K, X] keeps its memory order in LDS; bf16 fragments are read with ds_read_b64_tr_b16 (16-byte chunk
 // index XOR-ed so that the four K rows a read covers start in different banks), float32 ones with 32-bit reads: the
 // float32 matrix instruction takes 64 cycles, so LDS has time to spare.
+//
+// bf16 at few rows per expert is bound by the weight stream, so what counts is bytes in flight: LDS is a ring of as many
+// operand panels as fit (five of 16 KiB for 128 x 128, four stages of 20 KiB for 32 x 128), refilled one step behind the
+// reads, with counted waits.  Weights that meet one row block are loaded with the non-temporal hint: they are read once,
+// and behind a backward pass, whose weight gradients have just filled the caches, the up-projection of 130 tokens took
+// 143 us without and 83 with it (with it, weights that several row blocks read were slower: 117 -> 160 us at 600 tokens).
+// At d = 2048, eight experts of mean width 5632, in place of 256-row tiles (up / down + combine): 100 tokens 109 / 165 ->
+// 68 / 49 us, 389 tokens 117 / 170 -> 92 / 68; at d = 4096, one token, in place of 64-row tiles of 512 columns that left
+// half of the CUs without one: 131 / 79 -> 72 / 51 us, 5.6 TB/s.  At many rows it is bound by LDS reads and load issue
+// (0.87 PFLOP/s against 1.1 to 1.2 of the 256 x 256 kernel): gemm_choice picks.
 //
 // float32 is bound by the matrix pipe (157 TFLOP/s; a library product of 8192^3 reaches 153).  Measured in place of
 // vector-FMA tiles of 64 x 64 x 16: the five GEMMs of a training step at d = 1024, 4096 tokens, 8 experts of mean width
@@ -35,22 +45,28 @@ __device__ inline int tile_of_workgroup(int b) {
 }
 
 // BN: columns of C per tile.  NB = 2: two B matrices that share A (the up-projection's W1 and W3), BN columns of each.
-template <typename T, int BM, int BN, int NB, int EPI, int LAYOUT>
+template <typename T, int BM, int BN, int NB, int WAVES_M, int WAVES_N, int NSLOT, int EPI, int LAYOUT>
 __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int accumulate, int save_pre) {
   constexpr int ES = sizeof(T), CE = 16 / ES, BK = 128 / ES;
   constexpr bool A_T = (LAYOUT & 1) != 0, B_T = (LAYOUT & 2) != 0, F32 = ES == 4;
   constexpr int BR = NB * BN;               // B rows of a stage
   constexpr int STAGE = (BM + BR) * 128;
-  constexpr int UA = BM / 32, UB = BR / 32; // 1 KiB load units per wave and step
-  constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 32, NI = WN / 32;
-  static_assert(BM % 64 == 0 && BN % 64 == 0, "2 x 2 waves, wave tiles of 32 x 32 blocks");
+  constexpr int NW = WAVES_M * WAVES_N;
+  constexpr int UA = BM / 8 / NW, UB = BR / 8 / NW;  // 1 KiB load units per wave and step
+  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, MI = WM / 32, NI = WN / 32;
+  static_assert(BM % (32 * WAVES_M) == 0 && BN % (32 * WAVES_N) == 0 && UA >= 1, "wave tiles of 32 x 32 blocks");
   static_assert(!(B_T && NB != 1), "a [K, N] operand is a single matrix");
-  static_assert(STAGE / 4 >= 4096, "epilogue: 4 KiB of a stage per wave");
-  __shared__ __attribute__((aligned(1024))) char stages[2 * STAGE];
+  // Panels are numbered in the order in which they are loaded: 2 g is step g's B panel, 2 g + 1 its A panel.  Panel i lies
+  // in slot i mod NSLOT.  Panels of different sizes come in whole stages (an even NSLOT).
+  constexpr bool EQUAL = BM == BR;
+  static_assert(EQUAL || NSLOT % 2 == 0, "panels of different sizes: whole stages");
+  static_assert((NSLOT % 2 == 0 ? STAGE : BM * 128) >= NW * 4096, "epilogue: 4 KiB per wave in the slots of one step");
+  __shared__ __attribute__((aligned(1024))) char ring[EQUAL ? NSLOT * BM * 128 : NSLOT / 2 * STAGE];
+  auto slot_byte = [](int slot) { return EQUAL ? slot * (BM * 128) : (slot >> 1) * STAGE + (slot & 1) * (BR * 128); };
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   const int tile = tile_of_workgroup(blockIdx.x);
   // the tile's problem: the last one that starts at or before it (every lane looks at one entry of the list)
   const int n_prob = plan->n_prob;
@@ -71,7 +87,7 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   }
   const int nk = (K + BK - 1) / BK;
   const int nsteps = (EPI == EPI_STORE_DUALK) ? 2 * nk : nk;
-  const uint32_t lds_base = __builtin_amdgcn_readfirstlane(lds_address(stages));
+  const uint32_t lds_base = __builtin_amdgcn_readfirstlane(lds_address(ring));
 
   // ---- loads.  Which 16-byte chunk a lane fetches is chosen so that the data lands swizzled: unit u of a K-contiguous
   // panel is rows 8u .. 8u+7; of a [K, X] panel 1024 / (X * ES) rows of K.
@@ -103,36 +119,40 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   const bool second = NB == 2 && wave * UB * 8 >= BN;  // this wave's B units belong to the second matrix
   const char* sa = static_cast<const char*>(uniform_ptr(P.A() + a_org));
   const char* sb = static_cast<const char*>(uniform_ptr((second ? P.B2() : P.B()) + b_org));
-  int kstep = 0, pass = 0;
-  auto issue = [&](int buf) {
-    const uint32_t da = lds_base + buf * STAGE + wave * UA * 1024, db = lds_base + buf * STAGE + BM * 128 + wave * UB * 1024;
-    auto fetch = [&](const char* s, off_t_ off, uint32_t dst) {
-      if constexpr (F32) dma_b128(s + off, dst);
-      else dma_b128_s(s, off, dst);
-    };
-    if ((kstep + 1) * BK <= K) {
+  // weights that meet a single row block are read once in the whole launch
+  const bool stream_b = !A_T && P.mtiles() == 1;
+  // the loads of one operand's next panel into ring slot `slot`; the operand then moves on to its next K step
+  struct Walk {
+    int step = 0, kstep = 0;  // of all steps; of this pass
+  } wa, wb;
+  auto issue = [&](auto is_a, Walk& w, const char*& src, int slot) {
+    constexpr bool IS_A = decltype(is_a)::value;
+    constexpr int U = IS_A ? UA : UB;
+    if (w.step >= nsteps) return;
+    const uint32_t dst = lds_base + slot_byte(slot) + wave * U * 1024;
+    auto off = [&](int i) { if constexpr (IS_A) return offa[i]; else return offb[i]; };
+    auto kfirst = [&](int i) { if constexpr (IS_A) return ka[i]; else return kb[i]; };
+    if ((w.kstep + 1) * BK <= K) {
 #pragma unroll
-      for (int i = 0; i < UA; ++i) fetch(sa, offa[i], da + i * 1024);
-#pragma unroll
-      for (int i = 0; i < UB; ++i) fetch(sb, offb[i], db + i * 1024);
+      for (int i = 0; i < U; ++i) {
+        if constexpr (F32) dma_b128(src + off(i), dst + i * 1024);
+        else if (!IS_A && stream_b) dma_b128_s<true>(src, off(i), dst + i * 1024);
+        else dma_b128_s(src, off(i), dst + i * 1024);
+      }
     } else {  // the last step of a pass: what lies beyond K reads zeros
-      const char* zero = reinterpret_cast<const char*>(g_zero_chunk);
 #pragma unroll
-      for (int i = 0; i < UA; ++i) dma_b128(kstep * BK + ka[i] < K ? sa + offa[i] : zero, da + i * 1024);
-#pragma unroll
-      for (int i = 0; i < UB; ++i) dma_b128(kstep * BK + kb[i] < K ? sb + offb[i] : zero, db + i * 1024);
+      for (int i = 0; i < U; ++i)
+        dma_b128(w.kstep * BK + kfirst(i) < K ? src + off(i) : reinterpret_cast<const char*>(g_zero_chunk), dst + i * 1024);
     }
-    sa += a_step;
-    sb += b_step;
-    if (EPI == EPI_STORE_DUALK && ++kstep == nk && pass == 0) {
-      pass = 1;
-      kstep = 0;
-      sa = static_cast<const char*>(uniform_ptr(P.A2() + a_org));
-      sb = static_cast<const char*>(uniform_ptr(P.B2() + b_org));
-    } else if (EPI != EPI_STORE_DUALK) {
-      ++kstep;
+    src += IS_A ? a_step : b_step;
+    ++w.step;
+    if (++w.kstep == nk && EPI == EPI_STORE_DUALK) {
+      w.kstep = 0;
+      src = static_cast<const char*>(uniform_ptr((IS_A ? P.A2() : P.B2()) + (IS_A ? a_org : b_org)));
     }
   };
+  auto issue_a = [&](int slot) { issue(std::true_type{}, wa, sa, slot); };
+  auto issue_b = [&](int slot) { issue(std::false_type{}, wb, sb, slot); };
 
   // ---- fragments: K slice kk (two chunks of every row)
   typedef std::conditional_t<F32, f32x4, bf16x8> frag_t;
@@ -161,13 +181,13 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
     }
   };
   frag_t af[2][MI], bf[2][NB][NI];
-  auto load_frags = [&](const char* st, int kk, int set) {
+  auto load_frags = [&](const char* pa, const char* pb, int kk, int set) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i) af[set][i] = load_frag(A_T, st, BM, wm * WM + i * 32, kk);
+    for (int i = 0; i < MI; ++i) af[set][i] = load_frag(A_T, pa, BM, wm * WM + i * 32, kk);
 #pragma unroll
     for (int q = 0; q < NB; ++q)
 #pragma unroll
-      for (int j = 0; j < NI; ++j) bf[set][q][j] = load_frag(B_T, st + BM * 128, BN, q * BN + wn * WN + j * 32, kk);
+      for (int j = 0; j < NI; ++j) bf[set][q][j] = load_frag(B_T, pb, BN, q * BN + wn * WN + j * 32, kk);
   };
   f32x16 acc[NB][MI][NI];
 #pragma unroll
@@ -201,23 +221,41 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
     }
   };
 
-  if (nsteps > 0) issue(0);
+#pragma unroll
+  for (int i = 0; i < NSLOT - 2; ++i) {
+    if (i % 2 == 0) issue_b(i);
+    else issue_a(i);
+  }
+  int rb = 0;  // slot of step g's B panel; its A panel is in the next one
+  auto slot_add = [](int slot, int d) { return slot + d >= NSLOT ? slot + d - NSLOT : slot + d; };
 #pragma unroll 1
   for (int g = 0; g < nsteps; ++g) {
-    // my loads of step g have landed and my LDS reads of step g-1 have returned; then everybody meets: the stage of
-    // step g may be read and the other one refilled
+    // my loads of step g have landed (those of the NSLOT - 4 panels behind it may still be on their way; s_waitcnt simm16:
+    // vmcnt in bits [3:0] and [15:14]) and my LDS reads of step g - 1 have returned; then everybody meets: the panels of
+    // step g may be read and those of step g - 1 refilled
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+    constexpr int AHEAD = (NSLOT - 4) / 2 * UA + (NSLOT - 3) / 2 * UB;
+    static_assert(AHEAD < 64, "vmcnt field");
+    if (2 * g + NSLOT - 2 <= 2 * nsteps) __builtin_amdgcn_s_waitcnt(0x0070 | (AHEAD & 15) | (AHEAD >> 4) << 14);  // lgkmcnt(0)
+    else __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    const char* st = stages + (g & 1) * STAGE;
-    load_frags(st, 0, 0);
-    if (g + 1 < nsteps) issue((g + 1) & 1);
+    const char* pb = ring + slot_byte(rb);
+    const char* pa = ring + slot_byte(slot_add(rb, 1));
+    load_frags(pa, pb, 0, 0);
+    if constexpr (NSLOT % 2 == 0) {
+      issue_b(slot_add(rb, NSLOT - 2));
+      issue_a(slot_add(rb, NSLOT - 1));
+    } else {
+      issue_a(slot_add(rb, NSLOT - 2));
+      issue_b(slot_add(rb, NSLOT - 1));
+    }
+    rb = slot_add(rb, 2);
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      if (kk < 3) load_frags(st, kk + 1, (kk + 1) & 1);
+      if (kk < 3) load_frags(pa, pb, kk + 1, (kk + 1) & 1);
       mfma_slice(kk & 1);
     }
   }
@@ -225,13 +263,13 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
 
   // ---- epilogue.  For register group r of block (i, j) the lane holds columns 8 r + 4 khalf .. + 3 of row lane & 31.
   // A wave stages units of 32 rows x 128 bytes (64 for a 32-column bf16 tile) through LDS, so that global memory sees
-  // whole lines: written in accumulator order, read back row-wise.  The staging area is this wave's quarter of the
-  // stage that step nsteps - 1 did not use: nobody reads it any more.
+  // whole lines: written in accumulator order, read back row-wise.  The staging area lies in the slots that the step
+  // after the last one would use: nobody reads them any more and no load is on its way into them.
   typedef std::conditional_t<F32 || EPI == EPI_STORE_F32, float, bf16_t> out_t;
   constexpr int OS = sizeof(out_t), UC = OS == 4 ? 32 : (WN < 64 ? WN : 64);  // columns of a unit
   constexpr int CPR = UC * OS / 16, ITS = 32 * CPR / 64, NJU = WN / UC, JPU = UC / 32;
   typedef std::conditional_t<OS == 4, f32x4, bf16x8> chunk_t;
-  char* const slot = stages + (nsteps & 1) * STAGE + wave * (STAGE / 4);
+  char* const slot = ring + slot_byte(rb) + wave * 4096;
   const int er = lane & 31, esw = (er >> 1) & 7;
   const int ldc = P.ldc();
   auto stage = [&](auto value) {  // value(jj, idx): element idx of the accumulator of the unit's block jj
@@ -350,12 +388,25 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
 
 template <int BM, int BN, int NB, int EPI, int LAYOUT>
 __global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GemmPlan* __restrict__ plan, int accumulate, int save_pre) {
-  gg_block<float, BM, BN, NB, EPI, LAYOUT>(plan, accumulate, save_pre);
+  gg_block<float, BM, BN, NB, 2, 2, 4, EPI, LAYOUT>(plan, accumulate, save_pre);
 }
-template <int BM, int BN, int NB, int EPI, int LAYOUT>
-__global__ __launch_bounds__(256, 2) void gg_bf16_block_kernel(const GemmPlan* __restrict__ plan, int accumulate,
-                                                              int save_pre) {
-  gg_block<bf16_t, BM, BN, NB, EPI, LAYOUT>(plan, accumulate, save_pre);
+// as many ring slots as leave room for eight waves per CU
+constexpr int ring_slots(int bm, int br, int waves) {
+  const int lds = 160 * 1024 / 8 * waves;
+  return bm == br ? lds / (bm * 128) : lds / ((bm + br) * 128) * 2;
+}
+template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT>
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_block_kernel(const GemmPlan* __restrict__ plan,
+                                                                               int accumulate, int save_pre) {
+  gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, ring_slots(BM, NB * BN, WAVES_M * WAVES_N), EPI, LAYOUT>(plan, accumulate,
+                                                                                                      save_pre);
+}
+// tiles of 32 or 64 rows (decode-sized batches and experts with few tokens), under a name of their own for profiles
+template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT>
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_skinny_kernel(const GemmPlan* __restrict__ plan,
+                                                                                int accumulate, int save_pre) {
+  gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, ring_slots(BM, NB * BN, WAVES_M * WAVES_N), EPI, LAYOUT>(plan, accumulate,
+                                                                                                      save_pre);
 }
 
 }  // namespace modse_gemm

@@ -36,6 +36,10 @@ __device__ inline void finish_plan(GemmPlan* plan, int i, int n, int* s_tiles) {
 __device__ inline const char* cadd(const void* p, size_t bytes) { return static_cast<const char*>(p) + bytes; }
 __device__ inline char* vadd(void* p, size_t bytes) { return p ? static_cast<char*>(p) + bytes : nullptr; }
 
+// Length (whole K steps) of the nchunk chunks that K = f is cut into: about equal ones.  (The last may be short or even
+// empty; an empty one writes a slab of zeros.)
+__device__ inline int balanced_chunk(int f, int nchunk) { return ((f + nchunk - 1) / nchunk + 63) / 64 * 64; }
+
 // Problem tables of the two forward GEMMs.  Every thread of one block calls this (threads beyond the expert count
 // only take part in the barriers); s_tiles: MODSE_MAX_PROBLEMS ints of LDS.
 __device__ inline void plan_fwd_body(const LayerDims& L, int esize, const int32_t* counts, const int32_t* offsets,
@@ -68,13 +72,14 @@ __device__ inline void plan_fwd_body(const LayerDims& L, int esize, const int32_
     for (int q = 0; q < L.N; ++q) total += (L.f[q] + a.kchunk - 1) / a.kchunk;
     if (on) {
       const int nchunk = (f + a.kchunk - 1) / a.kchunk;
+      const int len = balanced_chunk(f, nchunk);
       for (int c = 0; c < nchunk; ++c) {
-        const int k0 = c * a.kchunk;
+        const int k0 = min(c * len, f);
         GemmProblem P = {};
         P.A = cadd(a.H, (hoff + k0) * es);
         P.B = cadd(a.W2, ((size_t)L.foff[e] * d + k0) * es);
         P.C = a.Opart + ((size_t)c * L.T * L.k + offsets[e]) * d;
-        P.M = n_e; P.N = d; P.K = min(a.kchunk, f - k0);
+        P.M = n_e; P.N = d; P.K = min(len, f - k0);
         P.lda = f; P.ldb = f; P.ldc = d;
         s_tiles[first + c] = set_tiles(P, a.down_tile.bm, a.down_tile.bn);
         a.down->prob[first + c] = P;

@@ -1232,14 +1232,29 @@ __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ O, i
   }
 }
 
+// acc[0..7] = the sum of n slabs at src, added in ascending order
+__device__ inline void sum_slabs8(const float* src, size_t slab, int n, float acc[8]) {
+#pragma unroll
+  for (int q = 0; q < 8; ++q) acc[q] = 0.f;
+#pragma unroll 4
+  for (int s = 0; s < n; ++s) {
+    float v[8];
+    load8(src + s * slab, v);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[q] += v[q];
+  }
+}
+
 // Combine after a split-K down-projection: expert e's output rows are the sum of ceil(f_e / kchunk) float32
-// partial slabs Opart[c] ([T*k, d] each), added in ascending c.  One thread per token and 8 columns.
+// partial slabs Opart[c] ([T*k, d] each), added in ascending c.  One thread per token and 8 columns.  O (may be null)
+// receives the summed rows.
 template <typename T>
 __global__ __launch_bounds__(256) void combine_split_kernel(const float* __restrict__ Opart, int ntok, int d,
                                                             int top_k, LayerDims L, int kchunk,
                                                             const int32_t* __restrict__ topk_idx,
                                                             const int32_t* __restrict__ row_of,
-                                                            const float* __restrict__ topk_w, T* __restrict__ y) {
+                                                            const float* __restrict__ topk_w, T* __restrict__ O,
+                                                            T* __restrict__ y) {
   const int per_tok = d / 8;
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
   if (i >= (long)ntok * per_tok) return;
@@ -1250,23 +1265,31 @@ __global__ __launch_bounds__(256) void combine_split_kernel(const float* __restr
   for (int q = 0; q < 8; ++q) o[q] = 0.f;
   for (int j = 0; j < top_k; ++j) {
     const int e = topk_idx[(size_t)t * top_k + j];
-    const float* src = Opart + (size_t)row_of[(size_t)t * top_k + j] * d + c;
+    const size_t at = (size_t)row_of[(size_t)t * top_k + j] * d + c;
     const float g = topk_w[(size_t)t * top_k + j];
-    const int nchunk = (L.f[e] + kchunk - 1) / kchunk;
     float acc[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] = 0.f;
-#pragma unroll 4
-    for (int s = 0; s < nchunk; ++s) {
-      float v[8];
-      load8(src + s * slab, v);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[q] += v[q];
-    }
+    sum_slabs8(Opart + at, slab, (L.f[e] + kchunk - 1) / kchunk, acc);
+    if (O) store8(O + at, acc);
 #pragma unroll
     for (int q = 0; q < 8; ++q) o[q] = fmaf(g, acc[q], o[q]);
   }
   store8(y + (size_t)t * d + c, o);
+}
+
+// One thread per permuted row and 8 columns.
+template <typename T>
+__global__ __launch_bounds__(256) void sum_slabs_kernel(const float* __restrict__ slabs, int nrows, int d, LayerDims L,
+                                                        int kchunk, int passes, const int32_t* __restrict__ topk_idx,
+                                                        const int32_t* __restrict__ src_of, T* __restrict__ out) {
+  const int per_row = d / 8;
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (long)nrows * per_row) return;
+  const int r = (int)(i / per_row), c = (int)(i % per_row) * 8;
+  const int e = topk_idx[src_of[r]];
+  const size_t at = (size_t)r * d + c;
+  float acc[8];
+  sum_slabs8(slabs + at, (size_t)nrows * d, passes * ((L.f[e] + kchunk - 1) / kchunk), acc);
+  store8(out + at, acc);
 }
 
 // Backward of the combine: for permuted row r = (token t, slot j):
@@ -1699,14 +1722,26 @@ hipError_t launch_combine(const LayerDims& L, modse_dtype dt, const void* O, con
 }
 
 hipError_t launch_combine_split(const LayerDims& L, modse_dtype dt, const float* Opart, int kchunk, const RoutingPtrs& R,
-                                void* y, hipStream_t s) {
+                                void* O, void* y, hipStream_t s) {
   const int nb = (int)(((long)L.T * (L.d / 8) + 255) / 256);
   if (dt == MODSE_F32)
     hipLaunchKernelGGL((combine_split_kernel<float>), dim3(nb), dim3(256), 0, s, Opart, L.T, L.d, L.k, L, kchunk,
-                       R.topk_idx, R.row_of, R.topk_w, static_cast<float*>(y));
+                       R.topk_idx, R.row_of, R.topk_w, static_cast<float*>(O), static_cast<float*>(y));
   else
     hipLaunchKernelGGL((combine_split_kernel<bf16_t>), dim3(nb), dim3(256), 0, s, Opart, L.T, L.d, L.k, L, kchunk,
-                       R.topk_idx, R.row_of, R.topk_w, static_cast<bf16_t*>(y));
+                       R.topk_idx, R.row_of, R.topk_w, static_cast<bf16_t*>(O), static_cast<bf16_t*>(y));
+  return hipGetLastError();
+}
+
+hipError_t launch_sum_slabs(const LayerDims& L, modse_dtype dt, const float* slabs, int kchunk, int passes,
+                            const RoutingPtrs& R, void* out, hipStream_t s) {
+  const int nrows = L.T * L.k, nb = (int)(((long)nrows * (L.d / 8) + 255) / 256);
+  if (dt == MODSE_F32)
+    hipLaunchKernelGGL((sum_slabs_kernel<float>), dim3(nb), dim3(256), 0, s, slabs, nrows, L.d, L, kchunk, passes,
+                       R.topk_idx, R.src_of, static_cast<float*>(out));
+  else
+    hipLaunchKernelGGL((sum_slabs_kernel<bf16_t>), dim3(nb), dim3(256), 0, s, slabs, nrows, L.d, L, kchunk, passes,
+                       R.topk_idx, R.src_of, static_cast<bf16_t*>(out));
   return hipGetLastError();
 }
 

@@ -15,6 +15,14 @@ CASES = [
     ("f32_tiles_128", 544, WIDE, 6205, "f32", 2),
     ("f32_tiles_64", 160, (32, 96, 224, 160), 259, "f32", 2),       # 64 x 64 tiles, one row past two of them
     ("f32_one_row", 64, (32, 96), 1, "f32", 1),
+    # bf16: 32-row tiles with K split into chunks (widths of 1 ... 4 chunks, the last ones ragged), one row to all 64 of a
+    # tile's upper bound; 64- and 128-row tiles, split; 128-row tiles, unsplit, experts one row past a block
+    ("bf16_one_row", 96, (32, 2720), 1, "bf16", 2),
+    ("bf16_rows_32", 96, (2720, 32, 1312, 640), 64, "bf16", 2),
+    ("bf16_rows_64", 160, (4128, 2048, 1952, 672), 97, "bf16", 2),
+    ("bf16_rows_128", 224, (4128, 96, 3104, 2016), 250, "bf16", 2),
+    ("bf16_rows_129", 288, (96, 160, 224, 288) * 4, 1033, "bf16", 2),
+    ("bf16_few_rows_many_experts", 64, (32,) * 64, 200, "bf16", 1),
 ]
 
 
@@ -33,3 +41,24 @@ def test_fwd_and_grads(case):
     r.bwd(accumulate=True)
     assert max_rel(to_host(r.dW1), 2 * g.dW1) <= TOL[dtype]
     assert max_rel(to_host(r.dW2), 2 * g.dW2) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("T", [40, 250])
+def test_workspace_without_room_for_partial_sums(T):
+    """A workspace that lacks the partial sums of the split products (one made for a batch that does not split) serves all
+    the same, unsplit, with results inside the same tolerance."""
+    import torch
+    import paper_2409_12210_amd as m
+    from paper_2409_12210_amd.harness import to_host
+    d_ff, k = (4128, 96, 3104, 2016), 2
+    inp = make("short_ws", 96, d_ff, T, "bf16", k, need_dy=True)
+    r = _runner(inp, need_bwd=True)
+    full = [m.modse_workspace_size(96, d_ff, k, "bf16", T, w) for w in (m.WS_FWD_SAVED, m.WS_BWD)]
+    slab = T * k * 96 * 4
+    for call, nbytes in ((r.fwd, full[0]), (r.bwd, full[1])):
+        r.ws = torch.empty(nbytes - slab, dtype=torch.uint8, device="cuda")
+        call()
+    idx, _ = check_routing(inp, r.routing_host())
+    y_ref = orc.layer_fwd(inp.x, inp.W_gate, inp.W1, inp.W3, inp.W2, d_ff, k, topk_idx=idx)
+    assert max_rel(to_host(r.y), y_ref) <= TOL["bf16"]
+    check_grads(r, inp, idx, TOL["bf16"])
