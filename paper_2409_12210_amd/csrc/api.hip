@@ -496,7 +496,6 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   const void* Xp = sb + sl.Xp;
   void* dO = wsb + w.dO;
   float* dg = reinterpret_cast<float*>(wsb + w.dg);
-  HIP_TRY(launch_bwd_prep(L, dt, dY, sb + sl.O, R, dO, dg, s));
   BwdPlanArgs pa;
   std::memset(&pa, 0, sizeof(pa));
   pa.Xp = Xp; pa.dO = dO; pa.H = sb + sl.H; pa.dHdA = sb + sl.dHdA; pa.dHdB = sb + sl.dHdB;
@@ -511,7 +510,7 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   pa.dh_tile = gemm_choice(L, dt, EPI_SWIGLU_BWD).tile;
   pa.dx_tile = w.dx.tile;
   pa.wg_tile = gemm_choice(L, dt, EPI_STORE_F32).tile;
-  HIP_TRY(launch_plan_bwd(L, dt, R.counts, R.offsets, pa, s));
+  HIP_TRY(launch_bwd_prep(L, dt, dY, sb + sl.O, R, dO, dg, pa, s));
   stamp.mark(MODSE_STAGE_BWD_PREP);
 
   HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU_BWD, pa.dh_tile, pa.dh, 0, 0, tiles_bound(L, pa.dh_tile, true), s));

@@ -7,7 +7,7 @@
 
 #define MODSE_MAX_EXPERTS 64
 #define MODSE_MAX_PROBLEMS (3 * MODSE_MAX_EXPERTS)  // the three weight-gradient GEMMs share one launch
-#define MODSE_PERMUTE_SMALL_MAX_T 64      // batches up to this size take the fused permute + plan launch
+#define MODSE_PERMUTE_FUSED_MAX_T 4096    // batches up to this size take the fused permute + plan launch
 #define MODSE_ROUTE_TOKENS_PER_BLOCK 32  // tokens handled by one block of the router / scatter kernels
 
 typedef __bf16 bf16_t;
@@ -158,7 +158,7 @@ hipError_t launch_router(const LayerDims& L, modse_dtype dt, const void* x, cons
                          const RoutingPtrs& R, const RouteBufs& B, const GateExtPtrs* G, hipStream_t s);
 struct FwdPlanArgs;
 // plan != null: the scan launch also makes the tile plans of the two forward GEMMs (batches of at most
-// MODSE_PERMUTE_SMALL_MAX_T tokens do all of this in one launch)
+// MODSE_PERMUTE_FUSED_MAX_T tokens do all of this in one launch)
 hipError_t launch_permute(const LayerDims& L, modse_dtype dt, const void* x, const RoutingPtrs& R, const RouteBufs& B,
                           void* Xp, const GateExtPtrs* G, const FwdPlanArgs* plan, hipStream_t s);
 hipError_t launch_route(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const float* bias,
@@ -173,8 +173,10 @@ hipError_t launch_combine_split(const LayerDims& L, modse_dtype dt, const float*
 // out[r] = sum over the slabs of row r's expert, passes * ceil(f_e / kchunk) of them, in ascending order
 hipError_t launch_sum_slabs(const LayerDims& L, modse_dtype dt, const float* slabs, int kchunk, int passes,
                             const RoutingPtrs& R, void* out, hipStream_t s);
+struct BwdPlanArgs;
+// backward of the combine, and the tile plans of the backward GEMMs
 hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, const void* O, const RoutingPtrs& R,
-                           void* dO, float* dg, hipStream_t s);
+                           void* dO, float* dg, const BwdPlanArgs& plan, hipStream_t s);
 struct BwdRouterBufs {  // workspace of the router's backward pass
   float* dl;           // [T, N] dense gradient of the logits
   float* du;           // [T, N] gradient of x W_noise
@@ -224,5 +226,3 @@ struct BwdPlanArgs {
   GemmPlan *dh, *dx, *wg;  // wg: dW1, dW3 and dW2 of every expert in one problem list
   TileShape dh_tile, dx_tile, wg_tile;
 };
-hipError_t launch_plan_bwd(const LayerDims& L, modse_dtype dt, const int32_t* counts, const int32_t* offsets,
-                           const BwdPlanArgs& a, hipStream_t s);

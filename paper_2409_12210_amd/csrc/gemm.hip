@@ -12,106 +12,10 @@
 #include "common.h"
 #include "gemm_bf16.h"
 #include "gemm_block.h"
-#include "gemm_plan.h"
 #include "gemm_tiles.h"
 
 namespace {
 using namespace modse_gemm;
-
-// ------------------------------------------------------------------------------------------------
-// plan kernel of the backward GEMMs (single block): device-side counts -> problem tables.  (The forward plans
-// are made by the routing stage's scan launch, see gemm_plan.h.)
-// ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void plan_bwd_kernel(LayerDims L, int esize, const int32_t* __restrict__ counts,
-                                                      const int32_t* __restrict__ offsets, BwdPlanArgs a) {
-  __shared__ int s_tiles[MODSE_MAX_PROBLEMS];
-  const int i = threadIdx.x;
-  const bool on = i < L.N;
-  const int e = on ? L.order[i] : 0;
-  size_t hoff = 0;
-  for (int q = 0; q < e; ++q) hoff += (size_t)counts[q] * L.f[q];
-  const int n_e = counts[e], f = L.f[e], d = L.d;
-  const size_t es = esize;
-  const size_t woff = (size_t)L.foff[e] * d;   // element offset of expert e in W1/W3/W2 and their gradients
-  const size_t roff = (size_t)offsets[e] * d;  // element offset of expert e's rows in [T*k, d] tensors
-  if (on) {  // dh = dO W2 (W2_e is [d, f]: a [K, N] operand), fused SwiGLU backward -> dA, dB
-    GemmProblem P = {};
-    P.A = cadd(a.dO, roff * es);
-    P.B = cadd(a.W2, woff * es);
-    P.C = vadd(a.dA, hoff * es);
-    P.C2 = vadd(a.dB, hoff * es);
-    P.E1 = cadd(a.dHdA, hoff * es);
-    P.E2 = cadd(a.dHdB, hoff * es);
-    P.M = n_e; P.N = f; P.K = d;
-    P.lda = d; P.ldb = f; P.ldc = f;
-    s_tiles[i] = set_tiles(P, a.dh_tile.bm, a.dh_tile.bn);
-    a.dh->prob[i] = P;
-  }
-  finish_plan(a.dh, i, L.N, s_tiles);
-  if (a.dx_kchunk > 0) {  // split: one problem per (expert, operand pair, chunk of K), float32 partial sums
-    int first = 0, total = 0;
-    for (int q = 0; q < L.N; ++q) {
-      const int n = 2 * ((L.f[L.order[q]] + a.dx_kchunk - 1) / a.dx_kchunk);
-      if (q < i) first += n;
-      total += n;
-    }
-    if (on) {
-      const int nchunk = (f + a.dx_kchunk - 1) / a.dx_kchunk;
-      const int len = balanced_chunk(f, nchunk);
-      for (int c = 0; c < 2 * nchunk; ++c) {
-        const int k0 = min((c % nchunk) * len, f);
-        GemmProblem P = {};
-        P.A = cadd(c < nchunk ? a.dA : a.dB, (hoff + k0) * es);
-        P.B = cadd(c < nchunk ? a.W1 : a.W3, (woff + (size_t)k0 * d) * es);
-        P.C = a.dXpart + ((size_t)c * L.T * L.k + offsets[e]) * d;
-        P.M = n_e; P.N = d; P.K = min(len, f - k0);
-        P.lda = f; P.ldb = d; P.ldc = d;
-        s_tiles[first + c] = set_tiles(P, a.dx_tile.bm, a.dx_tile.bn);
-        a.dx->prob[first + c] = P;
-      }
-    }
-    finish_plan(a.dx, i, total, s_tiles);
-  } else {
-  if (on) {  // dXp = dA W1 + dB W3 (W1_e, W3_e are [f, d]: [K, N] operands)
-    GemmProblem P = {};
-    P.A = cadd(a.dA, hoff * es);
-    P.B = cadd(a.W1, woff * es);
-    P.A2 = cadd(a.dB, hoff * es);
-    P.B2 = cadd(a.W3, woff * es);
-    P.C = vadd(a.dXp, roff * es);
-    P.M = n_e; P.N = d; P.K = f;
-    P.lda = f; P.ldb = d; P.ldc = d;
-    s_tiles[i] = set_tiles(P, a.dx_tile.bm, a.dx_tile.bn);
-    a.dx->prob[i] = P;
-  }
-  finish_plan(a.dx, i, L.N, s_tiles);
-  }
-  // Weight gradients contract over the expert's tokens, so a tile costs n_e K-steps whatever its expert's
-  // width: the three GEMMs of one expert are listed together, experts by falling token count.
-  if (on) {
-    int rank = 0;
-    for (int q = 0; q < L.N; ++q) rank += (counts[q] > n_e || (counts[q] == n_e && q < e)) ? 1 : 0;
-    for (int which = 0; which < 2; ++which) {  // dW1 = dA^T Xp, dW3 = dB^T Xp
-      GemmProblem P = {};
-      P.A = cadd(which ? a.dB : a.dA, hoff * es);  // [K = n_e, M = f]
-      P.B = cadd(a.Xp, roff * es);                  // [K = n_e, N = d]
-      P.C = (which ? a.dW3 : a.dW1) + woff;
-      P.M = f; P.N = d; P.K = n_e;
-      P.lda = f; P.ldb = d; P.ldc = d;
-      s_tiles[3 * rank + which] = set_tiles(P, a.wg_tile.bm, a.wg_tile.bn);
-      a.wg->prob[3 * rank + which] = P;
-    }
-    GemmProblem P = {};  // dW2 = dO^T H
-    P.A = cadd(a.dO, roff * es);  // [K = n_e, M = d]
-    P.B = cadd(a.H, hoff * es);   // [K = n_e, N = f]
-    P.C = a.dW2 + woff;
-    P.M = d; P.N = f; P.K = n_e;
-    P.lda = d; P.ldb = f; P.ldc = f;
-    s_tiles[3 * rank + 2] = set_tiles(P, a.wg_tile.bm, a.wg_tile.bn);
-    a.wg->prob[3 * rank + 2] = P;
-  }
-  finish_plan(a.wg, i, 3 * L.N, s_tiles);
-}
 
 int num_cus() {
   static int n = 0;
@@ -340,10 +244,4 @@ hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const 
       return run_bf16<256, 256, 1, 4, 2, EPI_STORE_F32, LAYOUT_AB_K>(plan, accumulate, save_pre, max_tiles, s);
   }
   return hipErrorInvalidValue;
-}
-
-hipError_t launch_plan_bwd(const LayerDims& L, modse_dtype dt, const int32_t* counts, const int32_t* offsets,
-                           const BwdPlanArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(plan_bwd_kernel, dim3(1), dim3(64), 0, s, L, dt == MODSE_F32 ? 4 : 2, counts, offsets, a);
-  return hipGetLastError();
 }

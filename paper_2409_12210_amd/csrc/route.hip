@@ -16,7 +16,6 @@ namespace {
 constexpr int TPB = MODSE_ROUTE_TOKENS_PER_BLOCK;  // tokens per block
 constexpr int ROUTE_THREADS = 256;
 constexpr int ROUTER_TOKEN_MAX_T = 4096;  // batches up to this size take router_token_kernel
-constexpr int TOK_PER_WAVE = TPB / (ROUTE_THREADS / 64);  // 8
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
@@ -728,7 +727,7 @@ __global__ __launch_bounds__(RW_THREADS) void router_kernel(const T* __restrict_
 // two rounds of memory latency.  Every thread leaves its G x N float64 partial sums in LDS; they are added
 // in two fixed-order steps (8 groups of 32 threads, then the 8 group sums), so the result does not depend
 // on timing; one thread per token then does top-k and gate.  The block histograms that the permutation
-// needs are made by route_hist_kernel from topk_idx and near_flag.
+// needs are counted by permute_fused_kernel from topk_idx and near_flag.
 template <typename T, int NE, int G>
 __global__ __launch_bounds__(ROUTE_THREADS, 2) void router_token_kernel(const T* __restrict__ x,
                                                                        const T* __restrict__ Wg,
@@ -860,163 +859,132 @@ __global__ __launch_bounds__(ROUTE_THREADS) void router_token_wide_kernel(const 
   }
 }
 
-// blockhist[b][0..N-1] = assignments per expert among the TPB tokens of block b, blockhist[b][N] = its
-// near-tie token count (integer atomics in LDS: the result does not depend on their order).
-__global__ __launch_bounds__(64) void route_hist_kernel(const int32_t* __restrict__ topk_idx,
-                                                        const int32_t* __restrict__ near_flag, int ntok, int N,
-                                                        int top_k, int32_t* __restrict__ blockhist) {
-  __shared__ int s_hist[MODSE_MAX_EXPERTS + 1];
-  const int tid = threadIdx.x;
-  for (int i = tid; i <= N; i += 64) s_hist[i] = 0;
-  __syncthreads();
-  const int t = blockIdx.x * TPB + tid;
-  if (tid < TPB && t < ntok) {
-    for (int j = 0; j < top_k; ++j) atomicAdd(&s_hist[topk_idx[(size_t)t * top_k + j]], 1);
-    if (near_flag[t]) atomicAdd(&s_hist[N], 1);
-  }
-  __syncthreads();
-  for (int i = tid; i <= N; i += 64) blockhist[(size_t)blockIdx.x * (N + 1) + i] = s_hist[i];
-}
-
 // Single block.  Turns blockhist[b][e] into the exclusive prefix over blocks (in place), writes counts, offsets
 // and the near-tie total and, when a forward pass follows, the tile plans of its two GEMMs (from the counts
-// still in LDS: no second launch, no round trip through memory).  Each thread owns a contiguous run of blocks.
-// Up to SCAN_EC expert columns are handled at once and a thread's blocks four at a time, so that the loads of
-// a step are all in flight together (the launch is a chain of memory latencies and nothing else); the 256 run
-// totals of a column are scanned by one wave.
-constexpr int SCAN_EC = 16, SCAN_NB = 4;
-__global__ __launch_bounds__(256) void route_scan_kernel(int32_t* __restrict__ blockhist, int nb, int N,
-                                                         int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-                                                         int32_t* __restrict__ near_tie_count, LayerDims L, int esize,
-                                                         FwdPlanArgs plan, int with_plan) {
-  __shared__ int s_part[SCAN_EC][256];
+// still in LDS: no second launch, no round trip through memory).  The launch is a chain of memory latencies and nothing
+// else.  The table lies [block][column]: a thread owns one column and a run of blocks, neighbours own neighbouring
+// columns, so that a step reads whole lines, and up to SCAN_NB blocks of a thread are loaded at once and stay in registers
+// for the second pass.  64 experts, 8192 tokens (65 columns of 256 blocks): 7 us in place of 46 with 16 columns per
+// pass; 8 experts, 16384 tokens: 7 to 11 in place of 12 to 19.
+constexpr int SCAN_THREADS = 1024, SCAN_NB = 20;
+__global__ __launch_bounds__(SCAN_THREADS) void route_scan_kernel(int32_t* __restrict__ blockhist, int nb, int N,
+                                                                  int32_t* __restrict__ counts,
+                                                                  int32_t* __restrict__ offsets,
+                                                                  int32_t* __restrict__ near_tie_count, LayerDims L,
+                                                                  int esize, FwdPlanArgs plan, int with_plan) {
+  __shared__ int s_part[SCAN_THREADS];  // [run][column]
   __shared__ int s_total[MODSE_MAX_EXPERTS + 1];
-  __shared__ int s_counts[MODSE_MAX_EXPERTS], s_offsets[MODSE_MAX_EXPERTS + 1];
-  __shared__ int s_tiles[MODSE_MAX_PROBLEMS];
+  __shared__ int s_counts[MODSE_MAX_EXPERTS], s_offsets[MODSE_MAX_EXPERTS];
+  __shared__ modse_gemm::PlanLds s_plan;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int per = (nb + 255) / 256;
-  const int b0 = min(tid * per, nb), b1 = min(b0 + per, nb);
-  const int W = N + 1;
-  for (int e0 = 0; e0 < W; e0 += SCAN_EC) {
-    const int ne = min(SCAN_EC, W - e0);
-    int sum[SCAN_EC];
+  const int W = N + 1, nrun = SCAN_THREADS / W, per = (nb + nrun - 1) / nrun;
+  const int c = tid % W, run_of = tid / W;
+  const int b0 = run_of < nrun ? min(run_of * per, nb) : nb, b1 = min(b0 + per, nb);
+  int32_t* const col = blockhist + c;
+  int v[SCAN_NB], sum = 0;
+  for (int b = b0; b < b1; b += SCAN_NB) {
 #pragma unroll
-    for (int j = 0; j < SCAN_EC; ++j) sum[j] = 0;
-    for (int b = b0; b < b1; b += SCAN_NB) {
-      int v[SCAN_NB][SCAN_EC];
+    for (int q = 0; q < SCAN_NB; ++q) v[q] = b + q < b1 ? col[(size_t)(b + q) * W] : 0;
 #pragma unroll
-      for (int q = 0; q < SCAN_NB; ++q)
-#pragma unroll
-        for (int j = 0; j < SCAN_EC; ++j)
-          v[q][j] = (b + q < b1 && j < ne) ? blockhist[(size_t)(b + q) * W + e0 + j] : 0;
-#pragma unroll
-      for (int q = 0; q < SCAN_NB; ++q)
-#pragma unroll
-        for (int j = 0; j < SCAN_EC; ++j) sum[j] += v[q][j];
-    }
-#pragma unroll
-    for (int j = 0; j < SCAN_EC; ++j) s_part[j][tid] = sum[j];
-    __syncthreads();
-    for (int j = wave; j < ne; j += 4) {  // exclusive scan of column j's 256 run totals
-      int v[4], local = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        v[i] = s_part[j][lane * 4 + i];
-        local += v[i];
-      }
-      int incl = local;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += up;
-      }
-      int run = incl - local;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        s_part[j][lane * 4 + i] = run;
-        run += v[i];
-      }
-      if (lane == 63) s_total[e0 + j] = incl;
-    }
-    __syncthreads();
-    int run[SCAN_EC];
-#pragma unroll
-    for (int j = 0; j < SCAN_EC; ++j) run[j] = s_part[j][tid];
-    for (int b = b0; b < b1; b += SCAN_NB) {  // (the near-tie column, e == N, keeps its counts)
-      int v[SCAN_NB][SCAN_EC];
-#pragma unroll
-      for (int q = 0; q < SCAN_NB; ++q)
-#pragma unroll
-        for (int j = 0; j < SCAN_EC; ++j)
-          v[q][j] = (b + q < b1 && e0 + j < N) ? blockhist[(size_t)(b + q) * W + e0 + j] : 0;
-#pragma unroll
-      for (int q = 0; q < SCAN_NB; ++q)
-#pragma unroll
-        for (int j = 0; j < SCAN_EC; ++j)
-          if (b + q < b1 && e0 + j < N) {
-            blockhist[(size_t)(b + q) * W + e0 + j] = run[j];
-            run[j] += v[q][j];
-          }
-    }
-    __syncthreads();
+    for (int q = 0; q < SCAN_NB; ++q) sum += v[q];
   }
-  if (tid == 0) {
-    int run = 0;
-    for (int e = 0; e < N; ++e) {
-      counts[e] = s_counts[e] = s_total[e];
-      offsets[e] = s_offsets[e] = run;
-      run += s_total[e];
+  if (run_of < nrun) s_part[run_of * W + c] = sum;
+  __syncthreads();
+  for (int j = wave; j < W; j += SCAN_THREADS / 64) {  // exclusive scan of column j's run totals (at most 512: W >= 2)
+    constexpr int PER = 8;
+    const int n = (nrun + 63) / 64;
+    int p[PER], local = 0, total;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int r = lane * n + i;
+      p[i] = i < n && r < nrun ? s_part[r * W + j] : 0;
+      local += p[i];
     }
-    offsets[N] = s_offsets[N] = run;
-    near_tie_count[0] = s_total[N];
+    int run = modse_gemm::wave_exclusive(local, lane, total);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int r = lane * n + i;
+      if (i < n && r < nrun) s_part[r * W + j] = run;
+      run += p[i];
+    }
+    if (lane == 0) s_total[j] = total;
+  }
+  __syncthreads();
+  if (c < N && run_of < nrun) {  // (the near-tie column, c == N, keeps its counts)
+    int run = s_part[run_of * W + c];
+    for (int b = b0; b < b1; b += SCAN_NB) {
+      if (per > SCAN_NB) {
+#pragma unroll
+        for (int q = 0; q < SCAN_NB; ++q) v[q] = b + q < b1 ? col[(size_t)(b + q) * W] : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < SCAN_NB; ++q)
+        if (b + q < b1) {
+          col[(size_t)(b + q) * W] = run;
+          run += v[q];
+        }
+    }
+  }
+  if (wave == 0) {
+    const int n = lane < N ? s_total[lane] : 0;
+    int total;
+    const int o = modse_gemm::wave_exclusive(n, lane, total);
+    if (lane < N) {
+      counts[lane] = s_counts[lane] = n;
+      offsets[lane] = s_offsets[lane] = o;
+    }
+    if (lane == 0) {
+      offsets[N] = total;
+      near_tie_count[0] = s_total[N];
+    }
   }
   if (with_plan) {
     __syncthreads();
-    modse_gemm::plan_fwd_body(L, esize, s_counts, s_offsets, plan, s_tiles);
+    modse_gemm::plan_fwd_body(L, esize, s_counts, s_offsets, plan, s_plan);
   }
 }
 
 // Auxiliary load-balance loss (Sec. 3.2 Eq. 9-12), single block: f_i = share of tokens whose first choice is
-// expert i, P_i = mean of p_i, L_a = alpha N sum_i f_i P_i.  Every thread sums its tokens in ascending
-// order and the per-thread sums are added in thread order, so the result does not depend on timing.
-__global__ __launch_bounds__(256) void aux_finish_kernel(const float* __restrict__ probs,
-                                                         const int32_t* __restrict__ topk_idx, int ntok, int N,
-                                                         int top_k, float alpha, float* __restrict__ f_out,
-                                                         float* __restrict__ P_out, float* __restrict__ loss) {
-  __shared__ float s_p[256];
-  __shared__ int s_c[256];
-  __shared__ float s_f[MODSE_MAX_EXPERTS], s_P[MODSE_MAX_EXPERTS];
+// expert i, P_i = mean of p_i, L_a = alpha N sum_i f_i P_i.  A thread sums one column over every nrow-th token (threads
+// side by side read whole lines of p, sixteen loads in flight), the threads' sums of a column are added in a fixed tree,
+// so the result does not depend on timing.  8192 tokens, 8 experts: 8 to 11 us in place of 61 to 83 with one pass over
+// all tokens per expert.
+constexpr int AUX_THREADS = 1024;
+__global__ __launch_bounds__(AUX_THREADS) void aux_finish_kernel(const float* __restrict__ probs,
+                                                                 const int32_t* __restrict__ topk_idx, int ntok, int N,
+                                                                 int top_k, float alpha, float* __restrict__ f_out,
+                                                                 float* __restrict__ P_out, float* __restrict__ loss) {
+  __shared__ float s_p[AUX_THREADS];
+  __shared__ int s_c[MODSE_MAX_EXPERTS];
   const int tid = threadIdx.x;
-  for (int e = 0; e < N; ++e) {
-    float acc = 0.f;
-    int cnt = 0;
-    for (int t = tid; t < ntok; t += 256) {
-      acc += probs[(size_t)t * N + e];
-      cnt += topk_idx[(size_t)t * top_k] == e ? 1 : 0;
-    }
-    s_p[tid] = acc;
-    s_c[tid] = cnt;
-    __syncthreads();
-    if (tid == 0) {
-      float tot = 0.f;
-      int c = 0;
-      for (int i = 0; i < 256; ++i) {
-        tot += s_p[i];
-        c += s_c[i];
-      }
-      s_P[e] = tot / (float)ntok;
-      s_f[e] = (float)c / (float)ntok;
-    }
+  if (tid < N) s_c[tid] = 0;
+  const int nrow = AUX_THREADS / N, e = tid % N, r0 = tid / N;
+  float acc = 0.f;
+  if (r0 < nrow) {
+#pragma unroll 16
+    for (int t = r0; t < ntok; t += nrow) acc += probs[(size_t)t * N + e];
+  }
+  s_p[tid] = acc;
+  __syncthreads();
+#pragma unroll 8
+  for (int t = tid; t < ntok; t += AUX_THREADS) atomicAdd(&s_c[topk_idx[(size_t)t * top_k]], 1);
+  for (int n = nrow; n > 1;) {  // rows r and r + half of the table [nrow][N]
+    const int half = (n + 1) / 2;
+    if (r0 < n - half) s_p[tid] += s_p[tid + half * N];
+    n = half;
     __syncthreads();
   }
-  if (tid < N) {
-    f_out[tid] = s_f[tid];
-    P_out[tid] = s_P[tid];
-  }
-  if (tid == 0) {
+  if (tid < 64) {
     float l = 0.f;
-    for (int e = 0; e < N; ++e) l += s_f[e] * s_P[e];
-    loss[0] = alpha * (float)N * l;
+    if (tid < N) {
+      const float P = s_p[tid] / (float)ntok, f = (float)s_c[tid] / (float)ntok;
+      f_out[tid] = f;
+      P_out[tid] = P;
+      l = f * P;
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) l += __shfl_xor(l, m, 64);
+    if (tid == 0) loss[0] = alpha * (float)N * l;
   }
 }
 
@@ -1065,10 +1033,12 @@ __global__ __launch_bounds__(ROUTE_THREADS) void scatter_kernel(const T* __restr
                                                                 const int32_t* __restrict__ offsets,
                                                                 const int32_t* __restrict__ blockbase,
                                                                 int32_t* __restrict__ row_of,
-                                                                int32_t* __restrict__ src_of, T* __restrict__ Xp) {
+                                                                int32_t* __restrict__ src_of, T* __restrict__ Xp,
+                                                                int parts) {
   __shared__ int s_row[TPB][2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int t0 = blockIdx.x * TPB;
+  const int block = blockIdx.x / parts, part = blockIdx.x % parts;  // parts: blocks that share the copies of TPB tokens
+  const int t0 = block * TPB;
   if (wave == 0) {
     const int t = t0 + lane;
     const bool valid = lane < TPB && t < ntok;
@@ -1086,23 +1056,26 @@ __global__ __launch_bounds__(ROUTE_THREADS) void scatter_kernel(const T* __restr
       if (e1 == e) r1 = rank;
     }
     if (valid) {
-      const int32_t* bb = blockbase + (size_t)blockIdx.x * (N + 1);
+      const int32_t* bb = blockbase + (size_t)block * (N + 1);
       const int row0 = offsets[e0] + bb[e0] + r0;
-      row_of[(size_t)t * top_k] = row0;
-      src_of[row0] = t * top_k;
+      if (part == 0) {
+        row_of[(size_t)t * top_k] = row0;
+        src_of[row0] = t * top_k;
+      }
       s_row[lane][0] = row0;
       if (top_k == 2) {
         const int row1 = offsets[e1] + bb[e1] + r1;
-        row_of[(size_t)t * top_k + 1] = row1;
-        src_of[row1] = t * top_k + 1;
+        if (part == 0) {
+          row_of[(size_t)t * top_k + 1] = row1;
+          src_of[row1] = t * top_k + 1;
+        }
         s_row[lane][1] = row1;
       }
     }
   }
   __syncthreads();
   if (Xp == nullptr) return;
-  for (int i = 0; i < TOK_PER_WAVE; ++i) {
-    const int tl = wave * TOK_PER_WAVE + i;
+  for (int tl = part * 4 + wave; tl < TPB; tl += parts * 4) {
     const int t = t0 + tl;
     if (t >= ntok) break;
     const int row0 = s_row[tl][0];
@@ -1116,92 +1089,123 @@ __global__ __launch_bounds__(ROUTE_THREADS) void scatter_kernel(const T* __restr
   }
 }
 
-// Decode-sized batches (at most 64 tokens): histogram, offsets, stable scatter and, when a forward pass follows,
-// the tile plans of its two GEMMs in ONE launch instead of four; at this size every launch gap shows in the
-// layer time.  One block per token.  Wave 0 of every block holds one token per lane and ranks all of them with
-// one ballot per expert (the same rows as scatter_kernel: tokens of an expert in token order); block 0 also
-// writes the routing outputs and the plans; block t copies token t's row to its permuted places.
-// Near-tie total: from near_flag (one-block-per-token router) or, when that is null, from the last column of
-// the router's block histograms.
+// Batches of at most MODSE_PERMUTE_FUSED_MAX_T tokens: histogram, offsets, stable scatter and, when a forward pass follows,
+// the tile plans of its two GEMMs in ONE launch instead of three; at these sizes a launch costs more than its work.
+// Every block counts all tokens' choices by itself (at most 32 KiB from the L2), those of the tokens before its own
+// sixteen apart from the rest, so no block waits for another.  A counter has 32 copies side by side, one per LDS bank: the
+// additions of a wave never meet.  The first block writes the routing totals and makes the plans, the others rank their
+// tokens (the same rows as scatter_kernel: tokens of an expert in token order) and copy their rows.
+// Near-tie total: from near_flag (the routers with one or four tokens per block) or, when that is null, from the last
+// column of the router's block histograms.
+// d = 2048, 389 / 2048 tokens: 7 / 11 us in place of 5 + 13 + 13 (15) and two launch gaps (blocks of 256 threads and eight
+// tokens: 8 / 15).
+constexpr int PF_TOKENS = 16, PF_THREADS = 1024;
 template <typename T>
-__global__ __launch_bounds__(256) void permute_small_kernel(const T* __restrict__ x, int ntok, int d, int N, int top_k,
+__global__ __launch_bounds__(PF_THREADS) void permute_fused_kernel(const T* __restrict__ x, int ntok, int d, int N, int top_k,
                                                             const int32_t* __restrict__ topk_idx,
                                                             const int32_t* __restrict__ near_flag,
                                                             const int32_t* __restrict__ blockhist, RoutingPtrs R,
                                                             T* __restrict__ Xp, LayerDims L, int esize,
                                                             FwdPlanArgs plan, int with_plan) {
-  __shared__ int s_row[64][2];
-  __shared__ int s_counts[MODSE_MAX_EXPERTS], s_offsets[MODSE_MAX_EXPERTS + 1];
-  __shared__ int s_tiles[MODSE_MAX_PROBLEMS];
+  constexpr int COPIES = 32;
+  __shared__ int s_cnt[2 * MODSE_MAX_EXPERTS * COPIES];  // [before my tokens, from them on][expert][copy]
+  __shared__ int s_sum[2 * MODSE_MAX_EXPERTS];
+  __shared__ int s_base[MODSE_MAX_EXPERTS];  // first row of my tokens' rows of an expert
+  __shared__ int s_counts[MODSE_MAX_EXPERTS], s_offsets[MODSE_MAX_EXPERTS];
+  __shared__ int s_row[PF_TOKENS][2], s_near;
+  __shared__ modse_gemm::PlanLds s_plan;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const bool first = blockIdx.x == 0;
+  const bool planner = blockIdx.x == 0;
+  const int t0 = planner ? ntok : (int)(blockIdx.x - 1) * PF_TOKENS;
+  for (int i = tid; i < 2 * N * COPIES; i += PF_THREADS) s_cnt[i] = 0;
+  if (tid == 0) s_near = 0;
+  __syncthreads();
+  const int n = ntok * top_k, before = t0 * top_k;
+#pragma unroll 8
+  for (int i = tid; i < n; i += PF_THREADS) atomicAdd(&s_cnt[((i < before ? 0 : N) + topk_idx[i]) * COPIES + (tid & (COPIES - 1))], 1);
+  if (planner) {
+    int near = 0;
+    if (near_flag) {
+      for (int t = tid; t < ntok; t += PF_THREADS) near += near_flag[t] != 0 ? 1 : 0;
+    } else {
+      for (int b = tid; b * TPB < ntok; b += PF_THREADS) near += blockhist[(size_t)b * (N + 1) + N];
+    }
+    if (near) atomicAdd(&s_near, near);
+  }
+  __syncthreads();
+  for (int i = tid; i < 2 * N * 8; i += PF_THREADS) {  // eight threads add up a counter's copies (whole groups of lanes run)
+    int sum = 0;
+#pragma unroll
+    for (int q = 0; q < COPIES / 8; ++q) sum += s_cnt[i / 8 * COPIES + q * 8 + (i & 7)];
+#pragma unroll
+    for (int m = 4; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
+    if ((i & 7) == 0) s_sum[i / 8] = sum;
+  }
+  __syncthreads();
   if (wave == 0) {
-    const int t = lane;
-    const bool valid = t < ntok;
-    int e0 = -1, e1 = -1;
-    if (valid) {
-      e0 = topk_idx[(size_t)t * top_k];
-      if (top_k == 2) e1 = topk_idx[(size_t)t * top_k + 1];
-    }
-    const unsigned long long below = (1ull << lane) - 1ull;
-    int run = 0, row0 = 0, row1 = 0, my_count = 0, my_offset = 0;
-    for (int e = 0; e < N; ++e) {
-      const unsigned long long m = __ballot(e0 == e || e1 == e);
-      const int rank = __popcll(m & below), c = __popcll(m);
-      if (e0 == e) row0 = run + rank;
-      if (e1 == e) row1 = run + rank;
-      if (lane == e) {
-        my_count = c;
-        my_offset = run;
-      }
-      run += c;
-    }
+    const int b = lane < N ? s_sum[lane] : 0, c = lane < N ? b + s_sum[N + lane] : 0;
+    int total;
+    const int o = modse_gemm::wave_exclusive(c, lane, total);
     if (lane < N) {
-      s_counts[lane] = my_count;
-      s_offsets[lane] = my_offset;
+      s_base[lane] = o + b;
+      s_counts[lane] = c;
+      s_offsets[lane] = o;
+      if (planner) {
+        R.counts[lane] = c;
+        R.offsets[lane] = o;
+      }
     }
-    if (lane == 0) s_offsets[N] = run;
+    if (planner && lane == 0) {
+      R.offsets[N] = total;
+      R.near_tie_count[0] = s_near;
+    }
+  }
+  __syncthreads();
+  if (planner) {
+    if (with_plan) modse_gemm::plan_fwd_body(L, esize, s_counts, s_offsets, plan, s_plan);
+    return;
+  }
+  if (wave == 0) {
+    const int t = t0 + lane;
+    const bool valid = lane < PF_TOKENS && t < ntok;
+    const int e0 = valid ? topk_idx[(size_t)t * top_k] : -1;
+    const int e1 = valid && top_k == 2 ? topk_idx[(size_t)t * top_k + 1] : -1;
+    int r0 = 0, r1 = 0;  // my block's earlier tokens with the same expert
+#pragma unroll 5
+    for (int i = 0; i < PF_TOKENS - 1; ++i) {
+      const int a = __shfl(e0, i, 64), b = __shfl(e1, i, 64);
+      if (i < lane) {
+        r0 += a == e0 || b == e0 ? 1 : 0;
+        r1 += a == e1 || b == e1 ? 1 : 0;
+      }
+    }
     if (valid) {
-      s_row[t][0] = row0;
-      s_row[t][1] = row1;
-    }
-    if (first) {
-      int near;
-      if (near_flag) {
-        near = __popcll(__ballot(valid && near_flag[t] != 0));
-      } else {
-        near = 0;
-        for (int b = 0; b * TPB < ntok; ++b) near += blockhist[(size_t)b * (N + 1) + N];
-      }
-      if (lane < N) {
-        R.counts[lane] = my_count;
-        R.offsets[lane] = my_offset;
-      }
-      if (lane == 0) {
-        R.offsets[N] = run;
-        R.near_tie_count[0] = near;
-      }
-      if (valid) {
-        R.row_of[(size_t)t * top_k] = row0;
-        R.src_of[row0] = t * top_k;
-        if (top_k == 2) {
-          R.row_of[(size_t)t * top_k + 1] = row1;
-          R.src_of[row1] = t * top_k + 1;
-        }
+      const int row0 = s_base[e0] + r0;
+      R.row_of[(size_t)t * top_k] = row0;
+      R.src_of[row0] = t * top_k;
+      s_row[lane][0] = row0;
+      if (top_k == 2) {
+        const int row1 = s_base[e1] + r1;
+        R.row_of[(size_t)t * top_k + 1] = row1;
+        R.src_of[row1] = t * top_k + 1;
+        s_row[lane][1] = row1;
       }
     }
   }
   __syncthreads();
-  if (first && with_plan) modse_gemm::plan_fwd_body(L, esize, s_counts, s_offsets, plan, s_tiles);
   if (Xp == nullptr) return;
-  const int t = blockIdx.x;
-  const int row0 = s_row[t][0];
-  const int row1 = top_k == 2 ? s_row[t][1] : -1;
   constexpr int VEC = 16 / sizeof(T);
-  for (int c = tid * VEC; c < d; c += 256 * VEC) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(x + (size_t)t * d + c);
-    *reinterpret_cast<f32x4*>(Xp + (size_t)row0 * d + c) = v;
-    if (row1 >= 0) *reinterpret_cast<f32x4*>(Xp + (size_t)row1 * d + c) = v;
+  static_assert(PF_TOKENS == PF_THREADS / 64, "a wave copies one token");
+  const int tl = wave;
+  if (t0 + tl < ntok) {
+    const int row0 = s_row[tl][0], row1 = top_k == 2 ? s_row[tl][1] : -1;
+    const T* const src = x + (size_t)(t0 + tl) * d;
+#pragma unroll 4
+    for (int c = lane * VEC; c < d; c += 64 * VEC) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(src + c);
+      *reinterpret_cast<f32x4*>(Xp + (size_t)row0 * d + c) = v;
+      if (row1 >= 0) *reinterpret_cast<f32x4*>(Xp + (size_t)row1 * d + c) = v;
+    }
   }
 }
 
@@ -1294,17 +1298,29 @@ __global__ __launch_bounds__(256) void sum_slabs_kernel(const float* __restrict_
 
 // Backward of the combine: for permuted row r = (token t, slot j):
 //   dO[r] = g[t,j] * dY[t]      d g[t,j] = <dY[t], O[r]>
+// The first block makes the tile plans of the backward GEMMs beside the others (a launch of its own took 9 us).
 template <typename T>
-__global__ __launch_bounds__(256) void bwd_prep_kernel(const T* __restrict__ dY, const T* __restrict__ O, int nrows,
-                                                       int d, int top_k, const int32_t* __restrict__ src_of,
-                                                       const float* __restrict__ topk_w, T* __restrict__ dO,
-                                                       float* __restrict__ dg) {
-  const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
+__global__ __launch_bounds__(256) void bwd_prep_plan_bwd_kernel(const T* __restrict__ dY, const T* __restrict__ O,
+                                                                int nrows, int d, int top_k, RoutingPtrs R,
+                                                                T* __restrict__ dO, float* __restrict__ dg,
+                                                                LayerDims L, int esize, BwdPlanArgs plan) {
+  __shared__ modse_gemm::PlanLds s_plan;
+  __shared__ int s_counts[MODSE_MAX_EXPERTS], s_offsets[MODSE_MAX_EXPERTS];
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < L.N) {
+      s_counts[threadIdx.x] = R.counts[threadIdx.x];
+      s_offsets[threadIdx.x] = R.offsets[threadIdx.x];
+    }
+    __syncthreads();
+    modse_gemm::plan_bwd_body(L, esize, s_counts, s_offsets, plan, s_plan);
+    return;
+  }
+  const int r = (blockIdx.x - 1) * 4 + (threadIdx.x >> 6);
   if (r >= nrows) return;
   const int lane = threadIdx.x & 63;
-  const int s = src_of[r];
+  const int s = R.src_of[r];
   const int t = s / top_k;
-  const float g = topk_w[s];
+  const float g = R.topk_w[s];
   float dot = 0.f;
   for (int c = lane * 8; c < d; c += 64 * 8) {
     float a[8], o[8], w[8];
@@ -1630,38 +1646,37 @@ hipError_t router_typed(const LayerDims& L, const void* xv, const void* Wgv, con
   }
   if (e != hipSuccess) return e;
   if (G && G->probs) {
-    hipLaunchKernelGGL(aux_finish_kernel, dim3(1), dim3(256), 0, s, G->probs, R.topk_idx, L.T, L.N, L.k, G->alpha,
+    hipLaunchKernelGGL(aux_finish_kernel, dim3(1), dim3(AUX_THREADS), 0, s, G->probs, R.topk_idx, L.T, L.N, L.k, G->alpha,
                        G->aux_f, G->aux_P, G->aux_loss);
     e = hipGetLastError();
   }
   return e;
 }
 
-// histogram (where the router has not made it), scan over blocks (which also makes the forward tile plans when
-// `plan` is given), stable scatter; batches of at most PERMUTE_SMALL_MAX_T tokens: one fused launch for all of it
+// The permutation (and the forward tile plans when `plan` is given).  Up to MODSE_PERMUTE_FUSED_MAX_T tokens: one launch for
+// all of it.  Beyond that the blocks' own counting would cost more than the two launches it saves (it grows with the
+// square of the batch): scan over the router's block histograms, then the scatter.
 template <typename T>
 hipError_t permute_typed(const LayerDims& L, modse_dtype dt, const void* xv, const RoutingPtrs& R, const RouteBufs& B,
                          void* Xpv, const GateExtPtrs* G, const FwdPlanArgs* plan, hipStream_t s) {
   const T* x = static_cast<const T*>(xv);
   const int nb = (L.T + TPB - 1) / TPB;
-  hipError_t e;
-  const bool token_router = router_kind(L, G) == ROUTER_TOKEN;
-  if (L.T <= MODSE_PERMUTE_SMALL_MAX_T) {
-    hipLaunchKernelGGL((permute_small_kernel<T>), dim3(L.T), dim3(256), 0, s, x, L.T, L.d, L.N, L.k, R.topk_idx,
-                       token_router ? B.near_flag : nullptr, B.blockhist, R, static_cast<T*>(Xpv), L,
+  static_assert(ROUTER_TOKEN_MAX_T <= MODSE_PERMUTE_FUSED_MAX_T, "the token routers make no block histograms");
+  if (L.T <= MODSE_PERMUTE_FUSED_MAX_T) {
+    const bool token_router = router_kind(L, G) == ROUTER_TOKEN;
+    hipLaunchKernelGGL((permute_fused_kernel<T>), dim3((L.T + PF_TOKENS - 1) / PF_TOKENS + 1), dim3(PF_THREADS), 0, s, x, L.T,
+                       L.d, L.N, L.k, R.topk_idx, token_router ? B.near_flag : nullptr, B.blockhist, R, static_cast<T*>(Xpv), L,
                        dt == MODSE_F32 ? 4 : 2, plan ? *plan : FwdPlanArgs{}, plan ? 1 : 0);
     return hipGetLastError();
   }
-  if (token_router) {
-    hipLaunchKernelGGL(route_hist_kernel, dim3(nb), dim3(64), 0, s, R.topk_idx, B.near_flag, L.T, L.N, L.k,
-                       B.blockhist);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(route_scan_kernel, dim3(1), dim3(256), 0, s, B.blockhist, nb, L.N, R.counts, R.offsets,
+  hipLaunchKernelGGL(route_scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, B.blockhist, nb, L.N, R.counts, R.offsets,
                      R.near_tie_count, L, dt == MODSE_F32 ? 4 : 2, plan ? *plan : FwdPlanArgs{}, plan ? 1 : 0);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL((scatter_kernel<T>), dim3(nb), dim3(ROUTE_THREADS), 0, s, x, L.T, L.d, L.N, L.k, R.topk_idx,
-                     R.offsets, B.blockhist, R.row_of, R.src_of, static_cast<T*>(Xpv));
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // two blocks share the copies of a histogram block's tokens while those blocks are few
+  const int parts = Xpv && nb < 512 ? 2 : 1;
+  hipLaunchKernelGGL((scatter_kernel<T>), dim3(nb * parts), dim3(ROUTE_THREADS), 0, s, x, L.T, L.d, L.N, L.k, R.topk_idx,
+                     R.offsets, B.blockhist, R.row_of, R.src_of, static_cast<T*>(Xpv), parts);
   return hipGetLastError();
 }
 
@@ -1746,16 +1761,15 @@ hipError_t launch_sum_slabs(const LayerDims& L, modse_dtype dt, const float* sla
 }
 
 hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, const void* O, const RoutingPtrs& R,
-                           void* dO, float* dg, hipStream_t s) {
+                           void* dO, float* dg, const BwdPlanArgs& plan, hipStream_t s) {
   const int nrows = L.T * L.k;
-  const int nb = (nrows + 3) / 4;
+  const dim3 grid((nrows + 3) / 4 + 1);
   if (dt == MODSE_F32)
-    hipLaunchKernelGGL((bwd_prep_kernel<float>), dim3(nb), dim3(256), 0, s, static_cast<const float*>(dY),
-                       static_cast<const float*>(O), nrows, L.d, L.k, R.src_of, R.topk_w, static_cast<float*>(dO), dg);
+    hipLaunchKernelGGL((bwd_prep_plan_bwd_kernel<float>), grid, dim3(256), 0, s, static_cast<const float*>(dY),
+                       static_cast<const float*>(O), nrows, L.d, L.k, R, static_cast<float*>(dO), dg, L, 4, plan);
   else
-    hipLaunchKernelGGL((bwd_prep_kernel<bf16_t>), dim3(nb), dim3(256), 0, s, static_cast<const bf16_t*>(dY),
-                       static_cast<const bf16_t*>(O), nrows, L.d, L.k, R.src_of, R.topk_w, static_cast<bf16_t*>(dO),
-                       dg);
+    hipLaunchKernelGGL((bwd_prep_plan_bwd_kernel<bf16_t>), grid, dim3(256), 0, s, static_cast<const bf16_t*>(dY),
+                       static_cast<const bf16_t*>(O), nrows, L.d, L.k, R, static_cast<bf16_t*>(dO), dg, L, 2, plan);
   return hipGetLastError();
 }
 

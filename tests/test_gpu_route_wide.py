@@ -28,6 +28,17 @@ def test_route_parity(case):
     check_routing(inp, r.routing_host())
 
 
+# the fused permutation (up to 4096 tokens) at the edges of its blocks of 16 tokens, and the scan over block histograms
+# beyond it: several blocks per thread, in registers and (more than 20) read twice; one to 64 experts
+@pytest.mark.parametrize("n,T,k", [(1, 15, 1), (2, 16, 2), (64, 17, 2), (3, 4096, 2), (64, 4096, 1), (1, 4097, 1), (2, 9000, 2),
+                                   (31, 5003, 2), (64, 12001, 2)])
+def test_permutation_parity(n, T, k):
+    inp = make("permute", 32, (32,) * n, T, "bf16", k, seed=21)
+    r = _runner(inp)
+    r.route()
+    check_routing(inp, r.routing_host())
+
+
 @pytest.mark.parametrize("T", [50, 600, 4200], ids=["token", "four_tokens", "block"])
 @pytest.mark.parametrize("keep", [(), (0,), (23,), (5, 20)])
 def test_masked_experts(T, keep):
