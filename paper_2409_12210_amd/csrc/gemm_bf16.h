@@ -539,19 +539,31 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
     const int ekhalf = elane >> 5;
     const int cM = cc.M, cN = cc.N, cld = cc.ldc;
     if constexpr (EPI == EPI_STORE_F32) {
-      // float32 output (weight gradients).  A tile inside the matrix that overwrites C goes through LDS, one
-      // 32 x 32 block (4 KiB) at a time: written in accumulator order (16 bytes per lane), read back row-wise,
-      // so that global memory sees whole 128-byte lines.  The slots are this wave's own load units in the
-      // two panels of the step just finished.
-      const bool interior = cc.w.m0 + BM <= cM && cc.w.n0 + BN <= cN;
-      if (interior && !accumulate && cc.nsteps != 0) {
+      // float32 output (weight gradients).  It goes through LDS, one 32 x 32 block (4 KiB) at a time: written in
+      // accumulator order (16 bytes per lane), read back row-wise, so that global memory sees whole 128-byte lines, also
+      // where the old values are added (they come in one block ahead; read and written in accumulator order they made the
+      // launch of 1021 tokens at d = 2048 take 694 us where overwriting took 333).  The slots are this wave's own load
+      // units in the two panels of the step just finished.  M and N are multiples of 32, so a block lies inside the
+      // matrix or outside as a whole.
+      const int erow = elane >> 3, echunk = elane & 7;
+      const uint32_t voff = (uint32_t)(erow * cld + echunk * 4) * 4u;
+      const int mleft = cM - cc.w.m0 - wm * WM, nleft = cN - cc.w.n0 - wn * WN;  // of the matrix, from the wave's corner on
+      const char* const wave_c = cc.C + ((size_t)(cc.w.m0 + wm * WM) * cld + cc.w.n0 + wn * WN) * 4;
+      auto inside = [&](int b) { return (b / NI) * 32 < mleft && (b % NI) * 32 < nleft; };
+      auto row_group = [&](int b, int it) { return wave_c + ((long)((b / NI) * 32 + it * 8) * cld + (b % NI) * 32) * 4; };
+      if (cc.nsteps == 0) {  // an expert without tokens: the ring holds nothing of this tile
+        if (!accumulate)
+#pragma unroll
+          for (int b = 0; b < MI * NI; ++b)
+            if (inside(b))
+#pragma unroll
+              for (int it = 0; it < 4; ++it) global_store16_s(row_group(b, it), voff, f32x4{0.f, 0.f, 0.f, 0.f});
+      } else {
         // (the late waves have already refilled their units of the A panel's slot: they have one slot, and
         // write a block into it only after the block before has been read back)
         char* const fslot[2] = {ring + slot_add(sa, grp_y ? NSLOT - 1 : NSLOT - 2) * PANEL + unit0 * 1024,
                                 ring + slot_add(sa, NSLOT - 1) * PANEL + unit0 * 1024};
-        const int er = elane & 31, esw = (er >> 1) & 7, rrow = elane >> 3, rchunk = elane & 7;
-        const uint32_t voff = (uint32_t)(rrow * cld + rchunk * 4) * 4u;
-        const char* const wave_c = cc.C + ((size_t)(cc.w.m0 + wm * WM) * cld + cc.w.n0 + wn * WN) * 4;
+        const int er = elane & 31, esw = (er >> 1) & 7;
         auto put = [&](int b) {  // block b = i * NI + j
           f32x16& c = acc[0][b / NI][b % NI];
           char* slot = fslot[b & 1];
@@ -563,43 +575,44 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
             for (int q = 0; q < 4; ++q) c[r * 4 + q] = 0.f;
           }
         };
-        if (!grp_y) put(0);
+        auto tile = [&](auto add_tag) {
+          constexpr bool ADD = decltype(add_tag)::value;
+          f32x4 old[4];
+          // (never masked, see the dH epilogue below: outside the matrix its last rows and columns are read instead)
+          auto fetch = [&](int b, int it) {
+            const int m = min((b / NI) * 32, mleft - 32), n = min((b % NI) * 32, nleft - 32);
+            old[it] = global_load16_f32_s(wave_c + ((long)(m + it * 8) * cld + n) * 4, voff);
+          };
+          if constexpr (ADD) {
 #pragma unroll
-        for (int b = 0; b < MI * NI; ++b) {
-          if (grp_y) put(b);
-          else if (b + 1 < MI * NI) put(b + 1);
-          char* slot = fslot[b & 1];
-#pragma unroll
-          for (int it = 0; it < 4; ++it) {
-            const int rr = it * 8 + rrow;
-            const f32x4 v = *reinterpret_cast<const f32x4*>(slot + rr * 128 + ((rchunk ^ ((rr >> 1) & 7)) << 4));
-            global_store16_s(wave_c + ((size_t)((b / NI) * 32 + it * 8) * cld + (b % NI) * 32) * 4, voff, v);
+            for (int it = 0; it < 4; ++it) fetch(0, it);
           }
-        }
-      } else {
-      const int mrow = cc.w.m0 + wm * WM + (elane & 31);
-      const int ncol = cc.w.n0 + wn * WN + 4 * ekhalf;
+          if (!grp_y) put(0);
 #pragma unroll
-      for (int i = 0; i < MI; ++i)
+          for (int b = 0; b < MI * NI; ++b) {
+            if (grp_y) put(b);
+            else if (b + 1 < MI * NI) put(b + 1);
+            char* slot = fslot[b & 1];
+            const bool in = inside(b);
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            float a[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) a[q] = acc[0][i][j][r * 4 + q];
-            const int m = mrow + i * 32, n = ncol + j * 32 + r * 8;
-            if (m < cM && n < cN) {
-              float* c = reinterpret_cast<float*>(const_cast<char*>(cc.C)) + (size_t)m * cld + n;
-              if (accumulate) {
-                float old[4];
-                load4(c, old);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) a[q] += old[q];
+            for (int it = 0; it < 4; ++it) {
+              const int rr = it * 8 + erow;
+              f32x4 v = *reinterpret_cast<const f32x4*>(slot + rr * 128 + ((echunk ^ ((rr >> 1) & 7)) << 4));
+              if constexpr (ADD) {
+                // loads issued after this one: the rest of this block's, and the next block's reloaded so far
+                if (b + 1 < MI * NI || it == 0) wait_loaded<3>(old[it]);
+                else if (it == 1) wait_loaded<2>(old[it]);
+                else if (it == 2) wait_loaded<1>(old[it]);
+                else wait_loaded<0>(old[it]);
+                v += old[it];
+                if (b + 1 < MI * NI) fetch(b + 1, it);
               }
-              store4(c, a);
+              if (in) global_store16_s(row_group(b, it), voff, v);
             }
           }
+        };
+        if (accumulate) tile(std::true_type{});
+        else tile(std::false_type{});
       }
     } else {
       // 16-bit outputs go through LDS so that global memory sees whole 128-byte lines: the wave works in

@@ -60,6 +60,16 @@ __device__ __forceinline__ bf16x8 global_load16_s(const void* base, uint32_t vof
   asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(v) : "v"(voff), "s"(base) : "memory");
   return v;
 }
+__device__ __forceinline__ f32x4 global_load16_f32_s(const void* base, uint32_t voff) {
+  f32x4 v;
+  asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(v) : "v"(voff), "s"(base) : "memory");
+  return v;
+}
+template <int YOUNGER>
+__device__ __forceinline__ void wait_loaded(f32x4& a) {
+  static_assert(YOUNGER >= 0 && YOUNGER < 16, "vmcnt field");
+  asm volatile("s_waitcnt vmcnt(%1)" : "+v"(a) : "n"(YOUNGER) : "memory");
+}
 template <int YOUNGER>
 __device__ __forceinline__ void wait_loaded(bf16x8& a, bf16x8& b) {
   static_assert(YOUNGER >= 0 && YOUNGER < 16, "vmcnt field");
