@@ -72,12 +72,13 @@ hipError_t run_block_tile(TileShape t, const GemmPlan* plan, int accumulate, int
 namespace {
 // ---- Which tiles a GEMM of the layer takes, and whether its K is split.  The realised token counts are known on the
 // device only, so the choice goes by the mean number of rows r = T k / N of an expert, with loads spread evenly over
-// 0.85 r .. 1.15 r.
+// r (1 - s) .. r (1 + s): s = 0.1 for up to a dozen experts and more for more, which are balanced less well.
 
 // expected number of row blocks of an expert
-double row_blocks(double r, int bm) {
+double row_blocks(const LayerDims& L, int bm) {
+  const double r = (double)L.T * L.k / L.N, s = std::max(0.1, std::min(0.5, L.N / 128.0)), most = r * (1 + s);
   double n = 1;
-  for (int j = 1; 1.15 * r > (double)j * bm; ++j) n += std::min(1.0, (1.15 * r - (double)j * bm) / (0.3 * r));
+  for (int j = 1; most > (double)j * bm; ++j) n += std::min(1.0, (most - (double)j * bm) / (2 * s * r));
   return n;
 }
 
@@ -92,7 +93,7 @@ struct Work {
   }
 };
 Work gemm_work(const LayerDims& L, int epilogue, TileShape t) {
-  const double r = (double)L.T * L.k / L.N, mb = row_blocks(r, t.bm);
+  const double mb = row_blocks(L, t.bm);
   auto blocks = [](int n, int b) { return (double)((n + b - 1) / b); };
   Work w;
   for (int e = 0; e < L.N; ++e) {
@@ -103,7 +104,7 @@ Work gemm_work(const LayerDims& L, int epilogue, TileShape t) {
       case EPI_STORE: w.add(mb * blocks(d, t.bn), blocks(f, 64)); break;
       case EPI_STORE_DUALK: w.add(mb * blocks(d, t.bn), 2 * blocks(f, 64)); break;
       case EPI_STORE_F32:
-        w.add(2 * blocks(f, t.bm) * blocks(d, t.bn) + blocks(d, t.bm) * blocks(f, t.bn), row_blocks(r, 64));
+        w.add(2 * blocks(f, t.bm) * blocks(d, t.bn) + blocks(d, t.bm) * blocks(f, t.bn), row_blocks(L, 64));
         break;
     }
   }
@@ -112,7 +113,7 @@ Work gemm_work(const LayerDims& L, int epilogue, TileShape t) {
 
 // Estimated time in us of a bf16 product (chunk: K steps of a split product's problems, 0 = not split), fitted to the
 // measured times of all five GEMMs at d = 1024 ... 4096, 4 ... 64 experts and 16 ... 8192 tokens.  A step of a tile takes
-// 1.67 us in the 256 x 256 kernel (one workgroup per CU), 1.1 us (weight gradients: 1.85) with 128-row tiles and 0.8 us (dH: 1.0) with 64-row ones
+// 1.6 us in the 256 x 256 kernel (one workgroup per CU), 1.1 us (weight gradients: 1.85, dH: 1.15) with 128-row tiles and 0.8 us (dH: 1.0) with 64-row ones
 // (two workgroups per CU); a tile pays for its opening and its epilogue with `fix` further steps, and the float32 slabs of
 // a split product are written and read at 4 TB/s.
 double gemm_cost(const LayerDims& L, int epilogue, TileShape t, int chunk) {
@@ -122,13 +123,15 @@ double gemm_cost(const LayerDims& L, int epilogue, TileShape t, int chunk) {
   const bool wgrad = epilogue == EPI_STORE_F32;
   const bool same = wgrad || epilogue == EPI_SWIGLU || epilogue == EPI_SWIGLU_BWD;  // tiles of one length
   if (t.bm == 256) {
-    const double fix = same && !wgrad ? 4 : 7;
+    const double fix = wgrad ? 6.8 : 4;
     const double mean = w.steps / w.tiles + fix;
-    if (same) return (std::ceil(w.tiles / cus) + (wgrad ? 0.3 : 0)) * mean * 1.67;  // whole rounds
+    const double rounds = w.tiles / cus;
+    if (wgrad) return (std::ceil(rounds) + 0.3) * mean * 1.67;  // (their number does not depend on the routing)
+    if (same) return (rounds < 0.9 ? 1 : rounds + 0.7) * mean * 1.58;  // whole rounds, of a number that is only expected
     // (a lone workgroup's steps are shorter when other CUs stand idle)
-    return std::max(w.tiles * mean / cus, (0.75 + 0.25 * std::min(1.0, w.tiles / cus)) * (w.longest + fix)) * 1.67;
+    return std::max((rounds + 0.2) * mean, (0.75 + 0.1 * std::min(1.0, w.tiles / cus)) * (w.longest + fix)) * 1.67;
   }
-  const double fix = 2.5, us = wgrad ? 1.85 : t.bm == 128 ? 1.1 : epilogue == EPI_SWIGLU_BWD ? 1.0 : 0.8, slots = 2 * cus;
+  const double fix = 2.5, us = wgrad ? 1.85 : epilogue == EPI_SWIGLU_BWD ? (t.bm == 128 ? 1.15 : 1.0) : t.bm == 128 ? 1.1 : 0.8, slots = 2 * cus;
   double mean = w.steps / w.tiles + fix, chain = w.longest + fix, slabs = 0;
   if (chunk) {
     const double n = std::max(1.0, w.steps / w.tiles / chunk);
@@ -138,7 +141,8 @@ double gemm_cost(const LayerDims& L, int epilogue, TileShape t, int chunk) {
   }
   // a workgroup that has its CU for itself runs faster
   const double alone = 0.62 + 0.38 * std::min(1.0, std::max(0.0, (w.tiles - cus) / cus));
-  return std::max((w.tiles / slots + (wgrad ? 0 : same ? 0.6 : 0.35)) * mean, chain * alone) * us + slabs;
+  const double rounds = wgrad ? w.tiles / slots : !same ? w.tiles / slots + 0.35 : w.tiles > slots ? w.tiles / slots + 0.6 : 0;
+  return std::max(rounds * mean, chain * alone) * us + slabs;
 }
 
 // Chunk length of a split K = f_e (a multiple of 64), or 0.  A batch with few rows has too few output tiles (d / bn per
@@ -153,7 +157,7 @@ int split_chunk(const LayerDims& L, modse_dtype dt, TileShape t, int passes) {
   const int64_t tiles = ((rows + t.bm - 1) / t.bm) * ((L.d + t.bn - 1) / t.bn);  // of one expert
   const int64_t cus = num_cus(), target = dt == MODSE_F32 ? (t.bm == 64 ? 4 : 2) * cus
                                           : t.bm == 32    ? 6 * cus
-                                          : t.bm == 64 && passes == 1 ? 4 * cus : 2 * cus;
+                                          : passes == 1     ? (t.bm == 64 ? 4 : 3) * cus : 2 * cus;
   if (t.bm > 128 || t.bn > 128 || tiles == 0 || 4 * L.N * tiles > 3 * target) return 0;
   int64_t F = 0, fmax = 0;
   for (int e = 0; e < L.N; ++e) {
@@ -189,13 +193,15 @@ GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue) {
   // us with 64 / 128-row tiles, 97 rows 74 / 71.
   if (passes) {
     if (passes == 1 && r <= 28) return with_chunk(TileShape{32, 128});
-    if (r <= 52) return with_chunk(TileShape{64, 128});
+    if (r <= 58) return with_chunk(TileShape{64, 128});
   }
   GemmChoice best = {swiglu ? TileShape{256, 128} : TileShape{256, 256}, 0};
-  // (loads less even than assumed cost the large tiles more, hence the 10 %)
-  double cost = 1.1 * gemm_cost(L, epilogue, best.tile, 0);
+  // (loads less even than assumed cost the large tiles more, hence the 5 %)
+  double cost = 1.05 * gemm_cost(L, epilogue, best.tile, 0);
   for (int bm = 128; bm >= 64; bm -= 64) {
     if (bm == 64 && (passes || epilogue == EPI_STORE_F32)) break;
+    // (weight gradients of many tiles are bound by their stores, which the larger tiles do better)
+    if (epilogue == EPI_STORE_F32 && gemm_work(L, epilogue, best.tile).tiles > 16 * num_cus()) break;
     const GemmChoice c = with_chunk(swiglu ? TileShape{bm, 64} : TileShape{bm, 128});
     const double mine = gemm_cost(L, epilogue, c.tile, c.kchunk / 64);
     if (mine < cost) {
