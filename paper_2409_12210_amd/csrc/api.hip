@@ -144,7 +144,7 @@ SavedLayout saved_layout(const LayerDims& L, modse_dtype dt) {
 }
 
 struct BwdLayout {
-  size_t plan[3], dO, dA, dB, dXp, dg, dl, du, dgamma_part, dWg_partial, dXpart, unsplit, total;
+  size_t plan[3], dO, dA, dB, dXp, dg, dl, du, dgamma_part, dWg_partial, Wt, dXpart, unsplit, total;
   GemmChoice dx;
 };
 
@@ -162,8 +162,9 @@ BwdLayout bwd_layout(const LayerDims& L, modse_dtype dt) {
   w.dg = c.take(Tk * 4);
   w.dl = c.take((size_t)L.T * L.N * 4);
   w.du = c.take((size_t)L.T * L.N * 4);
-  w.dgamma_part = c.take((((size_t)L.T + 255) / 256) * 4);
-  w.dWg_partial = c.take(nb * L.d * L.N * 4);
+  w.dgamma_part = c.take((((size_t)L.T + 63) / 64) * 4);
+  w.dWg_partial = c.take((nb + 1) * L.d * L.N * 4);  // (W_gate and W_noise: twice one per 64 tokens)
+  w.Wt = c.take((size_t)L.d * L.N * es);
   w.dx = gemm_choice(L, dt, EPI_STORE_DUALK);
   w.unsplit = c.off;
   w.dXpart = c.take(w.dx.kchunk ? (size_t)2 * splitk_max_chunks(L, w.dx.kchunk) * Tk * L.d * 4 : 0);
@@ -517,7 +518,6 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   if (pa.dx_kchunk) {
     HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.dx_tile, pa.dx, 0, 0, split_tiles_bound(L, pa.dx_tile, pa.dx_kchunk, 2),
                                 s, LAYOUT_B_KN));
-    HIP_TRY(launch_sum_slabs(L, dt, pa.dXpart, pa.dx_kchunk, 2, R, pa.dXp, s));
   } else {
     HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, 0, 0, tiles_bound(L, pa.dx_tile, false), s));
   }
@@ -528,8 +528,9 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
 
   const BwdRouterBufs rb = {reinterpret_cast<float*>(wsb + w.dl), reinterpret_cast<float*>(wsb + w.du),
                             reinterpret_cast<float*>(wsb + w.dgamma_part),
-                            reinterpret_cast<float*>(wsb + w.dWg_partial)};
-  HIP_TRY(launch_bwd_router(L, dt, x, W_gate, pa.dXp, dg, R, ext ? &G : nullptr, aux_grad, rb, dX, dW_gate, dW_noise,
+                            reinterpret_cast<float*>(wsb + w.dWg_partial), wsb + w.Wt};
+  const DxRows rows = {pa.dXp, pa.dXpart, pa.dx_kchunk};
+  HIP_TRY(launch_bwd_router(L, dt, x, W_gate, rows, dg, R, ext ? &G : nullptr, aux_grad, rb, dX, dW_gate, dW_noise,
                             dgamma, accumulate, s));
   stamp.mark(MODSE_STAGE_BWD_ROUTER);
   return MODSE_OK;

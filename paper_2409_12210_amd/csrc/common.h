@@ -170,9 +170,6 @@ hipError_t launch_combine(const LayerDims& L, modse_dtype dt, const void* O, con
 // O (may be null): the summed rows, for a backward pass to come
 hipError_t launch_combine_split(const LayerDims& L, modse_dtype dt, const float* Opart, int kchunk, const RoutingPtrs& R,
                                 void* O, void* y, hipStream_t s);
-// out[r] = sum over the slabs of row r's expert, passes * ceil(f_e / kchunk) of them, in ascending order
-hipError_t launch_sum_slabs(const LayerDims& L, modse_dtype dt, const float* slabs, int kchunk, int passes,
-                            const RoutingPtrs& R, void* out, hipStream_t s);
 struct BwdPlanArgs;
 // backward of the combine, and the tile plans of the backward GEMMs
 hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, const void* O, const RoutingPtrs& R,
@@ -180,10 +177,17 @@ hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, c
 struct BwdRouterBufs {  // workspace of the router's backward pass
   float* dl;           // [T, N] dense gradient of the logits
   float* du;           // [T, N] gradient of x W_noise
-  float* dgamma_part;  // [ceil(T / 256)]
-  float* dW_partial;   // [ceil(T / 32), d, N] per-block shares of a router-side weight gradient (32 tokens per block)
+  float* dgamma_part;  // [ceil(T / 64)]
+  float* dW_partial;   // [ceil(T / 32) + 1, d, N] shares of the router-side weight gradients
+  void* Wt;            // [N, d] W_gate's columns
 };
-hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const void* dXp,
+// The data gradient of the permuted rows: dXp, or (kchunk > 0) its partial sums, see BwdPlanArgs.
+struct DxRows {
+  void* dXp;
+  const float* slabs;
+  int32_t kchunk;
+};
+hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const DxRows& rows,
                              const float* dg, const RoutingPtrs& R, const GateExtPtrs* G, float aux_grad,
                              const BwdRouterBufs& B, void* dX, float* dW_gate, float* dW_noise, float* dgamma,
                              int accumulate, hipStream_t s);
@@ -220,7 +224,7 @@ struct BwdPlanArgs {
   void *dA, *dB, *dXp;
   float *dW1, *dW3, *dW2;
   // split dX product (batches with few tiles): K = f_e of either operand pair is cut into chunks of `dx_kchunk`; slab
-  // p * ceil(f_e / dx_kchunk) + c of dXpart holds chunk c of pair p, to be added up by launch_sum_slabs
+  // p * ceil(f_e / dx_kchunk) + c of dXpart holds chunk c of pair p, to be added up by the router's backward pass
   float* dXpart;
   int32_t dx_kchunk;  // 0 = one product over both pairs
   GemmPlan *dh, *dx, *wg;  // wg: dW1, dW3 and dW2 of every expert in one problem list

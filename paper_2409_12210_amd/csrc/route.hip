@@ -1345,25 +1345,42 @@ __global__ __launch_bounds__(256) void bwd_prep_plan_bwd_kernel(const T* __restr
 // and, when the noise term is on (z = gamma s / r, s = softplus(u), r = sqrt(mean s^2 + eps), Sec. 2
 // Eq. 4-5), the gradient of u = x W_n and this block's share of d gamma:
 //   du_i = gamma (dl_i / r - s_i <s, dl> / (N r^3)) sigmoid(u_i),   dgamma = sum_t <dl, s> / r.
-__global__ __launch_bounds__(256) void gate_bwd_kernel(const float* __restrict__ dg, int ntok, int N, int top_k,
-                                                       const int32_t* __restrict__ topk_idx,
-                                                       const float* __restrict__ topk_w,
-                                                       const int32_t* __restrict__ row_of, GateExtPtrs G,
-                                                       float aux_coef, float* __restrict__ dl, float* __restrict__ du,
-                                                       float* __restrict__ dgamma_part) {
-  __shared__ float s_red[256];
+// Blocks from `nbt` on copy W_gate [d, N] to Wt [N, d] for bwd_gate_rows_kernel, 64 rows each.
+constexpr int GB_THREADS = 64;  // (blocks of 256 threads left most CUs idle: 24 us at 8192 tokens with both gate extensions, now 11)
+template <typename T>
+__global__ __launch_bounds__(GB_THREADS) void gate_bwd_kernel(const float* __restrict__ dg, int ntok, int N, int top_k,
+                                                              const int32_t* __restrict__ topk_idx,
+                                                              const float* __restrict__ topk_w,
+                                                              const int32_t* __restrict__ row_of, GateExtPtrs G,
+                                                              float aux_coef, float* __restrict__ dl, float* __restrict__ du,
+                                                              float* __restrict__ dgamma_part, int nbt, int d,
+                                                              const T* __restrict__ Wg, T* __restrict__ Wt) {
   const int tid = threadIdx.x;
-  const int t = blockIdx.x * 256 + tid;
+  if ((int)blockIdx.x >= nbt) {
+    const int c = ((int)blockIdx.x - nbt) * GB_THREADS + tid;
+    if (c < d)
+#pragma unroll 8
+      for (int e = 0; e < N; ++e) Wt[(size_t)e * d + c] = Wg[(size_t)c * N + e];
+    return;
+  }
+  // (a token's row of dl is put together in LDS: in memory every step would wait for the one before)
+  __shared__ float s_row[MODSE_MAX_EXPERTS][GB_THREADS], s_sp[MODSE_MAX_EXPERTS][GB_THREADS];
+  const int t = blockIdx.x * GB_THREADS + tid;
   float dgam = 0.f;
   if (t < ntok) {
-    float* row = dl + (size_t)t * N;
     if (G.probs && aux_coef != 0.f) {
       const float* p = G.probs + (size_t)t * N;
       float fp = 0.f;
-      for (int e = 0; e < N; ++e) fp = fmaf(G.aux_f[e], p[e], fp);
-      for (int e = 0; e < N; ++e) row[e] = aux_coef * p[e] * (G.aux_f[e] - fp);
+#pragma unroll 8
+      for (int e = 0; e < N; ++e) {
+        const float v = p[e];
+        s_row[e][tid] = v;
+        fp = fmaf(G.aux_f[e], v, fp);
+      }
+#pragma unroll 8
+      for (int e = 0; e < N; ++e) s_row[e][tid] = aux_coef * s_row[e][tid] * (G.aux_f[e] - fp);
     } else {
-      for (int e = 0; e < N; ++e) row[e] = 0.f;
+      for (int e = 0; e < N; ++e) s_row[e][tid] = 0.f;
     }
     float g[2] = {0.f, 0.f}, dgv[2] = {0.f, 0.f};
     float mean = 0.f;
@@ -1372,145 +1389,279 @@ __global__ __launch_bounds__(256) void gate_bwd_kernel(const float* __restrict__
       dgv[j] = dg[row_of[(size_t)t * top_k + j]];
       mean += g[j] * dgv[j];
     }
-    for (int j = 0; j < top_k; ++j) row[topk_idx[(size_t)t * top_k + j]] += g[j] * (dgv[j] - mean);
+    for (int j = 0; j < top_k; ++j) s_row[topk_idx[(size_t)t * top_k + j]][tid] += g[j] * (dgv[j] - mean);
+#pragma unroll 8
+    for (int e = 0; e < N; ++e) dl[(size_t)t * N + e] = s_row[e][tid];
     if (G.W_noise) {
       const float* u = G.noise_pre + (size_t)t * N;
       float ss = 0.f, sd = 0.f;
+#pragma unroll 8
       for (int e = 0; e < N; ++e) {
-        const float sp = u[e] > 15.f ? u[e] : log1pf(__expf(u[e]));
+        const float v = u[e], sp = v > 15.f ? v : log1pf(__expf(v));
+        s_sp[e][tid] = sp;
         ss = fmaf(sp, sp, ss);
-        sd = fmaf(sp, row[e], sd);
+        sd = fmaf(sp, s_row[e][tid], sd);
       }
       const float r = sqrtf(ss / (float)N + G.eps), gam = G.gamma[0];
       const float k1 = gam / r, k2 = gam * sd / ((float)N * r * r * r);
-      for (int e = 0; e < N; ++e) {
-        const float sp = u[e] > 15.f ? u[e] : log1pf(__expf(u[e]));
-        du[(size_t)t * N + e] = (k1 * row[e] - k2 * sp) / (1.f + __expf(-u[e]));
-      }
+#pragma unroll 8
+      for (int e = 0; e < N; ++e)
+        du[(size_t)t * N + e] = (k1 * s_row[e][tid] - k2 * s_sp[e][tid]) / (1.f + __expf(-u[e]));
       dgam = sd / r;
     }
   }
   if (dgamma_part) {  // fixed-order sum over the block
-    s_red[tid] = dgam;
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) dgam += __shfl_xor(dgam, m, 64);
+    if (tid == 0) dgamma_part[blockIdx.x] = dgam;
+  }
+}
+
+// ---- backward through the router matrices.  "Column" e < N means W_gate with dl, e >= N (noise term on) W_noise with du.
+// All bound by memory.  (One kernel for dX and the partial gradients, a block of 256 threads per 32 tokens that walked
+// them four at a time, eight expert columns per launch, took 29 us at 1021 tokens and 8 experts, 129 at 32768, and 300 us
+// for the whole stage at 1021 tokens with 64 experts, where every launch read x and dX again.  The stage now takes 37 us
+// with 64 experts; at 32768 tokens and 8 experts 139 in place of 157, with both gate extensions at 8192 tokens 101 in
+// place of 146.)
+
+// Plain gate: dl is zero except for the chosen experts, so
+//   dX[t] = sum_j (dXp[row_of[t, j]] + W_gate[:, e_j] dl[t, e_j])
+// with W_gate's columns as rows of Wt: one thread per token and eight columns of d, four row reads and a write.  SPLIT: a
+// row of dXp is still the passes * ceil(f_e / kchunk) float32 slabs of the split product.
+template <typename T, bool SPLIT>
+__global__ __launch_bounds__(256) void bwd_gate_rows_kernel(const T* __restrict__ dXp, const float* __restrict__ slabs,
+                                                            LayerDims L, int kchunk, const T* __restrict__ Wt,
+                                                            const float* __restrict__ dl,
+                                                            const int32_t* __restrict__ topk_idx,
+                                                            const int32_t* __restrict__ row_of, T* __restrict__ dX) {
+  const int d = L.d, per_tok = d / 8;
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (long)L.T * per_tok) return;
+  const int t = (int)(i / per_tok), c = (int)(i % per_tok) * 8;
+  float o[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) o[q] = 0.f;
+  auto add = [&](int j) {
+    const int e = topk_idx[(size_t)t * L.k + j];
+    const size_t at = (size_t)row_of[(size_t)t * L.k + j] * d + c;
+    const float g = dl[(size_t)t * L.N + e];
+    float v[8], w[8];
+    if constexpr (SPLIT) sum_slabs8(slabs + at, (size_t)L.T * L.k * d, 2 * ((L.f[e] + kchunk - 1) / kchunk), v);
+    else load8(dXp + at, v);
+    load8(Wt + (size_t)e * d + c, w);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) o[q] = fmaf(w[q], g, o[q] + v[q]);
+  };
+  add(0);
+  if (L.k == 2) add(1);
+  store8(dX + (size_t)t * d + c, o);
+}
+
+constexpr int BR_SLAB = 512, BR_TOK = 32;  // columns of d that a wave (eight per lane) owns; tokens per block and step
+static_assert(BR_TOK == MODSE_ROUTE_TOKENS_PER_BLOCK, "the workspace holds one partial gradient per 32-token block");
+struct BwdRouterArgs {
+  const void *Wg, *Wn;        // [d, N]; Wn null: no noise term
+  const float *dl, *du;       // [T, N]
+  int ntok, d, N, NP, top_k;  // NP: N, or 2 N with the noise term
+  const int32_t *row_of;
+};
+
+// Gate extensions: dX[t] = sum_j dXp[row_of[t, j]] + W_gate dl[t] (+ W_noise du[t]).  A block owns a slab of 512 columns of
+// d and `rounds` groups of 32 tokens, eight per wave; all rows of a batch are loaded before any arithmetic.  The matrices
+// lie in LDS as [column e][512 columns of d], EMAX columns e at a time.
+template <typename T>
+__global__ __launch_bounds__(256) void bwd_gate_rows_ext_kernel(BwdRouterArgs a, const T* __restrict__ dXp, int rounds,
+                                                                T* __restrict__ dX) {
+  constexpr int TB = sizeof(T) == 2 ? 8 : 4;  // tokens per batch
+  constexpr int EMAX = 64 * 1024 / (BR_SLAB * sizeof(T));
+  __shared__ __attribute__((aligned(16))) T s_w[EMAX * BR_SLAB];  // [column e][column of d]
+  __shared__ __attribute__((aligned(16))) float s_dl[EMAX * BR_TOK];  // [column e][token]
+  __shared__ int s_row[BR_TOK][2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int d = a.d, N = a.N, c0 = blockIdx.y * BR_SLAB, c = c0 + lane * 8;
+  const int cl = min(c, d - 8);  // (lanes beyond the matrix repeat its last columns and store nothing)
+  const int npass = (a.NP + EMAX - 1) / EMAX;
+  auto stage_w = [&](int e0, int ne) {  // two columns of d per thread
+    const int cg = min(c0 + 2 * tid, d - 2);
+    for (int e = 0; e < ne; ++e) {
+      const int eg = e0 + e;
+      const T* const W = static_cast<const T*>(eg < N ? a.Wg : a.Wn) + (eg < N ? eg : eg - N);
+      s_w[e * BR_SLAB + 2 * tid] = W[(size_t)cg * N];
+      s_w[e * BR_SLAB + 2 * tid + 1] = W[(size_t)(cg + 1) * N];
+    }
+  };
+  auto stage_dl = [&](int t0, int e0, int ne) {
+    for (int i = tid; i < ne * BR_TOK; i += 256) {
+      const int t = i / ne, e = i % ne, eg = e0 + e;
+      s_dl[e * BR_TOK + t] = t0 + t < a.ntok ? (eg < N ? a.dl[(size_t)(t0 + t) * N + eg] : a.du[(size_t)(t0 + t) * N + eg - N]) : 0.f;
+    }
+  };
+  if (npass == 1) stage_w(0, a.NP);
+  for (int r = 0; r < rounds; ++r) {
+    const int t0 = (blockIdx.x * rounds + r) * BR_TOK;
+    if (t0 >= a.ntok) break;
+    const int nt = min(BR_TOK, a.ntok - t0);
+    __syncthreads();  // the round before has been read
+    if (tid < 2 * BR_TOK)
+      s_row[tid >> 1][tid & 1] = a.row_of[(size_t)(t0 + min(tid >> 1, nt - 1)) * a.top_k + min(tid & 1, a.top_k - 1)];
+    if (npass == 1) stage_dl(t0, 0, a.NP);
     __syncthreads();
-    if (tid == 0) {
-      float tot = 0.f;
-      for (int i = 0; i < 256; ++i) tot += s_red[i];
-      dgamma_part[blockIdx.x] = tot;
+    const float use_b = a.top_k == 2 ? 1.f : 0.f;
+#pragma unroll 1
+    for (int b = 0; b < BR_TOK / 4 / TB; ++b) {
+      const int tw = wave * (BR_TOK / 4) + b * TB;
+      float go[TB][8], bv[TB][8];
+#pragma unroll
+      for (int u = 0; u < TB; ++u) {  // (no branch between the loads: a missing row is a repeated one)
+        load8(dXp + (size_t)s_row[tw + u][0] * d + cl, go[u]);
+        load8(dXp + (size_t)s_row[tw + u][1] * d + cl, bv[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < TB; ++u)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) go[u][q] = fmaf(use_b, bv[u][q], go[u][q]);
+      for (int p = 0; p < npass; ++p) {
+        const int e0 = p * EMAX, ne = min(EMAX, a.NP - e0);
+        if (npass > 1) {
+          __syncthreads();
+          stage_w(e0, ne);
+          stage_dl(t0, e0, ne);
+          __syncthreads();
+        }
+        for (int e = 0; e < ne; ++e) {
+          float w[8], dv[TB];
+          load8(s_w + e * BR_SLAB + lane * 8, w);
+#pragma unroll
+          for (int u = 0; u < TB; u += 4) load4(s_dl + e * BR_TOK + tw + u, dv + u);
+#pragma unroll
+          for (int u = 0; u < TB; ++u)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) go[u][q] = fmaf(w[q], dv[u], go[u][q]);
+        }
+      }
+      if (c < d) {
+#pragma unroll
+        for (int u = 0; u < TB; ++u)
+          if (tw + u < nt) store8(dX + (size_t)(t0 + tw + u) * d + c, go[u]);
+      }
     }
   }
 }
 
-// Backward through a router-side matrix W [d, ldw] (W_gate with dl, or W_noise with du) for BR_TOK tokens per
-// block and up to 8 of its columns [e0, e0 + ne):
-//   dX[t]      = (first ? sum_j dXp[row_of[t, j]] : dX[t]) + W[:, e0 : e0+ne] dl[t, e0 : e0+ne]
-//   partial[b] = sum_{t in block} x[t] (outer) dl[t, e0 : e0+ne]      (reduced over blocks by dwg_reduce_kernel)
-// A thread owns 8 columns of d for all tokens of the block, keeps the 8 x 8 slice of W and of the partial in
-// registers, and per token reads x and the dXp rows once (16-byte loads, a full row per block instruction).
-constexpr int BR_TOK = 32;
-static_assert(BR_TOK == MODSE_ROUTE_TOKENS_PER_BLOCK, "the workspace holds one partial gradient per 32-token block");
+// partial[chunk][m][c][e] = sum over the chunk's tokens of x[t][c] dl[t][e] (m = 1: du), reduced over the chunks by
+// dwg_reduce_kernel.  A block owns a slab, eight columns e and `tok` tokens, a quarter of them per wave.  A lane keeps its 8
+// x 8 slice of the sum in registers; one load brings dl of eight tokens, which go to scalar registers; dl and the rows of the
+// next batch of tokens are on their way during the arithmetic of one, without any barrier; at the end the waves' sums
+// meet in LDS in a fixed order.
 template <typename T>
-__global__ __launch_bounds__(ROUTE_THREADS) void bwd_gate_rows_kernel(
-    const T* __restrict__ x, const T* __restrict__ W, int ldw, int e0, int ne, const T* __restrict__ dXp,
-    const float* __restrict__ dl, int ntok, int d, int top_k, const int32_t* __restrict__ row_of, int first,
-    T* __restrict__ dX, float* __restrict__ partial) {
-  __shared__ __attribute__((aligned(16))) float s_dl[BR_TOK][8];
-  __shared__ int s_row[BR_TOK][2];
-  const int tid = threadIdx.x;
-  const int t0 = blockIdx.x * BR_TOK;
-  for (int i = tid; i < BR_TOK * 8; i += ROUTE_THREADS) {
-    const int tl = i >> 3, e = i & 7;
-    (&s_dl[0][0])[i] = (t0 + tl < ntok && e < ne) ? dl[(size_t)(t0 + tl) * ldw + e0 + e] : 0.f;
-  }
-  if (first && tid < BR_TOK && t0 + tid < ntok)
-    for (int j = 0; j < top_k; ++j) s_row[tid][j] = row_of[(size_t)(t0 + tid) * top_k + j];
-  __syncthreads();
-  const int nt = min(BR_TOK, ntok - t0);
-  for (int c = tid * 8; c < d; c += ROUTE_THREADS * 8) {
-    float wg[8][8], acc[8][8];
-    if (ldw == 8) {  // whole rows: eight 16-byte loads in flight together
+__global__ __launch_bounds__(256, 3) void bwd_dwg_kernel(BwdRouterArgs a, const T* __restrict__ x, int tok,
+                                                         float* __restrict__ partial) {
+  constexpr int TB = sizeof(T) == 2 ? 8 : 4;
+  __shared__ float s_sum[2][64][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int d = a.d, N = a.N, c = blockIdx.y * BR_SLAB + lane * 8, cl = min(c, d - 8);
+  const int groups = (N + 7) / 8, m = blockIdx.z / groups, e0 = blockIdx.z % groups * 8, ne = min(8, N - e0);
+  const float* const dl = (m ? a.du : a.dl) + e0;
+  float acc[8][8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) load8(W + (size_t)(c + q) * 8, wg[q]);
-    } else {  // columns beyond ne repeat the last one and are zeroed afterwards (no branch per element)
+  for (int q = 0; q < 8; ++q)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[q][e] = 0.f;
+  const int per = tok / 4, t0 = blockIdx.x * tok + wave * per, t1 = min(t0 + per, a.ntok);
+  Raw8<T> cur[TB], nxt[TB];
+  auto fetch = [&](Raw8<T> (&r)[TB], int t) {  // (tokens beyond the last repeat it; their dl is zero)
+#pragma unroll
+    for (int u = 0; u < TB; ++u) r[u].load(x + (size_t)min(t + u, a.ntok - 1) * d + cl);
+  };
+  auto fetch_dl = [&](int t) -> float {  // lane 8 u + e: token t + u, column e0 + e
+    const int u = lane >> 3, e = lane & 7;
+    const float v = dl[(size_t)min(t + u, a.ntok - 1) * N + min(e, ne - 1)];
+    return e < ne && t + u < t1 ? v : 0.f;
+  };
+  float dcur = 0.f;
+  if (t0 < t1) {
+    fetch(cur, t0);
+    dcur = fetch_dl(t0);
+  }
+#pragma unroll 1
+  for (int t = t0; t < t1; t += TB) {
+    fetch(nxt, t + TB);
+    const float dnxt = fetch_dl(t + TB);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < TB; ++u) {
+      float dv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dv[e] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(dcur), u * 8 + e));
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float xv = cur[u].get(q);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[q][e] = fmaf(xv, dv[e], acc[q][e]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < TB; ++u) cur[u] = nxt[u];
+    dcur = dnxt;
+  }
+  // waves 2 and 3 hand their sums to waves 0 and 1, then wave 1 its own to wave 0
+#pragma unroll
+  for (int half = 2; half >= 1; half >>= 1) {
+    if (wave >= half && wave < 2 * half) {
 #pragma unroll
       for (int q = 0; q < 8; ++q)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float w = (float)W[(size_t)(c + q) * ldw + e0 + min(e, ne - 1)];
-          wg[q][e] = e < ne ? w : 0.f;
-        }
+        for (int e = 0; e < 8; ++e) s_sum[wave - half][q * 8 + e][lane] = acc[q][e];
     }
+    __syncthreads();
+    if (wave < half) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[q][e] += s_sum[wave][q * 8 + e][lane];
+    }
+    __syncthreads();
+  }
+  if (wave != 0 || c >= d) return;
+  float* const out = partial + (((size_t)blockIdx.x * (a.NP / N) + m) * d + c) * N + e0;
+  if (N == 8) {  // the lane's 8 x 8 block is 256 consecutive bytes
+#pragma unroll
+    for (int q = 0; q < 8; ++q) store8(out + q * 8, acc[q]);
+  } else {
 #pragma unroll
     for (int q = 0; q < 8; ++q)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[q][e] = 0.f;
-    // four tokens at a time, all twelve row loads issued before any arithmetic (no branch between them: a
-    // missing second row is read from the first one's address and multiplied by zero)
-    const float use_b = (first && top_k == 2) ? 1.f : 0.f;
-    for (int tl0 = 0; tl0 < nt; tl0 += 4) {
-      float xv[4][8], av[4][8], bv[4][8];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int tl = min(tl0 + u, nt - 1);
-        const int t = t0 + tl;
-        const T* pa = first ? dXp + (size_t)s_row[tl][0] * d : dX + (size_t)t * d;
-        const T* pb = use_b != 0.f ? dXp + (size_t)s_row[tl][1] * d : pa;
-        load8(x + (size_t)t * d + c, xv[u]);
-        load8(pa + c, av[u]);
-        load8(pb + c, bv[u]);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int tl = tl0 + u;
-        if (tl < nt) {
-          float dlv[8], o[8];
-          load8(&s_dl[tl][0], dlv);
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            float go = fmaf(use_b, bv[u][q], av[u][q]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              go = fmaf(wg[q][e], dlv[e], go);
-              acc[q][e] = fmaf(xv[u][q], dlv[e], acc[q][e]);
-            }
-            o[q] = go;
-          }
-          store8(dX + (size_t)(t0 + tl) * d + c, o);
-        }
-      }
-    }
-    float* out = partial + ((size_t)blockIdx.x * d + c) * ldw + e0;
-    if (ldw == 8) {  // the thread's 8 x 8 block is 256 consecutive bytes
-#pragma unroll
-      for (int q = 0; q < 8; ++q) store8(out + q * 8, acc[q]);
-    } else {
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (e < ne) out[q * ldw + e] = acc[q][e];
-    }
+      for (int e = 0; e < 8; ++e)
+        if (e < ne) out[(size_t)q * N + e] = acc[q][e];
   }
 }
 
-// dW_gate[i] (+)= sum_b partial[b][i] in a fixed order (deterministic): 64 outputs per block, the blocks'
-// partials are split over the 4 waves and combined through LDS.
-__global__ __launch_bounds__(256) void dwg_reduce_kernel(const float* __restrict__ partial, int nb, int n,
-                                                         int accumulate, float* __restrict__ dWg) {
+// The router's weight gradients (+)= the sum of the chunks' partials, in a fixed order (deterministic): 64 outputs per
+// block, the partials are split over the 4 waves and combined through LDS.  Outputs: dW_gate, then (noise term on)
+// dW_noise and dgamma, whose partials lie in an array of their own.
+__global__ __launch_bounds__(256) void dwg_reduce_kernel(const float* __restrict__ partial, int nchunk, int n, int nmat,
+                                                         const float* __restrict__ dgamma_part, int ngamma,
+                                                         int accumulate, float* __restrict__ dWg,
+                                                         float* __restrict__ dWn, float* __restrict__ dgamma) {
   __shared__ float s_part[4][64];
   const int li = threadIdx.x & 63, part = threadIdx.x >> 6;
-  const int i = blockIdx.x * 64 + li;
+  const int i = blockIdx.x * 64 + li, total = n * nmat;
   float acc = 0.f;
-  if (i < n) {
+  if (i < total) {
 #pragma unroll 8
-    for (int b = part; b < nb; b += 4) acc += partial[(size_t)b * n + i];  // unrolled: several loads in flight
+    for (int b = part; b < nchunk; b += 4) acc += partial[(size_t)b * total + i];  // unrolled: several loads in flight
+  } else if (nmat == 2 && blockIdx.x == gridDim.x - 1 && li == 63) {
+#pragma unroll 8
+    for (int b = part; b < ngamma; b += 4) acc += dgamma_part[b];
   }
   s_part[part][li] = acc;
   __syncthreads();
-  if (part == 0 && i < n) {
-    const float v = (s_part[0][li] + s_part[1][li]) + (s_part[2][li] + s_part[3][li]);
-    dWg[i] = accumulate ? dWg[i] + v : v;
-  }
+  if (part != 0) return;
+  float* const out = i < n ? dWg + i : i < total ? dWn + (i - n) : nmat == 2 && blockIdx.x == gridDim.x - 1 && li == 63 ? dgamma : nullptr;
+  if (!out) return;
+  const float v = (s_part[0][li] + s_part[1][li]) + (s_part[2][li] + s_part[3][li]);
+  *out = accumulate ? *out + v : v;
 }
 
 // [d, N] -> [d, NE] with zero columns behind the N real ones
@@ -1680,21 +1831,50 @@ hipError_t permute_typed(const LayerDims& L, modse_dtype dt, const void* xv, con
   return hipGetLastError();
 }
 
-// dX and the gradient of one router-side matrix, 8 expert columns per launch
 template <typename T>
-hipError_t gate_rows_typed(const LayerDims& L, const void* x, const void* W, const void* dXp, const float* dl,
-                           const RoutingPtrs& R, int first, void* dX, float* partial, float* dW, int accumulate,
-                           hipStream_t s) {
-  const int nb = (L.T + BR_TOK - 1) / BR_TOK;
-  for (int e0 = 0; e0 < L.N; e0 += 8) {
-    hipLaunchKernelGGL((bwd_gate_rows_kernel<T>), dim3(nb), dim3(ROUTE_THREADS), 0, s, static_cast<const T*>(x),
-                       static_cast<const T*>(W), L.N, e0, min(8, L.N - e0), static_cast<const T*>(dXp), dl, L.T, L.d,
-                       L.k, R.row_of, (first && e0 == 0) ? 1 : 0, static_cast<T*>(dX), partial);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+hipError_t bwd_router_typed(const LayerDims& L, const GateExtPtrs& G, float aux_coef, const void* xv, const void* Wv,
+                            const DxRows& rows, const float* dg, const RoutingPtrs& R, const BwdRouterBufs& B, void* dXv,
+                            float* dW_gate, float* dW_noise, float* dgamma, int accumulate, hipStream_t s) {
+  const T *x = static_cast<const T*>(xv), *W = static_cast<const T*>(Wv), *dXp = static_cast<const T*>(rows.dXp);
+  T* const dX = static_cast<T*>(dXv);
+  const bool noise = G.W_noise != nullptr, sparse = !noise && aux_coef == 0.f;  // dl is zero but for the chosen experts
+  const int nbt = (L.T + GB_THREADS - 1) / GB_THREADS, ntr = sparse ? (L.d + GB_THREADS - 1) / GB_THREADS : 0;
+  hipLaunchKernelGGL((gate_bwd_kernel<T>), dim3(nbt + ntr), dim3(GB_THREADS), 0, s, dg, L.T, L.N, L.k, R.topk_idx, R.topk_w,
+                     R.row_of, G, aux_coef, B.dl, noise ? B.du : nullptr, noise ? B.dgamma_part : nullptr, nbt, L.d, W,
+                     static_cast<T*>(B.Wt));
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int nmat = noise ? 2 : 1, slabs = (L.d + BR_SLAB - 1) / BR_SLAB, nb = (L.T + BR_TOK - 1) / BR_TOK;
+  const BwdRouterArgs a = {W, G.W_noise, B.dl, B.du, L.T, L.d, L.N, nmat * L.N, L.k, R.row_of};
+  if (sparse) {
+    const dim3 grid((unsigned)(((long)L.T * (L.d / 8) + 255) / 256));
+    if (rows.kchunk)
+      hipLaunchKernelGGL((bwd_gate_rows_kernel<T, true>), grid, dim3(256), 0, s, dXp, rows.slabs, L, rows.kchunk,
+                         static_cast<const T*>(B.Wt), B.dl, R.topk_idx, R.row_of, dX);
+    else
+      hipLaunchKernelGGL((bwd_gate_rows_kernel<T, false>), grid, dim3(256), 0, s, dXp, nullptr, L, 0,
+                         static_cast<const T*>(B.Wt), B.dl, R.topk_idx, R.row_of, dX);
+  } else {
+    if (rows.kchunk) {
+      const long n = (long)L.T * L.k * (L.d / 8);
+      hipLaunchKernelGGL((sum_slabs_kernel<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, rows.slabs, L.T * L.k, L.d,
+                         L, rows.kchunk, 2, R.topk_idx, R.src_of, static_cast<T*>(rows.dXp));
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    // several groups of tokens per block once there are four blocks per CU without
+    const int rounds = std::max(1, std::min(8, nb * slabs / 1024));
+    hipLaunchKernelGGL((bwd_gate_rows_ext_kernel<T>), dim3((nb + rounds - 1) / rounds, slabs), dim3(256), 0, s, a, dXp, rounds,
+                       dX);
   }
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  // about 512 blocks: fewer, longer chunks mean fewer partial gradients (two matrices: room for half as many)
+  const int groups = (L.N + 7) / 8 * nmat;
+  const int tok = std::max(nmat, std::min(16, nb * slabs * groups / 512)) * BR_TOK, nchunk = (L.T + tok - 1) / tok;
+  hipLaunchKernelGGL((bwd_dwg_kernel<T>), dim3(nchunk, slabs, groups), dim3(256), 0, s, a, x, tok, B.dW_partial);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   const int n = L.d * L.N;
-  hipLaunchKernelGGL(dwg_reduce_kernel, dim3((n + 63) / 64), dim3(256), 0, s, partial, nb, n, accumulate, dW);
+  hipLaunchKernelGGL(dwg_reduce_kernel, dim3((n * nmat + 63) / 64 + (noise ? 1 : 0)), dim3(256), 0, s, B.dW_partial, nchunk, n,
+                     nmat, B.dgamma_part, nbt, accumulate, dW_gate, dW_noise, dgamma);
   return hipGetLastError();
 }
 
@@ -1748,18 +1928,6 @@ hipError_t launch_combine_split(const LayerDims& L, modse_dtype dt, const float*
   return hipGetLastError();
 }
 
-hipError_t launch_sum_slabs(const LayerDims& L, modse_dtype dt, const float* slabs, int kchunk, int passes,
-                            const RoutingPtrs& R, void* out, hipStream_t s) {
-  const int nrows = L.T * L.k, nb = (int)(((long)nrows * (L.d / 8) + 255) / 256);
-  if (dt == MODSE_F32)
-    hipLaunchKernelGGL((sum_slabs_kernel<float>), dim3(nb), dim3(256), 0, s, slabs, nrows, L.d, L, kchunk, passes,
-                       R.topk_idx, R.src_of, static_cast<float*>(out));
-  else
-    hipLaunchKernelGGL((sum_slabs_kernel<bf16_t>), dim3(nb), dim3(256), 0, s, slabs, nrows, L.d, L, kchunk, passes,
-                       R.topk_idx, R.src_of, static_cast<bf16_t*>(out));
-  return hipGetLastError();
-}
-
 hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, const void* O, const RoutingPtrs& R,
                            void* dO, float* dg, const BwdPlanArgs& plan, hipStream_t s) {
   const int nrows = L.T * L.k;
@@ -1773,26 +1941,15 @@ hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, c
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const void* dXp,
+hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const DxRows& rows,
                              const float* dg, const RoutingPtrs& R, const GateExtPtrs* G, float aux_grad,
                              const BwdRouterBufs& B, void* dX, float* dW_gate, float* dW_noise, float* dgamma,
                              int accumulate, hipStream_t s) {
   const GateExtPtrs none = {};
   const GateExtPtrs& g = G ? *G : none;
-  const bool noise = g.W_noise != nullptr;
   const float aux_coef = g.probs ? aux_grad * g.alpha * (float)L.N / (float)L.T : 0.f;
-  const int nbt = (L.T + 255) / 256;
-  hipLaunchKernelGGL(gate_bwd_kernel, dim3(nbt), dim3(256), 0, s, dg, L.T, L.N, L.k, R.topk_idx, R.topk_w, R.row_of, g,
-                     aux_coef, B.dl, noise ? B.du : nullptr, noise ? B.dgamma_part : nullptr);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  e = dt == MODSE_F32 ? gate_rows_typed<float>(L, x, W_gate, dXp, B.dl, R, 1, dX, B.dW_partial, dW_gate, accumulate, s)
-                      : gate_rows_typed<bf16_t>(L, x, W_gate, dXp, B.dl, R, 1, dX, B.dW_partial, dW_gate, accumulate, s);
-  if (e != hipSuccess || !noise) return e;
-  e = dt == MODSE_F32
-          ? gate_rows_typed<float>(L, x, g.W_noise, nullptr, B.du, R, 0, dX, B.dW_partial, dW_noise, accumulate, s)
-          : gate_rows_typed<bf16_t>(L, x, g.W_noise, nullptr, B.du, R, 0, dX, B.dW_partial, dW_noise, accumulate, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(dwg_reduce_kernel, dim3(1), dim3(256), 0, s, B.dgamma_part, nbt, 1, accumulate, dgamma);
-  return hipGetLastError();
+  return dt == MODSE_F32 ? bwd_router_typed<float>(L, g, aux_coef, x, W_gate, rows, dg, R, B, dX, dW_gate, dW_noise, dgamma,
+                                                   accumulate, s)
+                         : bwd_router_typed<bf16_t>(L, g, aux_coef, x, W_gate, rows, dg, R, B, dX, dW_gate, dW_noise, dgamma,
+                                                    accumulate, s);
 }
