@@ -13,6 +13,9 @@ WIDE = tuple(32 * w for w in (21, 27, 17, 31, 24, 24, 23, 29))
 
 CASES = [
     ("f32_tiles_128", 544, WIDE, 6205, "f32", 2),
+    # rounds of 128-row tiles that fit: the forward and data-gradient products; the weight gradients
+    ("f32_tall", 736, (864, 992, 736, 992), 30001, "f32", 1),
+    ("f32_wide", 992, (992, 1120) * 8, 200, "f32", 2),
     ("f32_tiles_64", 160, (32, 96, 224, 160), 259, "f32", 2),       # 64 x 64 tiles, one row past two of them
     ("f32_one_row", 64, (32, 96), 1, "f32", 1),
     # bf16: 32-row tiles with K split into chunks (widths of 1 ... 4 chunks, the last ones ragged), one row to all 64 of a
