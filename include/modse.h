@@ -80,9 +80,12 @@ typedef struct {
  * MODSE_WS_FWD for modse_route and for modse_layer_fwd without `saved`,
  * MODSE_WS_BWD for modse_layer_bwd, MODSE_WS_FWD_SAVED for modse_layer_fwd
  * with `saved` (the permuted rows, hidden activations and expert outputs then
- * live in `saved`, and the workspace holds routing scratch and tile plans
- * only; a MODSE_WS_FWD workspace also serves that call).  Any other value:
- * MODSE_ERR_INVALID_ARG. */
+ * live in `saved`, and the workspace holds routing scratch, tile plans and, for
+ * small batches, float32 partial sums; a MODSE_WS_FWD workspace also serves
+ * that call).  The partial sums of split products are what a smaller batch may
+ * need more of than a larger one: a workspace without room for them (one sized
+ * for more tokens) is accepted, and the products are then not split.  Any
+ * other value of `which`: MODSE_ERR_INVALID_ARG. */
 #define MODSE_WS_FWD 0
 #define MODSE_WS_BWD 1
 #define MODSE_WS_FWD_SAVED 2

@@ -77,9 +77,9 @@ namespace {
 // expected number of row blocks of an expert
 double row_blocks(const LayerDims& L, int bm) {
   const double r = (double)L.T * L.k / L.N, s = std::max(0.1, std::min(0.5, L.N / 128.0)), most = r * (1 + s);
-  double n = 1;
-  for (int j = 1; most > (double)j * bm; ++j) n += std::min(1.0, (most - (double)j * bm) / (2 * s * r));
-  return n;
+  // 1 + the sum over j >= 1, j bm < most, of min(1, (most - j bm) / (2 s r))
+  const double last = std::max(0.0, std::ceil(most / bm) - 1), full = std::max(0.0, std::min(last, std::floor((most - 2 * s * r) / bm)));
+  return 1 + full + (r > 0 ? (last - full) * (most - bm * (full + 1 + last) / 2) / (2 * s * r) : 0);
 }
 
 // One product with output tiles of all experts: `tiles` of them with K steps of 64 each
@@ -113,7 +113,8 @@ Work gemm_work(const LayerDims& L, int epilogue, TileShape t) {
 
 // Estimated time in us of a bf16 product (chunk: K steps of a split product's problems, 0 = not split), fitted to the
 // measured times of all five GEMMs at d = 1024 ... 4096, 4 ... 64 experts and 16 ... 8192 tokens.  A step of a tile takes
-// 1.6 us in the 256 x 256 kernel (one workgroup per CU), 1.1 us (weight gradients: 1.85, dH: 1.15) with 128-row tiles and 0.8 us (dH: 1.0) with 64-row ones
+// 1.6 us in the 256 x 256 kernel (one workgroup per CU), 1.1 us (weight gradients: 1.85, dH: 1.15) with 128-row tiles and
+// 0.8 us (dH: 1.0) with 64-row ones
 // (two workgroups per CU); a tile pays for its opening and its epilogue with `fix` further steps, and the float32 slabs of
 // a split product are written and read at 4 TB/s.
 double gemm_cost(const LayerDims& L, int epilogue, TileShape t, int chunk) {
@@ -131,7 +132,8 @@ double gemm_cost(const LayerDims& L, int epilogue, TileShape t, int chunk) {
     // (a lone workgroup's steps are shorter when other CUs stand idle)
     return std::max((rounds + 0.2) * mean, (0.75 + 0.1 * std::min(1.0, w.tiles / cus)) * (w.longest + fix)) * 1.67;
   }
-  const double fix = 2.5, us = wgrad ? 1.85 : epilogue == EPI_SWIGLU_BWD ? (t.bm == 128 ? 1.15 : 1.0) : t.bm == 128 ? 1.1 : 0.8, slots = 2 * cus;
+  const double fix = 2.5, slots = 2 * cus;
+  const double us = wgrad ? 1.85 : epilogue == EPI_SWIGLU_BWD ? (t.bm == 128 ? 1.15 : 1.0) : t.bm == 128 ? 1.1 : 0.8;
   double mean = w.steps / w.tiles + fix, chain = w.longest + fix, slabs = 0;
   if (chunk) {
     const double n = std::max(1.0, w.steps / w.tiles / chunk);

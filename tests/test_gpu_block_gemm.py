@@ -3,6 +3,7 @@ fp64 CPU oracle, at sizes whose row, column and K remainders fall on every side 
 of the layer's parity tests: max|out - ref| <= tol * max|ref|, 1e-4 (fp32) and 2e-2 (bf16 storage of the activations)."""
 import pytest
 
+import test_gpu_gate_ext as gate_ext
 from oracle import modse_oracle as orc
 from test_gpu_parity import TOL, check_grads, check_routing, make, max_rel, _runner
 
@@ -18,6 +19,7 @@ CASES = [
     ("f32_wide", 992, (992, 1120) * 8, 200, "f32", 2),
     ("f32_tiles_64", 160, (32, 96, 224, 160), 259, "f32", 2),       # 64 x 64 tiles, one row past two of them
     ("f32_one_row", 64, (32, 96), 1, "f32", 1),
+    ("f32_split", 160, (4128, 2048, 1952, 672), 97, "f32", 2),
     # bf16: 32-row tiles with K split into chunks (widths of 1 ... 4 chunks, the last ones ragged), one row to all 64 of a
     # tile's upper bound; 64- and 128-row tiles, split; 128-row tiles, unsplit, experts one row past a block
     ("bf16_one_row", 96, (32, 2720), 1, "bf16", 2),
@@ -65,3 +67,22 @@ def test_workspace_without_room_for_partial_sums(T):
     y_ref = orc.layer_fwd(inp.x, inp.W_gate, inp.W1, inp.W3, inp.W2, d_ff, k, topk_idx=idx)
     assert max_rel(to_host(r.y), y_ref) <= TOL["bf16"]
     check_grads(r, inp, idx, TOL["bf16"])
+
+
+@pytest.mark.parametrize("case", [
+    ("ext_split", 96, (4128, 96, 3104, 2016), 130, "bf16", 2),   # dX in partial sums, both gate extensions
+    ("ext_many_tokens", 32, (32, 64, 32, 96), 65633, "bf16", 2),  # several groups of tokens per block of the router's backward
+], ids=lambda c: c[0])
+def test_gate_ext(case):
+    gate_ext.test_layer_fwd_bwd_ext_parity(case, True, True)
+
+
+def test_many_tokens_plain_gate():
+    """Chunks of several token groups in the router's weight gradient, columns that do not fill a slab."""
+    T, d, d_ff, k = 65633, 32, (32, 64, 96), 2
+    inp = make("many_tokens", d, d_ff, T, "f32", k, need_dy=True)
+    r = _runner(inp, need_bwd=True)
+    r.fwd()
+    r.bwd()
+    idx, _ = check_routing(inp, r.routing_host())
+    check_grads(r, inp, idx, TOL["f32"])
