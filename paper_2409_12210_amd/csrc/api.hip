@@ -6,8 +6,11 @@
 #include <cstring>
 
 #include "common.h"
+#include "gemm_choice.h"
 
 namespace {
+using modse_gemm::GemmChoice;
+using modse_gemm::gemm_choice;
 
 struct Carver {
   size_t off = 0;

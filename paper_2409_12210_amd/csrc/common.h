@@ -196,12 +196,6 @@ hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, 
 struct TileShape {
   int32_t bm, bn;
 };
-struct GemmChoice {
-  TileShape tile;
-  int32_t kchunk;  // the product's K = f_e is cut into ceil(f_e / kchunk) chunks (per operand pair); 0 = not split
-};
-// tiles (and split) of the GEMM with this epilogue; a pure function of its arguments
-GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue);
 // t: the tile shape that the plan was made with.  max_tiles: upper bound of the number of tiles.  layout < 0: the
 // layout that goes with the epilogue (see gemm.hip).
 hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int accumulate,
