@@ -135,7 +135,8 @@ modse_status modse_layer_fwd(const modse_desc* desc, int64_t T, const void* x, c
  * the same inputs.  dY [T,d] DEVICE in.  Outputs: dX [T,d] (desc.dtype),
  * dW_gate [d,N], dW1 [F,d], dW3 [F,d], dW2 (packed like W2), all float32.
  * accumulate = 0 overwrites the weight gradients, 1 adds to them (fp32
- * gradient accumulation); dX is always overwritten. */
+ * gradient accumulation); dX is always overwritten, and may lie in the buffer of
+ * dY or of x (which then no longer holds the layer's input). */
 modse_status modse_layer_bwd(const modse_desc* desc, int64_t T, const void* x, const void* W_gate, const void* W1,
                              const void* W3, const void* W2, const modse_routing* routing, const void* saved,
                              const void* dY, void* dX, float* dW_gate, float* dW1, float* dW3, float* dW2,

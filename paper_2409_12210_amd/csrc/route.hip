@@ -1846,6 +1846,16 @@ hipError_t bwd_router_typed(const LayerDims& L, const GateExtPtrs& G, float aux_
   if (e != hipSuccess) return e;
   const int nmat = noise ? 2 : 1, slabs = (L.d + BR_SLAB - 1) / BR_SLAB, nb = (L.T + BR_TOK - 1) / BR_TOK;
   const BwdRouterArgs a = {W, G.W_noise, B.dl, B.du, L.T, L.d, L.N, nmat * L.N, L.k, R.row_of};
+  // dX comes last: its buffer may be x's (nothing after the weight gradients reads x).
+  // about 512 blocks: fewer, longer chunks mean fewer partial gradients (two matrices: room for half as many)
+  const int groups = (L.N + 7) / 8 * nmat;
+  const int tok = std::max(nmat, std::min(16, nb * slabs * groups / 512)) * BR_TOK, nchunk = (L.T + tok - 1) / tok;
+  hipLaunchKernelGGL((bwd_dwg_kernel<T>), dim3(nchunk, slabs, groups), dim3(256), 0, s, a, x, tok, B.dW_partial);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const int n = L.d * L.N;
+  hipLaunchKernelGGL(dwg_reduce_kernel, dim3((n * nmat + 63) / 64 + (noise ? 1 : 0)), dim3(256), 0, s, B.dW_partial, nchunk, n,
+                     nmat, B.dgamma_part, nbt, accumulate, dW_gate, dW_noise, dgamma);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   if (sparse) {
     const dim3 grid((unsigned)(((long)L.T * (L.d / 8) + 255) / 256));
     if (rows.kchunk)
@@ -1856,8 +1866,8 @@ hipError_t bwd_router_typed(const LayerDims& L, const GateExtPtrs& G, float aux_
                          static_cast<const T*>(B.Wt), B.dl, R.topk_idx, R.row_of, dX);
   } else {
     if (rows.kchunk) {
-      const long n = (long)L.T * L.k * (L.d / 8);
-      hipLaunchKernelGGL((sum_slabs_kernel<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, rows.slabs, L.T * L.k, L.d,
+      const long chunks = (long)L.T * L.k * (L.d / 8);
+      hipLaunchKernelGGL((sum_slabs_kernel<T>), dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, s, rows.slabs, L.T * L.k, L.d,
                          L, rows.kchunk, 2, R.topk_idx, R.src_of, static_cast<T*>(rows.dXp));
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -1866,15 +1876,6 @@ hipError_t bwd_router_typed(const LayerDims& L, const GateExtPtrs& G, float aux_
     hipLaunchKernelGGL((bwd_gate_rows_ext_kernel<T>), dim3((nb + rounds - 1) / rounds, slabs), dim3(256), 0, s, a, dXp, rounds,
                        dX);
   }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  // about 512 blocks: fewer, longer chunks mean fewer partial gradients (two matrices: room for half as many)
-  const int groups = (L.N + 7) / 8 * nmat;
-  const int tok = std::max(nmat, std::min(16, nb * slabs * groups / 512)) * BR_TOK, nchunk = (L.T + tok - 1) / tok;
-  hipLaunchKernelGGL((bwd_dwg_kernel<T>), dim3(nchunk, slabs, groups), dim3(256), 0, s, a, x, tok, B.dW_partial);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int n = L.d * L.N;
-  hipLaunchKernelGGL(dwg_reduce_kernel, dim3((n * nmat + 63) / 64 + (noise ? 1 : 0)), dim3(256), 0, s, B.dW_partial, nchunk, n,
-                     nmat, B.dgamma_part, nbt, accumulate, dW_gate, dW_noise, dgamma);
   return hipGetLastError();
 }
 
