@@ -76,16 +76,18 @@ typedef struct {
                               logits among their top_k+1 largest */
 } modse_routing;
 
-/* Bytes of DEVICE workspace `ws` that a call requires for T tokens.  `which`:
- * MODSE_WS_FWD for modse_route and for modse_layer_fwd without `saved`,
+/* Bytes of DEVICE workspace `ws` that serve a call for T tokens or fewer.
+ * `which`: MODSE_WS_FWD for modse_route and for modse_layer_fwd without `saved`,
  * MODSE_WS_BWD for modse_layer_bwd, MODSE_WS_FWD_SAVED for modse_layer_fwd
  * with `saved` (the permuted rows, hidden activations and expert outputs then
- * live in `saved`, and the workspace holds routing scratch, tile plans and, for
- * small batches, float32 partial sums; a MODSE_WS_FWD workspace also serves
- * that call).  The partial sums of split products are what a smaller batch may
- * need more of than a larger one: a workspace without room for them (one sized
- * for more tokens) is accepted, and the products are then not split.  Any
- * other value of `which`: MODSE_ERR_INVALID_ARG. */
+ * live in `saved`, and the workspace holds routing scratch, tile plans and
+ * float32 partial sums; a MODSE_WS_FWD workspace also serves that call).  Any
+ * other value: MODSE_ERR_INVALID_ARG.
+ * Results do not depend on ws_bytes as long as it is at least the size for the
+ * call's T, so one workspace, sized for a program's largest batch, does for all.
+ * A smaller one is refused, unless all that it lacks is room for the partial sums
+ * of a product that small batches split: the product is then not split, which
+ * is slower and adds in another order. */
 #define MODSE_WS_FWD 0
 #define MODSE_WS_BWD 1
 #define MODSE_WS_FWD_SAVED 2

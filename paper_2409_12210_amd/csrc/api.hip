@@ -93,14 +93,15 @@ RouteBufs route_bufs(char* base, const RouteScratch& r) {
 
 struct FwdLayout {
   RouteScratch route;
-  size_t topk_idx, topk_w, counts, offsets, row_of, src_of, near_tie, plan_up, plan_down, Xp, H, O, Opart, unsplit, total;
-  GemmChoice down;
+  size_t topk_idx, topk_w, counts, offsets, row_of, src_of, near_tie, plan_up, plan_down, Xp, H, O, total;
 };
 
-int splitk_max_chunks(const LayerDims& L, int kchunk) {
-  int m = 0;
-  for (int e = 0; e < L.N; ++e) m = std::max(m, (L.f[e] + kchunk - 1) / kchunk);
-  return m;
+// Float32 partial sums of a product with d columns whose K = f_e is cut into chunks of kchunk (once per operand pair);
+// they lie behind the rest of a workspace.
+size_t partial_sum_bytes(const LayerDims& L, int kchunk, int passes) {
+  if (kchunk == 0) return 0;
+  const int fmax = L.f[L.order[0]];
+  return align_up((size_t)passes * ((fmax + kchunk - 1) / kchunk) * L.T * L.k * L.d * 4, 256);
 }
 
 // with_saved: the call is given the buffer that carries activations to the backward pass; the permuted rows,
@@ -122,9 +123,6 @@ FwdLayout fwd_layout(const LayerDims& L, modse_dtype dt, bool with_saved) {
   w.Xp = c.take(with_saved ? 0 : Tk * L.d * es);
   w.H = c.take(with_saved ? 0 : hidden_elems_max(L) * es);
   w.O = c.take(with_saved ? 0 : Tk * L.d * es);
-  w.down = gemm_choice(L, dt, EPI_STORE);
-  w.unsplit = c.off;
-  w.Opart = c.take(w.down.kchunk ? (size_t)splitk_max_chunks(L, w.down.kchunk) * Tk * L.d * 4 : 0);
   w.total = c.off;
   return w;
 }
@@ -147,8 +145,7 @@ SavedLayout saved_layout(const LayerDims& L, modse_dtype dt) {
 }
 
 struct BwdLayout {
-  size_t plan[3], dO, dA, dB, dXp, dg, dl, du, dgamma_part, dWg_partial, Wt, dXpart, unsplit, total;
-  GemmChoice dx;
+  size_t plan[3], dO, dA, dB, dXp, dg, dl, du, dgamma_part, dWg_partial, Wt, total;
 };
 
 BwdLayout bwd_layout(const LayerDims& L, modse_dtype dt) {
@@ -168,11 +165,22 @@ BwdLayout bwd_layout(const LayerDims& L, modse_dtype dt) {
   w.dgamma_part = c.take((((size_t)L.T + 63) / 64) * 4);
   w.dWg_partial = c.take((nb + 1) * L.d * L.N * 4);  // (W_gate and W_noise: twice one per 64 tokens)
   w.Wt = c.take((size_t)L.d * L.N * es);
-  w.dx = gemm_choice(L, dt, EPI_STORE_DUALK);
-  w.unsplit = c.off;
-  w.dXpart = c.take(w.dx.kchunk ? (size_t)2 * splitk_max_chunks(L, w.dx.kchunk) * Tk * L.d * 4 : 0);
   w.total = c.off;
   return w;
+}
+
+// A workspace that serves every batch of at most L.T tokens.  The parts of a layout grow with the batch, but the partial
+// sums of a split product do not: batches of a middling size have the most of them, and large ones none.  Sized for one
+// batch alone, the workspace of a program's largest one would leave the smaller ones without room for theirs.
+template <typename Layout>
+size_t workspace_bytes(const LayerDims& L, modse_dtype dt, int epilogue, Layout layout_bytes) {
+  size_t bytes = layout_bytes(L);
+  modse_gemm::for_each_split(L, dt, epilogue, [&](int64_t tokens, int kchunk) {
+    LayerDims M = L;
+    M.T = (int32_t)tokens;
+    bytes = std::max(bytes, layout_bytes(M) + partial_sum_bytes(M, kchunk, epilogue == EPI_STORE ? 1 : 2));
+  });
+  return bytes;
 }
 
 // Upper bound of the number of tiles of a GEMM whose rows are the experts' token rows (top_k * T in all, at most T of
@@ -297,8 +305,12 @@ modse_status modse_workspace_size(const modse_desc* desc, int64_t T, int need_bw
   if (st != MODSE_OK) return st;
   const LayerDims L = make_dims(desc, T);
   if (need_bwd != MODSE_WS_FWD && need_bwd != MODSE_WS_BWD && need_bwd != MODSE_WS_FWD_SAVED) return MODSE_ERR_INVALID_ARG;
-  *bytes = need_bwd == MODSE_WS_BWD ? bwd_layout(L, desc->dtype).total
-                                    : fwd_layout(L, desc->dtype, need_bwd == MODSE_WS_FWD_SAVED).total;
+  const modse_dtype dt = desc->dtype;
+  if (need_bwd == MODSE_WS_BWD)
+    *bytes = workspace_bytes(L, dt, EPI_STORE_DUALK, [&](const LayerDims& M) { return bwd_layout(M, dt).total; });
+  else
+    *bytes = workspace_bytes(L, dt, EPI_STORE,
+                             [&](const LayerDims& M) { return fwd_layout(M, dt, need_bwd == MODSE_WS_FWD_SAVED).total; });
   return MODSE_OK;
 }
 
@@ -407,11 +419,10 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   if (routing_out && !routing_complete(routing_out)) return MODSE_ERR_INVALID_ARG;
   const modse_dtype dt = desc->dtype;
   const LayerDims L = make_dims(desc, T);
-  FwdLayout w = fwd_layout(L, dt, saved != nullptr);
-  // a workspace made for more tokens may be too small for the partial sums that this batch would use: it then does
-  // without them
-  if (ws_bytes < w.total) w.down.kchunk = 0;
-  if (ws_bytes < w.unsplit) return MODSE_ERR_WORKSPACE;
+  const FwdLayout w = fwd_layout(L, dt, saved != nullptr);
+  if (ws_bytes < w.total) return MODSE_ERR_WORKSPACE;
+  GemmChoice down = gemm_choice(L, dt, EPI_STORE);
+  if (ws_bytes - w.total < partial_sum_bytes(L, down.kchunk, 1)) down.kchunk = 0;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   char* wsb = static_cast<char*>(ws);
   const RoutingPtrs R = routing_from(routing_out, wsb, w);
@@ -436,10 +447,10 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   pa.up = reinterpret_cast<GemmPlan*>(wsb + w.plan_up);
   pa.down = reinterpret_cast<GemmPlan*>(wsb + w.plan_down);
   pa.up_tile = gemm_choice(L, dt, EPI_SWIGLU).tile;
-  pa.down_tile = w.down.tile;
-  const int kchunk = w.down.kchunk;
+  pa.down_tile = down.tile;
+  const int kchunk = down.kchunk;
   pa.kchunk = kchunk;
-  pa.Opart = reinterpret_cast<float*>(wsb + w.Opart);
+  pa.Opart = reinterpret_cast<float*>(wsb + w.total);
   // histogram, scan (which also writes the tile plans), stable scatter: one launch for all of it on decode-sized
   // batches
   HIP_TRY(launch_permute(L, dt, x, R, RB, Xp, ext ? &G : nullptr, &pa, s));
@@ -486,9 +497,10 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   if (!routing_complete(routing)) return MODSE_ERR_INVALID_ARG;
   const modse_dtype dt = desc->dtype;
   const LayerDims L = make_dims(desc, T);
-  BwdLayout w = bwd_layout(L, dt);
-  if (ws_bytes < w.total) w.dx.kchunk = 0;  // (as in the forward pass)
-  if (ws_bytes < w.unsplit) return MODSE_ERR_WORKSPACE;
+  const BwdLayout w = bwd_layout(L, dt);
+  if (ws_bytes < w.total) return MODSE_ERR_WORKSPACE;
+  GemmChoice dx = gemm_choice(L, dt, EPI_STORE_DUALK);
+  if (ws_bytes - w.total < partial_sum_bytes(L, dx.kchunk, 2)) dx.kchunk = 0;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   char* wsb = static_cast<char*>(ws);
   const SavedLayout sl = saved_layout(L, dt);
@@ -506,13 +518,13 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   pa.W1 = W1; pa.W3 = W3; pa.W2 = W2;
   pa.dA = wsb + w.dA; pa.dB = wsb + w.dB; pa.dXp = wsb + w.dXp;
   pa.dW1 = dW1; pa.dW3 = dW3; pa.dW2 = dW2;
-  pa.dXpart = reinterpret_cast<float*>(wsb + w.dXpart);
-  pa.dx_kchunk = w.dx.kchunk;
+  pa.dXpart = reinterpret_cast<float*>(wsb + w.total);
+  pa.dx_kchunk = dx.kchunk;
   pa.dh = reinterpret_cast<GemmPlan*>(wsb + w.plan[0]);
   pa.dx = reinterpret_cast<GemmPlan*>(wsb + w.plan[1]);
   pa.wg = reinterpret_cast<GemmPlan*>(wsb + w.plan[2]);
   pa.dh_tile = gemm_choice(L, dt, EPI_SWIGLU_BWD).tile;
-  pa.dx_tile = w.dx.tile;
+  pa.dx_tile = dx.tile;
   pa.wg_tile = gemm_choice(L, dt, EPI_STORE_F32).tile;
   HIP_TRY(launch_bwd_prep(L, dt, dY, sb + sl.O, R, dO, dg, pa, s));
   stamp.mark(MODSE_STAGE_BWD_PREP);

@@ -117,6 +117,9 @@ inline int split_chunk(const LayerDims& L, modse_dtype dt, TileShape t, int pass
   chunk = (int64_t)align_up((size_t)std::max<int64_t>(chunk, (F + most - 1) / most), 64);
   return fmax > 2 * chunk ? (int)chunk : 0;
 }
+// bf16 products with d columns: mean rows of an expert up to which they take the tiles of 32 and 64 rows
+constexpr int split_rows_max(int bm) { return bm == 32 ? 28 : 58; }
+
 inline GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue) {
   const int passes = epilogue == EPI_STORE ? 1 : epilogue == EPI_STORE_DUALK ? 2 : 0;  // 0: never split
   auto with_chunk = [&](TileShape t) {
@@ -140,8 +143,8 @@ inline GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue) 
   // tiles as long as they hold an expert's rows.  d = 2048, eight experts: 32 rows (T = 130) 32 against 64 rows 54 / 56
   // us with 64 / 128-row tiles, 97 rows 74 / 71.
   if (passes) {
-    if (passes == 1 && r <= 28) return with_chunk(TileShape{32, 128});
-    if (r <= 58) return with_chunk(TileShape{64, 128});
+    if (passes == 1 && r <= split_rows_max(32)) return with_chunk(TileShape{32, 128});
+    if (r <= split_rows_max(64)) return with_chunk(TileShape{64, 128});
   }
   GemmChoice best = {swiglu ? TileShape{256, 128} : TileShape{256, 256}, 0};
   // (loads less even than assumed cost the large tiles more, hence the 5 %)
@@ -158,6 +161,29 @@ inline GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue) 
     }
   }
   return best;
+}
+
+// Calls visit(T', kchunk) with token counts T' <= L.T among which is the one whose split product has the largest partial
+// sums.  For a given tile the chunk length goes by the number of row blocks of an expert's mean rows, so the largest T' of
+// each number of them does (whether such a batch really takes that tile does not matter for an upper bound).  At most a few
+// hundred visits, for layers of a few narrow experts; usually one to twenty.
+template <typename Visit>
+inline void for_each_split(LayerDims L, modse_dtype dt, int epilogue, Visit visit) {
+  const int64_t T = L.T;
+  const int passes = epilogue == EPI_STORE ? 1 : 2;
+  for (int bm = dt == MODSE_BF16 && passes == 1 ? 32 : 64; bm <= 128; bm *= 2) {
+    const TileShape t = {bm, dt == MODSE_F32 ? bm : 128};
+    // (bf16: the tiles of 32 and 64 rows are for that many mean rows per expert only)
+    const int64_t most = std::min(T, dt == MODSE_BF16 && bm < 128 ? (int64_t)split_rows_max(bm) * L.N / L.k : T);
+    for (int64_t blocks = 1;; ++blocks) {
+      const int64_t tokens = std::min(most, blocks * bm * L.N / L.k);
+      L.T = (int32_t)tokens;
+      const int kchunk = split_chunk(L, dt, t, passes);
+      if (kchunk == 0) break;  // nor for more rows
+      visit(tokens, kchunk);
+      if (tokens == most) break;
+    }
+  }
 }
 
 }  // namespace modse_gemm

@@ -3,6 +3,8 @@ import os
 import subprocess
 import sys
 
+import paper_2409_12210_amd as m
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 WIDTHS = [2816, 8448, 4224, 7040, 4928, 6336, 5632, 5632]
 
@@ -40,3 +42,15 @@ def test_sizes_do_not_depend_on_a_device(tmp_path):
         out.append(r.stdout)
     assert out[0] == out[1]
     assert out[0].split()[-1] == "0", "device queries made"
+
+
+def test_a_workspace_for_a_larger_batch_serves_the_smaller_ones():
+    """Sizes never fall with the token count, although the partial sums of split products are a matter of small batches: a
+    program sizes once, for its largest batch."""
+    for d, d_ff, k in ((2048, WIDTHS, 2), (4096, [14336] * 8, 2), (1024, [2816] * 4, 1), (96, [4128, 96, 3104, 2016], 2),
+                       (32, [9600, 32], 1)):
+        for dtype in ("bf16", "f32"):
+            for which in (m.WS_FWD, m.WS_BWD, m.WS_FWD_SAVED):
+                sizes = [m.modse_workspace_size(d, d_ff, k, dtype, T, which)
+                         for T in list(range(1, 1200)) + list(range(1200, 40000, 371))]
+                assert sizes == sorted(sizes), (d, dtype, which)
