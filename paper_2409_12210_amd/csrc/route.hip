@@ -947,22 +947,23 @@ __global__ __launch_bounds__(SCAN_THREADS) void route_scan_kernel(int32_t* __res
 // Auxiliary load-balance loss (Sec. 3.2 Eq. 9-12), single block: f_i = share of tokens whose first choice is
 // expert i, P_i = mean of p_i, L_a = alpha N sum_i f_i P_i.  A thread sums one column over every nrow-th token (threads
 // side by side read whole lines of p, sixteen loads in flight), the threads' sums of a column are added in a fixed tree,
-// so the result does not depend on timing.  8192 tokens, 8 experts: 8 to 11 us in place of 61 to 83 with one pass over
-// all tokens per expert.
+// so the result does not depend on timing.  The sums are float64: a thread adds up to ntok N / 1024 values in a row, which
+// in float32 put P off by 7e-7 at 2^20 tokens and 64 experts.  8192 tokens, 8 experts: 8 to 11 us in place of 61 to 83
+// with one pass over all tokens per expert.
 constexpr int AUX_THREADS = 1024;
 __global__ __launch_bounds__(AUX_THREADS) void aux_finish_kernel(const float* __restrict__ probs,
                                                                  const int32_t* __restrict__ topk_idx, int ntok, int N,
                                                                  int top_k, float alpha, float* __restrict__ f_out,
                                                                  float* __restrict__ P_out, float* __restrict__ loss) {
-  __shared__ float s_p[AUX_THREADS];
+  __shared__ double s_p[AUX_THREADS];
   __shared__ int s_c[MODSE_MAX_EXPERTS];
   const int tid = threadIdx.x;
   if (tid < N) s_c[tid] = 0;
   const int nrow = AUX_THREADS / N, e = tid % N, r0 = tid / N;
-  float acc = 0.f;
+  double acc = 0.0;
   if (r0 < nrow) {
 #pragma unroll 16
-    for (int t = r0; t < ntok; t += nrow) acc += probs[(size_t)t * N + e];
+    for (int t = r0; t < ntok; t += nrow) acc += (double)probs[(size_t)t * N + e];
   }
   s_p[tid] = acc;
   __syncthreads();
@@ -975,16 +976,16 @@ __global__ __launch_bounds__(AUX_THREADS) void aux_finish_kernel(const float* __
     __syncthreads();
   }
   if (tid < 64) {
-    float l = 0.f;
+    double l = 0.0;
     if (tid < N) {
-      const float P = s_p[tid] / (float)ntok, f = (float)s_c[tid] / (float)ntok;
-      f_out[tid] = f;
-      P_out[tid] = P;
+      const double P = s_p[tid] / ntok, f = (double)s_c[tid] / ntok;
+      f_out[tid] = (float)f;
+      P_out[tid] = (float)P;
       l = f * P;
     }
 #pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) l += __shfl_xor(l, m, 64);
-    if (tid == 0) loss[0] = alpha * (float)N * l;
+    for (int m = 32; m >= 1; m >>= 1) l += shfl_xor_f64(l, m);
+    if (tid == 0) loss[0] = (float)((double)alpha * N * l);
   }
 }
 
