@@ -1653,8 +1653,10 @@ __global__ __launch_bounds__(256) void dwg_reduce_kernel(const float* __restrict
 #pragma unroll 8
     for (int b = part; b < nchunk; b += 4) acc += partial[(size_t)b * total + i];  // unrolled: several loads in flight
   } else if (nmat == 2 && blockIdx.x == gridDim.x - 1 && li == 63) {
+    double sum = 0.0;  // (T / 256 values in a row)
 #pragma unroll 8
-    for (int b = part; b < ngamma; b += 4) acc += dgamma_part[b];
+    for (int b = part; b < ngamma; b += 4) sum += (double)dgamma_part[b];
+    acc = (float)sum;
   }
   s_part[part][li] = acc;
   __syncthreads();

@@ -1,4 +1,4 @@
-"""The auxiliary loss over many tokens and experts: one block sums all probabilities, so its sums are long."""
+"""Sums of the gate extensions over many tokens: the means of the auxiliary loss, the gradient of the noise term's gain."""
 import pytest
 import torch
 
@@ -30,3 +30,32 @@ def test_means_are_rounded_once(T, N):
     assert (ext.aux_f.cpu().double() - f).abs().max() <= 6e-8
     loss = float(torch.tensor(0.01)) * N * float((f * P).sum())
     assert abs(float(ext.aux_loss) - loss) <= 1.2e-7 * loss
+
+
+def test_dgamma_of_many_equal_tokens():
+    """2^20 copies of one token: their shares of dgamma are equal, and the 64 that a wave adds up make a sum without rounding,
+    so that dgamma is 2^14 times what 64 copies give.  Four float32 partial sums are rounded and added: 3 * 2^-24 = 1.8e-7."""
+    d, d_ff = 32, [32, 32]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+
+    def normal(*shape, sigma=1.0):
+        return sigma * torch.randn(shape, generator=gen, device="cuda")
+
+    x1, dy1, Wg, Wn = normal(1, d), normal(1, d), normal(d, 2), normal(d, 2)
+    W1, W3, W2 = normal(64, d), normal(64, d), normal(64 * d)
+    got = []
+    for T in (64, 1 << 20):
+        layer = (d, d_ff, 2, "f32", T)
+        x, dY, y, dX = x1.repeat(T, 1), dy1.repeat(T, 1), torch.empty((T, d), device="cuda"), torch.empty((T, d), device="cuda")
+        ext = m.GateExt(W_noise=Wn, gamma=torch.ones(1, device="cuda"), eps=1e-6, noise_pre=torch.empty((T, 2), device="cuda"))
+        r = m.Routing.empty(T, 2, 2)
+        saved = torch.empty(m.modse_saved_size(*layer), dtype=torch.uint8, device="cuda")
+        ws = torch.empty(max(m.modse_workspace_size(*layer, w) for w in (m.WS_FWD_SAVED, m.WS_BWD)), dtype=torch.uint8,
+                         device="cuda")
+        g = [torch.empty(n, device="cuda") for n in (2 * d, 2 * d, 1, 64 * d, 64 * d, 64 * d)]
+        m.modse_layer_fwd_ext(*layer, x, Wg, None, ext, W1, W3, W2, y, r, saved, ws)
+        m.modse_layer_bwd_ext(*layer, x, Wg, ext, 0.0, W1, W3, W2, r, saved, dY, dX, *g, False, ws)
+        torch.cuda.synchronize()
+        got.append(float(g[2]) / T)
+    assert got[0] != 0.0
+    assert abs(got[1] - got[0]) <= 1.8e-7 * abs(got[0])
