@@ -1,0 +1,53 @@
+"""Which tiles the GPU parity cases take (host code, no GPU): a case that is there for a tile takes it, and every tile that
+some layer takes is met by a parity case with a K loop longer than any ring, a partial last K step and cut last tiles."""
+import random
+
+import pytest
+
+import test_gpu_block_gemm as block
+import test_gpu_gate_ext as ext
+import test_gpu_parity as parity
+import test_gpu_tile_choices as tiles
+from choice_probe import GEMMS, choice
+
+
+@pytest.mark.parametrize("case", tiles.CASES, ids=[c[0] for c in tiles.CASES])
+def test_case_takes_the_tiles_it_is_there_for(case):
+    name, d, d_ff, T, dtype, k, _, takes = case
+    for gemm, (bm, split) in takes.items():
+        c = choice(gemm, d, d_ff, k, T, dtype)
+        assert (c.bm, c.kchunk > 0) == (bm, split), (gemm, c)
+
+
+def meets_the_edges(gemm, d, d_ff, k, T, dtype, c):
+    step = 32 if dtype == "f32" else 64
+    if gemm == "wgrad":  # contracts over an expert's rows; its matrices are d_ff x d and d x d_ff
+        return T * k / len(d_ff) >= 4 * step and d % c.bn and any(f % c.bm for f in d_ff)
+    if gemm in ("up", "dh"):
+        depth, columns = [d], d_ff
+    else:
+        depth, columns = ([min(f, c.kchunk) for f in d_ff] if c.kchunk else d_ff), [d]
+    tail = dtype == "f32" or any(f % step for f in ([d] if gemm in ("up", "dh") else d_ff))
+    return max(depth) >= 4 * step and tail and any(n % c.bn for n in columns)
+
+
+def test_every_tile_has_a_parity_case():
+    cases = [(c[:6], GEMMS) for c in parity.BWD_CASES + ext.LAYER_CASES + block.CASES + tiles.CASES]
+    cases += [(c[:6], ("up", "down")) for c in parity.FWD_CASES]
+    met = set()
+    for (_, d, d_ff, T, dtype, k), gemms in cases:
+        for gemm in gemms:
+            c = choice(gemm, d, d_ff, k, T, dtype)
+            if meets_the_edges(gemm, d, d_ff, k, T, dtype, c):
+                met.add((dtype, gemm, c.bm, c.kchunk > 0))
+    rng, taken = random.Random(5), {}
+    for _ in range(20000):
+        n = rng.choice([1, 2, 4, 8, 8, 16, 32, 64])
+        d, T, k = 32 * int(2 ** rng.uniform(0, 7)), int(2 ** rng.uniform(0, 15)), min(n, rng.choice([1, 2]))
+        d_ff = [32 * int(2 ** rng.uniform(0, 8)) for _ in range(n)]
+        dtype = rng.choice(["bf16", "f32"])
+        for gemm in GEMMS:
+            c = choice(gemm, d, d_ff, k, T, dtype)
+            taken[dtype, gemm, c.bm, c.kchunk > 0] = (d, d_ff, T, k)
+    assert len(taken) >= 29
+    assert set(taken) <= met, {t: taken[t] for t in set(taken) - met}
