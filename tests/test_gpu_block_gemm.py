@@ -9,19 +9,20 @@ from test_gpu_parity import TOL, check_grads, check_routing, make, max_rel, _run
 
 pytestmark = pytest.mark.gpu
 
-# enough tiles for 128 x 128 ones in every GEMM; d and the widths are odd multiples of 32
+# d and the widths are odd multiples of 32
 WIDE = tuple(32 * w for w in (21, 27, 17, 31, 24, 24, 23, 29))
 
 CASES = [
-    ("f32_tiles_128", 544, WIDE, 6205, "f32", 2),
+    # 64 x 64 tiles, several rounds of them
+    ("f32_many_tiles_64", 544, WIDE, 6205, "f32", 2),
     # rounds of 128-row tiles that fit: the forward and data-gradient products; the weight gradients
     ("f32_tall", 736, (864, 992, 736, 992), 30001, "f32", 1),
     ("f32_wide", 992, (992, 1120) * 8, 200, "f32", 2),
-    ("f32_tiles_64", 160, (32, 96, 224, 160), 259, "f32", 2),       # 64 x 64 tiles, one row past two of them
+    ("f32_tiles_64", 160, (32, 96, 224, 160), 259, "f32", 2),       # one row past two tiles
     ("f32_one_row", 64, (32, 96), 1, "f32", 1),
     ("f32_split", 160, (4128, 2048, 1952, 672), 97, "f32", 2),
-    # bf16: 32-row tiles with K split into chunks (widths of 1 ... 4 chunks, the last ones ragged), one row to all 64 of a
-    # tile's upper bound; 64- and 128-row tiles, split; 128-row tiles, unsplit, experts one row past a block
+    # bf16, the products with d columns: K split into chunks (widths of 1 to 7 chunks, the last ones ragged) over 32-row
+    # tiles (one row), 64-row tiles (32 and 48 mean rows per expert) and 128-row ones (125); 128- and 32-row tiles, unsplit
     ("bf16_one_row", 96, (32, 2720), 1, "bf16", 2),
     ("bf16_rows_32", 96, (2720, 32, 1312, 640), 64, "bf16", 2),
     ("bf16_rows_64", 160, (4128, 2048, 1952, 672), 97, "bf16", 2),
@@ -44,8 +45,8 @@ def test_fwd_and_grads(case):
     assert max_rel(to_host(r.y), y_ref) <= TOL[dtype]
     g = check_grads(r, inp, idx, TOL[dtype])
     r.bwd(accumulate=True)
-    assert max_rel(to_host(r.dW1), 2 * g.dW1) <= TOL[dtype]
-    assert max_rel(to_host(r.dW2), 2 * g.dW2) <= TOL[dtype]
+    for n in ("dW1", "dW3", "dW2", "dW_gate"):
+        assert max_rel(to_host(getattr(r, n)), 2 * getattr(g, n)) <= TOL[dtype], n
 
 
 @pytest.mark.parametrize("T", [40, 250])

@@ -61,26 +61,28 @@ ROUTE_CASES = [
     ("n3", 96, (32, 64, 96), 130, "bf16", 2),
     ("n64", 64, (32,) * 64, 200, "f32", 2),
     ("wide_d", 4096, (64, 192, 128, 128), 70, "bf16", 2),
-    # decode-sized batches (at most 64 tokens) take the one-block-per-token router
+    # decode-sized batches: one block per token (as for every batch of up to 4096 tokens; with more than 16 experts the form
+    # in which sixteen threads share a row of W_gate)
     ("decode_n16", 128, (64,) * 16, 40, "f32", 2),
     ("decode_n3", 96, (32, 64, 96), 64, "bf16", 2),
     ("decode_top1", 256, (128, 384, 192, 320), 33, "bf16", 1),
     ("decode_wide", 4096, (64, 192, 128, 128, 64, 192, 128, 128), 64, "bf16", 2),
-    ("decode_n24", 64, (32,) * 24, 50, "bf16", 2),      # block router + the fused decode-sized permute
+    ("decode_n24", 64, (32,) * 24, 50, "bf16", 2),
     ("decode_n64_top1", 64, (32,) * 64, 64, "f32", 1),
-    # batches beyond 4096 tokens (or with more than 16 experts, from 1024 tokens) take the router that keeps
-    # W_gate in LDS: every padded expert count, both dtypes, ragged token counts, several groups per block
+    # batches beyond 4096 tokens with up to 16 experts take the router that keeps W_gate in LDS: every padded expert count,
+    # both dtypes, ragged token counts, several groups per block
     ("stream_n8", 256, (128, 384, 192, 320, 224, 288, 256, 256), 5000, "bf16", 2),
     ("stream_n8_f32", 256, (128, 384, 192, 320, 224, 288, 256, 256), 4133, "f32", 2),
     ("stream_n2", 64, (32, 96), 4200, "f32", 2),
     ("stream_n3", 96, (32, 64, 96), 4111, "bf16", 2),
     ("stream_n4_top1", 128, (32, 224, 96, 160), 4500, "bf16", 1),
     ("stream_n16", 128, (64,) * 16, 6001, "f32", 2),
+    ("stream_ragged_d", 1120, (64, 192, 128, 128), 4100, "bf16", 2),
+    ("stream_many_groups", 32, (32,) * 8, 40000, "bf16", 2),
+    # more than 16 experts, four tokens per block
     ("stream_n24", 64, (32,) * 24, 1500, "bf16", 2),
     ("stream_n64", 64, (32,) * 64, 3000, "f32", 2),
     ("stream_n64_bf16", 96, (32,) * 64, 1025, "bf16", 2),
-    ("stream_ragged_d", 1120, (64, 192, 128, 128), 4100, "bf16", 2),
-    ("stream_many_groups", 32, (32,) * 8, 40000, "bf16", 2),
     # the same router on the float64 matrix instruction (d a multiple of 256, at most 16 experts): both padded
     # expert counts, expert counts that are no multiple of 4, both dtypes, k = 1, ragged token counts, several
     # groups per workgroup, and a matrix that is one size too large for it (the vector form takes over)
@@ -92,11 +94,10 @@ ROUTE_CASES = [
     ("mfma_d768", 768, (64,) * 8, 4097, "bf16", 2),
     ("mfma_d2048", 2048, (32,) * 8, 4160, "bf16", 2),
     ("mfma_too_large_n16_d1024", 1024, (32,) * 16, 4100, "bf16", 2),
-    # scan over more than 4 blocks per thread, with one and with several 16-column steps
+    # scan with more blocks per thread than it keeps in registers, few and many columns
     ("scan_long_runs", 32, (32,) * 8, 140001, "bf16", 2),
     ("scan_long_runs_n40", 32, (32,) * 40, 35001, "f32", 2),
-    # more than 16 experts on a small batch, and an expert count that is not a power of two: the router that
-    # reads (a padded copy of) W_gate from memory
+    # more than 16 experts, one token per block, and an expert count that is not a power of two: a padded copy of W_gate
     ("block_n24", 64, (32,) * 24, 300, "bf16", 2),
     ("block_n40_f32", 96, (32,) * 40, 333, "f32", 2),
 ]
@@ -162,7 +163,7 @@ FWD_CASES = [
     ("bf16_tails", 320, (32, 608, 288, 352), 1531, "bf16", 2),
     ("bf16_top1", 256, (128, 384, 192, 320), 300, "bf16", 1),
     ("bf16_one_token", 256, (128, 384), 1, "bf16", 2),
-    # decode-sized batches: 64-row tiles and a split-K down-projection (ragged widths, chunk tails)
+    # decode-sized batches: 64-row tiles (up), 32-row ones (down; the long widths with K split, ragged chunks)
     ("bf16_decode", 512, (96, 416, 160, 352, 224, 288, 256, 256), 64, "bf16", 2),
     ("bf16_decode_17", 320, (32, 608, 288, 352), 17, "bf16", 2),
     ("bf16_decode_long_k", 256, (2080, 64, 1056, 992), 30, "bf16", 2),
@@ -227,7 +228,7 @@ BWD_CASES = [
     ("f32_top1", 128, (32, 224, 96, 160), 150, "f32", 1),
     ("bf16_mid", 512, (96, 416, 160, 352, 224, 288, 256, 256), 1000, "bf16", 2),
     ("bf16_tails", 320, (32, 608, 288, 352), 1531, "bf16", 2),
-    ("bf16_decode", 320, (32, 608, 288, 352), 40, "bf16", 2),   # forward with saved activations: no split-K
+    ("bf16_decode", 320, (32, 608, 288, 352), 40, "bf16", 2),   # widths too short to split
     # many experts: the fused weight-gradient plan is full (3 x 64 problems), several experts get no token
     ("bf16_n64", 64, tuple(32 * (1 + e % 4) for e in range(64)), 300, "bf16", 2),
     ("f32_n32", 96, tuple(32 * (1 + e % 3) for e in range(32)), 257, "f32", 2),
