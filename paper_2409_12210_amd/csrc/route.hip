@@ -947,8 +947,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void route_scan_kernel(int32_t* __res
 // Auxiliary load-balance loss (Sec. 3.2 Eq. 9-12), single block: f_i = share of tokens whose first choice is
 // expert i, P_i = mean of p_i, L_a = alpha N sum_i f_i P_i.  A thread sums one column over every nrow-th token (threads
 // side by side read whole lines of p, sixteen loads in flight), the threads' sums of a column are added in a fixed tree,
-// so the result does not depend on timing.  The sums are float64: a thread adds up to ntok N / 1024 values in a row, which
-// in float32 put P off by 7e-7 at 2^20 tokens and 64 experts.  8192 tokens, 8 experts: 8 to 11 us in place of 61 to 83
+// so the result does not depend on timing.  The sums over batches of sixteen are float64: a thread adds up to ntok N / 1024
+// values in a row, which in float32 put P off by 7e-7 at 2^20 tokens and 64 experts.  8192 tokens, 8 experts: 8 to 11 us in place of 61 to 83
 // with one pass over all tokens per expert.
 constexpr int AUX_THREADS = 1024;
 __global__ __launch_bounds__(AUX_THREADS) void aux_finish_kernel(const float* __restrict__ probs,
@@ -962,8 +962,19 @@ __global__ __launch_bounds__(AUX_THREADS) void aux_finish_kernel(const float* __
   const int nrow = AUX_THREADS / N, e = tid % N, r0 = tid / N;
   double acc = 0.0;
   if (r0 < nrow) {
+    int t = r0;
+    for (; (long)t + 15L * nrow < ntok; t += 16 * nrow) {
+      float v[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) v[q] = probs[(size_t)(t + q * nrow) * N + e];
+#pragma unroll
+      for (int half = 8; half >= 2; half >>= 1)
+#pragma unroll
+        for (int q = 0; q < half; ++q) v[q] += v[q + half];
+      acc += (double)v[0] + (double)v[1];
+    }
 #pragma unroll 16
-    for (int t = r0; t < ntok; t += nrow) acc += (double)probs[(size_t)t * N + e];
+    for (; t < ntok; t += nrow) acc += (double)probs[(size_t)t * N + e];
   }
   s_p[tid] = acc;
   __syncthreads();
