@@ -51,16 +51,6 @@ __device__ inline void load4(const bf16_t* p, float v[4]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) v[i] = (float)a[i];
 }
-__device__ inline void store4(float* p, const float v[4]) {
-  f32x4 a = {v[0], v[1], v[2], v[3]};
-  *reinterpret_cast<f32x4*>(p) = a;
-}
-__device__ inline void store4(bf16_t* p, const float v[4]) {
-  bf16x4 a;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) a[i] = (bf16_t)v[i];
-  *reinterpret_cast<bf16x4*>(p) = a;
-}
 
 // ---------------------------------------------------------------- grouped GEMM
 // One problem per expert:  C[M,N] (+)= A B^T (+ A2 B2^T).  How A and B lie in memory is a property of the

@@ -64,7 +64,8 @@ hipError_t run_block_tile(TileShape t, const GemmPlan* plan, int accumulate, int
   constexpr int BN = std::is_same_v<T, float> || EPI == EPI_SWIGLU ? 64 : 128;
   if constexpr (!std::is_same_v<T, float> && LAYOUT == LAYOUT_TN && EPI != EPI_SWIGLU)
     if (t.bm == 32) return run_block<T, 32, BN, EPI, LAYOUT, 1, 4>(plan, accumulate, save_pre, max_tiles, s);
-  return run_block<T, 64, BN, EPI, LAYOUT>(plan, accumulate, save_pre, max_tiles, s);
+  if constexpr (!std::is_same_v<T, float> && LAYOUT == LAYOUT_AB_K) return hipErrorInvalidValue;  // (128 rows or 256)
+  else return run_block<T, 64, BN, EPI, LAYOUT>(plan, accumulate, save_pre, max_tiles, s);
 }
 
 // The epilogue fixes the operand layout: forward GEMMs are K-contiguous on both sides, data gradients read

@@ -42,7 +42,6 @@ __device__ __forceinline__ void dma_b128_s(const void* base, uint32_t voff, uint
 // 16-byte accesses through the global address space (a generic pointer would make them flat accesses)
 typedef __attribute__((address_space(1))) bf16x8 global_bf16x8;
 __device__ __forceinline__ void global_store16(bf16_t* p, bf16x8 v) { *(global_bf16x8*)(uintptr_t)p = v; }
-__device__ __forceinline__ bf16x8 global_load16(const bf16_t* p) { return *(const global_bf16x8*)(uintptr_t)p; }
 // 16 bytes per lane to / from wave-uniform base + per-lane unsigned 32-bit byte offset.  (The two wait states
 // behind a store: a store of more than 64 bits must not be followed at once by a VALU write of its data
 // registers, and the compiler's hazard handling does not look inside assembly.)  The load is issued

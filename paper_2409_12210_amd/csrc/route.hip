@@ -129,11 +129,6 @@ __device__ inline bool write_gate(const TopPick& p, int t, int N, int top_k, int
 }
 
 // ---------------------------------------------------------------- the router's dot products
-// Both block-wise routers give lane l of a wave the columns 8l..8l+7 of every 512-column step of the token
-// rows: a row is read with one contiguous 1 KiB load per wave and step, and the loads of the next step are
-// issued before the arithmetic of the current one.  A wave holds TOK tokens x EC experts of float64 sums at a
-// time (at most 32, so that sums, the two sets of row registers and one converted matrix row fit the register
-// file without spilling); layers with more experts than EC take the expert columns in chunks.
 
 // eight consecutive elements as loaded, and element i of them as float
 template <typename T>
@@ -157,30 +152,20 @@ struct Raw8<float> {
   __device__ float get(int i) const { return i < 4 ? a[i] : b[i - 4]; }
 };
 
-// EC columns, from column e0, of row r of a router matrix in memory whose rows are ldw elements apart (ldw
-// is the padded expert count, so a row is a whole number of aligned vectors)
-template <typename T, int EC>
-struct GlobalRows {
-  const T* W;
-  int ldw, e0;
-  __device__ void fetch(int r, float (&wf)[EC]) const { load_row<EC>(W + (size_t)r * ldw + e0, wf); }
-};
-
-// The same from the LDS copy that router_stream_kernel keeps: elements of type W (double when the matrix
+// Row r of the LDS copy of W_gate that router_stream_kernel keeps: elements of type W (double when the matrix
 // fits that way, else float), NE per row; the eight rows of one lane and step lie together, followed by 16
 // bytes of padding, so that the 16 lanes which a 128-bit LDS read serves together fall into different banks.
 constexpr int rs_group_bytes(int NE, int elem) { return 8 * NE * elem + 16; }
-template <typename W, int NE, int EC>
+template <typename W, int NE>
 struct LdsRows {
   const char* base;
-  int e0;
-  __device__ void fetch(int r, W (&wf)[EC]) const {
+  __device__ void fetch(int r, W (&wf)[NE]) const {
     constexpr int PER = 16 / sizeof(W);  // elements per 128-bit read
     typedef W vec_t __attribute__((ext_vector_type(PER)));
-    const char* p = base + (r >> 3) * rs_group_bytes(NE, sizeof(W)) + (r & 7) * NE * (int)sizeof(W) + e0 * (int)sizeof(W);
-    if constexpr (EC >= PER) {
+    const char* p = base + (r >> 3) * rs_group_bytes(NE, sizeof(W)) + (r & 7) * NE * (int)sizeof(W);
+    if constexpr (NE >= PER) {
 #pragma unroll
-      for (int e = 0; e < EC; e += PER) {
+      for (int e = 0; e < NE; e += PER) {
         const vec_t q = *reinterpret_cast<const vec_t*>(p + e * sizeof(W));
 #pragma unroll
         for (int j = 0; j < PER; ++j) wf[e + j] = q[j];
@@ -192,21 +177,16 @@ struct LdsRows {
   }
 };
 
-// tokens x expert columns that a wave sums at a time
-template <int NE>
-struct RouterShape {
-  static constexpr int EC = NE < 16 ? NE : 16;
-  static constexpr int TOK = 32 / EC < 4 ? 32 / EC : 4;  // (more tokens: their row registers no longer fit)
-  static constexpr int V = TOK * EC;
-};
-
-// Router for large batches without the optional gate parts.  One 512-thread block per CU copies W_gate into LDS
-// once (as float64 when that fits RS_W_BYTES, else as float: both exact) and then walks over groups of 64 tokens
-// (two histogram blocks of TPB tokens), eight tokens per wave: the matrix rows then cost an LDS read instead of a
-// trip through the vector memory pipeline per TOK tokens, which is what holds router_kernel back.
-// A wave's work is a flat sequence of steps (group, pass of TOK tokens, chunk of EC expert columns, 512 columns
-// of the token rows); the loads of the step two ahead are issued before the arithmetic of the current step,
-// across pass and group boundaries, and the first two steps are under way while W_gate is being copied.
+// Router for large batches of layers with up to 16 experts, without the optional gate parts.  One 512-thread block per CU
+// copies W_gate into LDS once (as float64 when that fits RS_W_BYTES, else as float: both exact) and then walks over groups
+// of 64 tokens (two histogram blocks of TPB tokens), eight tokens per wave, so that a matrix row costs an LDS read instead
+// of a trip through the vector memory pipeline per TOK tokens.
+// Lane l of a wave takes the columns 8l..8l+7 of every 512-column step of the token rows: a row is read with one contiguous
+// 1 KiB load per wave and step.  A wave holds TOK tokens x NE experts of float64 sums at a time (at most 32, so that sums,
+// the row registers and one converted matrix row fit the register file without spilling).
+// A wave's work is a flat sequence of steps (group, pass of TOK tokens, 512 columns of the token rows); the loads of the
+// step two ahead are issued before the arithmetic of the current step, across pass and group boundaries, and the first two
+// steps are under way while W_gate is being copied.
 // Sums are float64 FMAs in a fixed order per lane, then wave_sum_values: results do not depend on timing.
 constexpr int RS_THREADS = 512, RS_WAVES = RS_THREADS / 64, RS_TOKENS = 64;
 constexpr int RS_W_BYTES = 136 * 1024;
@@ -217,9 +197,8 @@ __global__ __launch_bounds__(RS_THREADS) void router_stream_kernel(const T* __re
                                                                   int N, int top_k, int32_t* __restrict__ topk_idx,
                                                                   float* __restrict__ topk_w,
                                                                   int32_t* __restrict__ blockhist) {
-  using S = RouterShape<NE>;
-  constexpr int TOK = S::TOK, EC = S::EC, V = S::V;
-  constexpr int NPASS = 8 / TOK, NCHUNK = NE / EC;
+  constexpr int TOK = 32 / NE < 4 ? 32 / NE : 4;  // (more tokens: their row registers no longer fit)
+  constexpr int V = TOK * NE, NPASS = 8 / TOK;
   constexpr int GB = rs_group_bytes(NE, sizeof(W));
   constexpr int HW = MODSE_MAX_EXPERTS + 1;
   __shared__ __attribute__((aligned(16))) char s_w[RS_W_BYTES];
@@ -232,7 +211,7 @@ __global__ __launch_bounds__(RS_THREADS) void router_stream_kernel(const T* __re
 
   // the loader runs two steps ahead of the arithmetic
   Raw8<T> cur[TOK], nx1[TOK], nx2[TOK];
-  int l_grp = blockIdx.x, l_pass = 0, l_chunk = 0, l_st = 0;
+  int l_grp = blockIdx.x, l_pass = 0, l_st = 0;
   auto load_next = [&](Raw8<T> (&dst)[TOK]) {
     if (l_grp < ngroups) {
       const int tbase = l_grp * RS_TOKENS + wave * 8 + l_pass * TOK;
@@ -243,12 +222,9 @@ __global__ __launch_bounds__(RS_THREADS) void router_stream_kernel(const T* __re
     }
     if (++l_st == nstep) {
       l_st = 0;
-      if (++l_chunk == NCHUNK) {
-        l_chunk = 0;
-        if (++l_pass == NPASS) {
-          l_pass = 0;
-          l_grp += gridDim.x;
-        }
+      if (++l_pass == NPASS) {
+        l_pass = 0;
+        l_grp += gridDim.x;
       }
     }
   };
@@ -273,49 +249,48 @@ __global__ __launch_bounds__(RS_THREADS) void router_stream_kernel(const T* __re
   for (int grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
     for (int pass = 0; pass < NPASS; ++pass) {
       const int tbase = grp * RS_TOKENS + wave * 8 + pass * TOK;
-#pragma unroll 1
-      for (int e0 = 0; e0 < NE; e0 += EC) {
-        const LdsRows<W, NE, EC> rows = {s_w, e0};
-        double acc[V];
+      const LdsRows<W, NE> rows = {s_w};
+      double acc[V];
 #pragma unroll
-        for (int i = 0; i < V; ++i) acc[i] = 0.0;
-        for (int st = 0; st < nstep; ++st) {
-          load_next(nx2);
-          const int c = st * 512 + lane * 8;
-          if (c < d) {
-            W wf[EC];
-            rows.fetch(c, wf);
+      for (int i = 0; i < V; ++i) acc[i] = 0.0;
+      for (int st = 0; st < nstep; ++st) {
+        load_next(nx2);
+        const int c = st * 512 + lane * 8;
+        if (c < d) {
+          W wf[NE];
+          rows.fetch(c, wf);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-              W wn[EC];
-              if (i < 7) rows.fetch(c + i + 1, wn);  // the next matrix row is on its way during this row's arithmetic
-              double wd[EC];
+          for (int i = 0; i < 8; ++i) {
+            W wn[NE];
+            if (i < 7) rows.fetch(c + i + 1, wn);  // the next matrix row is on its way during this row's arithmetic
+            double wd[NE];
 #pragma unroll
-              for (int e = 0; e < EC; ++e) wd[e] = (double)wf[e];
+            for (int e = 0; e < NE; ++e) wd[e] = (double)wf[e];
 #pragma unroll
-              for (int tt = 0; tt < TOK; ++tt) {
-                const double xd = (double)cur[tt].get(i);
+            for (int tt = 0; tt < TOK; ++tt) {
+              const double xd = (double)cur[tt].get(i);
 #pragma unroll
-                for (int e = 0; e < EC; ++e) acc[tt * EC + e] = fma(xd, wd[e], acc[tt * EC + e]);
-              }
-              if (i < 7) {
-#pragma unroll
-                for (int e = 0; e < EC; ++e) wf[e] = wn[e];
-              }
-              __builtin_amdgcn_sched_barrier(0);  // (see lane_dots)
+              for (int e = 0; e < NE; ++e) acc[tt * NE + e] = fma(xd, wd[e], acc[tt * NE + e]);
             }
-          }
+            if (i < 7) {
 #pragma unroll
-          for (int tt = 0; tt < TOK; ++tt) {
-            cur[tt] = nx1[tt];
-            nx1[tt] = nx2[tt];
+              for (int e = 0; e < NE; ++e) wf[e] = wn[e];
+            }
+            // keeps the scheduler from fetching and converting all eight rows ahead of the arithmetic, which costs more
+            // registers than there are
+            __builtin_amdgcn_sched_barrier(0);
           }
         }
-        wave_sum_values<V>(acc, lane);
-        if (lane < V) {
-          const int v = bitrev<Log2<V>::value>(lane);
-          s_logit[wave][v / EC][e0 + v % EC] = acc[0];
+#pragma unroll
+        for (int tt = 0; tt < TOK; ++tt) {
+          cur[tt] = nx1[tt];
+          nx1[tt] = nx2[tt];
         }
+      }
+      wave_sum_values<V>(acc, lane);
+      if (lane < V) {
+        const int v = bitrev<Log2<V>::value>(lane);
+        s_logit[wave][v / NE][v % NE] = acc[0];
       }
       __syncthreads();
       if (lane < TOK && tbase + lane < ntok) {
@@ -749,13 +724,12 @@ __global__ __launch_bounds__(ROUTE_THREADS, 2) void router_token_kernel(const T*
     float xv[G][8];
 #pragma unroll
     for (int g = 0; g < G; ++g) load8(x + (size_t)min(t0 + g, ntok - 1) * d + c, xv[g]);  // (clamped rows: never written)
-    const GlobalRows<T, NE> rows = {Wg, NE, 0};
     float wf[NE];
-    rows.fetch(c, wf);
+    load_row<NE>(Wg + (size_t)c * NE, wf);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       float wn[NE];
-      if (i < 7) rows.fetch(c + i + 1, wn);
+      if (i < 7) load_row<NE>(Wg + (size_t)(c + i + 1) * NE, wn);
 #pragma unroll
       for (int e = 0; e < NE; ++e) {
         const double wd = (double)wf[e];
@@ -766,7 +740,7 @@ __global__ __launch_bounds__(ROUTE_THREADS, 2) void router_token_kernel(const T*
 #pragma unroll
         for (int e = 0; e < NE; ++e) wf[e] = wn[e];
       }
-      __builtin_amdgcn_sched_barrier(0);  // (see lane_dots)
+      __builtin_amdgcn_sched_barrier(0);  // (as in router_stream_kernel: one row ahead, no more)
     }
   }
 #pragma unroll
