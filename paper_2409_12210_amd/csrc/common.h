@@ -7,6 +7,7 @@
 
 #define MODSE_MAX_EXPERTS 64
 #define MODSE_MAX_PROBLEMS (3 * MODSE_MAX_EXPERTS)  // the three weight-gradient GEMMs share one launch
+#define MODSE_PERMUTE_SMALL_MAX_T 64      // batches up to this size may take it in a form with one token per lane
 #define MODSE_PERMUTE_FUSED_MAX_T 4096    // batches up to this size take the fused permute + plan launch
 #define MODSE_ROUTE_TOKENS_PER_BLOCK 32  // tokens handled by one block of the router / scatter kernels
 

@@ -1075,8 +1075,94 @@ __global__ __launch_bounds__(ROUTE_THREADS) void scatter_kernel(const T* __restr
   }
 }
 
-// Batches of at most MODSE_PERMUTE_FUSED_MAX_T tokens: histogram, offsets, stable scatter and, when a forward pass follows,
-// the tile plans of its two GEMMs in ONE launch instead of three; at these sizes a launch costs more than its work.
+// Decode-sized batches of layers with few experts, one token per lane of a wave: histogram, offsets, stable scatter and, when a forward pass follows,
+// the tile plans of its two GEMMs in one launch of small blocks.  Wave 0 of every block ranks all tokens with one ballot per
+// expert (the same rows as scatter_kernel: tokens of an expert in token order).  The first block writes the routing outputs
+// and makes the plans, block 1 + t copies token t's row (no such blocks when there is no Xp).
+// Near-tie total: from near_flag (the routers with one or four tokens per block) or, when that is null, from the last
+// column of the router's block histograms.
+// Bound by latency: 4 barriers and 16 waves less than permute_fused_kernel, but a step per expert.  The routing call, replayed
+// from a graph: one token, 8 experts, d = 256: 5.3 us in place of 7.1; 64 tokens, 16 experts: 7.4 / 8.9, but 64 experts
+// 10.0 / 9.0; a forward pass of 64 tokens with 32 or 64 experts is 1 to 2.5 us slower with it, with 8 to 16 0.2 to 0.7 faster.
+constexpr int PS_THREADS = 256, PS_EXPERTS = 16;
+static_assert(MODSE_PERMUTE_SMALL_MAX_T <= 64, "a token per lane");
+template <typename T>
+__global__ __launch_bounds__(PS_THREADS) void permute_small_kernel(const T* __restrict__ x, int ntok, int d, int N, int top_k,
+                                                                   const int32_t* __restrict__ topk_idx,
+                                                                   const int32_t* __restrict__ near_flag,
+                                                                   const int32_t* __restrict__ blockhist, RoutingPtrs R,
+                                                                   T* __restrict__ Xp, LayerDims L, int esize,
+                                                                   FwdPlanArgs plan, int with_plan) {
+  __shared__ int s_row[2];  // of the block's token
+  __shared__ int s_counts[MODSE_MAX_EXPERTS], s_offsets[MODSE_MAX_EXPERTS];
+  __shared__ modse_gemm::PlanLds s_plan;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool planner = blockIdx.x == 0;
+  const int mine = (int)blockIdx.x - 1;
+  if (wave == 0) {
+    const int t = lane;
+    const bool valid = t < ntok;
+    const int e0 = valid ? topk_idx[(size_t)t * top_k] : -1;
+    const int e1 = valid && top_k == 2 ? topk_idx[(size_t)t * top_k + 1] : -1;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int run = 0, row0 = 0, row1 = 0, my_count = 0, my_offset = 0;
+#pragma unroll 4
+    for (int e = 0; e < N; ++e) {
+      const unsigned long long m = __ballot(e0 == e || e1 == e);
+      const int rank = __popcll(m & below), c = __popcll(m);
+      if (e0 == e) row0 = run + rank;
+      if (e1 == e) row1 = run + rank;
+      if (lane == e) {
+        my_count = c;
+        my_offset = run;
+      }
+      run += c;
+    }
+    if (t == mine) {
+      s_row[0] = row0;
+      s_row[1] = row1;
+    }
+    if (planner) {
+      int near = 0;
+      if (near_flag) {
+        near = __popcll(__ballot(valid && near_flag[valid ? t : 0] != 0));
+      } else {
+        for (int b = 0; b * TPB < ntok; ++b) near += blockhist[(size_t)b * (N + 1) + N];
+      }
+      if (lane < N) {
+        R.counts[lane] = s_counts[lane] = my_count;
+        R.offsets[lane] = s_offsets[lane] = my_offset;
+      }
+      if (lane == 0) {
+        R.offsets[N] = run;
+        R.near_tie_count[0] = near;
+      }
+      if (valid) {
+        R.row_of[(size_t)t * top_k] = row0;
+        R.src_of[row0] = t * top_k;
+        if (top_k == 2) {
+          R.row_of[(size_t)t * top_k + 1] = row1;
+          R.src_of[row1] = t * top_k + 1;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (planner) {
+    if (with_plan) modse_gemm::plan_fwd_body(L, esize, s_counts, s_offsets, plan, s_plan);
+    return;
+  }
+  const int row0 = s_row[0], row1 = top_k == 2 ? s_row[1] : -1;
+  constexpr int VEC = 16 / sizeof(T);
+  for (int c = tid * VEC; c < d; c += PS_THREADS * VEC) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(x + (size_t)mine * d + c);
+    *reinterpret_cast<f32x4*>(Xp + (size_t)row0 * d + c) = v;
+    if (row1 >= 0) *reinterpret_cast<f32x4*>(Xp + (size_t)row1 * d + c) = v;
+  }
+}
+
+// Larger batches, of at most MODSE_PERMUTE_FUSED_MAX_T tokens: the same in one launch instead of three; at these sizes a
+// launch costs more than its work.
 // Every block counts all tokens' choices by itself (at most 32 KiB from the L2), those of the tokens before its own
 // sixteen apart from the rest, so no block waits for another.  A counter has 32 copies side by side, one per LDS bank: the
 // additions of a wave never meet.  The first block writes the routing totals and makes the plans, the others rank their
@@ -1801,11 +1887,17 @@ hipError_t permute_typed(const LayerDims& L, modse_dtype dt, const void* xv, con
   const T* x = static_cast<const T*>(xv);
   const int nb = (L.T + TPB - 1) / TPB;
   static_assert(ROUTER_TOKEN_MAX_T <= MODSE_PERMUTE_FUSED_MAX_T, "the token routers make no block histograms");
+  const int32_t* const near_flag = router_kind(L, G) == ROUTER_TOKEN ? B.near_flag : nullptr;
+  if (L.T <= MODSE_PERMUTE_SMALL_MAX_T && L.N <= PS_EXPERTS) {
+    hipLaunchKernelGGL((permute_small_kernel<T>), dim3(Xpv ? L.T + 1 : 1), dim3(PS_THREADS), 0, s, x, L.T, L.d, L.N, L.k,
+                       R.topk_idx, near_flag, B.blockhist, R, static_cast<T*>(Xpv), L, dt == MODSE_F32 ? 4 : 2,
+                       plan ? *plan : FwdPlanArgs{}, plan ? 1 : 0);
+    return hipGetLastError();
+  }
   if (L.T <= MODSE_PERMUTE_FUSED_MAX_T) {
-    const bool token_router = router_kind(L, G) == ROUTER_TOKEN;
     hipLaunchKernelGGL((permute_fused_kernel<T>), dim3((L.T + PF_TOKENS - 1) / PF_TOKENS + 1), dim3(PF_THREADS), 0, s, x, L.T,
-                       L.d, L.N, L.k, R.topk_idx, token_router ? B.near_flag : nullptr, B.blockhist, R, static_cast<T*>(Xpv), L,
-                       dt == MODSE_F32 ? 4 : 2, plan ? *plan : FwdPlanArgs{}, plan ? 1 : 0);
+                       L.d, L.N, L.k, R.topk_idx, near_flag, B.blockhist, R, static_cast<T*>(Xpv), L, dt == MODSE_F32 ? 4 : 2,
+                       plan ? *plan : FwdPlanArgs{}, plan ? 1 : 0);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(route_scan_kernel, dim3(1), dim3(SCAN_THREADS), 0, s, B.blockhist, nb, L.N, R.counts, R.offsets,

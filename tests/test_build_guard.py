@@ -52,8 +52,8 @@ def test_every_built_kernel_is_within_the_register_budget():
     assert len(rows) >= 60                                   # every instantiation of every kernel is listed
     names = " ".join(r[0] for r in rows)
     for k in ("router_kernel", "router_mfma_kernel", "router_stream_kernel", "router_token_kernel", "router_token_wide_kernel",
-              "pad_rows_kernel", "permute_fused_kernel", "route_scan_kernel", "scatter_kernel", "combine_kernel",
-              "combine_split_kernel", "bwd_prep_plan_bwd_kernel", "gate_bwd_kernel", "bwd_gate_rows_kernel",
+              "pad_rows_kernel", "permute_small_kernel", "permute_fused_kernel", "route_scan_kernel", "scatter_kernel",
+              "combine_kernel", "combine_split_kernel", "bwd_prep_plan_bwd_kernel", "gate_bwd_kernel", "bwd_gate_rows_kernel",
               "bwd_gate_rows_ext_kernel", "sum_slabs_kernel", "bwd_dwg_kernel", "dwg_reduce_kernel", "aux_finish_kernel",
               "routing_stats_kernel", "gg_bf16_kernel", "gg_bf16_block_kernel", "gg_bf16_skinny_kernel", "gg_f32_kernel"):
         assert "%d%s" % (len(k), k) in names, k              # (a mangled name has the length in front: no part of a longer one)

@@ -28,9 +28,11 @@ def test_route_parity(case):
     check_routing(inp, r.routing_host())
 
 
-# the fused permutation (up to 4096 tokens) at the edges of its blocks of 16 tokens, and the scan over block histograms
-# beyond it: several blocks per thread, in registers and (more than 20) read twice; one to 64 experts
-@pytest.mark.parametrize("n,T,k", [(1, 15, 1), (2, 16, 2), (64, 17, 2), (3, 4096, 2), (64, 4096, 1), (1, 4097, 1), (2, 9000, 2),
+# the permutation with one token per lane (up to 64 tokens and 16 experts), the fused one (up to 4096 tokens) at the edges of
+# its blocks of 16, and the scan over block histograms beyond it: several blocks per thread, in registers and (more than 20)
+# read twice; one to 64 experts
+@pytest.mark.parametrize("n,T,k", [(1, 15, 1), (2, 16, 2), (64, 17, 2), (16, 64, 2), (1, 64, 1), (17, 64, 2), (8, 65, 2),
+                                   (3, 4096, 2), (64, 4096, 1), (1, 4097, 1), (2, 9000, 2),
                                    (31, 5003, 2), (64, 12001, 2)])
 def test_permutation_parity(n, T, k):
     inp = make("permute", 32, (32,) * n, T, "bf16", k, seed=21)
