@@ -451,8 +451,7 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   const int kchunk = down.kchunk;
   pa.kchunk = kchunk;
   pa.Opart = reinterpret_cast<float*>(wsb + w.total);
-  // histogram, scan (which also writes the tile plans), stable scatter: one launch for all of it on decode-sized
-  // batches
+  // histogram, scan (which also writes the tile plans), stable scatter: one launch for all of it up to 4096 tokens
   HIP_TRY(launch_permute(L, dt, x, R, RB, Xp, ext ? &G : nullptr, &pa, s));
   stamp.mark(MODSE_STAGE_PERMUTE);
 

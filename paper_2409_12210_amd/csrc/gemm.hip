@@ -1,7 +1,7 @@
 // Ragged grouped GEMMs of the MoDSE layer on gfx950: one problem per expert, M = tokens routed to the
 // expert (known only on the device), N or K = the expert's own hidden width d_ff[e] (Sec. 3.1 of
-// arXiv 2409.12210).  A tiny plan kernel turns the device-side counts into a problem table and a tile
-// prefix; persistent GEMM workgroups walk the tile list without any host round trip.
+// arXiv 2409.12210).  A block of the launch before turns the device-side counts into a problem table and a tile prefix
+// (gemm_plan.h); the workgroups, persistent ones or one per tile, find their tiles in it without any host round trip.
 //
 // Operand layouts (GemmLayout): every tensor of the layer is used as it lies in memory.  The forward
 // GEMMs have both operands K-contiguous; the data-gradient GEMMs read the weights as [K, N]; the

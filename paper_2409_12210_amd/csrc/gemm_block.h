@@ -22,9 +22,9 @@
 // reads, with counted waits.  Weights that meet one row block are loaded with the non-temporal hint: they are read once,
 // and behind a backward pass, whose weight gradients have just filled the caches, the up-projection of 130 tokens took
 // 143 us without and 83 with it (with it, weights that several row blocks read were slower: 117 -> 160 us at 600 tokens).
-// At d = 2048, eight experts of mean width 5632, in place of 256-row tiles (up / down + combine): 100 tokens 109 / 165 ->
-// 68 / 49 us, 389 tokens 117 / 170 -> 92 / 68; at d = 4096, one token, in place of 64-row tiles of 512 columns that left
-// half of the CUs without one: 131 / 79 -> 72 / 51 us, 5.6 TB/s.  At many rows it is bound by LDS reads and load issue
+// At d = 2048, eight experts of mean width 5632, in place of 256-row tiles (up / down + combine): 389 tokens 117 / 170 ->
+// 91 / 60 us; at d = 4096, one token, in place of 64-row tiles of 512 columns that left half of the CUs without one: 131 /
+// 79 -> 69 / 44 us, weights at 6.5 TB/s.  At many rows it is bound by LDS reads and load issue
 // (0.87 PFLOP/s against 1.1 to 1.2 of the 256 x 256 kernel): gemm_choice picks.
 //
 // float32 is bound by the matrix pipe (157 TFLOP/s; a library product of 8192^3 reaches 153).  Measured in place of

@@ -15,7 +15,7 @@ namespace {
 
 constexpr int TPB = MODSE_ROUTE_TOKENS_PER_BLOCK;  // tokens per block
 constexpr int ROUTE_THREADS = 256;
-constexpr int ROUTER_TOKEN_MAX_T = 4096;  // batches up to this size take router_token_kernel
+constexpr int ROUTER_TOKEN_MAX_T = 4096;  // plain-gate batches up to this size take a token router (one or four per block)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
@@ -572,7 +572,7 @@ __device__ inline TopPick route_token16(double (&l)[PER], double (&u)[PER], int 
 // A block of eight waves takes 32 tokens; wave w takes the column steps w, w + 8, ...; the matrices come from L2 (32
 // tokens share a read) straight into operand order, and the eight partial sums meet in LDS in a fixed order.
 // Bound by the float64 matrix pipe: 73 TFLOP/s of a probe, 29 us for 8192 tokens, d = 2048, 64 experts, where the launch
-// takes 42 us; the vector-FMA form before it, which fetched every matrix row for two tokens, took 178.
+// takes 46 us; the vector-FMA form before it, which fetched every matrix row for two tokens, took 178.
 constexpr int RW_THREADS = 512, RW_WAVES = RW_THREADS / 64, RW_TOKENS = 32;
 static_assert(RW_TOKENS == TPB && RW_TOKENS * 16 == RW_THREADS, "one histogram block per group; 16 threads per token");
 template <typename T, int NE, bool NOISE>
@@ -702,7 +702,7 @@ __global__ __launch_bounds__(RW_THREADS) void router_kernel(const T* __restrict_
 // two rounds of memory latency.  Every thread leaves its G x N float64 partial sums in LDS; they are added
 // in two fixed-order steps (8 groups of 32 threads, then the 8 group sums), so the result does not depend
 // on timing; one thread per token then does top-k and gate.  The block histograms that the permutation
-// needs are counted by permute_fused_kernel from topk_idx and near_flag.
+// needs are counted by the permutation itself from topk_idx and near_flag.
 template <typename T, int NE, int G>
 __global__ __launch_bounds__(ROUTE_THREADS, 2) void router_token_kernel(const T* __restrict__ x,
                                                                        const T* __restrict__ Wg,
@@ -922,8 +922,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void route_scan_kernel(int32_t* __res
 // expert i, P_i = mean of p_i, L_a = alpha N sum_i f_i P_i.  A thread sums one column over every nrow-th token (threads
 // side by side read whole lines of p, sixteen loads in flight), the threads' sums of a column are added in a fixed tree,
 // so the result does not depend on timing.  The sums over batches of sixteen are float64: a thread adds up to ntok N / 1024
-// values in a row, which in float32 put P off by 7e-7 at 2^20 tokens and 64 experts.  8192 tokens, 8 experts: 8 to 11 us in place of 61 to 83
-// with one pass over all tokens per expert.
+// values in a row, which in float32 put P off by 7e-7 at 2^20 tokens and 64 experts.  8192 tokens, 8 experts: 8 to 12 us in
+// place of 61 to 83 with one pass over all tokens per expert.
 constexpr int AUX_THREADS = 1024;
 __global__ __launch_bounds__(AUX_THREADS) void aux_finish_kernel(const float* __restrict__ probs,
                                                                  const int32_t* __restrict__ topk_idx, int ntok, int N,
@@ -1075,10 +1075,10 @@ __global__ __launch_bounds__(ROUTE_THREADS) void scatter_kernel(const T* __restr
   }
 }
 
-// Decode-sized batches of layers with few experts, one token per lane of a wave: histogram, offsets, stable scatter and, when a forward pass follows,
-// the tile plans of its two GEMMs in one launch of small blocks.  Wave 0 of every block ranks all tokens with one ballot per
-// expert (the same rows as scatter_kernel: tokens of an expert in token order).  The first block writes the routing outputs
-// and makes the plans, block 1 + t copies token t's row (no such blocks when there is no Xp).
+// Decode-sized batches of layers with few experts, one token per lane of a wave: histogram, offsets, stable scatter and, when
+// a forward pass follows, the tile plans of its two GEMMs in one launch of small blocks.  Wave 0 of every block ranks all
+// tokens with one ballot per expert (the same rows as scatter_kernel: tokens of an expert in token order).  The first block
+// writes the routing outputs and makes the plans, block 1 + t copies token t's row (no such blocks when there is no Xp).
 // Near-tie total: from near_flag (the routers with one or four tokens per block) or, when that is null, from the last
 // column of the router's block histograms.
 // Bound by latency: 4 barriers and 16 waves less than permute_fused_kernel, but a step per expert.  The routing call, replayed
@@ -1164,9 +1164,10 @@ __global__ __launch_bounds__(PS_THREADS) void permute_small_kernel(const T* __re
 // Larger batches, of at most MODSE_PERMUTE_FUSED_MAX_T tokens: the same in one launch instead of three; at these sizes a
 // launch costs more than its work.
 // Every block counts all tokens' choices by itself (at most 32 KiB from the L2), those of the tokens before its own
-// sixteen apart from the rest, so no block waits for another.  A counter has 32 copies side by side, one per LDS bank: the
-// additions of a wave never meet.  The first block writes the routing totals and makes the plans, the others rank their
-// tokens (the same rows as scatter_kernel: tokens of an expert in token order) and copy their rows.
+// sixteen apart from the rest, so no block waits for another.  A counter has 32 copies side by side, lane l of a wave adding
+// to copy l mod 32: at most two additions of a wave meet in a word.  The first block writes the routing totals and makes the
+// plans, the others rank their tokens (the same rows as scatter_kernel: tokens of an expert in token order) and copy their
+// rows.
 // Near-tie total: from near_flag (the routers with one or four tokens per block) or, when that is null, from the last
 // column of the router's block histograms.
 // d = 2048, 389 / 2048 tokens: 7 / 11 us in place of 5 + 13 + 13 (15) and two launch gaps (blocks of 256 threads and eight
