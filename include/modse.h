@@ -45,7 +45,7 @@ typedef enum {
   MODSE_OK = 0,
   MODSE_ERR_INVALID_ARG = 1, /* null pointer, negative size, bad d_ff, ... */
   MODSE_ERR_UNSUPPORTED = 2, /* top_k not in {1,2}, n_experts > 64, unknown dtype */
-  MODSE_ERR_WORKSPACE = 3,   /* ws_bytes smaller than modse_workspace_size() */
+  MODSE_ERR_WORKSPACE = 3,   /* ws_bytes too small, see modse_workspace_size() */
   MODSE_ERR_HIP = 4          /* a HIP launch failed */
 } modse_status;
 
