@@ -78,14 +78,25 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   ProblemRegs P;
   P.load(plan->prob + p);
   const int M = P.M(), N = P.N(), K = P.K();
-  int m0, n0;
+  int m0, n0, first_k;  // first_k: K step that the tile's loop starts with
   {
     int mt, nt;
     decode_local(tile - uniform_int(plan->tile_start[p]), P.mtiles(), P.ntiles(), P.magic_group(), P.magic_tail(), mt, nt);
     m0 = mt * BM;
     n0 = nt * BN;
+    first_k = nt;
   }
   const int nk = (K + BK - 1) / BK;
+  // Weights that meet a single row block are read once in the whole launch, and their stream is what bounds it.  Their rows
+  // usually lie a power of two apart, so what the workgroups of a launch read at the same K step shares the low bits of its
+  // address, and few memory channels serve it: a bare loader of these tiles reaches 5.3 TB/s, and 6.3 when the workgroups
+  // start their K loops at different places.  So they do, at 32 of them: 64 tokens at d = 4096 493 -> 470 us for the layer, 389
+  // tokens at d = 2048 169 -> 155.  (With several row blocks, which have to meet in L2, different places made two
+  // micro-batches of 1021 tokens 3 % slower.)
+  const bool stream_b = !A_T && P.mtiles() == 1;
+  constexpr bool ROTATE = !F32 && !A_T;
+  if constexpr (ROTATE) first_k = stream_b ? (nk * ((first_k * 5 + p) & 31)) >> 5 : 0;
+  else first_k = 0;
   const int nsteps = (EPI == EPI_STORE_DUALK) ? 2 * nk : nk;
   const uint32_t lds_base = __builtin_amdgcn_readfirstlane(lds_address(ring));
 
@@ -117,14 +128,18 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   const size_t b_org = (B_T ? (size_t)n0 : (size_t)n0 * P.ldb()) * ES;
   const size_t a_step = A_T ? (size_t)128 * P.lda() : 128, b_step = B_T ? (size_t)128 * P.ldb() : 128;
   const bool second = NB == 2 && wave * UB * 8 >= BN;  // this wave's B units belong to the second matrix
-  const char* sa = static_cast<const char*>(uniform_ptr(P.A() + a_org));
-  const char* sb = static_cast<const char*>(uniform_ptr((second ? P.B2() : P.B()) + b_org));
-  // weights that meet a single row block are read once in the whole launch
-  const bool stream_b = !A_T && P.mtiles() == 1;
+  // an operand of a pass at K step k
+  auto at_k = [&](bool is_a, bool pass2, int k) {
+    const char* const b = is_a ? (pass2 ? P.A2() : P.A()) : (second || pass2 ? P.B2() : P.B());
+    return static_cast<const char*>(uniform_ptr(b + (is_a ? a_org + k * a_step : b_org + k * b_step)));
+  };
+  const char* sa = at_k(true, false, first_k);
+  const char* sb = at_k(false, false, first_k);
   // the loads of one operand's next panel into ring slot `slot`; the operand then moves on to its next K step
   struct Walk {
-    int step = 0, kstep = 0;  // of all steps; of this pass
+    int step = 0, kstep;  // of all steps; along K
   } wa, wb;
+  wa.kstep = wb.kstep = first_k;
   auto issue = [&](auto is_a, Walk& w, const char*& src, int slot) {
     constexpr bool IS_A = decltype(is_a)::value;
     constexpr int U = IS_A ? UA : UB;
@@ -146,9 +161,14 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
     }
     src += IS_A ? a_step : b_step;
     ++w.step;
-    if (++w.kstep == nk && EPI == EPI_STORE_DUALK) {
+    ++w.kstep;
+    if (ROTATE && w.kstep == nk && first_k != 0) {  // from the end of K back to its beginning
       w.kstep = 0;
-      src = static_cast<const char*>(uniform_ptr((IS_A ? P.A2() : P.B2()) + (IS_A ? a_org : b_org)));
+      src = at_k(IS_A, EPI == EPI_STORE_DUALK && w.step > nk, 0);
+    }
+    if (EPI == EPI_STORE_DUALK && w.step == nk) {
+      w.kstep = first_k;
+      src = at_k(IS_A, true, first_k);
     }
   };
   auto issue_a = [&](int slot) { issue(std::true_type{}, wa, sa, slot); };

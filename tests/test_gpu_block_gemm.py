@@ -29,6 +29,10 @@ CASES = [
     ("bf16_rows_128", 224, (4128, 96, 3104, 2016), 250, "bf16", 2),
     ("bf16_rows_129", 288, (96, 160, 224, 288) * 4, 1033, "bf16", 2),
     ("bf16_few_rows_many_experts", 64, (32,) * 64, 200, "bf16", 1),
+    # one row block per expert, whose K loops start anywhere: 33 and 34 K steps, the last ones partial; dX with both operand
+    # pairs in one loop (many experts: not split)
+    ("bf16_one_block_33_steps", 2080, (2144, 96, 2080, 1184), 60, "bf16", 2),
+    ("bf16_one_block_17_steps", 1056, (1056, 1120, 992, 1184) * 8, 300, "bf16", 2),
 ]
 
 
