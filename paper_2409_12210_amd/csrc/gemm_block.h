@@ -91,11 +91,13 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   // usually lie a power of two apart, so what the workgroups of a launch read at the same K step shares the low bits of its
   // address, and few memory channels serve it: a bare loader of these tiles reaches 5.3 TB/s, and 6.3 when the workgroups
   // start their K loops at different places.  So they do, at 32 of them: 64 tokens at d = 4096 493 -> 470 us for the layer, 389
-  // tokens at d = 2048 169 -> 155.  (With several row blocks, which have to meet in L2, different places made two
-  // micro-batches of 1021 tokens 3 % slower.)
+  // tokens at d = 2048 169 -> 155.  Row blocks that share weights have to read them at the same time, and the column
+  // tiles of an XCD the same part of the rows, which then stay in its L2: there every XCD starts at a place of its own (5003
+  // tokens, 64 experts 266 -> 260 us, two micro-batches of 1021 tokens 1957 -> 1937; by column tile 3 % slower than by none).
   const bool stream_b = !A_T && P.mtiles() == 1;
   constexpr bool ROTATE = !F32 && !A_T;
-  if constexpr (ROTATE) first_k = stream_b ? (nk * ((first_k * 5 + p) & 31)) >> 5 : 0;
+  if constexpr (ROTATE)
+    first_k = stream_b ? (nk * ((first_k * 5 + p) & 31)) >> 5 : (nk * (int)(blockIdx.x % NUM_XCD)) / NUM_XCD;
   else first_k = 0;
   const int nsteps = (EPI == EPI_STORE_DUALK) ? 2 * nk : nk;
   const uint32_t lds_base = __builtin_amdgcn_readfirstlane(lds_address(ring));
