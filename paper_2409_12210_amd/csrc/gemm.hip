@@ -45,7 +45,9 @@ template <typename T, int BM, int BN, int EPI, int LAYOUT, int WAVES_M = 2, int 
 hipError_t run_block(const GemmPlan* plan, int accumulate, int save_pre, int64_t max_tiles, hipStream_t s) {
   constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
   const int64_t grid = (int64_t)align_up((size_t)std::max<int64_t>(max_tiles, 1), NUM_XCD * TILE_RUN);
-  if constexpr (std::is_same_v<T, float>)
+  if constexpr (std::is_same_v<T, float> && BM == 32)
+    hipLaunchKernelGGL((gg_f32_small_kernel<NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan, accumulate, save_pre);
+  else if constexpr (std::is_same_v<T, float>)
     hipLaunchKernelGGL((gg_f32_kernel<BM, BN, NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan, accumulate,
                        save_pre);
   else if constexpr (BM < 128)
@@ -61,6 +63,8 @@ hipError_t run_block(const GemmPlan* plan, int accumulate, int save_pre, int64_t
 template <typename T, int EPI, int LAYOUT>
 hipError_t run_block_tile(TileShape t, const GemmPlan* plan, int accumulate, int save_pre, int64_t max_tiles, hipStream_t s) {
   if (t.bm == 128) return run_block<T, 128, EPI == EPI_SWIGLU ? 64 : 128, EPI, LAYOUT>(plan, accumulate, save_pre, max_tiles, s);
+  if constexpr (std::is_same_v<T, float> && EPI != EPI_STORE_F32)
+    if (t.bm == 32) return run_block<T, 32, 32, EPI, LAYOUT>(plan, accumulate, save_pre, max_tiles, s);
   constexpr int BN = std::is_same_v<T, float> || EPI == EPI_SWIGLU ? 64 : 128;
   if constexpr (!std::is_same_v<T, float> && LAYOUT == LAYOUT_TN && EPI != EPI_SWIGLU)
     if (t.bm == 32) return run_block<T, 32, BN, EPI, LAYOUT, 1, 4>(plan, accumulate, save_pre, max_tiles, s);

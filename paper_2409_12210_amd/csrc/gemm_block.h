@@ -1,5 +1,5 @@
-// Grouped GEMM with small tiles for gfx950: 128 x 128 down to 32 x 128 tiles, one per workgroup of four waves, float32
-// and bf16, every layout and epilogue of the layer.
+// Grouped GEMM with small tiles for gfx950: 128 x 128 down to 32 x 128 (float32: 32 x 32) tiles, one per workgroup of four
+// waves, float32 and bf16, every layout and epilogue of the layer.
 //
 // Where the 256 x 256 kernel of gemm_bf16.h wants tall problems (one workgroup per CU, a ring of five panels), this one
 // serves problems that do not fill such tiles: the workgroup is small enough (80 KiB of LDS) that two of them share a
@@ -45,13 +45,14 @@ __device__ inline int tile_of_workgroup(int b) {
 }
 
 // BN: columns of C per tile.  NB = 2: two B matrices that share A (the up-projection's W1 and W3), BN columns of each.
-template <typename T, int BM, int BN, int NB, int WAVES_M, int WAVES_N, int NSLOT, int EPI, int LAYOUT>
+// KG > 1: KG groups of waves share the tile, each takes every KG-th of a step's four K slices, and the sums meet in LDS.
+template <typename T, int BM, int BN, int NB, int WAVES_M, int WAVES_N, int NSLOT, int EPI, int LAYOUT, int KG = 1>
 __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int accumulate, int save_pre) {
   constexpr int ES = sizeof(T), CE = 16 / ES, BK = 128 / ES;
   constexpr bool A_T = (LAYOUT & 1) != 0, B_T = (LAYOUT & 2) != 0, F32 = ES == 4;
   constexpr int BR = NB * BN;               // B rows of a stage
   constexpr int STAGE = (BM + BR) * 128;
-  constexpr int NW = WAVES_M * WAVES_N;
+  constexpr int NW = WAVES_M * WAVES_N * KG;
   constexpr int UA = BM / 8 / NW, UB = BR / 8 / NW;  // 1 KiB load units per wave and step
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, MI = WM / 32, NI = WN / 32;
   static_assert(BM % (32 * WAVES_M) == 0 && BN % (32 * WAVES_N) == 0 && UA >= 1, "wave tiles of 32 x 32 blocks");
@@ -60,13 +61,15 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   // in slot i mod NSLOT.  Panels of different sizes come in whole stages (an even NSLOT).
   constexpr bool EQUAL = BM == BR;
   static_assert(EQUAL || NSLOT % 2 == 0, "panels of different sizes: whole stages");
-  static_assert((NSLOT % 2 == 0 ? STAGE : BM * 128) >= NW * 4096, "epilogue: 4 KiB per wave in the slots of one step");
+  static_assert(KG == 1 || (KG == 4 && MI * NI == 1), "a slice and a block per wave");
+  static_assert((NSLOT % 2 == 0 ? STAGE : BM * 128) >= NW / KG * 4096, "epilogue: 4 KiB per wave in the slots of one step");
   __shared__ __attribute__((aligned(1024))) char ring[EQUAL ? NSLOT * BM * 128 : NSLOT / 2 * STAGE];
   auto slot_byte = [](int slot) { return EQUAL ? slot * (BM * 128) : (slot >> 1) * STAGE + (slot & 1) * (BR * 128); };
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int kg = wave / (WAVES_M * WAVES_N);
+  const int wm = wave % (WAVES_M * WAVES_N) / WAVES_N, wn = wave % WAVES_N;
   const int tile = tile_of_workgroup(blockIdx.x);
   // the tile's problem: the last one that starts at or before it (every lane looks at one entry of the list)
   const int n_prob = plan->n_prob;
@@ -266,7 +269,7 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
     __builtin_amdgcn_sched_barrier(0);
     const char* pb = ring + slot_byte(rb);
     const char* pa = ring + slot_byte(slot_add(rb, 1));
-    load_frags(pa, pb, 0, 0);
+    load_frags(pa, pb, KG > 1 ? kg : 0, 0);
     if constexpr (NSLOT % 2 == 0) {
       issue_b(slot_add(rb, NSLOT - 2));
       issue_a(slot_add(rb, NSLOT - 1));
@@ -276,12 +279,38 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
     }
     rb = slot_add(rb, 2);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      if (kk < 3) load_frags(pa, pb, kk + 1, (kk + 1) & 1);
+    for (int kk = 0; kk < 4 / KG; ++kk) {
+      if (kk < 4 / KG - 1) load_frags(pa, pb, kk + 1, (kk + 1) & 1);
       mfma_slice(kk & 1);
     }
   }
   __builtin_amdgcn_sched_barrier(0);
+
+  if constexpr (KG > 1) {  // (nothing is on its way into LDS any more, and behind the barrier nobody reads a panel)
+    char* const sums = ring + lane * 16;
+    auto part = [&](int g, int q, int r) { return reinterpret_cast<f32x4*>(sums + (((g - 1) * NB + q) * 4 + r) * 1024); };
+    static_assert(sizeof(ring) >= (KG - 1) * NB * 4096, "the groups' sums");
+    __syncthreads();
+    if (kg > 0) {
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          *part(kg, q, r) = f32x4{acc[q][0][0][4 * r], acc[q][0][0][4 * r + 1], acc[q][0][0][4 * r + 2], acc[q][0][0][4 * r + 3]};
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int g = 1; g < KG; ++g)
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const f32x4 v = *part(g, q, r);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[q][0][0][4 * r + c] += v[c];
+        }
+  }
 
   // ---- epilogue.  For register group r of block (i, j) the lane holds columns 8 r + 4 khalf .. + 3 of row lane & 31.
   // A wave stages units of 32 rows x 128 bytes (64 for a 32-column bf16 tile) through LDS, so that global memory sees
@@ -411,6 +440,14 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
 template <int BM, int BN, int NB, int EPI, int LAYOUT>
 __global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GemmPlan* __restrict__ plan, int accumulate, int save_pre) {
   gg_block<float, BM, BN, NB, 2, 2, 4, EPI, LAYOUT>(plan, accumulate, save_pre);
+}
+// Launches of few tiles.  Bound by latency: of the workgroup's start, of the loads of a K step, of the dependent matrix
+// instructions of a wave.  So the tile is small (32 x 32), its four waves take one K slice of a step each and add up through
+// LDS, and 32 to 36 KiB of ring let four workgroups of a CU wait at a time.  d = 256, 512 tokens: up-projection 14 -> 11 us,
+// dX 19 -> 11; with twice the ring and two workgroups per CU the same there, but up to 6 % slower for whole layers of more tiles.
+template <int NB, int EPI, int LAYOUT>
+__global__ __launch_bounds__(256, 4) void gg_f32_small_kernel(const GemmPlan* __restrict__ plan, int accumulate, int save_pre) {
+  gg_block<float, 32, 32, NB, 1, 1, NB == 1 ? 8 : 6, EPI, LAYOUT, 4>(plan, accumulate, save_pre);
 }
 // as many ring slots as leave room for eight waves per CU
 constexpr int ring_slots(int bm, int br, int waves) {

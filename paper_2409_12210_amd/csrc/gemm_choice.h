@@ -137,7 +137,13 @@ inline GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue) 
     const TileShape t = swiglu ? TileShape{128, 64} : TileShape{128, 128}, t64 = {64, 64};
     const double slots = 2 * GEMM_CUS, rounds = gemm_work(L, epilogue, t).tiles / slots;
     const double small = gemm_work(L, epilogue, t64).tiles / (swiglu ? 2 : 4) / slots;  // in units of a large tile's work
-    return with_chunk(rounds >= 1 && rounds + 0.3 <= 1.07 * small + 0.15 ? t : t64);
+    const GemmChoice c = with_chunk(rounds >= 1 && rounds + 0.3 <= 1.07 * small + 0.15 ? t : t64);
+    // Fewer than one and a half 64 x 64 tiles per CU leave matrix pipes idle and each K loop's chain of latencies exposed:
+    // 32 x 32 tiles, four to a CU, whose four waves share out the K slices.  Sum of the four products, 64 -> 32: d = 256, 512
+    // tokens (80 tiles) 62 -> 46 us, 2048 tokens (272 tiles) 84 -> 78; d = 512, 256 tokens 99 -> 68, 1024 tokens (280) 138 ->
+    // 114; from 400 tiles on about even (d = 384, 700 tokens, up-projection of 440 tiles 36 -> 42).
+    const bool few = epilogue != EPI_STORE_F32 && c.kchunk == 0 && 2 * gemm_work(L, epilogue, t64).tiles < 3 * GEMM_CUS;
+    return few ? GemmChoice{TileShape{32, 32}, 0} : c;
   }
   // The products with d columns: 32-row tiles for decode-sized batches (20 KiB a K step, four of them in flight), 64-row
   // tiles as long as they hold an expert's rows.  d = 2048, eight experts: 32 rows (T = 130) 32 against 64 rows 54 / 56
