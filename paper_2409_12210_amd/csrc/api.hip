@@ -525,7 +525,10 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   pa.dh_tile = gemm_choice(L, dt, EPI_SWIGLU_BWD).tile;
   pa.dx_tile = dx.tile;
   pa.wg_tile = gemm_choice(L, dt, EPI_STORE_F32).tile;
-  HIP_TRY(launch_bwd_prep(L, dt, dY, sb + sl.O, R, dO, dg, pa, s));
+  const BwdRouterBufs rb = {reinterpret_cast<float*>(wsb + w.dl), reinterpret_cast<float*>(wsb + w.du),
+                            reinterpret_cast<float*>(wsb + w.dgamma_part),
+                            reinterpret_cast<float*>(wsb + w.dWg_partial), wsb + w.Wt};
+  HIP_TRY(launch_bwd_prep(L, dt, dY, sb + sl.O, R, dO, dg, pa, ext ? &G : nullptr, aux_grad, W_gate, rb, s));
   stamp.mark(MODSE_STAGE_BWD_PREP);
 
   HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU_BWD, pa.dh_tile, pa.dh, 0, 0, tiles_bound(L, pa.dh_tile, true), s));
@@ -540,9 +543,6 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, accumulate, 0, wgrad_tiles(L, pa.wg_tile), s));
   stamp.mark(MODSE_STAGE_BWD_WGRAD);
 
-  const BwdRouterBufs rb = {reinterpret_cast<float*>(wsb + w.dl), reinterpret_cast<float*>(wsb + w.du),
-                            reinterpret_cast<float*>(wsb + w.dgamma_part),
-                            reinterpret_cast<float*>(wsb + w.dWg_partial), wsb + w.Wt};
   const DxRows rows = {pa.dXp, pa.dXpart, pa.dx_kchunk};
   HIP_TRY(launch_bwd_router(L, dt, x, W_gate, rows, dg, R, ext ? &G : nullptr, aux_grad, rb, dX, dW_gate, dW_noise,
                             dgamma, accumulate, s));

@@ -163,8 +163,6 @@ hipError_t launch_combine_split(const LayerDims& L, modse_dtype dt, const float*
                                 void* O, void* y, hipStream_t s);
 struct BwdPlanArgs;
 // backward of the combine, and the tile plans of the backward GEMMs
-hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, const void* O, const RoutingPtrs& R,
-                           void* dO, float* dg, const BwdPlanArgs& plan, hipStream_t s);
 struct BwdRouterBufs {  // workspace of the router's backward pass
   float* dl;           // [T, N] dense gradient of the logits
   float* du;           // [T, N] gradient of x W_noise
@@ -172,6 +170,10 @@ struct BwdRouterBufs {  // workspace of the router's backward pass
   float* dW_partial;   // [ceil(T / 32) + 1, d, N] shares of the router-side weight gradients
   void* Wt;            // [N, d] W_gate's columns
 };
+// G, aux_grad, W_gate, B: for the gradient of the logits of a plain gate, which launch_bwd_router expects in B
+hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, const void* O, const RoutingPtrs& R,
+                           void* dO, float* dg, const BwdPlanArgs& plan, const GateExtPtrs* G, float aux_grad,
+                           const void* W_gate, const BwdRouterBufs& B, hipStream_t s);
 // The data gradient of the permuted rows: dXp, or (kchunk > 0) its partial sums, see BwdPlanArgs.
 struct DxRows {
   void* dXp;

@@ -1309,16 +1309,25 @@ __global__ __launch_bounds__(256) void combine_kernel(const T* __restrict__ O, i
   }
 }
 
-// acc[0..7] = the sum of n slabs at src, added in ascending order
-__device__ inline void sum_slabs8(const float* src, size_t slab, int n, float acc[8]) {
+// acc[j] = the sum of the n[j] slabs at src[j], added in ascending order; the loads of the K rows go out side by side
+template <int K>
+__device__ inline void sum_slabs8(const float* const (&src)[K], size_t slab, const int (&n)[K], float (&acc)[K][8]) {
+  int most = n[0];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = 0.f;
+  for (int j = 0; j < K; ++j) {
+    most = max(most, n[j]);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[j][q] = 0.f;
+  }
 #pragma unroll 4
-  for (int s = 0; s < n; ++s) {
-    float v[8];
-    load8(src + s * slab, v);
+  for (int s = 0; s < most; ++s) {
+    float v[K][8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) acc[q] += v[q];
+    for (int j = 0; j < K; ++j) load8(src[j] + min(s, n[j] - 1) * slab, v[j]);  // (a row with fewer slabs repeats its last)
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) acc[j][q] = s < n[j] ? acc[j][q] + v[j][q] : acc[j][q];
   }
 }
 
@@ -1337,20 +1346,32 @@ __global__ __launch_bounds__(256) void combine_split_kernel(const float* __restr
   if (i >= (long)ntok * per_tok) return;
   const int t = (int)(i / per_tok), c = (int)(i % per_tok) * 8;
   const size_t slab = (size_t)ntok * top_k * d;
-  float o[8];
+  auto row = [&](auto two_tag) {
+    constexpr int K = decltype(two_tag)::value ? 2 : 1;
+    const float* src[K];
+    int n[K];
+    size_t at[K];
+    float g[K], acc[K][8], o[8];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) o[q] = 0.f;
-  for (int j = 0; j < top_k; ++j) {
-    const int e = topk_idx[(size_t)t * top_k + j];
-    const size_t at = (size_t)row_of[(size_t)t * top_k + j] * d + c;
-    const float g = topk_w[(size_t)t * top_k + j];
-    float acc[8];
-    sum_slabs8(Opart + at, slab, (L.f[e] + kchunk - 1) / kchunk, acc);
-    if (O) store8(O + at, acc);
+    for (int j = 0; j < K; ++j) {
+      n[j] = (L.f[topk_idx[(size_t)t * K + j]] + kchunk - 1) / kchunk;
+      at[j] = (size_t)row_of[(size_t)t * K + j] * d + c;
+      g[j] = topk_w[(size_t)t * K + j];
+      src[j] = Opart + at[j];
+    }
+    sum_slabs8(src, slab, n, acc);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) o[q] = fmaf(g, acc[q], o[q]);
-  }
-  store8(y + (size_t)t * d + c, o);
+    for (int q = 0; q < 8; ++q) o[q] = 0.f;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      if (O) store8(O + at[j], acc[j]);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) o[q] = fmaf(g[j], acc[j][q], o[q]);
+    }
+    store8(y + (size_t)t * d + c, o);
+  };
+  if (top_k == 2) row(std::true_type{});
+  else row(std::false_type{});
 }
 
 // One thread per permuted row and 8 columns.
@@ -1364,23 +1385,33 @@ __global__ __launch_bounds__(256) void sum_slabs_kernel(const float* __restrict_
   const int r = (int)(i / per_row), c = (int)(i % per_row) * 8;
   const int e = topk_idx[src_of[r]];
   const size_t at = (size_t)r * d + c;
-  float acc[8];
-  sum_slabs8(slabs + at, (size_t)nrows * d, passes * ((L.f[e] + kchunk - 1) / kchunk), acc);
-  store8(out + at, acc);
+  const float* const src[1] = {slabs + at};
+  const int n[1] = {passes * ((L.f[e] + kchunk - 1) / kchunk)};
+  float acc[1][8];
+  sum_slabs8(src, (size_t)nrows * d, n, acc);
+  store8(out + at, acc[0]);
 }
 
-// Backward of the combine: for permuted row r = (token t, slot j):
-//   dO[r] = g[t,j] * dY[t]      d g[t,j] = <dY[t], O[r]>
-// The first block makes the tile plans of the backward GEMMs beside the others (a launch of its own took 9 us).
-template <typename T>
-__global__ __launch_bounds__(256) void bwd_prep_plan_bwd_kernel(const T* __restrict__ dY, const T* __restrict__ O,
-                                                                int nrows, int d, int top_k, RoutingPtrs R,
+// Backward of the combine, one wave per token: for its permuted rows r_j
+//   dO[r_j] = g_j * dY[t]      d g_j = <dY[t], O[r_j]>
+// and, where the gate has none of its optional parts (GATE), the gradient of the logits in the same breath:
+//   dl_j = g_j (dg_j - sum_m g_m dg_m) on the kept logits (softmax over KeepTopK), 0 elsewhere.
+// The first block makes the tile plans of the backward GEMMs beside the others, the blocks behind the tokens' (GATE) copy
+// W_gate [d, N] to Wt [N, d] for bwd_gate_rows_kernel, 256 rows each.
+// Bound by memory; dY is read once per token, not once per row, and the gate's gradient needs no launch.  d = 2048, 32768
+// tokens: 131 -> 122 us; the launch of the gate's gradient took 4 to 6 us.
+constexpr int PREP_TOKENS = 4;
+template <typename T, bool GATE>
+__global__ __launch_bounds__(256) void bwd_prep_plan_bwd_kernel(const T* __restrict__ dY, const T* __restrict__ O, RoutingPtrs R,
                                                                 T* __restrict__ dO, float* __restrict__ dg,
-                                                                LayerDims L, int esize, BwdPlanArgs plan) {
+                                                                LayerDims L, int esize, BwdPlanArgs plan,
+                                                                float* __restrict__ dl, const T* __restrict__ Wg,
+                                                                T* __restrict__ Wt) {
   __shared__ modse_gemm::PlanLds s_plan;
   __shared__ int s_counts[MODSE_MAX_EXPERTS], s_offsets[MODSE_MAX_EXPERTS];
+  const int d = L.d, N = L.N, ntok = L.T, top_k = L.k;
   if (blockIdx.x == 0) {
-    if (threadIdx.x < L.N) {
+    if (threadIdx.x < N) {
       s_counts[threadIdx.x] = R.counts[threadIdx.x];
       s_offsets[threadIdx.x] = R.offsets[threadIdx.x];
     }
@@ -1388,54 +1419,80 @@ __global__ __launch_bounds__(256) void bwd_prep_plan_bwd_kernel(const T* __restr
     modse_gemm::plan_bwd_body(L, esize, s_counts, s_offsets, plan, s_plan);
     return;
   }
-  const int r = (blockIdx.x - 1) * 4 + (threadIdx.x >> 6);
-  if (r >= nrows) return;
-  const int lane = threadIdx.x & 63;
-  const int s = R.src_of[r];
-  const int t = s / top_k;
-  const float g = R.topk_w[s];
-  float dot = 0.f;
-  for (int c = lane * 8; c < d; c += 64 * 8) {
-    float a[8], o[8], w[8];
-    load8(dY + (size_t)t * d + c, a);
-    load8(O + (size_t)r * d + c, o);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      dot = fmaf(a[i], o[i], dot);
-      w[i] = g * a[i];
-    }
-    store8(dO + (size_t)r * d + c, w);
+  const int nbt = (ntok + PREP_TOKENS - 1) / PREP_TOKENS;
+  if (GATE && (int)blockIdx.x > nbt) {
+    const int c = ((int)blockIdx.x - 1 - nbt) * 256 + threadIdx.x;
+    if (c < d)
+#pragma unroll 8
+      for (int e = 0; e < N; ++e) Wt[(size_t)e * d + c] = Wg[(size_t)c * N + e];
+    return;
   }
+  const int t = (blockIdx.x - 1) * PREP_TOKENS + (threadIdx.x >> 6);
+  if (t >= ntok) return;
+  const int lane = threadIdx.x & 63;
+  auto rows = [&](auto two_tag) {
+    constexpr int K = decltype(two_tag)::value ? 2 : 1;
+    int r[K];
+    float g[K], dot[K];
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) dot += __shfl_xor(dot, m, 64);
-  if (lane == 0) dg[r] = dot;
+    for (int j = 0; j < K; ++j) {
+      r[j] = R.row_of[(size_t)t * K + j];
+      g[j] = R.topk_w[(size_t)t * K + j];
+      dot[j] = 0.f;
+    }
+#pragma unroll 2
+    for (int c = lane * 8; c < d; c += 64 * 8) {
+      float a[8], o[K][8], w[8];
+      load8(dY + (size_t)t * d + c, a);
+#pragma unroll
+      for (int j = 0; j < K; ++j) load8(O + (size_t)r[j] * d + c, o[j]);
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          dot[j] = fmaf(a[i], o[j][i], dot[j]);
+          w[i] = g[j] * a[i];
+        }
+        store8(dO + (size_t)r[j] * d + c, w);
+      }
+    }
+    float mean = 0.f;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) dot[j] += __shfl_xor(dot[j], m, 64);
+      mean += g[j] * dot[j];
+    }
+    if constexpr (GATE) {
+      float v = 0.f;
+#pragma unroll
+      for (int j = 0; j < K; ++j)
+        if (R.topk_idx[(size_t)t * K + j] == lane) v = g[j] * (dot[j] - mean);
+      if (lane < N) dl[(size_t)t * N + lane] = v;
+    } else if (lane == 0) {
+#pragma unroll
+      for (int j = 0; j < K; ++j) dg[r[j]] = dot[j];
+    }
+  };
+  if (top_k == 2) rows(std::true_type{});
+  else rows(std::false_type{});
 }
 
-// Backward through the gate, one thread per token: the dense gradient of the logits H(x),
+// Backward through a gate with optional parts, one thread per token: the dense gradient of the logits H(x),
 //   dl_j = g_j (dg_j - sum_m g_m dg_m) on the kept logits (softmax over KeepTopK), 0 elsewhere,
 //   + aux_coef p_i (f_i - sum_m f_m p_m)  when the auxiliary loss is on (Sec. 3.2 Eq. 9-12 with f constant;
 //     aux_coef = dLoss/dL_a * alpha N / T),
 // and, when the noise term is on (z = gamma s / r, s = softplus(u), r = sqrt(mean s^2 + eps), Sec. 2
 // Eq. 4-5), the gradient of u = x W_n and this block's share of d gamma:
 //   du_i = gamma (dl_i / r - s_i <s, dl> / (N r^3)) sigmoid(u_i),   dgamma = sum_t <dl, s> / r.
-// Blocks from `nbt` on copy W_gate [d, N] to Wt [N, d] for bwd_gate_rows_kernel, 64 rows each.
 constexpr int GB_THREADS = 64;  // (blocks of 256 threads left most CUs idle: 24 us at 8192 tokens with both gate extensions, now 11)
-template <typename T>
 __global__ __launch_bounds__(GB_THREADS) void gate_bwd_kernel(const float* __restrict__ dg, int ntok, int N, int top_k,
                                                               const int32_t* __restrict__ topk_idx,
                                                               const float* __restrict__ topk_w,
                                                               const int32_t* __restrict__ row_of, GateExtPtrs G,
                                                               float aux_coef, float* __restrict__ dl, float* __restrict__ du,
-                                                              float* __restrict__ dgamma_part, int nbt, int d,
-                                                              const T* __restrict__ Wg, T* __restrict__ Wt) {
+                                                              float* __restrict__ dgamma_part) {
   const int tid = threadIdx.x;
-  if ((int)blockIdx.x >= nbt) {
-    const int c = ((int)blockIdx.x - nbt) * GB_THREADS + tid;
-    if (c < d)
-#pragma unroll 8
-      for (int e = 0; e < N; ++e) Wt[(size_t)e * d + c] = Wg[(size_t)c * N + e];
-    return;
-  }
   // (a token's row of dl is put together in LDS: in memory every step would wait for the one before)
   __shared__ float s_row[MODSE_MAX_EXPERTS][GB_THREADS], s_sp[MODSE_MAX_EXPERTS][GB_THREADS];
   const int t = blockIdx.x * GB_THREADS + tid;
@@ -1497,37 +1554,105 @@ __global__ __launch_bounds__(GB_THREADS) void gate_bwd_kernel(const float* __res
 // with 64 experts; at 32768 tokens and 8 experts 139 in place of 157, with both gate extensions at 8192 tokens 101 in
 // place of 146.)
 
+// The router's weight gradients (+)= the sum of the chunks' partials, in a fixed order (deterministic): 64 outputs per
+// block, the partials are split over the 4 waves and combined through LDS.  Outputs: dW_gate, then (noise term on)
+// dW_noise and dgamma, whose partials lie in an array of their own.
+struct DwgReduceArgs {
+  const float* partial;
+  int nchunk, n, nmat;  // chunks; elements of a matrix; matrices
+  const float* dgamma_part;
+  int ngamma, accumulate;
+  float *dWg, *dWn, *dgamma;
+};
+inline int dwg_reduce_blocks(const DwgReduceArgs& a) { return (a.n * a.nmat + 63) / 64 + (a.nmat == 2 ? 1 : 0); }
+__device__ inline void dwg_reduce(const DwgReduceArgs& a, int block, int nblock, float (&s_part)[4][64]) {
+  const int li = threadIdx.x & 63, part = threadIdx.x >> 6;
+  const int i = block * 64 + li, total = a.n * a.nmat;
+  const bool gamma = a.nmat == 2 && block == nblock - 1 && li == 63 && i >= total;
+  float acc = 0.f;
+  if (i < total) {
+#pragma unroll 8
+    for (int b = part; b < a.nchunk; b += 4) acc += a.partial[(size_t)b * total + i];  // unrolled: several loads in flight
+  } else if (gamma) {
+    double sum = 0.0;  // (T / 256 values in a row)
+#pragma unroll 8
+    for (int b = part; b < a.ngamma; b += 4) sum += (double)a.dgamma_part[b];
+    acc = (float)sum;
+  }
+  s_part[part][li] = acc;
+  __syncthreads();
+  if (part != 0) return;
+  float* const out = i < a.n ? a.dWg + i : i < total ? a.dWn + (i - a.n) : gamma ? a.dgamma : nullptr;
+  if (!out) return;
+  const float v = (s_part[0][li] + s_part[1][li]) + (s_part[2][li] + s_part[3][li]);
+  *out = a.accumulate ? *out + v : v;
+}
+__global__ __launch_bounds__(256) void dwg_reduce_kernel(DwgReduceArgs a) {
+  __shared__ float s_part[4][64];
+  dwg_reduce(a, blockIdx.x, gridDim.x, s_part);
+}
+
 // Plain gate: dl is zero except for the chosen experts, so
 //   dX[t] = sum_j (dXp[row_of[t, j]] + W_gate[:, e_j] dl[t, e_j])
 // with W_gate's columns as rows of Wt: one thread per token and eight columns of d, four row reads and a write.  SPLIT: a
 // row of dXp is still the passes * ceil(f_e / kchunk) float32 slabs of the split product.
+// The first `nreduce` blocks finish the router's weight gradient, which as a launch of its own took 4 to 5 us.  Stage of the
+// router's backward pass without that launch and the gate's: d = 256, 512 tokens 18.7 -> 12.4 us; d = 2048, 1021 tokens 45 -> 37
+// (and the slabs of a token's two rows fetched side by side), 32768 tokens 135 -> 122.
 template <typename T, bool SPLIT>
 __global__ __launch_bounds__(256) void bwd_gate_rows_kernel(const T* __restrict__ dXp, const float* __restrict__ slabs,
                                                             LayerDims L, int kchunk, const T* __restrict__ Wt,
                                                             const float* __restrict__ dl,
                                                             const int32_t* __restrict__ topk_idx,
-                                                            const int32_t* __restrict__ row_of, T* __restrict__ dX) {
+                                                            const int32_t* __restrict__ row_of, T* __restrict__ dX,
+                                                            DwgReduceArgs reduce, int nreduce) {
+  __shared__ float s_part[4][64];
+  if ((int)blockIdx.x < nreduce) {
+    dwg_reduce(reduce, blockIdx.x, nreduce, s_part);
+    return;
+  }
   const int d = L.d, per_tok = d / 8;
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  const long i = (long)((int)blockIdx.x - nreduce) * 256 + threadIdx.x;
   if (i >= (long)L.T * per_tok) return;
   const int t = (int)(i / per_tok), c = (int)(i % per_tok) * 8;
-  float o[8];
+  auto row = [&](auto two_tag) {
+    constexpr int K = decltype(two_tag)::value ? 2 : 1;
+    int e[K];
+    size_t at[K];
+    float g[K], v[K][8], w[K][8], o[8];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) o[q] = 0.f;
-  auto add = [&](int j) {
-    const int e = topk_idx[(size_t)t * L.k + j];
-    const size_t at = (size_t)row_of[(size_t)t * L.k + j] * d + c;
-    const float g = dl[(size_t)t * L.N + e];
-    float v[8], w[8];
-    if constexpr (SPLIT) sum_slabs8(slabs + at, (size_t)L.T * L.k * d, 2 * ((L.f[e] + kchunk - 1) / kchunk), v);
-    else load8(dXp + at, v);
-    load8(Wt + (size_t)e * d + c, w);
+    for (int j = 0; j < K; ++j) {
+      e[j] = topk_idx[(size_t)t * K + j];
+      at[j] = (size_t)row_of[(size_t)t * K + j] * d + c;
+    }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) o[q] = fmaf(w[q], g, o[q] + v[q]);
+    for (int j = 0; j < K; ++j) {
+      g[j] = dl[(size_t)t * L.N + e[j]];
+      load8(Wt + (size_t)e[j] * d + c, w[j]);
+    }
+    if constexpr (SPLIT) {
+      const float* src[K];
+      int n[K];
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        src[j] = slabs + at[j];
+        n[j] = 2 * ((L.f[e[j]] + kchunk - 1) / kchunk);
+      }
+      sum_slabs8(src, (size_t)L.T * L.k * d, n, v);
+    } else {
+#pragma unroll
+      for (int j = 0; j < K; ++j) load8(dXp + at[j], v[j]);
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) o[q] = 0.f;
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) o[q] = fmaf(w[j][q], g[j], o[q] + v[j][q]);
+    store8(dX + (size_t)t * d + c, o);
   };
-  add(0);
-  if (L.k == 2) add(1);
-  store8(dX + (size_t)t * d + c, o);
+  if (L.k == 2) row(std::true_type{});
+  else row(std::false_type{});
 }
 
 constexpr int BR_SLAB = 512, BR_TOK = 32;  // columns of d that a wave (eight per lane) owns; tokens per block and step
@@ -1710,35 +1835,6 @@ __global__ __launch_bounds__(256, 3) void bwd_dwg_kernel(BwdRouterArgs a, const 
   }
 }
 
-// The router's weight gradients (+)= the sum of the chunks' partials, in a fixed order (deterministic): 64 outputs per
-// block, the partials are split over the 4 waves and combined through LDS.  Outputs: dW_gate, then (noise term on)
-// dW_noise and dgamma, whose partials lie in an array of their own.
-__global__ __launch_bounds__(256) void dwg_reduce_kernel(const float* __restrict__ partial, int nchunk, int n, int nmat,
-                                                         const float* __restrict__ dgamma_part, int ngamma,
-                                                         int accumulate, float* __restrict__ dWg,
-                                                         float* __restrict__ dWn, float* __restrict__ dgamma) {
-  __shared__ float s_part[4][64];
-  const int li = threadIdx.x & 63, part = threadIdx.x >> 6;
-  const int i = blockIdx.x * 64 + li, total = n * nmat;
-  float acc = 0.f;
-  if (i < total) {
-#pragma unroll 8
-    for (int b = part; b < nchunk; b += 4) acc += partial[(size_t)b * total + i];  // unrolled: several loads in flight
-  } else if (nmat == 2 && blockIdx.x == gridDim.x - 1 && li == 63) {
-    double sum = 0.0;  // (T / 256 values in a row)
-#pragma unroll 8
-    for (int b = part; b < ngamma; b += 4) sum += (double)dgamma_part[b];
-    acc = (float)sum;
-  }
-  s_part[part][li] = acc;
-  __syncthreads();
-  if (part != 0) return;
-  float* const out = i < n ? dWg + i : i < total ? dWn + (i - n) : nmat == 2 && blockIdx.x == gridDim.x - 1 && li == 63 ? dgamma : nullptr;
-  if (!out) return;
-  const float v = (s_part[0][li] + s_part[1][li]) + (s_part[2][li] + s_part[3][li]);
-  *out = accumulate ? *out + v : v;
-}
-
 // [d, N] -> [d, NE] with zero columns behind the N real ones
 template <typename T>
 __global__ __launch_bounds__(256) void pad_rows_kernel(const T* __restrict__ W, int d, int N, int NE,
@@ -1912,19 +2008,41 @@ hipError_t permute_typed(const LayerDims& L, modse_dtype dt, const void* xv, con
   return hipGetLastError();
 }
 
+// dLoss/dL_a * alpha N / T, the factor of the auxiliary loss in the gradient of the logits
+float aux_coefficient(const LayerDims& L, const GateExtPtrs& G, float aux_grad) {
+  return G.probs ? aux_grad * G.alpha * (float)L.N / (float)L.T : 0.f;
+}
+// neither optional part of the gate takes part in the backward pass
+bool gate_is_plain(const GateExtPtrs& G, float aux_coef) { return !G.W_noise && aux_coef == 0.f; }
+
+template <typename T>
+hipError_t bwd_prep_typed(const LayerDims& L, const void* dY, const void* O, const RoutingPtrs& R, void* dO, float* dg,
+                          const BwdPlanArgs& plan, bool plain, const void* Wg, const BwdRouterBufs& B, hipStream_t s) {
+  const dim3 grid(1 + (L.T + PREP_TOKENS - 1) / PREP_TOKENS + (plain ? (L.d + 255) / 256 : 0));
+  const T *dYt = static_cast<const T*>(dY), *Ot = static_cast<const T*>(O), *Wt = static_cast<const T*>(Wg);
+  if (plain)
+    hipLaunchKernelGGL((bwd_prep_plan_bwd_kernel<T, true>), grid, dim3(256), 0, s, dYt, Ot, R, static_cast<T*>(dO), dg, L,
+                       (int)sizeof(T), plan, B.dl, Wt, static_cast<T*>(B.Wt));
+  else
+    hipLaunchKernelGGL((bwd_prep_plan_bwd_kernel<T, false>), grid, dim3(256), 0, s, dYt, Ot, R, static_cast<T*>(dO), dg, L,
+                       (int)sizeof(T), plan, nullptr, nullptr, nullptr);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t bwd_router_typed(const LayerDims& L, const GateExtPtrs& G, float aux_coef, const void* xv, const void* Wv,
                             const DxRows& rows, const float* dg, const RoutingPtrs& R, const BwdRouterBufs& B, void* dXv,
                             float* dW_gate, float* dW_noise, float* dgamma, int accumulate, hipStream_t s) {
   const T *x = static_cast<const T*>(xv), *W = static_cast<const T*>(Wv), *dXp = static_cast<const T*>(rows.dXp);
   T* const dX = static_cast<T*>(dXv);
-  const bool noise = G.W_noise != nullptr, sparse = !noise && aux_coef == 0.f;  // dl is zero but for the chosen experts
-  const int nbt = (L.T + GB_THREADS - 1) / GB_THREADS, ntr = sparse ? (L.d + GB_THREADS - 1) / GB_THREADS : 0;
-  hipLaunchKernelGGL((gate_bwd_kernel<T>), dim3(nbt + ntr), dim3(GB_THREADS), 0, s, dg, L.T, L.N, L.k, R.topk_idx, R.topk_w,
-                     R.row_of, G, aux_coef, B.dl, noise ? B.du : nullptr, noise ? B.dgamma_part : nullptr, nbt, L.d, W,
-                     static_cast<T*>(B.Wt));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const bool noise = G.W_noise != nullptr, sparse = gate_is_plain(G, aux_coef);  // dl is zero but for the chosen experts
+  const int nbt = (L.T + GB_THREADS - 1) / GB_THREADS;
+  hipError_t e;
+  if (!sparse) {  // (otherwise launch_bwd_prep has seen to dl and Wt)
+    hipLaunchKernelGGL(gate_bwd_kernel, dim3(nbt), dim3(GB_THREADS), 0, s, dg, L.T, L.N, L.k, R.topk_idx, R.topk_w, R.row_of, G,
+                       aux_coef, B.dl, noise ? B.du : nullptr, noise ? B.dgamma_part : nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   const int nmat = noise ? 2 : 1, slabs = (L.d + BR_SLAB - 1) / BR_SLAB, nb = (L.T + BR_TOK - 1) / BR_TOK;
   const BwdRouterArgs a = {W, G.W_noise, B.dl, B.du, L.T, L.d, L.N, nmat * L.N, L.k, R.row_of};
   // dX comes last: its buffer may be x's (nothing after the weight gradients reads x).
@@ -1933,19 +2051,19 @@ hipError_t bwd_router_typed(const LayerDims& L, const GateExtPtrs& G, float aux_
   const int tok = std::max(nmat, std::min(16, nb * slabs * groups / 512)) * BR_TOK, nchunk = (L.T + tok - 1) / tok;
   hipLaunchKernelGGL((bwd_dwg_kernel<T>), dim3(nchunk, slabs, groups), dim3(256), 0, s, a, x, tok, B.dW_partial);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int n = L.d * L.N;
-  hipLaunchKernelGGL(dwg_reduce_kernel, dim3((n * nmat + 63) / 64 + (noise ? 1 : 0)), dim3(256), 0, s, B.dW_partial, nchunk, n,
-                     nmat, B.dgamma_part, nbt, accumulate, dW_gate, dW_noise, dgamma);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const DwgReduceArgs red = {B.dW_partial, nchunk, L.d * L.N, nmat, B.dgamma_part, nbt, accumulate, dW_gate, dW_noise, dgamma};
+  const int nred = dwg_reduce_blocks(red);
   if (sparse) {
-    const dim3 grid((unsigned)(((long)L.T * (L.d / 8) + 255) / 256));
+    const dim3 grid((unsigned)(((long)L.T * (L.d / 8) + 255) / 256 + nred));
     if (rows.kchunk)
       hipLaunchKernelGGL((bwd_gate_rows_kernel<T, true>), grid, dim3(256), 0, s, dXp, rows.slabs, L, rows.kchunk,
-                         static_cast<const T*>(B.Wt), B.dl, R.topk_idx, R.row_of, dX);
+                         static_cast<const T*>(B.Wt), B.dl, R.topk_idx, R.row_of, dX, red, nred);
     else
       hipLaunchKernelGGL((bwd_gate_rows_kernel<T, false>), grid, dim3(256), 0, s, dXp, nullptr, L, 0,
-                         static_cast<const T*>(B.Wt), B.dl, R.topk_idx, R.row_of, dX);
+                         static_cast<const T*>(B.Wt), B.dl, R.topk_idx, R.row_of, dX, red, nred);
   } else {
+    hipLaunchKernelGGL(dwg_reduce_kernel, dim3(nred), dim3(256), 0, s, red);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     if (rows.kchunk) {
       const long chunks = (long)L.T * L.k * (L.d / 8);
       hipLaunchKernelGGL((sum_slabs_kernel<T>), dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, s, rows.slabs, L.T * L.k, L.d,
@@ -2011,16 +2129,13 @@ hipError_t launch_combine_split(const LayerDims& L, modse_dtype dt, const float*
 }
 
 hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, const void* O, const RoutingPtrs& R,
-                           void* dO, float* dg, const BwdPlanArgs& plan, hipStream_t s) {
-  const int nrows = L.T * L.k;
-  const dim3 grid((nrows + 3) / 4 + 1);
-  if (dt == MODSE_F32)
-    hipLaunchKernelGGL((bwd_prep_plan_bwd_kernel<float>), grid, dim3(256), 0, s, static_cast<const float*>(dY),
-                       static_cast<const float*>(O), nrows, L.d, L.k, R, static_cast<float*>(dO), dg, L, 4, plan);
-  else
-    hipLaunchKernelGGL((bwd_prep_plan_bwd_kernel<bf16_t>), grid, dim3(256), 0, s, static_cast<const bf16_t*>(dY),
-                       static_cast<const bf16_t*>(O), nrows, L.d, L.k, R, static_cast<bf16_t*>(dO), dg, L, 2, plan);
-  return hipGetLastError();
+                           void* dO, float* dg, const BwdPlanArgs& plan, const GateExtPtrs* G, float aux_grad,
+                           const void* W_gate, const BwdRouterBufs& B, hipStream_t s) {
+  const GateExtPtrs none = {};
+  const GateExtPtrs& g = G ? *G : none;
+  const bool plain = gate_is_plain(g, aux_coefficient(L, g, aux_grad));
+  return dt == MODSE_F32 ? bwd_prep_typed<float>(L, dY, O, R, dO, dg, plan, plain, W_gate, B, s)
+                         : bwd_prep_typed<bf16_t>(L, dY, O, R, dO, dg, plan, plain, W_gate, B, s);
 }
 
 hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const DxRows& rows,
@@ -2029,7 +2144,7 @@ hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, 
                              int accumulate, hipStream_t s) {
   const GateExtPtrs none = {};
   const GateExtPtrs& g = G ? *G : none;
-  const float aux_coef = g.probs ? aux_grad * g.alpha * (float)L.N / (float)L.T : 0.f;
+  const float aux_coef = aux_coefficient(L, g, aux_grad);
   return dt == MODSE_F32 ? bwd_router_typed<float>(L, g, aux_coef, x, W_gate, rows, dg, R, B, dX, dW_gate, dW_noise, dgamma,
                                                    accumulate, s)
                          : bwd_router_typed<bf16_t>(L, g, aux_coef, x, W_gate, rows, dg, R, B, dX, dW_gate, dW_noise, dgamma,
