@@ -192,7 +192,7 @@ struct TileShape {
 // t: the tile shape that the plan was made with.  max_tiles: upper bound of the number of tiles.  layout < 0: the
 // layout that goes with the epilogue (see gemm.hip).
 hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int accumulate,
-                               int save_pre, int64_t max_tiles, hipStream_t s, int layout = -1);
+                               int option, int64_t max_tiles, hipStream_t s, int layout = -1);
 
 struct FwdPlanArgs {
   const void *Xp, *W1, *W3, *W2;

@@ -51,17 +51,20 @@ __device__ __forceinline__ void global_store16(bf16_t* p, bf16x8 v) { *(global_b
 __device__ __forceinline__ void global_store16_s(const void* base, uint32_t voff, bf16x8 v) {
   asm volatile("global_store_dwordx4 %0, %1, %2\n\ts_nop 1" ::"v"(voff), "v"(v), "s"(base) : "memory");
 }
-__device__ __forceinline__ void global_store16_s(const void* base, uint32_t voff, f32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, %2\n\ts_nop 1" ::"v"(voff), "v"(v), "s"(base) : "memory");
+// (stream: with the non-temporal hint)
+__device__ __forceinline__ void global_store16_s(const void* base, uint32_t voff, f32x4 v, bool stream) {
+  if (stream) asm volatile("global_store_dwordx4 %0, %1, %2 nt\n\ts_nop 1" ::"v"(voff), "v"(v), "s"(base) : "memory");
+  else asm volatile("global_store_dwordx4 %0, %1, %2\n\ts_nop 1" ::"v"(voff), "v"(v), "s"(base) : "memory");
 }
 __device__ __forceinline__ bf16x8 global_load16_s(const void* base, uint32_t voff) {
   bf16x8 v;
   asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(v) : "v"(voff), "s"(base) : "memory");
   return v;
 }
+// (non-temporal: gradients that are added to, read once; two micro-batches of 1021 tokens 1882 -> 1849 us)
 __device__ __forceinline__ f32x4 global_load16_f32_s(const void* base, uint32_t voff) {
   f32x4 v;
-  asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(v) : "v"(voff), "s"(base) : "memory");
+  asm volatile("global_load_dwordx4 %0, %1, %2 nt" : "=v"(v) : "v"(voff), "s"(base) : "memory");
   return v;
 }
 template <int YOUNGER>

@@ -47,7 +47,7 @@ __device__ inline int tile_of_workgroup(int b) {
 // BN: columns of C per tile.  NB = 2: two B matrices that share A (the up-projection's W1 and W3), BN columns of each.
 // KG > 1: KG groups of waves share the tile, each takes every KG-th of a step's four K slices, and the sums meet in LDS.
 template <typename T, int BM, int BN, int NB, int WAVES_M, int WAVES_N, int NSLOT, int EPI, int LAYOUT, int KG = 1>
-__device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int accumulate, int save_pre) {
+__device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int accumulate, int option) {
   constexpr int ES = sizeof(T), CE = 16 / ES, BK = 128 / ES;
   constexpr bool A_T = (LAYOUT & 1) != 0, B_T = (LAYOUT & 2) != 0, F32 = ES == 4;
   constexpr int BR = NB * BN;               // B rows of a stage
@@ -351,12 +351,16 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
     return (m < M && n < N) ? (long)m * ldc + n : -1;
   };
   auto at = [&](const void* base, long o) { return (global_chunk_t*)(uintptr_t)(static_cast<const out_t*>(base) + o); };
+  auto put = [&](void* C, long o, chunk_t v) {
+    if (A_T && option) __builtin_nontemporal_store(v, at(C, o));
+    else *at(C, o) = v;
+  };
   auto store_unit = [&](int i, int ju, void* C) {
 #pragma unroll
     for (int it = 0; it < ITS; ++it) {
       const chunk_t v = *chunk(it);
       const long o = offset(i, ju, it);
-      if (o >= 0) *at(C, o) = v;
+      if (o >= 0) put(C, o, v);
     }
   };
 #pragma unroll
@@ -375,7 +379,7 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
           return h;
         });
         store_unit(i, ju, P.C());
-        if (save_pre) {
+        if (option) {
           stage([&](int jj, int x) { return acc[0][i][j0 + jj][x]; });
           store_unit(i, ju, P.C2());
           stage([&](int jj, int x) { return acc[NB - 1][i][j0 + jj][x]; });
@@ -426,7 +430,7 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
             for (int it = 0; it < ITS; ++it) {
               const chunk_t v = *chunk(it) + old[it];
               const long o = offset(i, ju, it);
-              if (o >= 0) *at(P.C(), o) = v;
+              if (o >= 0) put(P.C(), o, v);
             }
             continue;
           }
@@ -438,16 +442,16 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
 }
 
 template <int BM, int BN, int NB, int EPI, int LAYOUT>
-__global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GemmPlan* __restrict__ plan, int accumulate, int save_pre) {
-  gg_block<float, BM, BN, NB, 2, 2, 4, EPI, LAYOUT>(plan, accumulate, save_pre);
+__global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GemmPlan* __restrict__ plan, int accumulate, int option) {
+  gg_block<float, BM, BN, NB, 2, 2, 4, EPI, LAYOUT>(plan, accumulate, option);
 }
 // Launches of few tiles.  Bound by latency: of the workgroup's start, of the loads of a K step, of the dependent matrix
 // instructions of a wave.  So the tile is small (32 x 32), its four waves take one K slice of a step each and add up through
 // LDS, and 32 to 36 KiB of ring let four workgroups of a CU wait at a time.  d = 256, 512 tokens: up-projection 14 -> 11 us,
 // dX 19 -> 11; with twice the ring and two workgroups per CU the same there, but up to 6 % slower for whole layers of more tiles.
 template <int NB, int EPI, int LAYOUT>
-__global__ __launch_bounds__(256, 4) void gg_f32_small_kernel(const GemmPlan* __restrict__ plan, int accumulate, int save_pre) {
-  gg_block<float, 32, 32, NB, 1, 1, NB == 1 ? 8 : 6, EPI, LAYOUT, 4>(plan, accumulate, save_pre);
+__global__ __launch_bounds__(256, 4) void gg_f32_small_kernel(const GemmPlan* __restrict__ plan, int accumulate, int option) {
+  gg_block<float, 32, 32, NB, 1, 1, NB == 1 ? 8 : 6, EPI, LAYOUT, 4>(plan, accumulate, option);
 }
 // as many ring slots as leave room for eight waves per CU
 constexpr int ring_slots(int bm, int br, int waves) {
@@ -456,16 +460,16 @@ constexpr int ring_slots(int bm, int br, int waves) {
 }
 template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_block_kernel(const GemmPlan* __restrict__ plan,
-                                                                               int accumulate, int save_pre) {
+                                                                               int accumulate, int option) {
   gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, ring_slots(BM, NB * BN, WAVES_M * WAVES_N), EPI, LAYOUT>(plan, accumulate,
-                                                                                                      save_pre);
+                                                                                                      option);
 }
 // tiles of 32 or 64 rows (decode-sized batches and experts with few tokens), under a name of their own for profiles
 template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_skinny_kernel(const GemmPlan* __restrict__ plan,
-                                                                                int accumulate, int save_pre) {
+                                                                                int accumulate, int option) {
   gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, ring_slots(BM, NB * BN, WAVES_M * WAVES_N), EPI, LAYOUT>(plan, accumulate,
-                                                                                                      save_pre);
+                                                                                                      option);
 }
 
 }  // namespace modse_gemm
