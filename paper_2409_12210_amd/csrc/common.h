@@ -78,8 +78,6 @@ struct alignas(128) GemmProblem {
 struct GemmPlan {
   GemmProblem prob[MODSE_MAX_PROBLEMS];
   int32_t tile_start[MODSE_MAX_PROBLEMS + 1];  // prefix sum of mtiles*ntiles in problem order
-  int32_t n_prob;
-  int32_t pad[2];
 };
 
 enum GemmEpilogue {
@@ -191,7 +189,7 @@ struct TileShape {
 };
 // t: the tile shape that the plan was made with.  max_tiles: upper bound of the number of tiles.  layout < 0: the
 // layout that goes with the epilogue (see gemm.hip).
-hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int accumulate,
+hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int n_prob, int accumulate,
                                int option, int64_t max_tiles, hipStream_t s, int layout = -1);
 
 struct FwdPlanArgs {

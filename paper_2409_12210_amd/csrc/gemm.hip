@@ -30,83 +30,83 @@ int num_cus() {
 }
 
 template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT>
-hipError_t run_bf16(const GemmPlan* plan, int accumulate, int option, int64_t max_tiles, hipStream_t s) {
+hipError_t run_bf16(const GemmPlan* plan, int n_prob, int accumulate, int option, int64_t max_tiles, hipStream_t s) {
   constexpr int NT = WAVES_M * WAVES_N * 64;
   int64_t grid = num_cus();  // the LDS panels fill a CU: one persistent workgroup per CU
   if (max_tiles < grid) grid = max_tiles;
   if (grid < 1) grid = 1;
   hipLaunchKernelGGL((gg_bf16_kernel<BM, BN, NB, WAVES_M, WAVES_N, EPI, LAYOUT>), dim3((unsigned)grid), dim3(NT), 0, s,
-                     plan, accumulate, option);
+                     plan, n_prob, accumulate, option);
   return hipGetLastError();
 }
 
 // max_tiles: an upper bound of the tile list's length; one workgroup per tile
 template <typename T, int BM, int BN, int EPI, int LAYOUT, int WAVES_M = 2, int WAVES_N = 2>
-hipError_t run_block(const GemmPlan* plan, int accumulate, int option, int64_t max_tiles, hipStream_t s) {
+hipError_t run_block(const GemmPlan* plan, int n_prob, int accumulate, int option, int64_t max_tiles, hipStream_t s) {
   constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
   const int64_t grid = (int64_t)align_up((size_t)std::max<int64_t>(max_tiles, 1), NUM_XCD * TILE_RUN);
   if constexpr (std::is_same_v<T, float> && BM == 32)
-    hipLaunchKernelGGL((gg_f32_small_kernel<NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan, accumulate, option);
+    hipLaunchKernelGGL((gg_f32_small_kernel<NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan, n_prob, accumulate, option);
   else if constexpr (std::is_same_v<T, float>)
-    hipLaunchKernelGGL((gg_f32_kernel<BM, BN, NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan, accumulate,
+    hipLaunchKernelGGL((gg_f32_kernel<BM, BN, NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan, n_prob, accumulate,
                        option);
   else if constexpr (BM < 128)
     hipLaunchKernelGGL((gg_bf16_skinny_kernel<BM, BN, NB, WAVES_M, WAVES_N, EPI, LAYOUT>), dim3((unsigned)grid),
-                       dim3(WAVES_M * WAVES_N * 64), 0, s, plan, accumulate, option);
+                       dim3(WAVES_M * WAVES_N * 64), 0, s, plan, n_prob, accumulate, option);
   else
     hipLaunchKernelGGL((gg_bf16_block_kernel<BM, BN, NB, WAVES_M, WAVES_N, EPI, LAYOUT>), dim3((unsigned)grid),
-                       dim3(WAVES_M * WAVES_N * 64), 0, s, plan, accumulate, option);
+                       dim3(WAVES_M * WAVES_N * 64), 0, s, plan, n_prob, accumulate, option);
   return hipGetLastError();
 }
 
 // EPI_SWIGLU: `bn` columns of each of the two matrices
 template <typename T, int EPI, int LAYOUT>
-hipError_t run_block_tile(TileShape t, const GemmPlan* plan, int accumulate, int option, int64_t max_tiles, hipStream_t s) {
-  if (t.bm == 128) return run_block<T, 128, EPI == EPI_SWIGLU ? 64 : 128, EPI, LAYOUT>(plan, accumulate, option, max_tiles, s);
+hipError_t run_block_tile(TileShape t, const GemmPlan* plan, int n_prob, int accumulate, int option, int64_t max_tiles, hipStream_t s) {
+  if (t.bm == 128) return run_block<T, 128, EPI == EPI_SWIGLU ? 64 : 128, EPI, LAYOUT>(plan, n_prob, accumulate, option, max_tiles, s);
   if constexpr (std::is_same_v<T, float> && EPI != EPI_STORE_F32)
-    if (t.bm == 32) return run_block<T, 32, 32, EPI, LAYOUT>(plan, accumulate, option, max_tiles, s);
+    if (t.bm == 32) return run_block<T, 32, 32, EPI, LAYOUT>(plan, n_prob, accumulate, option, max_tiles, s);
   constexpr int BN = std::is_same_v<T, float> || EPI == EPI_SWIGLU ? 64 : 128;
   if constexpr (!std::is_same_v<T, float> && LAYOUT == LAYOUT_TN && EPI != EPI_SWIGLU)
-    if (t.bm == 32) return run_block<T, 32, BN, EPI, LAYOUT, 1, 4>(plan, accumulate, option, max_tiles, s);
+    if (t.bm == 32) return run_block<T, 32, BN, EPI, LAYOUT, 1, 4>(plan, n_prob, accumulate, option, max_tiles, s);
   if constexpr (!std::is_same_v<T, float> && LAYOUT == LAYOUT_AB_K) return hipErrorInvalidValue;  // (128 rows or 256)
-  else return run_block<T, 64, BN, EPI, LAYOUT>(plan, accumulate, option, max_tiles, s);
+  else return run_block<T, 64, BN, EPI, LAYOUT>(plan, n_prob, accumulate, option, max_tiles, s);
 }
 
 // The epilogue fixes the operand layout: forward GEMMs are K-contiguous on both sides, data gradients read
 // the weights as [K, N], weight gradients read both activations token-major; split-K partial sums of a forward GEMM
 // (EPI_STORE_F32 with LAYOUT_TN) are the one exception.
 template <typename T>
-hipError_t launch_block(int epilogue, int layout, TileShape t, const GemmPlan* plan, int accumulate, int option,
+hipError_t launch_block(int epilogue, int layout, TileShape t, const GemmPlan* plan, int n_prob, int accumulate, int option,
                         int64_t max_tiles, hipStream_t s) {
   switch (epilogue) {
-    case EPI_STORE: return run_block_tile<T, EPI_STORE, LAYOUT_TN>(t, plan, accumulate, option, max_tiles, s);
-    case EPI_SWIGLU: return run_block_tile<T, EPI_SWIGLU, LAYOUT_TN>(t, plan, accumulate, option, max_tiles, s);
-    case EPI_SWIGLU_BWD: return run_block_tile<T, EPI_SWIGLU_BWD, LAYOUT_B_KN>(t, plan, accumulate, option, max_tiles, s);
-    case EPI_STORE_DUALK: return run_block_tile<T, EPI_STORE_DUALK, LAYOUT_B_KN>(t, plan, accumulate, option, max_tiles, s);
+    case EPI_STORE: return run_block_tile<T, EPI_STORE, LAYOUT_TN>(t, plan, n_prob, accumulate, option, max_tiles, s);
+    case EPI_SWIGLU: return run_block_tile<T, EPI_SWIGLU, LAYOUT_TN>(t, plan, n_prob, accumulate, option, max_tiles, s);
+    case EPI_SWIGLU_BWD: return run_block_tile<T, EPI_SWIGLU_BWD, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
+    case EPI_STORE_DUALK: return run_block_tile<T, EPI_STORE_DUALK, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
     case EPI_STORE_F32:
-      if (layout == LAYOUT_B_KN) return run_block_tile<T, EPI_STORE_F32, LAYOUT_B_KN>(t, plan, accumulate, option, max_tiles, s);
-      if (layout == LAYOUT_TN) return run_block_tile<T, EPI_STORE_F32, LAYOUT_TN>(t, plan, accumulate, option, max_tiles, s);
-      return run_block_tile<T, EPI_STORE_F32, LAYOUT_AB_K>(t, plan, accumulate, option, max_tiles, s);
+      if (layout == LAYOUT_B_KN) return run_block_tile<T, EPI_STORE_F32, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
+      if (layout == LAYOUT_TN) return run_block_tile<T, EPI_STORE_F32, LAYOUT_TN>(t, plan, n_prob, accumulate, option, max_tiles, s);
+      return run_block_tile<T, EPI_STORE_F32, LAYOUT_AB_K>(t, plan, n_prob, accumulate, option, max_tiles, s);
   }
   return hipErrorInvalidValue;
 }
 }  // namespace
 
-hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int accumulate,
+hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int n_prob, int accumulate,
                                int option, int64_t max_tiles, hipStream_t s, int layout) {
-  if (dt == MODSE_F32) return launch_block<float>(epilogue, layout, t, plan, accumulate, option, max_tiles, s);
-  if (t.bm <= 128 && t.bn <= 128) return launch_block<bf16_t>(epilogue, layout, t, plan, accumulate, option, max_tiles, s);
+  if (dt == MODSE_F32) return launch_block<float>(epilogue, layout, t, plan, n_prob, accumulate, option, max_tiles, s);
+  if (t.bm <= 128 && t.bn <= 128) return launch_block<bf16_t>(epilogue, layout, t, plan, n_prob, accumulate, option, max_tiles, s);
   switch (epilogue) {
     case EPI_STORE:
-      return run_bf16<256, 256, 1, 4, 2, EPI_STORE, LAYOUT_TN>(plan, accumulate, option, max_tiles, s);
+      return run_bf16<256, 256, 1, 4, 2, EPI_STORE, LAYOUT_TN>(plan, n_prob, accumulate, option, max_tiles, s);
     case EPI_SWIGLU:
-      return run_bf16<256, 128, 2, 4, 2, EPI_SWIGLU, LAYOUT_TN>(plan, accumulate, option, max_tiles, s);
+      return run_bf16<256, 128, 2, 4, 2, EPI_SWIGLU, LAYOUT_TN>(plan, n_prob, accumulate, option, max_tiles, s);
     case EPI_SWIGLU_BWD:
-      return run_bf16<256, 256, 1, 4, 2, EPI_SWIGLU_BWD, LAYOUT_B_KN>(plan, accumulate, option, max_tiles, s);
+      return run_bf16<256, 256, 1, 4, 2, EPI_SWIGLU_BWD, LAYOUT_B_KN>(plan, n_prob, accumulate, option, max_tiles, s);
     case EPI_STORE_DUALK:
-      return run_bf16<256, 256, 1, 4, 2, EPI_STORE_DUALK, LAYOUT_B_KN>(plan, accumulate, option, max_tiles, s);
+      return run_bf16<256, 256, 1, 4, 2, EPI_STORE_DUALK, LAYOUT_B_KN>(plan, n_prob, accumulate, option, max_tiles, s);
     case EPI_STORE_F32:
-      return run_bf16<256, 256, 1, 4, 2, EPI_STORE_F32, LAYOUT_AB_K>(plan, accumulate, option, max_tiles, s);
+      return run_bf16<256, 256, 1, 4, 2, EPI_STORE_F32, LAYOUT_AB_K>(plan, n_prob, accumulate, option, max_tiles, s);
   }
   return hipErrorInvalidValue;
 }

@@ -130,7 +130,7 @@ struct ComputeCursor {
 // option: EPI_SWIGLU: the derivative terms are saved; EPI_STORE_F32: C is written with the non-temporal hint.
 // LAYOUT bit 0: A is stored [K, M] (M contiguous) instead of [M, K]; bit 1: B is stored [K, N].
 template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT = 0>
-__global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const GemmPlan* __restrict__ plan,
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const GemmPlan* __restrict__ plan, int n_prob,
                                                                         int accumulate, int option) {
   using Cfg = Bf16Tile<BM, BN, NB, WAVES_M, WAVES_N>;
   constexpr int BK = Cfg::BK, MI = Cfg::MI, NI = Cfg::NI, UPW = Cfg::UPW, PANEL = Cfg::PANEL, NSLOT = Cfg::NSLOT;
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   const bool grp_y = wave >= Cfg::NWAVES / 2;  // the second wave of each SIMD
-  const int total = __builtin_amdgcn_readfirstlane(plan->tile_start[plan->n_prob]);
+  const int total = __builtin_amdgcn_readfirstlane(plan->tile_start[n_prob]);
   const int first_tile = first_tile_of_block();
   const uint32_t lds_base = __builtin_amdgcn_readfirstlane(lds_address(ring));
   const int unit0 = wave * UPW;  // this wave loads units unit0 .. unit0 + 3 of every panel

@@ -47,7 +47,7 @@ __device__ inline int tile_of_workgroup(int b) {
 // BN: columns of C per tile.  NB = 2: two B matrices that share A (the up-projection's W1 and W3), BN columns of each.
 // KG > 1: KG groups of waves share the tile, each takes every KG-th of a step's four K slices, and the sums meet in LDS.
 template <typename T, int BM, int BN, int NB, int WAVES_M, int WAVES_N, int NSLOT, int EPI, int LAYOUT, int KG = 1>
-__device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int accumulate, int option) {
+__device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int n_prob, int accumulate, int option) {
   constexpr int ES = sizeof(T), CE = 16 / ES, BK = 128 / ES;
   constexpr bool A_T = (LAYOUT & 1) != 0, B_T = (LAYOUT & 2) != 0, F32 = ES == 4;
   constexpr int BR = NB * BN;               // B rows of a stage
@@ -71,12 +71,30 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   const int kg = wave / (WAVES_M * WAVES_N);
   const int wm = wave % (WAVES_M * WAVES_N) / WAVES_N, wn = wave % WAVES_N;
   const int tile = tile_of_workgroup(blockIdx.x);
-  // the tile's problem: the last one that starts at or before it (every lane looks at one entry of the list)
-  const int n_prob = plan->n_prob;
-  if (tile >= plan->tile_start[n_prob]) return;
-  int p = -1;
-  for (int i0 = 0; i0 < n_prob; i0 += 64)
-    p += __popcll(__ballot(i0 + lane < n_prob && plan->tile_start[min(i0 + lane, n_prob)] <= tile));
+  // The tile's problem: the last one that starts at or before it.  Every lane looks at the first tile of up to four problems
+  // and touches their entries, all in one round trip: a launch's first workgroups find the lists in no cache, and one load
+  // after the other (number of problems, their list, the tile's, its entry) took them about a microsecond more: training pass of
+  // 512 tokens, d = 256, float32 75.5 -> 72.2 us, 389 tokens, d = 2048 154 -> 151.
+  constexpr int CHUNKS = MODSE_MAX_PROBLEMS / 64;
+  const int total = plan->tile_start[n_prob];
+  int starts[CHUNKS], touch[CHUNKS];
+#pragma unroll
+  for (int j = 0; j < CHUNKS; ++j) {
+    if (j > 0 && j * 64 >= n_prob) break;
+    starts[j] = plan->tile_start[min(j * 64 + lane, n_prob)];
+    touch[j] = plan->prob[min(j * 64 + lane, n_prob - 1)].M;
+  }
+  if (tile >= total) return;
+  int p = -1, start = 0;
+#pragma unroll
+  for (int j = 0; j < CHUNKS; ++j) {
+    if (j > 0 && j * 64 >= n_prob) break;
+    asm volatile("" ::"v"(touch[j]));
+    const unsigned long long at = __ballot(j * 64 + lane < n_prob && starts[j] <= tile);
+    if (at == 0) break;
+    start = __builtin_amdgcn_readlane(starts[j], 63 - __builtin_clzll(at));
+    p += __popcll(at);
+  }
   p = uniform_int(p);
   ProblemRegs P;
   P.load(plan->prob + p);
@@ -84,7 +102,7 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   int m0, n0, first_k;  // first_k: K step that the tile's loop starts with
   {
     int mt, nt;
-    decode_local(tile - uniform_int(plan->tile_start[p]), P.mtiles(), P.ntiles(), P.magic_group(), P.magic_tail(), mt, nt);
+    decode_local(tile - uniform_int(start), P.mtiles(), P.ntiles(), P.magic_group(), P.magic_tail(), mt, nt);
     m0 = mt * BM;
     n0 = nt * BN;
     first_k = nt;
@@ -442,16 +460,16 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
 }
 
 template <int BM, int BN, int NB, int EPI, int LAYOUT>
-__global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GemmPlan* __restrict__ plan, int accumulate, int option) {
-  gg_block<float, BM, BN, NB, 2, 2, 4, EPI, LAYOUT>(plan, accumulate, option);
+__global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GemmPlan* __restrict__ plan, int n_prob, int accumulate, int option) {
+  gg_block<float, BM, BN, NB, 2, 2, 4, EPI, LAYOUT>(plan, n_prob, accumulate, option);
 }
 // Launches of few tiles.  Bound by latency: of the workgroup's start, of the loads of a K step, of the dependent matrix
 // instructions of a wave.  So the tile is small (32 x 32), its four waves take one K slice of a step each and add up through
 // LDS, and 32 to 36 KiB of ring let four workgroups of a CU wait at a time.  d = 256, 512 tokens: up-projection 14 -> 11 us,
 // dX 19 -> 11; with twice the ring and two workgroups per CU the same there, but up to 6 % slower for whole layers of more tiles.
 template <int NB, int EPI, int LAYOUT>
-__global__ __launch_bounds__(256, 4) void gg_f32_small_kernel(const GemmPlan* __restrict__ plan, int accumulate, int option) {
-  gg_block<float, 32, 32, NB, 1, 1, NB == 1 ? 8 : 6, EPI, LAYOUT, 4>(plan, accumulate, option);
+__global__ __launch_bounds__(256, 4) void gg_f32_small_kernel(const GemmPlan* __restrict__ plan, int n_prob, int accumulate, int option) {
+  gg_block<float, 32, 32, NB, 1, 1, NB == 1 ? 8 : 6, EPI, LAYOUT, 4>(plan, n_prob, accumulate, option);
 }
 // as many ring slots as leave room for eight waves per CU
 constexpr int ring_slots(int bm, int br, int waves) {
@@ -459,17 +477,15 @@ constexpr int ring_slots(int bm, int br, int waves) {
   return bm == br ? lds / (bm * 128) : lds / ((bm + br) * 128) * 2;
 }
 template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT>
-__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_block_kernel(const GemmPlan* __restrict__ plan,
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_block_kernel(const GemmPlan* __restrict__ plan, int n_prob,
                                                                                int accumulate, int option) {
-  gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, ring_slots(BM, NB * BN, WAVES_M * WAVES_N), EPI, LAYOUT>(plan, accumulate,
-                                                                                                      option);
+  gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, ring_slots(BM, NB * BN, WAVES_M * WAVES_N), EPI, LAYOUT>(plan, n_prob, accumulate, option);
 }
 // tiles of 32 or 64 rows (decode-sized batches and experts with few tokens), under a name of their own for profiles
 template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT>
-__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_skinny_kernel(const GemmPlan* __restrict__ plan,
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_skinny_kernel(const GemmPlan* __restrict__ plan, int n_prob,
                                                                                 int accumulate, int option) {
-  gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, ring_slots(BM, NB * BN, WAVES_M * WAVES_N), EPI, LAYOUT>(plan, accumulate,
-                                                                                                      option);
+  gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, ring_slots(BM, NB * BN, WAVES_M * WAVES_N), EPI, LAYOUT>(plan, n_prob, accumulate, option);
 }
 
 }  // namespace modse_gemm

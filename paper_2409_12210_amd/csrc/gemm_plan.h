@@ -45,10 +45,7 @@ __device__ inline void finish_plan(GemmPlan* plan, int lane, int n, const int* s
     if (lane * PER + i < n) plan->tile_start[lane * PER + i] = run;
     run += v[i];
   }
-  if (lane == 0) {
-    plan->tile_start[n] = total;
-    plan->n_prob = n;
-  }
+  if (lane == 0) plan->tile_start[n] = total;
 }
 
 // What the planning block keeps in LDS.  It is the tail of a launch whose other blocks are long done (or the body of an
