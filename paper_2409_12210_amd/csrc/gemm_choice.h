@@ -142,7 +142,10 @@ inline GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue) 
     // 32 x 32 tiles, four to a CU, whose four waves share out the K slices.  Sum of the four products, 64 -> 32: d = 256, 512
     // tokens (80 tiles) 62 -> 46 us, 2048 tokens (272 tiles) 84 -> 78; d = 512, 256 tokens 99 -> 68, 1024 tokens (280) 138 ->
     // 114; from 400 tiles on about even (d = 384, 700 tokens, up-projection of 440 tiles 36 -> 42).
-    const bool few = epilogue != EPI_STORE_F32 && c.kchunk == 0 && 2 * gemm_work(L, epilogue, t64).tiles < 3 * GEMM_CUS;
+    // K loops of at most 64 columns have nothing to share out and keep the 64 x 64 tiles (d and eight widths of 64, 256 tokens:
+    // 53 us a training pass with either, which is what its launches take).
+    const Work w = gemm_work(L, epilogue, t64);
+    const bool few = epilogue != EPI_STORE_F32 && c.kchunk == 0 && 2 * w.tiles < 3 * GEMM_CUS && w.longest >= 2;
     return few ? GemmChoice{TileShape{32, 32}, 0} : c;
   }
   // The products with d columns: 32-row tiles for decode-sized batches (20 KiB a K step, four of them in flight), 64-row

@@ -20,8 +20,8 @@ CASES = [
     ("f32_wide", 992, (992, 1120) * 8, 200, "f32", 2),
     ("f32_tiles_64", 160, (32, 96, 224, 160), 259, "f32", 2),       # one row past two tiles
     ("f32_one_row", 64, (32, 96), 1, "f32", 1),
-    # 32 x 32 tiles whose waves share out K: one step; loops longer than the ring, row remainders of 1 and 31
-    ("f32_tiles_32_one_step", 32, (32, 64, 32), 95, "f32", 2),
+    # 32 x 32 tiles whose waves share out K: loops as long as the ring and longer, row remainders of 1 and 31
+    ("f32_tiles_32_four_steps", 128, (32, 128, 64), 95, "f32", 2),
     ("f32_tiles_32_long_loops", 416, (672, 32, 352, 544), 130, "f32", 2),
     ("f32_split", 160, (4128, 2048, 1952, 672), 97, "f32", 2),
     # bf16, the products with d columns: K split into chunks (widths of 1 to 7 chunks, the last ones ragged) over 32-row
