@@ -207,7 +207,9 @@ int64_t split_tiles_bound(const LayerDims& L, const TileShape& t, int kchunk, in
   }
   return s;
 }
-// problems of such a product: the chunks of all experts
+// the launch option that goes with such tiles
+int spread(const LayerDims& L, modse_dtype dt, const TileShape& t) { return modse_gemm::spread_k(L, dt, t) ? GEMM_SPREAD_K : 0; }
+// problems of a split product: the chunks of all experts
 int split_problems(const LayerDims& L, int kchunk, int passes) {
   int n = 0;
   for (int e = 0; e < L.N; ++e) n += passes * ((L.f[e] + kchunk - 1) / kchunk);
@@ -461,17 +463,20 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   HIP_TRY(launch_permute(L, dt, x, R, RB, Xp, ext ? &G : nullptr, &pa, s));
   stamp.mark(MODSE_STAGE_PERMUTE);
 
-  HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU, pa.up_tile, pa.up, L.N, 0, saved != nullptr, tiles_bound(L, pa.up_tile, true), s));
+  HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU, pa.up_tile, pa.up, L.N, 0, (saved ? GEMM_SAVE_TERMS : 0) | spread(L, dt, pa.up_tile),
+                              tiles_bound(L, pa.up_tile, true), s));
   stamp.mark(MODSE_STAGE_UP);
   if (kchunk) {
     const int64_t bound = split_tiles_bound(L, pa.down_tile, kchunk, 1);
-    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.down_tile, pa.down, split_problems(L, kchunk, 1), 0, 0, bound, s, LAYOUT_TN));
+    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.down_tile, pa.down, split_problems(L, kchunk, 1), 0,
+                                spread(L, dt, pa.down_tile), bound, s, LAYOUT_TN));
     stamp.mark(MODSE_STAGE_DOWN);
     HIP_TRY(launch_combine_split(L, dt, pa.Opart, kchunk, R, saved ? pa.O : nullptr, y, s));
     stamp.mark(MODSE_STAGE_COMBINE);
     return MODSE_OK;
   }
-  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE, pa.down_tile, pa.down, L.N, 0, 0, tiles_bound(L, pa.down_tile, false), s));
+  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE, pa.down_tile, pa.down, L.N, 0, spread(L, dt, pa.down_tile),
+                              tiles_bound(L, pa.down_tile, false), s));
   stamp.mark(MODSE_STAGE_DOWN);
   HIP_TRY(launch_combine(L, dt, pa.O, R, y, s));
   stamp.mark(MODSE_STAGE_COMBINE);
@@ -537,12 +542,14 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   HIP_TRY(launch_bwd_prep(L, dt, dY, sb + sl.O, R, dO, dg, pa, ext ? &G : nullptr, aux_grad, W_gate, rb, s));
   stamp.mark(MODSE_STAGE_BWD_PREP);
 
-  HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU_BWD, pa.dh_tile, pa.dh, L.N, 0, 0, tiles_bound(L, pa.dh_tile, true), s));
+  HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU_BWD, pa.dh_tile, pa.dh, L.N, 0, spread(L, dt, pa.dh_tile),
+                              tiles_bound(L, pa.dh_tile, true), s));
   if (pa.dx_kchunk) {
-    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.dx_tile, pa.dx, split_problems(L, pa.dx_kchunk, 2), 0, 0,
-                                split_tiles_bound(L, pa.dx_tile, pa.dx_kchunk, 2), s, LAYOUT_B_KN));
+    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.dx_tile, pa.dx, split_problems(L, pa.dx_kchunk, 2), 0,
+                                spread(L, dt, pa.dx_tile), split_tiles_bound(L, pa.dx_tile, pa.dx_kchunk, 2), s, LAYOUT_B_KN));
   } else {
-    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, L.N, 0, 0, tiles_bound(L, pa.dx_tile, false), s));
+    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, L.N, 0, spread(L, dt, pa.dx_tile),
+                                tiles_bound(L, pa.dx_tile, false), s));
   }
   stamp.mark(MODSE_STAGE_BWD_DGRAD);
 
@@ -551,7 +558,8 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   // with the non-temporal hint.  1.1 GB of gradients: this launch takes as long, but the router's backward pass behind it 26
   // us in place of 40, a training pass of 1021 tokens 856 in place of 888.
   const bool stream = 3 * (size_t)L.foff[L.N] * L.d * sizeof(float) > ((size_t)128 << 20);
-  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, 3 * L.N, accumulate, stream, wgrad_tiles(L, pa.wg_tile), s));
+  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, 3 * L.N, accumulate, stream ? GEMM_STREAM_C : 0,
+                              wgrad_tiles(L, pa.wg_tile), s));
   stamp.mark(MODSE_STAGE_BWD_WGRAD);
 
   const DxRows rows = {pa.dXp, pa.dXpart, pa.dx_kchunk};

@@ -187,8 +187,13 @@ hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, 
 struct TileShape {
   int32_t bm, bn;
 };
-// t: the tile shape that the plan was made with.  max_tiles: upper bound of the number of tiles.  layout < 0: the
-// layout that goes with the epilogue (see gemm.hip).
+enum GemmOption {
+  GEMM_SAVE_TERMS = 1,  // EPI_SWIGLU: the derivatives of h are stored too
+  GEMM_STREAM_C = 2,    // EPI_STORE_F32: C goes past the caches
+  GEMM_SPREAD_K = 4,    // small bf16 tiles: K loops start at different places (see gemm_block.h)
+};
+// t: the tile shape that the plan was made with.  option: of GemmOption.  max_tiles: upper bound of the number of tiles.
+// layout < 0: the layout that goes with the epilogue (see gemm.hip).
 hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int n_prob, int accumulate,
                                int option, int64_t max_tiles, hipStream_t s, int layout = -1);
 

@@ -127,7 +127,7 @@ struct ComputeCursor {
   int M, N, ldc, nsteps;
 };
 
-// option: EPI_SWIGLU: the derivative terms are saved; EPI_STORE_F32: C is written with the non-temporal hint.
+// option: of GemmOption
 // LAYOUT bit 0: A is stored [K, M] (M contiguous) instead of [M, K]; bit 1: B is stored [K, N].
 template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT = 0>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const GemmPlan* __restrict__ plan, int n_prob,
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
           for (int b = 0; b < MI * NI; ++b)
             if (inside(b))
 #pragma unroll
-              for (int it = 0; it < 4; ++it) global_store16_s(row_group(b, it), voff, f32x4{0.f, 0.f, 0.f, 0.f}, option != 0);
+              for (int it = 0; it < 4; ++it) global_store16_s(row_group(b, it), voff, f32x4{0.f, 0.f, 0.f, 0.f}, (option & GEMM_STREAM_C) != 0);
       } else {
         // (the late waves have already refilled their units of the A panel's slot: they have one slot, and
         // write a block into it only after the block before has been read back)
@@ -608,7 +608,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
                 v += old[it];
                 if (b + 1 < MI * NI) fetch(b + 1, it);
               }
-              if (in) global_store16_s(row_group(b, it), voff, v, option != 0);
+              if (in) global_store16_s(row_group(b, it), voff, v, (option & GEMM_STREAM_C) != 0);
             }
           }
         };
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
             }
           }
         };
-        if (option) swiglu_tile(std::true_type{});
+        if (option & GEMM_SAVE_TERMS) swiglu_tile(std::true_type{});
         else swiglu_tile(std::false_type{});
       } else if constexpr (EPI == EPI_SWIGLU_BWD) {
         {

@@ -99,27 +99,19 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   ProblemRegs P;
   P.load(plan->prob + p);
   const int M = P.M(), N = P.N(), K = P.K();
-  int m0, n0, first_k;  // first_k: K step that the tile's loop starts with
-  {
-    int mt, nt;
-    decode_local(tile - uniform_int(start), P.mtiles(), P.ntiles(), P.magic_group(), P.magic_tail(), mt, nt);
-    m0 = mt * BM;
-    n0 = nt * BN;
-    first_k = nt;
-  }
+  int mt, nt;
+  decode_local(tile - uniform_int(start), P.mtiles(), P.ntiles(), P.magic_group(), P.magic_tail(), mt, nt);
+  const int m0 = mt * BM, n0 = nt * BN;
   const int nk = (K + BK - 1) / BK;
-  // Weights that meet a single row block are read once in the whole launch, and their stream is what bounds it.  Their rows
-  // usually lie a power of two apart, so what the workgroups of a launch read at the same K step shares the low bits of its
-  // address, and few memory channels serve it: a bare loader of these tiles reaches 5.3 TB/s, and 6.3 when the workgroups
-  // start their K loops at different places.  So they do, at 32 of them: 64 tokens at d = 4096 493 -> 470 us for the layer, 389
-  // tokens at d = 2048 169 -> 155.  Row blocks that share weights have to read them at the same time, and the column
-  // tiles of an XCD the same part of the rows, which then stay in its L2: there every XCD starts at a place of its own (5003
-  // tokens, 64 experts 266 -> 260 us, two micro-batches of 1021 tokens 1957 -> 1937; by column tile 3 % slower than by none).
-  const bool stream_b = !A_T && P.mtiles() == 1;
+  const bool stream_b = !A_T && P.mtiles() == 1;  // weights that meet a single row block are read once in the whole launch
+  // Where most problems have one row block, the weight stream is what bounds the launch.  Their rows usually lie a power of
+  // two apart, so what the workgroups of a launch read at the same K step shares the low bits of its address, and few memory
+  // channels serve it: a bare loader of these tiles reaches 5.3 TB/s, and 6.3 when the workgroups start their K loops at
+  // different places.  So they do (GEMM_SPREAD_K), at 32 of them: 64 tokens at d = 4096 493 -> 470 us for the layer, 389 tokens
+  // at d = 2048 169 -> 155.  The place goes by problem and column alone, and the launch by the batch's size: a row's result
+  // then depends neither on the other rows nor on its place among them.
   constexpr bool ROTATE = !F32 && !A_T;
-  if constexpr (ROTATE)
-    first_k = stream_b ? (nk * ((first_k * 5 + p) & 31)) >> 5 : (nk * (int)(blockIdx.x % NUM_XCD)) / NUM_XCD;
-  else first_k = 0;
+  const int first_k = ROTATE && (option & GEMM_SPREAD_K) ? (nk * ((nt * 5 + p) & 31)) >> 5 : 0;  // K step to start with
   const int nsteps = (EPI == EPI_STORE_DUALK) ? 2 * nk : nk;
   const uint32_t lds_base = __builtin_amdgcn_readfirstlane(lds_address(ring));
 
@@ -370,7 +362,7 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   };
   auto at = [&](const void* base, long o) { return (global_chunk_t*)(uintptr_t)(static_cast<const out_t*>(base) + o); };
   auto put = [&](void* C, long o, chunk_t v) {
-    if (A_T && option) __builtin_nontemporal_store(v, at(C, o));
+    if (A_T && (option & GEMM_STREAM_C)) __builtin_nontemporal_store(v, at(C, o));
     else *at(C, o) = v;
   };
   auto store_unit = [&](int i, int ju, void* C) {
@@ -397,7 +389,7 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
           return h;
         });
         store_unit(i, ju, P.C());
-        if (option) {
+        if (option & GEMM_SAVE_TERMS) {
           stage([&](int jj, int x) { return acc[0][i][j0 + jj][x]; });
           store_unit(i, ju, P.C2());
           stage([&](int jj, int x) { return acc[NB - 1][i][j0 + jj][x]; });
