@@ -145,14 +145,17 @@ inline GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue) 
     const double slots = 2 * GEMM_CUS, rounds = gemm_work(L, epilogue, t).tiles / slots;
     const double small = gemm_work(L, epilogue, t64).tiles / (swiglu ? 2 : 4) / slots;  // in units of a large tile's work
     const GemmChoice c = with_chunk(rounds >= 1 && rounds + 0.3 <= 1.07 * small + 0.15 ? t : t64);
-    // Fewer than one and a half 64 x 64 tiles per CU leave matrix pipes idle and each K loop's chain of latencies exposed:
-    // 32 x 32 tiles, four to a CU, whose four waves share out the K slices.  Sum of the four products, 64 -> 32: d = 256, 512
-    // tokens (80 tiles) 62 -> 46 us, 2048 tokens (272 tiles) 84 -> 78; d = 512, 256 tokens 99 -> 68, 1024 tokens (280) 138 ->
-    // 114; from 400 tiles on about even (d = 384, 700 tokens, up-projection of 440 tiles 36 -> 42).
-    // K loops of at most 64 columns have nothing to share out and keep the 64 x 64 tiles (d and eight widths of 64, 256 tokens:
-    // 53 us a training pass with either, which is what its launches take).
-    const Work w = gemm_work(L, epilogue, t64);
-    const bool few = epilogue != EPI_STORE_F32 && c.kchunk == 0 && 2 * w.tiles < 3 * GEMM_CUS && w.longest >= 2;
+    // Fewer than one and a half 64 x 64 tiles per CU leave matrix pipes idle and each K loop's chain of latencies exposed: 32 x
+    // 32 tiles, four to a CU, whose four waves share out the K slices, unless the 64 x 64 ones fill the CUs once (or twice) and
+    // the others mean a further part of a round.  Estimates in K steps of a 64 x 64 tile alone on its CU (two of them take
+    // 1.7), fitted to four products each of 100 layers, d = 32 ... 2528.  Sum of the four products in us, 64 -> 32: eight
+    // experts, d = d_ff = 256, 512 tokens (80 tiles) 48 -> 36, 1500 tokens (204) 49 -> 57, 2048 tokens (272) 73 -> 70; d = d_ff =
+    // 1024, 100 tokens (128) 129 -> 92, 384 tokens (256) 132 -> 157, 500 tokens (320) 226 -> 196.
+    // K loops of at most 64 columns keep the 64 x 64 tiles.
+    const Work w = gemm_work(L, epilogue, t64), w32 = gemm_work(L, epilogue, TileShape{32, 32});
+    const double large = std::max(w.longest, w.tiles > GEMM_CUS ? 1.7 * w.steps / w.tiles : 0.0);
+    const bool few = epilogue != EPI_STORE_F32 && c.kchunk == 0 && 2 * w.tiles < 3 * GEMM_CUS && w.longest >= 2 &&
+                     0.35 * w.longest + 0.25 * w32.steps / GEMM_CUS < large;
     return few ? GemmChoice{TileShape{32, 32}, 0} : c;
   }
   // The products with d columns: 32-row tiles for decode-sized batches (20 KiB a K step, four of them in flight), 64-row

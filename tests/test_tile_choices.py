@@ -19,6 +19,25 @@ def test_case_takes_the_tiles_it_is_there_for(case):
         assert (c.bm, c.kchunk > 0) == (bm, split), (gemm, c)
 
 
+# d, width of the experts, their number, T, {GEMM: rows of its tiles}: the faster of the tiles where both were measured
+F32_FASTER = [
+    (256, 256, 8, 512, dict.fromkeys(("up", "down", "dh", "dx"), 32)),
+    (256, 256, 8, 1500, dict.fromkeys(("up", "down", "dh", "dx"), 64)),
+    (256, 256, 8, 2048, {"up": 32, "dx": 32}),
+    (1024, 1024, 8, 100, dict.fromkeys(("up", "down", "dh", "dx"), 32)),
+    (1024, 1024, 8, 384, dict.fromkeys(("up", "down", "dh", "dx"), 64)),
+    (1024, 1024, 8, 500, dict.fromkeys(("up", "down", "dh", "dx"), 32)),
+    (2048, 256, 8, 300, {"up": 32, "dh": 32}),
+    (2048, 1280, 4, 200, {"dx": 64}),
+]
+
+
+@pytest.mark.parametrize("case", F32_FASTER, ids=["d%d_f%d_n%d_t%d" % c[:4] for c in F32_FASTER])
+def test_f32_layers_of_few_tiles_take_the_faster_ones(case):
+    d, f, n, T, takes = case
+    assert {g: choice(g, d, [f] * n, 2, T, "f32").bm for g in takes} == takes
+
+
 def meets_the_edges(gemm, d, d_ff, k, T, dtype, c):
     step = 32 if dtype == "f32" else 64
     if gemm == "wgrad":  # contracts over an expert's rows; its matrices are d_ff x d and d x d_ff
