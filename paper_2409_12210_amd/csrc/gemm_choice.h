@@ -150,11 +150,11 @@ inline GemmChoice gemm_choice(const LayerDims& L, modse_dtype dt, int epilogue) 
     // the others mean a further part of a round.  Estimates in K steps of a 64 x 64 tile alone on its CU (two of them take
     // 1.7), fitted to four products each of 100 layers, d = 32 ... 2528.  Sum of the four products in us, 64 -> 32: eight
     // experts, d = d_ff = 256, 512 tokens (80 tiles) 48 -> 36, 1500 tokens (204) 49 -> 57, 2048 tokens (272) 73 -> 70; d = d_ff =
-    // 1024, 100 tokens (128) 129 -> 92, 384 tokens (256) 132 -> 157, 500 tokens (320) 226 -> 196.
-    // K loops of at most 64 columns keep the 64 x 64 tiles.
+    // 1024, 100 tokens (128) 129 -> 92, 384 tokens (256) 132 -> 157, 500 tokens (320) 226 -> 196.  One K step is enough
+    // to share out: d = d_ff = 32, 256 tokens 16.1 -> 14.8, d = d_ff = 64 20.2 -> 18.2.
     const Work w = gemm_work(L, epilogue, t64), w32 = gemm_work(L, epilogue, TileShape{32, 32});
     const double large = std::max(w.longest, w.tiles > GEMM_CUS ? 1.7 * w.steps / w.tiles : 0.0);
-    const bool few = epilogue != EPI_STORE_F32 && c.kchunk == 0 && 2 * w.tiles < 3 * GEMM_CUS && w.longest >= 2 &&
+    const bool few = epilogue != EPI_STORE_F32 && c.kchunk == 0 && 2 * w.tiles < 3 * GEMM_CUS &&
                      0.35 * w.longest + 0.25 * w32.steps / GEMM_CUS < large;
     return few ? GemmChoice{TileShape{32, 32}, 0} : c;
   }

@@ -3,6 +3,7 @@ import pytest
 import torch
 
 import paper_2409_12210_amd as m
+from choice_probe import choice
 
 pytestmark = pytest.mark.gpu
 
@@ -33,9 +34,12 @@ def test_means_are_rounded_once(T, N):
 
 
 def test_dgamma_of_many_equal_tokens():
-    """2^20 copies of one token: their shares of dgamma are equal, and the 64 that a wave adds up make a sum without rounding,
-    so that dgamma is 2^14 times what 64 copies give.  Four float32 partial sums are rounded and added: 3 * 2^-24 = 1.8e-7."""
+    """2^20 copies of one token: their shares of dgamma are equal, and the 64 that a wave adds up make a sum without rounding.
+    2^14 copies give four float64 sums of 64 such sums each, all of them exact, so that dgamma of 2^20 copies is 64 times theirs.
+    Four float32 partial sums are rounded and added: 3 * 2^-24 = 1.8e-7.  (A share's own last bit goes by the order of the
+    GEMMs' sums, which a tile shape may change: both batches take the same ones.)"""
     d, d_ff = 32, [32, 32]
+    assert len({tuple(choice(g, d, d_ff, 2, T, "f32").bm == 32 for g in ("up", "down", "dh", "dx")) for T in (1 << 14, 1 << 20)}) == 1
     gen = torch.Generator(device="cuda").manual_seed(3)
 
     def normal(*shape, sigma=1.0):
@@ -44,7 +48,7 @@ def test_dgamma_of_many_equal_tokens():
     x1, dy1, Wg, Wn = normal(1, d), normal(1, d), normal(d, 2), normal(d, 2)
     W1, W3, W2 = normal(64, d), normal(64, d), normal(64 * d)
     got = []
-    for T in (64, 1 << 20):
+    for T in (1 << 14, 1 << 20):
         layer = (d, d_ff, 2, "f32", T)
         x, dY, y, dX = x1.repeat(T, 1), dy1.repeat(T, 1), torch.empty((T, d), device="cuda"), torch.empty((T, d), device="cuda")
         ext = m.GateExt(W_noise=Wn, gamma=torch.ones(1, device="cuda"), eps=1e-6, noise_pre=torch.empty((T, 2), device="cuda"))

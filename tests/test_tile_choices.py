@@ -21,6 +21,8 @@ def test_case_takes_the_tiles_it_is_there_for(case):
 
 # d, width of the experts, their number, T, {GEMM: rows of its tiles}: the faster of the tiles where both were measured
 F32_FASTER = [
+    (32, 32, 8, 256, dict.fromkeys(("up", "down", "dh", "dx"), 32)),
+    (64, 64, 8, 256, dict.fromkeys(("up", "down", "dh", "dx"), 32)),
     (256, 256, 8, 512, dict.fromkeys(("up", "down", "dh", "dx"), 32)),
     (256, 256, 8, 1500, dict.fromkeys(("up", "down", "dh", "dx"), 64)),
     (256, 256, 8, 2048, {"up": 32, "dx": 32}),
