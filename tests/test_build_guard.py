@@ -55,7 +55,8 @@ def test_every_built_kernel_is_within_the_register_budget():
               "pad_rows_kernel", "permute_small_kernel", "permute_fused_kernel", "route_scan_kernel", "scatter_kernel",
               "combine_kernel", "combine_split_kernel", "bwd_prep_plan_bwd_kernel", "gate_bwd_kernel", "bwd_gate_rows_kernel",
               "bwd_gate_rows_ext_kernel", "sum_slabs_kernel", "bwd_dwg_kernel", "dwg_reduce_kernel", "aux_finish_kernel",
-              "routing_stats_kernel", "gg_bf16_kernel", "gg_bf16_block_kernel", "gg_bf16_skinny_kernel", "gg_f32_kernel"):
+              "routing_stats_kernel", "gg_bf16_kernel", "gg_bf16_block_kernel", "gg_bf16_skinny_kernel", "gg_f32_kernel",
+              "gg_f32_small_kernel"):
         assert "%d%s" % (len(k), k) in names, k              # (a mangled name has the length in front: no part of a longer one)
     for name, vgprs, agprs, scratch, spill, occupancy, lds in rows:
         assert int(scratch) == 0 and int(spill) == 0 and int(agprs) == 0, name

@@ -18,11 +18,14 @@ CASES = [
     # rounds of 128-row tiles that fit: the forward and data-gradient products; the weight gradients
     ("f32_tall", 736, (864, 992, 736, 992), 30001, "f32", 1),
     ("f32_wide", 992, (992, 1120) * 8, 200, "f32", 2),
-    ("f32_tiles_64", 160, (32, 96, 224, 160), 259, "f32", 2),       # one row past two tiles
+    ("f32_tiles_64_last_rows", 544, WIDE, 1324, "f32", 2),
+    ("f32_narrow", 160, (32, 96, 224, 160), 259, "f32", 2),
     ("f32_one_row", 64, (32, 96), 1, "f32", 1),
-    # 32 x 32 tiles whose waves share out K: loops as long as the ring and longer, row remainders of 1 and 31
+    # 32 x 32 tiles whose waves share out K: loops as long as the ring and longer
     ("f32_tiles_32_four_steps", 128, (32, 128, 64), 95, "f32", 2),
+    ("f32_tiles_32_four_steps_last_rows", 128, (32, 128, 64), 191, "f32", 2),
     ("f32_tiles_32_long_loops", 416, (672, 32, 352, 544), 130, "f32", 2),
+    ("f32_tiles_32_long_loops_last_rows", 416, (672, 32, 352, 544), 120, "f32", 2),
     ("f32_split", 160, (4128, 2048, 1952, 672), 97, "f32", 2),
     # bf16, the products with d columns: K split into chunks (widths of 1 to 7 chunks, the last ones ragged) over 32-row
     # tiles (one row), 64-row tiles (32 and 48 mean rows per expert) and 128-row ones (125); 128- and 32-row tiles, unsplit
@@ -37,6 +40,13 @@ CASES = [
     ("bf16_one_block_33_steps", 2080, (2144, 96, 2080, 1184), 60, "bf16", 2),
     ("bf16_one_block_17_steps", 1056, (1056, 1120, 992, 1184) * 8, 300, "bf16", 2),
 ]
+# cases that are there for the last row block of an expert: rows of the tiles of all four products; rows that it has, each at
+# one expert at least
+LAST_ROWS = {
+    "f32_tiles_64_last_rows": (64, {1, 55}),
+    "f32_tiles_32_four_steps_last_rows": (32, {1, 30, 31}),
+    "f32_tiles_32_long_loops_last_rows": (32, {1, 18, 30, 31}),
+}
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
@@ -47,7 +57,11 @@ def test_fwd_and_grads(case):
     r = _runner(inp, need_bwd=True)
     r.fwd()
     r.bwd()
-    idx, _ = check_routing(inp, r.routing_host())
+    got = r.routing_host()
+    idx, _ = check_routing(inp, got)
+    if name in LAST_ROWS:
+        bm, rows = LAST_ROWS[name]
+        assert rows <= {int(c) % bm for c in got["counts"]}
     y_ref = orc.layer_fwd(inp.x, inp.W_gate, inp.W1, inp.W3, inp.W2, d_ff, k, topk_idx=idx)
     assert max_rel(to_host(r.y), y_ref) <= TOL[dtype]
     g = check_grads(r, inp, idx, TOL[dtype])

@@ -16,6 +16,9 @@ CASES = [
     # expert 2 gets no token, expert 5 fewer than one K step of the weight gradients
     ("wgrad_up_256", 416, (1312, 1056, 1248, 1056, 1184, 1120, 1120, 1312), 3392, "bf16", 1, (0, 0, -100, 0, 0, -0.6, 0, 0),
      {"wgrad": BIG, "up": BIG}),
+    # more than 128 MB of weight gradients, which go past the caches; expert 2 gets no token
+    ("wgrad_256_streamed", 1056, (1312, 1440, 1376, 1344, 1312, 1440, 1344, 1376), 4001, "bf16", 1, (0, 0, -100, 0, 0, 0, 0, 0),
+     {"wgrad": BIG}),
     ("up_down_dx_256", 672, (288, 288), 6995, "bf16", 2, None, {"up": BIG, "down": BIG, "dx": BIG}),
     ("dh_dx_256", 416, (224, 160, 288, 288, 160, 288), 14009, "bf16", 2, None, {"dh": BIG, "dx": BIG}),
     ("up_dh_128", 352, (672, 544, 480), 2005, "bf16", 2, None, {"up": MID, "dh": MID}),
@@ -44,8 +47,8 @@ def test_parity(case):
     y_ref = orc.layer_fwd(inp.x, inp.W_gate, inp.W1, inp.W3, inp.W2, d_ff, k, bias, topk_idx=idx)
     assert max_rel(to_host(r.y), y_ref) <= TOL[dtype]
     check_grads(r, inp, idx, TOL[dtype])
-    if name == "wgrad_up_256":
-        assert got["counts"][2] == 0 and 0 < got["counts"][5] < 64
+    if name.startswith("wgrad") and dtype == "bf16":
+        assert got["counts"][2] == 0 and (name != "wgrad_up_256" or 0 < got["counts"][5] < 64)
         assert float(r.dW1[sum(d_ff[:2]):sum(d_ff[:3])].abs().max()) == 0.0
     if name == "down_32_crowded":
         assert got["counts"][0] > 96

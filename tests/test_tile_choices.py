@@ -17,6 +17,14 @@ def test_case_takes_the_tiles_it_is_there_for(case):
     for gemm, (bm, split) in takes.items():
         c = choice(gemm, d, d_ff, k, T, dtype)
         assert (c.bm, c.kchunk > 0) == (bm, split), (gemm, c)
+    if name == "wgrad_256_streamed":
+        assert 12 * d * sum(d_ff) > 128 << 20
+
+
+@pytest.mark.parametrize("name", block.LAST_ROWS)
+def test_last_rows_case_takes_its_tiles(name):
+    _, d, d_ff, T, dtype, k = next(c for c in block.CASES if c[0] == name)
+    assert {choice(g, d, d_ff, k, T, dtype).bm for g in ("up", "down", "dh", "dx")} == {block.LAST_ROWS[name][0]}
 
 
 # d, width of the experts, their number, T, {GEMM: rows of its tiles}: the faster of the tiles where both were measured
@@ -71,5 +79,5 @@ def test_every_tile_has_a_parity_case():
         for gemm in GEMMS:
             c = choice(gemm, d, d_ff, k, T, dtype)
             taken[dtype, gemm, c.bm, c.kchunk > 0] = (d, d_ff, T, k)
-    assert len(taken) >= 29
+    assert len(taken) >= 36
     assert set(taken) <= met, {t: taken[t] for t in set(taken) - met}
