@@ -555,8 +555,10 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
 
   // Gradients of more than half the memory-side cache (256 MB) would be gone from it before anybody reads them, and with
   // them what the launches around this one leave for each other (partial sums of dX, activations, weights): they are stored
-  // with the non-temporal hint.  1.1 GB of gradients: this launch takes as long, but the router's backward pass behind it 26
-  // us in place of 40, a training pass of 1021 tokens 856 in place of 888.
+  // with the non-temporal hint, and old ones that are added to are read with it.  1.1 GB of gradients: this launch takes as
+  // long, but the router's backward pass behind it 26 us in place of 40, a training pass of 1021 tokens 856 in place of 888, and
+  // reading with the hint takes a step of two such passes from 1882 to 1849.  Smaller gradients are still in the cache when the
+  // next micro-batch adds to them; the hint changes nothing there (two passes with 48 MB 595 us with it, 597 without).
   const bool stream = 3 * (size_t)L.foff[L.N] * L.d * sizeof(float) > ((size_t)128 << 20);
   HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, 3 * L.N, accumulate, stream ? GEMM_STREAM_C : 0,
                               wgrad_tiles(L, pa.wg_tile), s));

@@ -552,13 +552,14 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
       const char* const wave_c = cc.C + ((size_t)(cc.w.m0 + wm * WM) * cld + cc.w.n0 + wn * WN) * 4;
       auto inside = [&](int b) { return (b / NI) * 32 < mleft && (b % NI) * 32 < nleft; };
       auto row_group = [&](int b, int it) { return wave_c + ((long)((b / NI) * 32 + it * 8) * cld + (b % NI) * 32) * 4; };
+      const bool stream_c = (option & GEMM_STREAM_C) != 0;
       if (cc.nsteps == 0) {  // an expert without tokens: the ring holds nothing of this tile
         if (!accumulate)
 #pragma unroll
           for (int b = 0; b < MI * NI; ++b)
             if (inside(b))
 #pragma unroll
-              for (int it = 0; it < 4; ++it) global_store16_s(row_group(b, it), voff, f32x4{0.f, 0.f, 0.f, 0.f}, (option & GEMM_STREAM_C) != 0);
+              for (int it = 0; it < 4; ++it) global_store16_s(row_group(b, it), voff, f32x4{0.f, 0.f, 0.f, 0.f}, stream_c);
       } else {
         // (the late waves have already refilled their units of the A panel's slot: they have one slot, and
         // write a block into it only after the block before has been read back)
@@ -576,13 +577,14 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
             for (int q = 0; q < 4; ++q) c[r * 4 + q] = 0.f;
           }
         };
-        auto tile = [&](auto add_tag) {
-          constexpr bool ADD = decltype(add_tag)::value;
+        // STREAM: of the old values (a template, not a branch: loads in flight must not meet at a join)
+        auto tile = [&](auto add_tag, auto stream_tag) {
+          constexpr bool ADD = decltype(add_tag)::value, STREAM = decltype(stream_tag)::value;
           f32x4 old[4];
           // (never masked, see the dH epilogue below: outside the matrix its last rows and columns are read instead)
           auto fetch = [&](int b, int it) {
             const int m = min((b / NI) * 32, mleft - 32), n = min((b % NI) * 32, nleft - 32);
-            old[it] = global_load16_f32_s(wave_c + ((long)(m + it * 8) * cld + n) * 4, voff);
+            old[it] = global_load16_f32_s<STREAM>(wave_c + ((long)(m + it * 8) * cld + n) * 4, voff);
           };
           if constexpr (ADD) {
 #pragma unroll
@@ -608,12 +610,13 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
                 v += old[it];
                 if (b + 1 < MI * NI) fetch(b + 1, it);
               }
-              if (in) global_store16_s(row_group(b, it), voff, v, (option & GEMM_STREAM_C) != 0);
+              if (in) global_store16_s(row_group(b, it), voff, v, stream_c);
             }
           }
         };
-        if (accumulate) tile(std::true_type{});
-        else tile(std::false_type{});
+        if (accumulate && stream_c) tile(std::true_type{}, std::true_type{});
+        else if (accumulate) tile(std::true_type{}, std::false_type{});
+        else tile(std::false_type{}, std::false_type{});
       }
     } else {
       // 16-bit outputs go through LDS so that global memory sees whole 128-byte lines: the wave works in

@@ -365,6 +365,9 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
     if (A_T && (option & GEMM_STREAM_C)) __builtin_nontemporal_store(v, at(C, o));
     else *at(C, o) = v;
   };
+  auto get = [&](const void* C, long o) -> chunk_t {  // old values of C that are added to
+    return option & GEMM_STREAM_C ? __builtin_nontemporal_load(at(C, o)) : *at(C, o);
+  };
   auto store_unit = [&](int i, int ju, void* C) {
 #pragma unroll
     for (int it = 0; it < ITS; ++it) {
@@ -434,7 +437,7 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
 #pragma unroll
             for (int it = 0; it < ITS; ++it) {
               const long o = offset(i, ju, it);
-              old[it] = o >= 0 ? *at(P.C(), o) : chunk_t{};
+              old[it] = o >= 0 ? get(P.C(), o) : chunk_t{};
             }
 #pragma unroll
             for (int it = 0; it < ITS; ++it) {
