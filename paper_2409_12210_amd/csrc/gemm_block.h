@@ -29,7 +29,7 @@
 //
 // float32 is bound by the matrix pipe (157 TFLOP/s; a library product of 8192^3 reaches 153).  Measured in place of
 // vector-FMA tiles of 64 x 64 x 16: the five GEMMs of a training step at d = 1024, 4096 tokens, 8 experts of mean width
-// 2816 take 3.9 ms instead of 7.0 (60 -> 109 TFLOP/s); at d = 256, 512 tokens 48 us instead of 174.
+// 2816 take 3.9 ms instead of 7.0 (60 -> 109 TFLOP/s); at d = 256, 512 tokens 46 us instead of 174.
 #pragma once
 #include "gemm_bf16.h"
 
