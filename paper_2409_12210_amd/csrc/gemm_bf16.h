@@ -1,4 +1,4 @@
-// bf16 grouped GEMM for gfx950: MFMA 32x32x16, fp32 accumulate, direct global->LDS loads, ping-pong waves
+// bf16 grouped GEMM for gfx950: MFMA 16x16x32, fp32 accumulate, direct global->LDS loads, ping-pong waves
 // over a ring of five LDS panels.
 //
 // One persistent workgroup of 8 waves (WAVES_M x WAVES_N, two per SIMD) walks the tile list.  A tile is
@@ -13,9 +13,9 @@
 //
 // Ping-pong: the two waves of a SIMD (wave w and w + 4) run one phase apart.  Every step has four phases
 // separated by workgroup barriers.  In a memory phase a wave only reads the MFMA fragments of one K half
-// from LDS (12 ds_read_b128); in a compute phase it issues the 16 MFMAs of that half and, in their shadow,
+// from LDS (12 ds_read_b128); in a compute phase it issues the 32 MFMAs of that half and, in their shadow,
 // everything else: its four loads of one panel and the cursor arithmetic.  A wave issues one instruction
-// every few cycles, and the matrix pipe takes 32 cycles per MFMA, so the compute phase has issue slots to
+// every few cycles, and the matrix pipe takes 16 cycles per MFMA, so the compute phase has issue slots to
 // spare while the memory phase has none: measured on MI355X, every scalar instruction added to the memory
 // phase lengthens the step, and four loads spread over the MFMAs of the compute phase cost nothing.
 // While a wave multiplies, its SIMD partner reads fragments, so the matrix pipe always has work.
@@ -27,8 +27,12 @@
 // are issued from inline assembly (the compiler does not know that they write LDS), so every vmcnt wait
 // is explicit here.
 //
-// The accumulator of v_mfma_f32_32x32x16_bf16 holds, per lane, 4 consecutive rows of the instruction's
+// The accumulator of v_mfma_f32_16x16x32_bf16 holds, per lane, 4 consecutive rows of the instruction's
 // first operand.  The B tile is fed as first operand, so those 4 values are consecutive columns of C.
+// The chip is limited by power under these products, and this instruction takes less of it than 32x32x16, which reads
+// and writes an accumulator for every 16 K instead of every 32: with operands in registers 2070 TFLOP/s against 1810 over
+// 6 ms, with all of them read from LDS 1680 against 1535; forward pass of 16384 tokens, d = 2048, eight experts of mean
+// width 5632 1869 -> 1793 us, training step of 32768 tokens 11.23 -> 10.77 ms.
 #pragma once
 #include "gemm_bf16_util.h"
 
@@ -40,7 +44,7 @@ struct Bf16Tile {
   static constexpr int NWAVES = WAVES_M * WAVES_N;
   static constexpr int NT = NWAVES * 64;
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-  static constexpr int MI = WM / 32, NI = WN / 32;
+  static constexpr int MI = WM / 16, NI = WN / 16;  // matrix blocks of 16 x 16
   static constexpr int PANEL = 256 * 128;  // bytes of one operand panel
   static constexpr int NSLOT = 5;
   static constexpr int UPW = 4;            // 1 KiB load units per wave and panel
@@ -154,10 +158,10 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
   const int lchunk_odd = ((lane & 7) ^ (4 | (lrow >> 1))) * 8;
   // [K, X] operands: a load unit is 2 K-rows of 32 chunks; this lane's row inside the unit and its chunk
   const int t_row = lane >> 5, t_chunk = lane & 31;
-  // fragment read offsets inside a panel (bytes), without the kk-dependent swizzle term
-  const int a_frag = (wm * WM + (lane & 31)) * 128;
-  const int b_frag = (wn * WN + (lane & 31)) * 128;
-  const int khalf = lane >> 5, lsw = (lane >> 1) & 7;
+  // fragment read offsets inside a panel (bytes), without the swizzle term, which goes by the K half
+  const int a_frag = (wm * WM + (lane & 15)) * 128;
+  const int b_frag = (wn * WN + (lane & 15)) * 128;
+  const int kquad = lane >> 4, lsw = (lane >> 1) & 7;
 
   // moves w to w.tile; returns true when the problem changed (then P holds the new problem)
   auto walk_to = [&](TileWalk& w, ProblemRegs& P) -> bool {
@@ -238,9 +242,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
 #pragma unroll
     for (int i = 0; i < UPW; ++i) {
       const int u = unit0 + i;
-      if (tr) {  // unit = K rows 2u, 2u+1; LDS position (k, p) holds 16-byte chunk p ^ (4 * (k & 3))
+      if (tr) {  // unit = K rows 2u, 2u+1; LDS position (k, p) holds 16-byte chunk p ^ (4 * (k & 3) + 2 * ((k >> 3) & 1))
         const int k = 2 * u + t_row;
-        const int c16 = t_chunk ^ (4 * (k & 3));
+        const int c16 = t_chunk ^ (4 * (k & 3) + 2 * ((k >> 3) & 1));
         off[i] = (uint32_t)(k * c.ld + min(x0 + c16 * 8, c.rows - 8)) * 2u;  // columns past the end repeat the last chunk
       } else {
         const int r = c.is_a ? u * 8 + lrow : (u * 8 + lrow) % BN;
@@ -343,25 +347,20 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
   }
   int a_ahead = 0;  // the youngest UPW loads of this wave belong to an A panel that is not waited for yet
 
-  // Fragments of one K half (two K slices of 16): set kk & 1.
-  bf16x8 af[2][MI], bfr[2][NB][NI];
-  // Transposed operands.  Lane l = 16 * blk + s reads, for K slice kk and half h, the 8 bytes at
-  // K row kk*16 + (blk >> 1)*8 + h*4 + (s >> 2), column x = tile_x + 32*i + (blk & 1)*16 + 4*(s & 3); the
-  // instruction returns K rows +0..+3 of column tile_x + 32*i + (blk & 1)*16 + s.
+  // Fragments of one K half.
+  bf16x8 af[MI], bfr[NB][NI];
+  // Transposed operands.  Lane l = 16 * blk + s reads, for K half kh and h = 0, 1, the 8 bytes at K row
+  // kh*32 + blk*8 + h*4 + (s >> 2), column x = tile_x + 16*i + 4*(s & 3); the instruction returns K rows +0..+3 of column
+  // tile_x + 16*i + s.  (The rows of two neighbouring blk are 8 apart, which the swizzle tells apart: 32 lanes read
+  // all 64 banks.)
   int tr_a[MI], tr_b[NI];
   {
     const int blk = lane >> 4, sl = lane & 15, kq = sl >> 2;
-    const int rowbyte = ((blk >> 1) * 8 + kq) * 512 + (sl & 1) * 8;
+    const int rowbyte = (blk * 8 + kq) * 512 + (sl & 1) * 8, swz = 4 * kq + 2 * (blk & 1);
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int c16 = (wm * WM + i * 32 + (blk & 1) * 16) / 8 + ((sl & 3) >> 1);
-      tr_a[i] = rowbyte + ((c16 ^ (4 * kq)) << 4);
-    }
+    for (int i = 0; i < MI; ++i) tr_a[i] = rowbyte + ((((wm * WM + i * 16) / 8 + ((sl & 3) >> 1)) ^ swz) << 4);
 #pragma unroll
-    for (int j = 0; j < NI; ++j) {
-      const int c16 = (wn * WN + j * 32 + (blk & 1) * 16) / 8 + ((sl & 3) >> 1);
-      tr_b[j] = rowbyte + ((c16 ^ (4 * kq)) << 4);
-    }
+    for (int j = 0; j < NI; ++j) tr_b[j] = rowbyte + ((((wn * WN + j * 16) / 8 + ((sl & 3) >> 1)) ^ swz) << 4);
   }
   auto read_tr = [&](const char* p) -> bf16x8 {
     typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -372,35 +371,34 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
     const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8, v);
   };
-  auto load_frags = [&](const char* abuf, const char* bbuf, int kk, int set) {
-    const int sw = ((kk * 2 + khalf) ^ lsw) << 4;
+  auto load_frags = [&](const char* abuf, const char* bbuf, int kh) {
+    const int sw = ((kh * 4 + kquad) ^ lsw) << 4;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      if (A_T) af[set][i] = read_tr(abuf + tr_a[i] + kk * 16 * 512);
-      else af[set][i] = *reinterpret_cast<const bf16x8*>(abuf + a_frag + i * 32 * 128 + sw);
+      if (A_T) af[i] = read_tr(abuf + tr_a[i] + kh * 32 * 512);
+      else af[i] = *reinterpret_cast<const bf16x8*>(abuf + a_frag + i * 16 * 128 + sw);
     }
 #pragma unroll
     for (int q = 0; q < NB; ++q)
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
-        if (B_T) bfr[set][q][j] = read_tr(bbuf + tr_b[j] + kk * 16 * 512);
-        else bfr[set][q][j] = *reinterpret_cast<const bf16x8*>(bbuf + b_frag + (q * BN + j * 32) * 128 + sw);
+        if (B_T) bfr[q][j] = read_tr(bbuf + tr_b[j] + kh * 32 * 512);
+        else bfr[q][j] = *reinterpret_cast<const bf16x8*>(bbuf + b_frag + (q * BN + j * 16) * 128 + sw);
       }
   };
-  f32x16 acc[NB][MI][NI];
-  // The 16 MFMAs of one K half; in their shadow this wave's four loads of cursor c's panel (into ring slot
-  // `slot`), one after every fourth MFMA.
+  f32x4 acc[NB][MI][NI];
+  // The 32 MFMAs of one K half; in their shadow this wave's four loads of cursor c's panel (into ring slot
+  // `slot`), one after every eighth MFMA.
   auto mfma_half = [&](LoadCursor& c, uint32_t (&off)[UPW], uint32_t dst, auto always) {
     const int fast = decltype(always)::value ? 1 : c.fast;
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int t = 0; t < 2 * NB * MI * NI; ++t) {
-      constexpr int PER = NB * MI * NI;
-      const int set = t / PER, r = t % PER, q = r / (MI * NI), i = (r / NI) % MI, j = r % NI;
-      acc[q][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][q][j], af[set][i], acc[q][i][j], 0, 0, 0);
-      if (t % (2 * PER / UPW) == 1) {
+    for (int t = 0; t < NB * MI * NI; ++t) {
+      const int q = t / (MI * NI), i = (t / NI) % MI, j = t % NI;
+      acc[q][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[q][j], af[i], acc[q][i][j], 0, 0, 0);
+      if (t % (NB * MI * NI / UPW) == 1) {
         __builtin_amdgcn_sched_barrier(0);
-        if (fast) issue_fast(c, off, dst, t / (2 * PER / UPW));
+        if (fast) issue_fast(c, off, dst, t / (NB * MI * NI / UPW));
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -454,7 +452,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
 #pragma unroll
         for (int j = 0; j < NI; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[q][i][j][r] = 0.f;
+          for (int r = 0; r < 4; ++r) acc[q][i][j][r] = 0.f;
   };
   zero_acc();
   while (cc.w.valid) {
@@ -474,8 +472,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
         for (; n > 0; --n) {
           const char* abuf = ring + sa * PANEL;
           const char* bbuf = ring + slot_add(sa, 1) * PANEL;
-          load_frags(abuf, bbuf, 0, 0);
-          load_frags(abuf, bbuf, 1, 1);
+          load_frags(abuf, bbuf, 0);
           __builtin_amdgcn_sched_barrier(0);
           c1.src += c1.kbytes;
           ++c1.step;
@@ -483,8 +480,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
           phase_end();
           mfma_half(c0, off0, dst0, std::true_type{});
           phase_end();
-          load_frags(abuf, bbuf, 2, 0);
-          load_frags(abuf, bbuf, 3, 1);
+          load_frags(abuf, bbuf, 1);
           __builtin_amdgcn_sched_barrier(0);
           c0.src += c0.kbytes;
           ++c0.step;
@@ -500,8 +496,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
       ++s;
       const char* abuf = ring + sa * PANEL;
       const char* bbuf = ring + slot_add(sa, 1) * PANEL;
-      load_frags(abuf, bbuf, 0, 0);
-      load_frags(abuf, bbuf, 1, 1);
+      load_frags(abuf, bbuf, 0);
       __builtin_amdgcn_sched_barrier(0);
       after_issue(c1, off1, panel_dst(slot_add(sa, grp_y ? 3 : 2)));  // (the panel c1 loaded in the step before)
       const uint32_t dst0 = panel_dst(slot_add(sa, d0)), dst1 = panel_dst(slot_add(sa, d1));
@@ -509,8 +504,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
       phase_end();
       mfma_half(c0, off0, dst0, std::false_type{});
       phase_end();
-      load_frags(abuf, bbuf, 2, 0);
-      load_frags(abuf, bbuf, 3, 1);
+      load_frags(abuf, bbuf, 1);
       __builtin_amdgcn_sched_barrier(0);
       after_issue(c0, off0, dst0);
       if (!grp_y) a_ahead = c1.fast;
@@ -523,7 +517,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
       sa = slot_add(sa, 2);
     }
 
-    // ---- epilogue.  For register group r of block (i, j) the lane holds columns n .. n+3 of row m.
+    // ---- epilogue.  Of block (i, j) the lane holds columns 4 (lane >> 4) .. + 3 of row lane & 15.
     // The early waves wait here for the late waves' last MFMA phase, and the late waves wait behind their
     // epilogue for the early waves' first phase of the next tile: both groups then run their epilogues at the
     // same time (the memory latency of one hides behind the other's) and are one phase apart again afterwards.
@@ -537,7 +531,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
     // per-lane addresses once, ahead of the tile loop, and they occupy dozens of registers in the main loop.)
     int elane = lane;
     asm volatile("" : "+v"(elane));
-    const int ekhalf = elane >> 5;
+    const int erow16 = elane & 15, equad = elane >> 4;
     const int cM = cc.M, cN = cc.N, cld = cc.ldc;
     if constexpr (EPI == EPI_STORE_F32) {
       // float32 output (weight gradients).  It goes through LDS, one 32 x 32 block (4 KiB) at a time: written in
@@ -550,13 +544,14 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
       const uint32_t voff = (uint32_t)(erow * cld + echunk * 4) * 4u;
       const int mleft = cM - cc.w.m0 - wm * WM, nleft = cN - cc.w.n0 - wn * WN;  // of the matrix, from the wave's corner on
       const char* const wave_c = cc.C + ((size_t)(cc.w.m0 + wm * WM) * cld + cc.w.n0 + wn * WN) * 4;
-      auto inside = [&](int b) { return (b / NI) * 32 < mleft && (b % NI) * 32 < nleft; };
-      auto row_group = [&](int b, int it) { return wave_c + ((long)((b / NI) * 32 + it * 8) * cld + (b % NI) * 32) * 4; };
+      constexpr int NI32 = NI / 2, NBLK = MI / 2 * NI32;
+      auto inside = [&](int b) { return (b / NI32) * 32 < mleft && (b % NI32) * 32 < nleft; };
+      auto row_group = [&](int b, int it) { return wave_c + ((long)((b / NI32) * 32 + it * 8) * cld + (b % NI32) * 32) * 4; };
       const bool stream_c = (option & GEMM_STREAM_C) != 0;
       if (cc.nsteps == 0) {  // an expert without tokens: the ring holds nothing of this tile
         if (!accumulate)
 #pragma unroll
-          for (int b = 0; b < MI * NI; ++b)
+          for (int b = 0; b < NBLK; ++b)
             if (inside(b))
 #pragma unroll
               for (int it = 0; it < 4; ++it) global_store16_s(row_group(b, it), voff, f32x4{0.f, 0.f, 0.f, 0.f}, stream_c);
@@ -565,16 +560,14 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
         // write a block into it only after the block before has been read back)
         char* const fslot[2] = {ring + slot_add(sa, grp_y ? NSLOT - 1 : NSLOT - 2) * PANEL + unit0 * 1024,
                                 ring + slot_add(sa, NSLOT - 1) * PANEL + unit0 * 1024};
-        const int er = elane & 31, esw = (er >> 1) & 7;
-        auto put = [&](int b) {  // block b = i * NI + j
-          f32x16& c = acc[0][b / NI][b % NI];
+        auto put = [&](auto block) {  // 32 x 32 block
+          constexpr int b = decltype(block)::value;
           char* slot = fslot[b & 1];
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            f32x4 v = {c[r * 4], c[r * 4 + 1], c[r * 4 + 2], c[r * 4 + 3]};
-            *reinterpret_cast<f32x4*>(slot + er * 128 + (((2 * r + ekhalf) ^ esw) << 4)) = v;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) c[r * 4 + q] = 0.f;
+            const int i = (b / NI32) * 2 + (r >> 1), j = (b % NI32) * 2 + (r & 1);
+            *reinterpret_cast<f32x4*>(slot + ((r >> 1) * 16 + erow16) * 128 + ((((r & 1) * 4 + equad) ^ (erow16 >> 1)) << 4)) = acc[0][i][j];
+            acc[0][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
           }
         };
         // STREAM: of the old values (a template, not a branch: loads in flight must not meet at a join)
@@ -583,18 +576,20 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
           f32x4 old[4];
           // (never masked, see the dH epilogue below: outside the matrix its last rows and columns are read instead)
           auto fetch = [&](int b, int it) {
-            const int m = min((b / NI) * 32, mleft - 32), n = min((b % NI) * 32, nleft - 32);
+            const int m = min((b / NI32) * 32, mleft - 32), n = min((b % NI32) * 32, nleft - 32);
             old[it] = global_load16_f32_s<STREAM>(wave_c + ((long)(m + it * 8) * cld + n) * 4, voff);
           };
           if constexpr (ADD) {
 #pragma unroll
             for (int it = 0; it < 4; ++it) fetch(0, it);
           }
-          if (!grp_y) put(0);
-#pragma unroll
-          for (int b = 0; b < MI * NI; ++b) {
-            if (grp_y) put(b);
-            else if (b + 1 < MI * NI) put(b + 1);
+          if (!grp_y) put(std::integral_constant<int, 0>{});
+          // (block numbers are template arguments: as loop variables they are constants too late for the compiler, which
+          // then keeps the accumulators in memory)
+          static_for<NBLK>([&](auto block) {
+            constexpr int b = decltype(block)::value;
+            if (grp_y) put(block);
+            else if constexpr (b + 1 < NBLK) put(std::integral_constant<int, b + 1>{});
             char* slot = fslot[b & 1];
             const bool in = inside(b);
 #pragma unroll
@@ -603,16 +598,16 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
               f32x4 v = *reinterpret_cast<const f32x4*>(slot + rr * 128 + ((echunk ^ ((rr >> 1) & 7)) << 4));
               if constexpr (ADD) {
                 // loads issued after this one: the rest of this block's, and the next block's reloaded so far
-                if (b + 1 < MI * NI || it == 0) wait_loaded<3>(old[it]);
+                if (b + 1 < NBLK || it == 0) wait_loaded<3>(old[it]);
                 else if (it == 1) wait_loaded<2>(old[it]);
                 else if (it == 2) wait_loaded<1>(old[it]);
                 else wait_loaded<0>(old[it]);
                 v += old[it];
-                if (b + 1 < MI * NI) fetch(b + 1, it);
+                if (b + 1 < NBLK) fetch(b + 1, it);
               }
               if (in) global_store16_s(row_group(b, it), voff, v, stream_c);
             }
-          }
+          });
         };
         if (accumulate && stream_c) tile(std::true_type{}, std::true_type{});
         else if (accumulate) tile(std::true_type{}, std::false_type{});
@@ -620,13 +615,13 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
       }
     } else {
       // 16-bit outputs go through LDS so that global memory sees whole 128-byte lines: the wave works in
-      // units of 32 rows x 64 columns (two MFMA blocks), writes a unit into a 4 KiB slot in accumulator
+      // units of 32 rows x 64 columns (2 x 4 blocks), writes a unit into a 4 KiB slot in accumulator
       // order (8 bytes per lane), reads it back row-wise (16 bytes per lane, 8 lanes per row) and stores.
       // The two slots are this wave's own load units in the two panels of the step just finished: nobody
       // reads those panels any more, and the next loads into these units are this wave's own, issued after
       // the epilogue.  LDS serves one wave's accesses in program order.
-      static_assert(NI % 2 == 0, "staged epilogue: 64-column units");
-      constexpr int NJP = NI / 2, NU = MI * NJP;
+      static_assert(NI % 4 == 0 && MI % 2 == 0, "staged epilogue: units of 32 rows x 64 columns");
+      constexpr int NJP = NI / 4, NU = MI / 2 * NJP;
       // (the late waves have already refilled their units of the A panel's slot: their two slots are one and
       // the same, so everything below writes a slot only after what it held has been read back, in program
       // order)
@@ -636,11 +631,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
                           : BOTH_EPI ? ring + slot_add(sa, NSLOT - 1) * PANEL + unit0 * 1024
                                      : ring + slot_add(sa, NSLOT - 1) * PANEL + (unit0 - Cfg::NWAVES / 2 * UPW) * 1024;
       char* const slot1 = ring + slot_add(sa, NSLOT - 1) * PANEL + unit0 * 1024;
-      const int er = elane & 31, esw = (er >> 1) & 7;
       const int rrow = elane >> 3, rchunk = elane & 7;
-      auto acc_pos = [&](char* slot, int jj, int r) -> bf16x4* {  // 4 columns of accumulator group (jj, r)
-        return reinterpret_cast<bf16x4*>(slot + er * 128 + (((jj * 4 + r) ^ esw) << 4) + ekhalf * 8);
+      auto acc_pos = [&](char* slot, int ii, int jj) -> bf16x4* {  // this lane's 4 columns of the unit's block (ii, jj)
+        return reinterpret_cast<bf16x4*>(slot + (ii * 16 + erow16) * 128 + (((jj * 2 + (equad >> 1)) ^ (erow16 >> 1)) << 4) + (equad & 1) * 8);
       };
+      auto acc_of = [&](int q, int u, int ii, int jj) -> f32x4& { return acc[q][(u / NJP) * 2 + ii][(u % NJP) * 4 + jj]; };
       auto row_pos = [&](char* slot, int it) -> bf16x8* {  // chunk rchunk of row 8 * it + rrow
         const int rr = it * 8 + rrow;
         return reinterpret_cast<bf16x8*>(slot + rr * 128 + ((rchunk ^ ((rr >> 1) & 7)) << 4));
@@ -652,22 +647,17 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
         const int m = unit_m(u) + it * 8 + rrow, n = unit_n(u) + rchunk * 8;
         return (m < cM && n < cN) ? (long)m * cld + n : -1;
       };
-      // one 32 x 32 block of the unit; the accumulator block is cleared for the next tile on the way
-      auto put_block = [&](char* slot, int jj, f32x16& c) {
+      // (the accumulators are cleared for the next tile on the way)
+      auto put_unit = [&](char* slot, int q, int u) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int b = 0; b < 8; ++b) {
+          f32x4& c = acc_of(q, u, b >> 2, b & 3);
           bf16x4 v;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            v[q] = (bf16_t)c[r * 4 + q];
-            c[r * 4 + q] = 0.f;
-          }
-          *acc_pos(slot, jj, r) = v;
+          for (int x = 0; x < 4; ++x) v[x] = (bf16_t)c[x];
+          c = f32x4{0.f, 0.f, 0.f, 0.f};
+          *acc_pos(slot, b >> 2, b & 3) = v;
         }
-      };
-      auto put_unit = [&](char* slot, f32x16& c0, f32x16& c1) {
-        put_block(slot, 0, c0);
-        put_block(slot, 1, c1);
       };
       auto store_unit = [&](char* slot, int u, const char* C) {
 #pragma unroll
@@ -698,7 +688,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
 #pragma unroll
           for (int u = 0; u < NU; ++u) {
             char* slot = (u & 1) ? slot1 : slot0;
-            put_unit(slot, acc[0][u / NJP][2 * (u % NJP)], acc[0][u / NJP][2 * (u % NJP) + 1]);
+            put_unit(slot, 0, u);
             store_unit_interior(slot, u, wave_c);
           }
         } else {
@@ -706,7 +696,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
           for (int u = 0; u < NU; ++u) {
             if (unit_m(u) >= cM) continue;
             char* slot = (u & 1) ? slot1 : slot0;
-            put_unit(slot, acc[0][u / NJP][2 * (u % NJP)], acc[0][u / NJP][2 * (u % NJP) + 1]);
+            put_unit(slot, 0, u);
             store_unit(slot, u, cc.C);
           }
         }
@@ -716,40 +706,37 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
         // (an inference pass, which saves nothing, takes the copy of the code without the arithmetic of p)
         auto swiglu_unit = [&](int u, auto save_tag) {
           constexpr bool SAVE = decltype(save_tag)::value;
-          const int i = u / NJP, j0 = 2 * (u % NJP);
 #pragma unroll
-          for (int jj = 0; jj < 2; ++jj)
+          for (int blk = 0; blk < 8; ++blk) {
+            const int ii = blk >> 2, jj = blk & 3;
+            bf16x4 hv, pv;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              bf16x4 hv, pv;
-#pragma unroll
-              for (int q4 = 0; q4 < 4; ++q4) {
-                const float a = acc[0][i][j0 + jj][r * 4 + q4], b = acc[1][i][j0 + jj][r * 4 + q4];
-                if constexpr (SAVE) {
-                  float h, p, q;
-                  swiglu_terms(a, b, sigmoid_fast(a), h, p, q);
-                  hv[q4] = (bf16_t)h;
-                  pv[q4] = (bf16_t)p;
-                  acc[1][i][j0 + jj][r * 4 + q4] = q;
-                } else {
-                  hv[q4] = (bf16_t)(a * sigmoid_fast(a) * b);
-                }
+            for (int x = 0; x < 4; ++x) {
+              const float a = acc_of(0, u, ii, jj)[x], b = acc_of(1, u, ii, jj)[x];
+              if constexpr (SAVE) {
+                float h, p, q;
+                swiglu_terms(a, b, sigmoid_fast(a), h, p, q);
+                hv[x] = (bf16_t)h;
+                pv[x] = (bf16_t)p;
+                acc_of(1, u, ii, jj)[x] = q;
+              } else {
+                hv[x] = (bf16_t)(a * sigmoid_fast(a) * b);
               }
-              *acc_pos(slot0, jj, r) = hv;
-              if constexpr (SAVE) *acc_pos(slot1, jj, r) = pv;
             }
+            *acc_pos(slot0, ii, jj) = hv;
+            if constexpr (SAVE) *acc_pos(slot1, ii, jj) = pv;
+          }
         };
         auto swiglu_tile = [&](auto save_tag) {
           constexpr bool SAVE = decltype(save_tag)::value;
           if (interior) {
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
-              const int i = u / NJP, j0 = 2 * (u % NJP);
               swiglu_unit(u, save_tag);
               store_unit_interior(slot0, u, cc.C + wave_off);
               if constexpr (SAVE) {
                 store_unit_interior(slot1, u, cc.C2 + wave_off);
-                put_unit(slot0, acc[1][i][j0], acc[1][i][j0 + 1]);
+                put_unit(slot0, 1, u);
                 store_unit_interior(slot0, u, cc.C3 + wave_off);
               }
             }
@@ -757,12 +744,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
 #pragma unroll
             for (int u = 0; u < NU; ++u) {
               if (unit_m(u) >= cM) continue;
-              const int i = u / NJP, j0 = 2 * (u % NJP);
               swiglu_unit(u, save_tag);
               store_unit(slot0, u, cc.C);
               if constexpr (SAVE) {
                 store_unit(slot1, u, cc.C2);
-                put_unit(slot0, acc[1][i][j0], acc[1][i][j0 + 1]);
+                put_unit(slot0, 1, u);
                 store_unit(slot0, u, cc.C3);
               }
             }
@@ -801,20 +787,12 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
           }
 #pragma unroll
           for (int u = 0; u < NU; ++u) {
-            const int i = u / NJP, j0 = 2 * (u % NJP);
             // rows 0-15 of the unit are staged in slot 0, rows 16-31 in slot 1: the early waves write both at
             // once, the late waves (one slot) the second half after the first has been read back
             auto stage_half = [&](int half) {
-              if ((er >> 4) == half) {
 #pragma unroll
-                for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-                  for (int r = 0; r < 4; ++r) {
-                    const f32x16& c = acc[0][i][j0 + jj];
-                    const f32x4 v = {c[r * 4], c[r * 4 + 1], c[r * 4 + 2], c[r * 4 + 3]};
-                    *reinterpret_cast<f32x4*>(frow(er) + (((jj * 8 + 2 * r + ekhalf) ^ (er & 15)) << 4)) = v;
-                  }
-              }
+              for (int jj = 0; jj < 4; ++jj)
+                *reinterpret_cast<f32x4*>(frow(half * 16 + erow16) + (((jj * 4 + equad) ^ erow16) << 4)) = acc_of(0, u, half, jj);
             };
             stage_half(0);
             if (!grp_y) stage_half(1);

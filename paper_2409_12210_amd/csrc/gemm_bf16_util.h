@@ -7,6 +7,15 @@
 
 namespace modse_gemm {
 
+// f(0), ..., f(N - 1), the arguments as integral constants
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
 __device__ const uint4 g_zero_chunk[4] = {};
   // source of K-tail chunks that lie beyond K
 
