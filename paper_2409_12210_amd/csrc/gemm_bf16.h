@@ -32,7 +32,9 @@
 // The chip is limited by power under these products, and this instruction takes less of it than 32x32x16, which reads
 // and writes an accumulator for every 16 K instead of every 32: with operands in registers 2070 TFLOP/s against 1810 over
 // 6 ms, with all of them read from LDS 1680 against 1535; forward pass of 16384 tokens, d = 2048, eight experts of mean
-// width 5632 1869 -> 1793 us, training step of 32768 tokens 11.23 -> 10.77 ms.
+// width 5632 1869 -> 1793 us, training step of 32768 tokens 11.23 -> 10.77 ms.  For the same reason the blocks of a wave are
+// walked to and fro, so that from one MFMA to the next only one operand changes: 1793 -> 1731 us and 10.77 -> 10.45 ms.
+// (The tiles of gemm_block.h wait for their loads, not for power: the instruction changed nothing there.)
 #pragma once
 #include "gemm_bf16_util.h"
 
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gg_bf16_kernel(const Ge
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int t = 0; t < NB * MI * NI; ++t) {
-      const int q = t / (MI * NI), i = (t / NI) % MI, j = t % NI;
+      const int q = t / (MI * NI), j = (t / MI) % NI, i = (j & 1) ? MI - 1 - t % MI : t % MI;  // (to and fro: one operand changes at a time)
       acc[q][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[q][j], af[i], acc[q][i][j], 0, 0, 0);
       if (t % (NB * MI * NI / UPW) == 1) {
         __builtin_amdgcn_sched_barrier(0);
