@@ -86,9 +86,13 @@ void carve_route(Carver& c, const LayerDims& L, modse_dtype dt, RouteScratch& r)
   r.wpad = c.take(route_wpad_bytes(L, esize_of(dt)));
   r.total = c.off;
 }
-RouteBufs route_bufs(char* base, const RouteScratch& r) {
+RouteBufs route_bufs(char* base, const RouteScratch& r, void* wt) {
   return RouteBufs{reinterpret_cast<int32_t*>(base + r.blockhist), reinterpret_cast<int32_t*>(base + r.near_flag),
-                   base + r.wpad};
+                   base + r.wpad, wt};
+}
+// W_gate's columns, for the routers that want them: behind the scratch, if there is room
+void* wt_behind(char* base, const RouteScratch& r, size_t bytes, const LayerDims& L, modse_dtype dt) {
+  return bytes - r.total >= route_wt_bytes(L, esize_of(dt)) ? base + r.total : nullptr;
 }
 
 struct FwdLayout {
@@ -352,7 +356,8 @@ modse_status modse_route_ext(const modse_desc* desc, int64_t T, const void* x, c
   if (ws_bytes < w.total) return MODSE_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   const RoutingPtrs R = {out->topk_idx, out->topk_w, out->counts, out->offsets, out->row_of, out->src_of, out->near_tie_count};
-  HIP_TRY(launch_route(L, desc->dtype, x, W_gate, logit_bias, R, route_bufs(static_cast<char*>(ws), w), nullptr,
+  HIP_TRY(launch_route(L, desc->dtype, x, W_gate, logit_bias, R,
+                       route_bufs(static_cast<char*>(ws), w, wt_behind(static_cast<char*>(ws), w, ws_bytes, L, desc->dtype)), nullptr,
                        ext ? &G : nullptr, s));
   return MODSE_OK;
 }
@@ -391,7 +396,8 @@ modse_status modse_route_static(const modse_desc* desc, int64_t T, const void* x
   char* scratch = static_cast<char*>(g_route_scratch_ptr[dev]);
   const RoutingPtrs R = {out->topk_idx, out->topk_w, out->counts, out->offsets, out->row_of, out->src_of, out->near_tie_count};
   // every word of the scratch that a kernel reads has been written by an earlier kernel of this call
-  HIP_TRY(launch_route(L, desc->dtype, x, W_gate, logit_bias, R, route_bufs(scratch, w), nullptr, nullptr,
+  HIP_TRY(launch_route(L, desc->dtype, x, W_gate, logit_bias, R,
+                       route_bufs(scratch, w, wt_behind(scratch, w, MODSE_ROUTE_STATIC_SCRATCH_BYTES, L, desc->dtype)), nullptr, nullptr,
                        static_cast<hipStream_t>(hip_stream)));
   return MODSE_OK;
 }
@@ -434,7 +440,9 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   char* wsb = static_cast<char*>(ws);
   const RoutingPtrs R = routing_from(routing_out, wsb, w);
-  const RouteBufs RB = route_bufs(wsb, w.route);
+  // (W_gate's columns lie where the experts' outputs will: those are T k rows of d, written long after the routing)
+  void* const wt = (int64_t)L.T * L.k >= L.N ? (saved ? static_cast<char*>(saved) + saved_layout(L, dt).O : wsb + w.O) : nullptr;
+  const RouteBufs RB = route_bufs(wsb, w.route, wt);
   Stamp stamp(0, s);
 
   // with a backward pass to follow, the permuted rows go straight into the saved buffer

@@ -135,12 +135,14 @@ struct RouteBufs {
   int32_t* blockhist;  // [ceil(T / MODSE_ROUTE_TOKENS_PER_BLOCK), N + 1]
   int32_t* near_flag;  // [T]
   void* wpad;          // route_wpad_bytes()
+  void* wt;            // W_gate's columns, route_wt_bytes(), or null: the routers that need them are not taken then
 };
 inline int padded_experts(int N) { return N <= 2 ? 2 : N <= 4 ? 4 : N <= 8 ? 8 : N <= 16 ? 16 : N <= 32 ? 32 : 64; }
 inline size_t route_wpad_bytes(const LayerDims& L, size_t elem_size) {
   const int NE = padded_experts(L.N);
   return NE == L.N ? 0 : 2 * (size_t)L.d * NE * elem_size;
 }
+inline size_t route_wt_bytes(const LayerDims& L, size_t elem_size) { return (size_t)L.N * L.d * elem_size; }
 // launch_route = launch_router (logits, top-k, gate) + launch_permute (histogram, scan, stable scatter; Xp may
 // be null).
 hipError_t launch_router(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const float* bias,

@@ -697,6 +697,331 @@ __global__ __launch_bounds__(RW_THREADS) void router_kernel(const T* __restrict_
   }
 }
 
+// ---------------------------------------------------------------- screened router
+// Plain gate, bf16, more than 16 experts: of a token's logits only the top k and their rivals matter in float64.  A first
+// launch takes all logits on the bf16 matrix pipe with a bound of their error and keeps, per token, the experts that can
+// be among the top k or within the near-tie distance of them; a second one takes those experts' dot products in
+// float64 and decides as the other routers do.  The decision and the gate weights are therefore the same float64 results.
+//
+// Bound of the error: a product of two bf16 values is exact in float32, and whatever the order in which the matrix pipe adds
+// up n terms, and if it truncates, each of the additions is off by at most 2^-23 of the sum of the terms' magnitudes.  That
+// sum is at most |x| |w|, the lengths of the token's row and the expert's column.  A wave adds d / 8 terms (and the
+// accumulator, once per 32), so gamma = 1.1 (d / 8 + 64) 2^-23 times |x| |w| covers it (4e-5 of it at d = 2048, 1.5e-3
+// for logits of deviation 0.9: a few of a hundred tokens get more than k candidates).  What the lengths lose of values
+// below 2^-63, whose squares are subnormal, and the matrix pipe of subnormal inputs is less than d 2^-32 of |x| |w| as
+// long as no length exceeds 2^30; a block that meets a longer row or column, an infinity or no number leaves all experts to
+// the second launch.
+//
+// 64 experts, d = 2048, 8192 tokens: the launches take 12.7 and 11.5 us, the general router 46.9 (float64 matrix pipe); routing
+// call 55.0 -> 35.1.  The first is a chain of latencies (loads, then the sums and bounds of a token: 8 + 4 us), the second
+// half float64 arithmetic, half the same.  Tried on the first without gain: sixteen waves of half as many steps, blocks
+// that start at different columns, loops that are not unrolled (14.7).
+constexpr int SC_THREADS = 512, SC_WAVES = SC_THREADS / 64, SC_TOKENS = 32, SC_TRANSPOSE_ROWS = 64;
+constexpr double SC_NEAR = 1.1e-6;  // (the near-tie distance of write_gate, and some)
+constexpr float SC_LARGE = 0x1p60f;  // square of the largest length
+// Columns of W_gate as rows (the second launch reads them): 64 rows of W_gate per block.
+__device__ inline void transpose_block(const bf16_t* __restrict__ W, int d, int N, int k0, bf16_t* __restrict__ Wt,
+                                       bf16_t (*tile)[SC_TRANSPOSE_ROWS + 8]) {
+  static_assert(SC_THREADS == 8 * MODSE_MAX_EXPERTS && SC_TRANSPOSE_ROWS == 64, "an expert per eight threads, a row per wave and round");
+  const int rows = min(SC_TRANSPOSE_ROWS, d - k0), col = threadIdx.x & 63;
+  bf16_t v[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const int k = (threadIdx.x >> 6) + 8 * r;
+    v[r] = col < N && k < rows ? W[(size_t)(k0 + k) * N + col] : (bf16_t)0.f;
+  }
+#pragma unroll
+  for (int r = 0; r < 8; ++r) tile[col][(threadIdx.x >> 6) + 8 * r] = v[r];
+  __syncthreads();
+  const int e = threadIdx.x >> 3, c = (threadIdx.x & 7) * 8;
+  if (e < N && c < rows) *reinterpret_cast<bf16x8*>(Wt + (size_t)e * d + k0 + c) = *reinterpret_cast<const bf16x8*>(&tile[e][c]);
+}
+// cand_lo / cand_hi [t * top_k]: bits of token t's candidates.  The first nscreen blocks take 32 tokens each, the others
+// transpose W (rows of N; Wg: the same in rows of NE).  blockhist (may be null) is cleared for the second launch.
+template <int NE>
+__global__ __launch_bounds__(SC_THREADS, 4) void router_screen_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wg,
+                                                                   const bf16_t* __restrict__ W, const float* __restrict__ bias,
+                                                                   int ntok, int d, int N, int top_k, int nscreen,
+                                                                   uint32_t* __restrict__ cand_lo, uint32_t* __restrict__ cand_hi,
+                                                                   bf16_t* __restrict__ Wt, int32_t* __restrict__ blockhist) {
+  // A lane reads EPL neighbouring experts of eight matrix rows; column j of group g is expert EPL j + g.  TRADE: it reads
+  // twice as many of four rows and trades half of them with lane j ^ 8, which has the next four rows (half as many loads; 64
+  // experts 13.8 -> 12.7 us, but with 32 9.7 -> 11.0); column j of group g is then expert 2 EPL (j & 7) + EPL (j >> 3) + g.
+  constexpr int EPL = NE / 16, WORDS = EPL / 2;
+  constexpr bool TRADE = NE == 64;
+  constexpr int LROWS = TRADE ? 4 : 8, LWORDS = TRADE ? 2 * WORDS : WORDS;
+  struct Sums {
+    float l[SC_WAVES / 2][SC_TOKENS][NE + 1];
+    float x2[SC_WAVES][SC_TOKENS], w2[SC_WAVES][NE];  // squares of the lengths
+  };
+  __shared__ union {
+    Sums part;
+    bf16_t tile[MODSE_MAX_EXPERTS][SC_TRANSPOSE_ROWS + 8];
+  } s;
+  __shared__ int s_large;
+  if ((int)blockIdx.x >= nscreen) {
+    transpose_block(W, d, N, ((int)blockIdx.x - nscreen) * SC_TRANSPOSE_ROWS, Wt, s.tile);
+    return;
+  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane >> 4, j = lane & 15, t0 = blockIdx.x * SC_TOKENS;
+  if (tid == 0) s_large = 0;
+  if (blockhist && tid <= N) blockhist[(size_t)blockIdx.x * (N + 1) + tid] = 0;
+  const int nstep = (d / 32 - wave + SC_WAVES - 1) / SC_WAVES;  // this wave's steps of 32 columns: wave, wave + 8, ...
+  struct Step {
+    u32x4 x[2];
+    uint32_t w[LROWS][LWORDS];
+  };
+  int xoff[2];  // (rows past the end repeat the last one; never written)
+#pragma unroll
+  for (int h = 0; h < 2; ++h) xoff[h] = min(h * 16 + j, ntok - 1 - t0) * d + q * 8;
+  const int woff = TRADE ? (q * 8 + (j >> 3) * 4) * NE + (j & 7) * 2 * EPL : q * 8 * NE + j * EPL;
+  auto load = [&](Step& st, int i) {
+    const int c = (wave + min(i, nstep - 1) * SC_WAVES) * 32;
+    const bf16_t* const xc = x + (size_t)t0 * d + c;
+    const bf16_t* const wc = Wg + (size_t)c * NE;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) st.x[h] = *reinterpret_cast<const u32x4*>(xc + xoff[h]);
+#pragma unroll
+    for (int m = 0; m < LROWS; ++m) {
+      typedef uint32_t vec_t __attribute__((ext_vector_type(LWORDS)));
+      const vec_t v = *reinterpret_cast<const vec_t*>(wc + woff + m * NE);
+#pragma unroll
+      for (int w = 0; w < LWORDS; ++w) st.w[m][w] = v[w];
+    }
+  };
+  f32x4 acc[2][EPL];
+  float x2[2] = {0.f, 0.f}, w2[EPL] = {};
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int g = 0; g < EPL; ++g) acc[h][g] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto add_squares = [](u32x4 v, float sum) {
+    typedef bf16_t bf16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bf16x2 p = __builtin_bit_cast(bf16x2, (uint32_t)v[i]);
+      sum = __builtin_amdgcn_fdot2_f32_bf16(p, p, sum, false);
+    }
+    return sum;
+  };
+  auto bf = [](u32x4 v) { return __builtin_bit_cast(bf16x8, v); };
+  auto multiply = [&](const Step& st) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) x2[h] = add_squares(st.x[h], x2[h]);
+    uint32_t row[8][WORDS];
+#pragma unroll
+    for (int m = 0; m < LROWS; ++m)
+#pragma unroll
+      for (int w = 0; w < WORDS; ++w) {
+        if constexpr (TRADE) {  // row_ror:8, into lanes 8-15 of sixteen the upper experts of rows 0-3, into lanes 0-7 the lower ones of rows 4-7
+          row[m][w] = __builtin_amdgcn_update_dpp(st.w[m][w], st.w[m][WORDS + w], 0x128, 0xf, 0xc, false);
+          row[4 + m][w] = __builtin_amdgcn_update_dpp(st.w[m][WORDS + w], st.w[m][w], 0x128, 0xf, 0x3, false);
+        } else {
+          row[m][w] = st.w[m][w];
+        }
+      }
+#pragma unroll
+    for (int g = 0; g < EPL; ++g) {
+      u32x4 w;  // eight rows of column j of group g
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        w[m] = __builtin_amdgcn_perm(row[2 * m + 1][g / 2], row[2 * m][g / 2], (g & 1) ? 0x07060302u : 0x05040100u);
+      w2[g] = add_squares(w, w2[g]);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) acc[h][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf(st.x[h]), bf(w), acc[h][g], 0, 0, 0);
+    }
+  };
+  if (nstep > 0) {  // two steps ahead (the fences keep the compiler from moving the loads to their uses)
+    Step buf[3];
+    load(buf[0], 0);
+    load(buf[1], 1);
+    int i = 0;
+#pragma unroll 1
+    for (; i + 3 <= nstep; i += 3) {
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        load(buf[(b + 2) % 3], i + b + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(buf[b]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (i < nstep) multiply(buf[0]);
+    if (i + 1 < nstep) multiply(buf[1]);
+  }
+  // result lane 16 q + j, register r: token 4 q + r of the half, column j.  Waves 4-7 hand their sums to waves 0-3.
+  auto put = [&](int w, auto add) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int g = 0; g < EPL; ++g)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          float& l = s.part.l[w][h * 16 + 4 * q + r][g * 16 + j];
+          l = acc[h][g][r] + (decltype(add)::value ? l : 0.f);
+        }
+  };
+  if (wave >= SC_WAVES / 2) put(wave - SC_WAVES / 2, std::false_type{});
+  auto over_quarters = [](float v) {
+    v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
+  };
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const float v = over_quarters(x2[h]);
+    if (q == h) s.part.x2[wave][h * 16 + j] = v;
+  }
+#pragma unroll
+  for (int g = 0; g < EPL; ++g) {
+    const float v = over_quarters(w2[g]);
+    if (q == g) s.part.w2[wave][g * 16 + j] = v;
+  }
+  __syncthreads();
+  if (wave < SC_WAVES / 2) put(wave, std::true_type{});
+  // the lengths: of token tid, of column tid - 32
+  float len = 0.f;
+  const bool is_x = tid < SC_TOKENS;
+  if (tid < SC_TOKENS + NE) {
+#pragma unroll
+    for (int w = 0; w < SC_WAVES; ++w) len += is_x ? s.part.x2[w][tid] : s.part.w2[w][tid - SC_TOKENS];
+    if (!(len <= SC_LARGE)) s_large = 1;
+  }
+  __syncthreads();
+  if (is_x) s.part.x2[0][tid] = sqrtf(len);
+  else if (tid < SC_TOKENS + NE) s.part.w2[0][tid - SC_TOKENS] = sqrtf(len);
+  __syncthreads();
+  // sixteen threads per token, EPL experts each
+  const int tl = tid >> 4, t16 = tid & 15, t = t0 + tl;
+  auto expert = [&](int i) { return TRADE ? 2 * EPL * (t16 & 7) + EPL * (t16 >> 3) + i : EPL * t16 + i; };
+  const double gamma = 1.1 * (d / 8 + 64) * 0x1p-23;
+  double hi[EPL], m1 = -INFINITY, m2 = -INFINITY;  // m1, m2: the largest lower bounds
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const int e = expert(i), c = i * 16 + t16;
+    double l = 0.0;
+#pragma unroll
+    for (int w = 0; w < SC_WAVES / 2; ++w) l += (double)s.part.l[w][tl][c];
+    if (bias && e < N) l += (double)bias[e];
+    const double err = gamma * ((double)(s.part.x2[0][tl] * s.part.w2[0][c]) + d * 0x1p-32) + 1e-12, lo = e < N ? l - err : -INFINITY;
+    hi[i] = l + err;
+    if (lo > m1) {
+      m2 = m1;
+      m1 = lo;
+    } else if (lo > m2) {
+      m2 = lo;
+    }
+  }
+#pragma unroll
+  for (int b = 1; b < 16; b <<= 1) {
+    const double o1 = shfl_xor_f64(m1, b), o2 = shfl_xor_f64(m2, b);
+    m2 = o1 > m1 ? fmax(m1, o2) : fmax(o1, m2);
+    m1 = fmax(m1, o1);
+  }
+  const double least = (top_k == 2 ? m2 : m1) - SC_NEAR;
+  uint64_t mask = 0;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const int e = expert(i);
+    if (e < N && (s_large || hi[i] >= least)) mask |= 1ull << e;
+  }
+#pragma unroll
+  for (int b = 1; b < 16; b <<= 1) {
+    const uint32_t lo32 = __shfl_xor((uint32_t)mask, b, 64), hi32 = __shfl_xor((uint32_t)(mask >> 32), b, 64);
+    mask |= ((uint64_t)hi32 << 32) | lo32;
+  }
+  if (t16 == 0 && t < ntok) {
+    cand_lo[(size_t)t * top_k] = (uint32_t)mask;
+    cand_hi[(size_t)t * top_k] = (uint32_t)(mask >> 32);
+  }
+}
+
+// The candidates' dot products in float64, top-k and gate: 32 threads per token, two candidates at a time, in ascending
+// order.  topk_idx and topk_w hold the token's candidates when the launch starts.  A sum runs over a thread's columns and then
+// over a fixed tree: it depends on the token and the expert alone.
+constexpr int EX_LANES = 32, EX_TOKENS = 8, EX_THREADS = EX_LANES * EX_TOKENS;
+__global__ __launch_bounds__(EX_THREADS) void router_exact_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wt,
+                                                                  const float* __restrict__ bias, int ntok, int d, int N,
+                                                                  int top_k, int32_t* topk_idx, float* topk_w,
+                                                                  int32_t* __restrict__ blockhist,
+                                                                  int32_t* __restrict__ near_flag) {
+  __shared__ int s_hist[MODSE_MAX_EXPERTS + 1];
+  const int tid = threadIdx.x, tl = tid / EX_LANES, ln = tid % EX_LANES, t = blockIdx.x * EX_TOKENS + tl;
+  if (tid <= MODSE_MAX_EXPERTS) s_hist[tid] = 0;
+  __syncthreads();
+  if (t < ntok) {
+    const size_t at = (size_t)t * top_k;
+    uint64_t mask = ((uint64_t)__float_as_uint(topk_w[at]) << 32) | (uint32_t)topk_idx[at];
+    const bf16_t* const row = x + (size_t)t * d;
+    TopPick p = {-INFINITY, -INFINITY, -INFINITY, -1, -1};
+    while (mask) {
+      int e[2];
+      e[0] = __builtin_ctzll(mask);
+      mask &= mask - 1;
+      const bool two = mask != 0;
+      e[1] = two ? __builtin_ctzll(mask) : e[0];
+      mask &= mask - 1;  // (0 stays 0)
+      const bf16_t* const w0 = Wt + (size_t)e[0] * d;
+      const bf16_t* const w1 = Wt + (size_t)e[1] * d;
+      double sum[2] = {0.0, 0.0};
+      // `n` pieces of 256 columns from column c0 on, all their loads in flight at once (the fence keeps them there)
+      auto pieces = [&](auto n, int c0) {
+        constexpr int P = decltype(n)::value;
+        Raw8<bf16_t> xv[P], wv[2][P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+          const int c = c0 + (i * EX_LANES + ln) * 8;
+          xv[i].load(row + c);
+          wv[0][i].load(w0 + c);
+          wv[1][i].load(w1 + c);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+#pragma unroll
+          for (int m = 0; m < 8; ++m) {
+            const double xd = (double)xv[i].get(m);
+            sum[0] = fma(xd, (double)wv[0][i].get(m), sum[0]);
+            sum[1] = fma(xd, (double)wv[1][i].get(m), sum[1]);
+          }
+      };
+      int c0 = 0;
+      for (; c0 + 4 * EX_LANES * 8 <= d; c0 += 4 * EX_LANES * 8) pieces(std::integral_constant<int, 4>{}, c0);
+      for (; c0 + ln * 8 < d; c0 += EX_LANES * 8) pieces(std::integral_constant<int, 1>{}, c0);
+#pragma unroll
+      for (int b = 1; b < EX_LANES; b <<= 1) {
+        sum[0] += shfl_xor_f64(sum[0], b);
+        sum[1] += shfl_xor_f64(sum[1], b);
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        if (c == 1 && !two) break;
+        const double l = sum[c] + (bias ? (double)bias[e[c]] : 0.0);
+        if (l > p.m1) {
+          p.m3 = p.m2; p.m2 = p.m1; p.i2 = p.i1; p.m1 = l; p.i1 = e[c];
+        } else if (l > p.m2) {
+          p.m3 = p.m2; p.m2 = l; p.i2 = e[c];
+        } else if (l > p.m3) {
+          p.m3 = l;
+        }
+      }
+    }
+    if (p.i1 < 0) p.i1 = 0;                                  // every logit is -inf
+    if (p.i2 < 0 || p.i2 == p.i1) p.i2 = p.i1 == 0 ? 1 : 0;  // no second one above -inf (see pick_top)
+    if (ln == 0) {
+      const bool near = write_gate(p, t, N, top_k, topk_idx, topk_w);
+      if (near_flag) near_flag[t] = near ? 1 : 0;
+      atomicAdd(&s_hist[p.i1], 1);
+      if (top_k == 2) atomicAdd(&s_hist[p.i2], 1);
+      if (near) atomicAdd(&s_hist[N], 1);
+    }
+  }
+  if (near_flag) return;  // (the permutation of a small batch counts by itself)
+  __syncthreads();
+  static_assert(TPB % EX_TOKENS == 0, "the tokens of a block belong to one histogram");
+  if (tid <= N && s_hist[tid]) atomicAdd(&blockhist[(size_t)(blockIdx.x * EX_TOKENS / TPB) * (N + 1) + tid], s_hist[tid]);
+}
+
 // Router without the optional gate parts: one block per G tokens, the 256 threads split the d columns, so
 // a token row and the router matrix are read once with 16-byte loads and the whole dot product is one or
 // two rounds of memory latency.  Every thread leaves its G x N float64 partial sums in LDS; they are added
@@ -1861,11 +2186,16 @@ hipError_t run_router(const LayerDims& L, const T* x, const T* Wg, const float* 
 // Which router a layer takes.  Plain gate, small and medium batches: one block per token (or four) keeps the chip busy
 // where 32-token blocks would leave most CUs idle.  Larger plain batches of up to 16 experts: router_stream_kernel (or
 // its matrix-instruction form) when W_gate fits its LDS area.  Otherwise, and with the optional gate parts,
-// router_kernel.  At d = 2048 the routing call takes 15 / 56 / 81 us for 64 / 1024 / 4096 tokens with 64 experts on
-// the token router, where router_kernel takes 46 / 78 / 79.
-enum RouterKind { ROUTER_TOKEN, ROUTER_STREAM, ROUTER_BLOCK };
-RouterKind router_kind(const LayerDims& L, const GateExtPtrs* G) {
+// router_kernel.  bf16 with more than 16 experts, and room for W_gate's columns: the screened router as soon as its two
+// launches beat the token router's rounds (four tokens per block): routing call at d = 2048, token router / screened, 64
+// experts 1024 tokens 19.9 / 21.4 us, 1536 27.8 / 21.8, 4096 47.6 / 28.1; 32 experts 1536 20.6 / 20.5, 3072 26.4 / 22.3 (d =
+// 1024, 2048 tokens: 19.8 / 20.1 and 15.5 / 18.0).
+// whether the router leaves flags and no block histograms
+bool router_leaves_flags(const LayerDims& L, const GateExtPtrs* G) { return !G && L.T <= ROUTER_TOKEN_MAX_T; }
+enum RouterKind { ROUTER_TOKEN, ROUTER_STREAM, ROUTER_SCREEN, ROUTER_BLOCK };
+RouterKind router_kind(const LayerDims& L, modse_dtype dt, const GateExtPtrs* G, const RouteBufs& B) {
   if (G) return ROUTER_BLOCK;
+  if (dt == MODSE_BF16 && L.N > 16 && L.T > (L.N > 32 ? 1535 : 2048) && B.wt) return ROUTER_SCREEN;
   if (L.T <= ROUTER_TOKEN_MAX_T) return ROUTER_TOKEN;
   if (L.N <= 16 && (size_t)(L.d / 8) * rs_group_bytes(padded_experts(L.N), 4) <= (size_t)RS_W_BYTES) return ROUTER_STREAM;
   return ROUTER_BLOCK;
@@ -1884,7 +2214,7 @@ hipError_t router_typed(const LayerDims& L, const void* xv, const void* Wgv, con
   const T* x = static_cast<const T*>(xv);
   const T* Wg = static_cast<const T*>(Wgv);
   hipError_t e;
-  const RouterKind kind = router_kind(L, G);
+  const RouterKind kind = router_kind(L, std::is_same_v<T, float> ? MODSE_F32 : MODSE_BF16, G, B);
   const int NE = padded_experts(L.N);
   GateExtPtrs Gp;
   if (G) Gp = *G;
@@ -1923,6 +2253,25 @@ hipError_t router_typed(const LayerDims& L, const void* xv, const void* Wgv, con
     }
 #undef MODSE_LAUNCH_TOKEN_WIDE
 #undef MODSE_LAUNCH_TOKEN_ROUTER
+    e = hipGetLastError();
+  } else if (kind == ROUTER_SCREEN) {
+    if constexpr (std::is_same_v<T, bf16_t>) {
+      const int nscreen = (L.T + SC_TOKENS - 1) / SC_TOKENS;
+      const dim3 grid(nscreen + (L.d + SC_TRANSPOSE_ROWS - 1) / SC_TRANSPOSE_ROWS);
+      uint32_t* const lo = reinterpret_cast<uint32_t*>(R.topk_idx);
+      uint32_t* const hi = reinterpret_cast<uint32_t*>(R.topk_w);
+      bf16_t* const wt = static_cast<bf16_t*>(B.wt);
+      int32_t* const hist = router_leaves_flags(L, G) ? nullptr : B.blockhist;
+      if (NE == 32)
+        hipLaunchKernelGGL((router_screen_kernel<32>), grid, dim3(SC_THREADS), 0, s, x, Wg, static_cast<const T*>(Wgv), bias, L.T, L.d,
+                           L.N, L.k, nscreen, lo, hi, wt, hist);
+      else
+        hipLaunchKernelGGL((router_screen_kernel<64>), grid, dim3(SC_THREADS), 0, s, x, Wg, static_cast<const T*>(Wgv), bias, L.T, L.d,
+                           L.N, L.k, nscreen, lo, hi, wt, hist);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      hipLaunchKernelGGL(router_exact_kernel, dim3((L.T + EX_TOKENS - 1) / EX_TOKENS), dim3(EX_THREADS), 0, s, x, wt, bias, L.T, L.d,
+                         L.N, L.k, R.topk_idx, R.topk_w, hist, hist ? nullptr : B.near_flag);
+    }
     e = hipGetLastError();
   } else if (kind == ROUTER_STREAM && router_on_mfma(L)) {
     const int ngroups = (L.T + RM_TOKENS - 1) / RM_TOKENS;
@@ -1983,8 +2332,8 @@ hipError_t permute_typed(const LayerDims& L, modse_dtype dt, const void* xv, con
                          void* Xpv, const GateExtPtrs* G, const FwdPlanArgs* plan, hipStream_t s) {
   const T* x = static_cast<const T*>(xv);
   const int nb = (L.T + TPB - 1) / TPB;
-  static_assert(ROUTER_TOKEN_MAX_T <= MODSE_PERMUTE_FUSED_MAX_T, "the token routers make no block histograms");
-  const int32_t* const near_flag = router_kind(L, G) == ROUTER_TOKEN ? B.near_flag : nullptr;
+  static_assert(ROUTER_TOKEN_MAX_T == MODSE_PERMUTE_FUSED_MAX_T, "the routers of small batches make no block histograms");
+  const int32_t* const near_flag = router_leaves_flags(L, G) ? B.near_flag : nullptr;
   if (L.T <= MODSE_PERMUTE_SMALL_MAX_T && L.N <= PS_EXPERTS) {
     hipLaunchKernelGGL((permute_small_kernel<T>), dim3(Xpv ? L.T + 1 : 1), dim3(PS_THREADS), 0, s, x, L.T, L.d, L.N, L.k,
                        R.topk_idx, near_flag, B.blockhist, R, static_cast<T*>(Xpv), L, dt == MODSE_F32 ? 4 : 2,

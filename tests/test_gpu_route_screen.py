@@ -1,0 +1,81 @@
+"""The screened router (bf16, more than 16 experts, batches that are not small) against the general ones, which take every logit
+in float64 and which a workspace of the bare scratch's size selects: all integers bit for bit, gate weights to the rounding of
+the last float32 bit (their float64 sums run in another order).  Inputs that the screening could get wrong: equal experts,
+experts a hair apart, tokens of zeros, infinite biases, values beyond its error bound, subnormal values, no numbers."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2409_12210_amd as modse
+
+pytestmark = pytest.mark.gpu
+
+
+def _scratch_bytes(n, d, T):
+    up = lambda v: (v + 255) // 256 * 256  # noqa: E731
+    padded = 32 if n <= 32 else 64
+    return up((T + 31) // 32 * (n + 1) * 4) + up(T * 4) + up(0 if n == padded else 2 * d * padded * 2)
+
+
+def _route(layer, x, W, bias, nbytes):
+    d, d_ff, k, dtype, T = layer
+    r = modse.Routing.empty(T, len(d_ff), k)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    modse.modse_route(d, d_ff, k, dtype, T, x, W, bias, r, ws, ws_bytes=nbytes)
+    return r
+
+
+# rows of 1 .. 65 steps of 32 columns (fewer and more than the block's waves, no multiples), padded and whole matrix rows,
+# last blocks of 1 .. 32 tokens; up to 4096 tokens it leaves flags, beyond that histograms
+@pytest.mark.parametrize("values", ["plain", "bias", "masked", "equal", "close", "odd"])
+@pytest.mark.parametrize("n,k,d,T", [(17, 1, 32, 4097), (30, 2, 1312, 2049), (60, 2, 512, 1537), (24, 2, 96, 4128), (32, 2, 1024, 5003), (33, 2, 288, 4111),
+                                     (48, 1, 224, 4100), (64, 2, 2080, 4999)])
+def test_same_as_general_router(n, k, d, T, values):
+    gen = torch.Generator(device="cuda").manual_seed(n * d + T)
+    x = torch.randn((T, d), device="cuda", generator=gen).bfloat16()
+    W = (0.02 * torch.randn((d, n), device="cuda", generator=gen)).bfloat16()
+    bias = None
+    if values != "plain":
+        bias = 0.1 * torch.randn(n, device="cuda", generator=gen)
+    if values == "masked":
+        bias[3:] = float("-inf")
+        bias[:1] = float("-inf")  # two experts left: the third of k + 1 is at -inf
+    if values == "equal":
+        bias = None
+        W[:, 1::2] = W[:, 0:1]  # ties of many experts
+        x[::3] = 0
+    if values == "close":  # gaps on both sides of the near-tie distance
+        bias = (torch.arange(n, device="cuda") % 4) * 7e-7
+        W[:, 1:4] = W[:, 0:1]
+        W[:, 9:12] = W[:, 8:9]
+    if values == "odd":
+        x[0, 0], x[40, 1], x[80, 2] = float("inf"), float("nan"), 2.0 ** 100
+        x[120] *= 1e-39
+        x[T - 1, d - 1] = -3e38
+        bias[5], bias[6] = float("inf"), float("nan")
+    layer = (d, (32,) * n, k, "bf16", T)
+    scratch = _scratch_bytes(n, d, T)
+    want = _route(layer, x, W, bias, scratch)
+    with pytest.raises(modse.ModseError):
+        _route(layer, x, W, bias, scratch - 256)
+    got = _route(layer, x, W, bias, scratch + n * d * 2)
+    for f in ("topk_idx", "counts", "offsets", "row_of", "src_of", "near_tie_count"):
+        assert torch.equal(getattr(got, f), getattr(want, f)), f
+    np.testing.assert_allclose(got.topk_w.cpu().numpy(), want.topk_w.cpu().numpy(), rtol=2.0 ** -23, atol=2.0 ** -126)
+    if values == "close":
+        assert 0 < int(want.near_tie_count) < T
+    if values == "equal":
+        assert int(want.near_tie_count) > T // 4
+
+
+def test_huge_matrix_values():
+    d, n, T = 64, 20, 4200
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn((T, d), device="cuda", generator=gen).bfloat16()
+    W = torch.randn((d, n), device="cuda", generator=gen).bfloat16()
+    x[:, 0] = 1e-39  # times 3e38 it counts, and a matrix pipe that takes subnormal inputs as zeros would lose it
+    W[0] = 3e38 * torch.rand(n, device="cuda", generator=gen)
+    layer = (d, (32,) * n, 2, "bf16", T)
+    scratch = _scratch_bytes(n, d, T)
+    want, got = _route(layer, x, W, None, scratch), _route(layer, x, W, None, scratch + n * d * 2)
+    assert torch.equal(got.topk_idx, want.topk_idx) and torch.equal(got.near_tie_count, want.near_tie_count)
