@@ -118,27 +118,31 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   // ---- loads.  Which 16-byte chunk a lane fetches is chosen so that the data lands swizzled: unit u of a K-contiguous
   // panel is rows 8u .. 8u+7; of a [K, X] panel 1024 / (X * ES) rows of K.
   auto tr_swz = [](int k, int row_bytes) { return F32 ? 0 : row_bytes >= 256 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); };
-  // offset (bytes) of this lane's chunk of unit u from the tile's first element of the operand, and its K index
-  typedef std::conditional_t<F32, int64_t, uint32_t> off_t_;  // (bf16 matrices stay below 2^32 bytes, float32 ones need not)
-  auto chunk_offset = [&](bool tr, int X, int u, int x0, int rows, int ld, int& kfirst) -> off_t_ {
+  // Offset (bytes) of this lane's chunk of unit u from the unit's first row (`unit`: that row's offset from the tile's first element),
+  // and its K index.  (bf16 tiles stay below 2^32 bytes and count from the tile's first element; of float32 ones that holds for
+  // the few rows of a unit.)
+  auto chunk_offset = [&](bool tr, int X, int u, int x0, int rows, int ld, int& kfirst, size_t& unit) -> uint32_t {
     if (tr) {
-      const int rb = X * ES, byte = lane * 16;
-      const int k = u * (1024 / rb) + byte / rb;
+      const int rb = X * ES, byte = lane * 16, k0 = u * (1024 / rb);
+      const int k = k0 + byte / rb;
       const int c = ((byte % rb) >> 4) ^ tr_swz(k, rb);
       kfirst = k;
-      return ((off_t_)k * ld + (min(x0 + c * CE, rows - CE) - x0)) * ES;  // columns past the end repeat the last chunk
+      unit = F32 ? (size_t)k0 * ld * ES : 0;
+      return (uint32_t)((F32 ? k - k0 : k) * ld + (min(x0 + c * CE, rows - CE) - x0)) * ES;  // columns past the end repeat the last chunk
     }
-    const int r = u * 8 + (lane >> 3);
+    const int r = u * 8 + (lane >> 3), first = F32 ? min(x0 + u * 8 % X, rows - 1) : x0;
     const int c = (lane & 7) ^ ((r >> 1) & 7);
     kfirst = c * CE;
-    return ((off_t_)(min(x0 + r % X, rows - 1) - x0) * ld + c * CE) * ES;
+    unit = (size_t)(first - x0) * ld * ES;
+    return (uint32_t)((min(x0 + r % X, rows - 1) - first) * ld + c * CE) * ES;
   };
-  off_t_ offa[UA], offb[UB];
+  uint32_t offa[UA], offb[UB];
+  size_t unita[UA], unitb[UB];
   int ka[UA], kb[UB];
 #pragma unroll
-  for (int i = 0; i < UA; ++i) offa[i] = chunk_offset(A_T, BM, wave * UA + i, m0, M, P.lda(), ka[i]);
+  for (int i = 0; i < UA; ++i) offa[i] = chunk_offset(A_T, BM, wave * UA + i, m0, M, P.lda(), ka[i], unita[i]);
 #pragma unroll
-  for (int i = 0; i < UB; ++i) offb[i] = chunk_offset(B_T, BN, wave * UB + i, n0, N, P.ldb(), kb[i]);
+  for (int i = 0; i < UB; ++i) offb[i] = chunk_offset(B_T, BN, wave * UB + i, n0, N, P.ldb(), kb[i], unitb[i]);
   const size_t a_org = (A_T ? (size_t)m0 : (size_t)m0 * P.lda()) * ES;
   const size_t b_org = (B_T ? (size_t)n0 : (size_t)n0 * P.ldb()) * ES;
   const size_t a_step = A_T ? (size_t)128 * P.lda() : 128, b_step = B_T ? (size_t)128 * P.ldb() : 128;
@@ -161,18 +165,18 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
     if (w.step >= nsteps) return;
     const uint32_t dst = lds_base + slot_byte(slot) + wave * U * 1024;
     auto off = [&](int i) { if constexpr (IS_A) return offa[i]; else return offb[i]; };
+    auto unit = [&](int i) -> size_t { if constexpr (!F32) return 0; else if constexpr (IS_A) return unita[i]; else return unitb[i]; };
     auto kfirst = [&](int i) { if constexpr (IS_A) return ka[i]; else return kb[i]; };
     if ((w.kstep + 1) * BK <= K) {
 #pragma unroll
       for (int i = 0; i < U; ++i) {
-        if constexpr (F32) dma_b128(src + off(i), dst + i * 1024);
-        else if (!IS_A && stream_b) dma_b128_s<true>(src, off(i), dst + i * 1024);
-        else dma_b128_s(src, off(i), dst + i * 1024);
+        if (!F32 && !IS_A && stream_b) dma_b128_s<true>(src, off(i), dst + i * 1024);
+        else dma_b128_s(src + unit(i), off(i), dst + i * 1024);
       }
     } else {  // the last step of a pass: what lies beyond K reads zeros
 #pragma unroll
       for (int i = 0; i < U; ++i)
-        dma_b128(w.kstep * BK + kfirst(i) < K ? src + off(i) : reinterpret_cast<const char*>(g_zero_chunk), dst + i * 1024);
+        dma_b128(w.kstep * BK + kfirst(i) < K ? src + unit(i) + off(i) : reinterpret_cast<const char*>(g_zero_chunk), dst + i * 1024);
     }
     src += IS_A ? a_step : b_step;
     ++w.step;
@@ -234,7 +238,7 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[q][i][j][r] = 0.f;
   // (the B fragment is the instruction's first operand: a lane's accumulator then holds four consecutive columns of C)
-  auto mfma_slice = [&](int set) {
+  auto mfma_slice = [&](int set, auto behind_first) {  // behind_first(): called behind the slice's first MFMA
     if constexpr (F32) {
 #pragma unroll
       for (int s = 0; s < 4; ++s)
@@ -243,8 +247,10 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
 #pragma unroll
           for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < NI; ++j)
+            for (int j = 0; j < NI; ++j) {
               acc[q][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[set][q][j][s], af[set][i][s], acc[q][i][j], 0, 0, 0);
+              if (s + q + i + j == 0) behind_first();
+            }
     } else {
 #pragma unroll
       for (int q = 0; q < NB; ++q)
@@ -256,42 +262,89 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
     }
   };
 
-#pragma unroll
-  for (int i = 0; i < NSLOT - 2; ++i) {
-    if (i % 2 == 0) issue_b(i);
-    else issue_a(i);
-  }
   int rb = 0;  // slot of step g's B panel; its A panel is in the next one
   auto slot_add = [](int slot, int d) { return slot + d >= NSLOT ? slot + d - NSLOT : slot + d; };
+  if constexpr (F32 && KG == 1) {
+    // The matrix pipe is the bound, so nothing may stand between two MFMAs of a wave but what runs in their shadow.  Everybody meets
+    // before the last slice of a step, whose fragments are in registers: the first ones of the next step are then read behind its
+    // MFMAs, and the step's own panels, which nobody reads any more, are refilled behind them, a step and a quarter ahead.
+    // Against meeting between two steps, with the loads in front of the first MFMA: training pass of 4096 tokens, d = 1024, 3775 ->
+    // 3738 us; with a scalar base per load unit and 32-bit lane offsets, which issue faster than 64-bit addresses, 3492.
+    // (Loads spread one by one over the step's MFMAs: 128 x 128 tiles no better than before.)
+    static_assert(NSLOT == 4, "two stages");
+    auto meet = [&](bool one_stage_behind) {  // my LDS reads have returned and my loads have landed (but the youngest stage's)
+      __builtin_amdgcn_sched_barrier(0);
+      if (one_stage_behind) __builtin_amdgcn_s_waitcnt(0x0070 | (UA + UB));
+      else __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    static_assert(UA + UB < 16, "vmcnt field");
 #pragma unroll 1
-  for (int g = 0; g < nsteps; ++g) {
-    // my loads of step g have landed (those of the NSLOT - 4 panels behind it may still be on their way; s_waitcnt simm16:
-    // vmcnt in bits [3:0] and [15:14]) and my LDS reads of step g - 1 have returned; then everybody meets: the panels of
-    // step g may be read and those of step g - 1 refilled
-    __builtin_amdgcn_sched_barrier(0);
-    constexpr int AHEAD = (NSLOT - 4) / 2 * UA + (NSLOT - 3) / 2 * UB;
-    static_assert(AHEAD < 64, "vmcnt field");
-    if (2 * g + NSLOT - 2 <= 2 * nsteps) __builtin_amdgcn_s_waitcnt(0x0070 | (AHEAD & 15) | (AHEAD >> 4) << 14);  // lgkmcnt(0)
-    else __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    const char* pb = ring + slot_byte(rb);
-    const char* pa = ring + slot_byte(slot_add(rb, 1));
-    load_frags(pa, pb, KG > 1 ? kg : 0, 0);
-    if constexpr (NSLOT % 2 == 0) {
-      issue_b(slot_add(rb, NSLOT - 2));
-      issue_a(slot_add(rb, NSLOT - 1));
-    } else {
-      issue_a(slot_add(rb, NSLOT - 2));
-      issue_b(slot_add(rb, NSLOT - 1));
+    for (int slot = 0; slot < NSLOT; slot += 2) {
+      issue_b(slot);
+      issue_a(slot + 1);
     }
-    rb = slot_add(rb, 2);
+    if (nsteps > 0) {
+      meet(nsteps > 1);
+      load_frags(ring + slot_byte(1), ring + slot_byte(0), 0, 0);
+    }
+#pragma unroll 1
+    for (int g = 0; g < nsteps; ++g) {
+      const int next = slot_add(rb, 2);
 #pragma unroll
-    for (int kk = 0; kk < 4 / KG; ++kk) {
-      if (kk < 4 / KG - 1) load_frags(pa, pb, kk + 1, (kk + 1) & 1);
-      mfma_slice(kk & 1);
+      for (int kk = 0; kk < 3; ++kk) {
+        load_frags(ring + slot_byte(slot_add(rb, 1)), ring + slot_byte(rb), kk + 1, (kk + 1) & 1);
+        mfma_slice(kk & 1, [] {});
+      }
+      meet(false);
+      if (g + 1 < nsteps) load_frags(ring + slot_byte(slot_add(next, 1)), ring + slot_byte(next), 0, 0);
+      mfma_slice(1, [&] {
+        __builtin_amdgcn_sched_barrier(0);
+        issue_b(rb);
+        issue_a(slot_add(rb, 1));
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      rb = next;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NSLOT - 2; ++i) {
+      if (i % 2 == 0) issue_b(i);
+      else issue_a(i);
+    }
+#pragma unroll 1
+    for (int g = 0; g < nsteps; ++g) {
+      // my loads of step g have landed (those of the NSLOT - 4 panels behind it may still be on their way; s_waitcnt simm16:
+      // vmcnt in bits [3:0] and [15:14]) and my LDS reads of step g - 1 have returned; then everybody meets: the panels of
+      // step g may be read and those of step g - 1 refilled
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int AHEAD = (NSLOT - 4) / 2 * UA + (NSLOT - 3) / 2 * UB;
+      static_assert(AHEAD < 64, "vmcnt field");
+      if (2 * g + NSLOT - 2 <= 2 * nsteps) __builtin_amdgcn_s_waitcnt(0x0070 | (AHEAD & 15) | (AHEAD >> 4) << 14);  // lgkmcnt(0)
+      else __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      const char* pb = ring + slot_byte(rb);
+      const char* pa = ring + slot_byte(slot_add(rb, 1));
+      load_frags(pa, pb, KG > 1 ? kg : 0, 0);
+      if constexpr (NSLOT % 2 == 0) {
+        issue_b(slot_add(rb, NSLOT - 2));
+        issue_a(slot_add(rb, NSLOT - 1));
+      } else {
+        issue_a(slot_add(rb, NSLOT - 2));
+        issue_b(slot_add(rb, NSLOT - 1));
+      }
+      rb = slot_add(rb, 2);
+#pragma unroll
+      for (int kk = 0; kk < 4 / KG; ++kk) {
+        if (kk < 4 / KG - 1) load_frags(pa, pb, kk + 1, (kk + 1) & 1);
+        mfma_slice(kk & 1, [] {});
+      }
     }
   }
   __builtin_amdgcn_sched_barrier(0);
