@@ -552,15 +552,6 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
 
   HIP_TRY(launch_grouped_gemm(dt, EPI_SWIGLU_BWD, pa.dh_tile, pa.dh, L.N, 0, spread(L, dt, pa.dh_tile),
                               tiles_bound(L, pa.dh_tile, true), s));
-  if (pa.dx_kchunk) {
-    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.dx_tile, pa.dx, split_problems(L, pa.dx_kchunk, 2), 0,
-                                spread(L, dt, pa.dx_tile), split_tiles_bound(L, pa.dx_tile, pa.dx_kchunk, 2), s, LAYOUT_B_KN));
-  } else {
-    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, L.N, 0, spread(L, dt, pa.dx_tile),
-                                tiles_bound(L, pa.dx_tile, false), s));
-  }
-  stamp.mark(MODSE_STAGE_BWD_DGRAD);
-
   // Gradients of more than half the memory-side cache (256 MB) would be gone from it before anybody reads them, and with
   // them what the launches around this one leave for each other (partial sums of dX, activations, weights): they are stored
   // with the non-temporal hint, and old ones that are added to are read with it.  1.1 GB of gradients: this launch takes as
@@ -568,8 +559,21 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   // reading with the hint takes a step of two such passes from 1882 to 1849.  Smaller gradients are still in the cache when the
   // next micro-batch adds to them; the hint changes nothing there (two passes with 48 MB 595 us with it, 597 without).
   const bool stream = 3 * (size_t)L.foff[L.N] * L.d * sizeof(float) > ((size_t)128 << 20);
-  HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, 3 * L.N, accumulate, stream ? GEMM_STREAM_C : 0,
-                              wgrad_tiles(L, pa.wg_tile), s));
+  const int n_dx = pa.dx_kchunk ? split_problems(L, pa.dx_kchunk, 2) : L.N, wg_option = stream ? GEMM_STREAM_C : 0;
+  const int64_t dx_tiles =
+      pa.dx_kchunk ? split_tiles_bound(L, pa.dx_tile, pa.dx_kchunk, 2) : tiles_bound(L, pa.dx_tile, false);
+  if (dx_wgrad_in_one_launch(dt, pa.dx_tile, pa.wg_tile)) {
+    stamp.mark(MODSE_STAGE_BWD_DGRAD);  // (dX counts with the weight gradients)
+    HIP_TRY(launch_dx_wgrad(pa.dx_tile, pa.dx_kchunk != 0, pa.dx, n_dx, dx_tiles, pa.wg, 3 * L.N, wgrad_tiles(L, pa.wg_tile), accumulate,
+                            wg_option, s));
+  } else {
+    if (pa.dx_kchunk)
+      HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.dx_tile, pa.dx, n_dx, 0, spread(L, dt, pa.dx_tile), dx_tiles, s, LAYOUT_B_KN));
+    else
+      HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, n_dx, 0, spread(L, dt, pa.dx_tile), dx_tiles, s));
+    stamp.mark(MODSE_STAGE_BWD_DGRAD);
+    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, 3 * L.N, accumulate, wg_option, wgrad_tiles(L, pa.wg_tile), s));
+  }
   stamp.mark(MODSE_STAGE_BWD_WGRAD);
 
   const DxRows rows = {pa.dXp, pa.dXpart, pa.dx_kchunk};

@@ -199,6 +199,11 @@ enum GemmOption {
 hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int n_prob, int accumulate,
                                int option, int64_t max_tiles, hipStream_t s, int layout = -1);
 
+// dX and the weight gradients in one launch, for float32 layers of small tiles
+bool dx_wgrad_in_one_launch(modse_dtype dt, TileShape dx_tile, TileShape wg_tile);
+hipError_t launch_dx_wgrad(TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, const GemmPlan* wg, int n_wg,
+                           int64_t wg_tiles, int accumulate, int option, hipStream_t s);
+
 struct FwdPlanArgs {
   const void *Xp, *W1, *W3, *W2;
   void *H, *dHdA, *dHdB, *O;  // dHdA/dHdB (derivatives of h by the two pre-activations) may be null

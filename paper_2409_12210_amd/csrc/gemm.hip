@@ -40,11 +40,13 @@ hipError_t run_bf16(const GemmPlan* plan, int n_prob, int accumulate, int option
   return hipGetLastError();
 }
 
-// max_tiles: an upper bound of the tile list's length; one workgroup per tile
+// Workgroups of a launch with one per tile (max_tiles: an upper bound of the tile list's length)
+int64_t block_grid(int64_t max_tiles) { return (int64_t)align_up((size_t)std::max<int64_t>(max_tiles, 1), NUM_XCD * TILE_RUN); }
+
 template <typename T, int BM, int BN, int EPI, int LAYOUT, int WAVES_M = 2, int WAVES_N = 2>
 hipError_t run_block(const GemmPlan* plan, int n_prob, int accumulate, int option, int64_t max_tiles, hipStream_t s) {
   constexpr int NB = EPI == EPI_SWIGLU ? 2 : 1;
-  const int64_t grid = (int64_t)align_up((size_t)std::max<int64_t>(max_tiles, 1), NUM_XCD * TILE_RUN);
+  const int64_t grid = block_grid(max_tiles);
   if constexpr (std::is_same_v<T, float> && BM == 32)
     hipLaunchKernelGGL((gg_f32_small_kernel<NB, EPI, LAYOUT>), dim3((unsigned)grid), dim3(256), 0, s, plan, n_prob, accumulate, option);
   else if constexpr (std::is_same_v<T, float>)
@@ -109,4 +111,20 @@ hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const 
       return run_bf16<256, 256, 1, 4, 2, EPI_STORE_F32, LAYOUT_AB_K>(plan, n_prob, accumulate, option, max_tiles, s);
   }
   return hipErrorInvalidValue;
+}
+
+bool dx_wgrad_in_one_launch(modse_dtype dt, TileShape dx_tile, TileShape wg_tile) {
+  return dt == MODSE_F32 && dx_tile.bm <= 64 && wg_tile.bm == 64;
+}
+hipError_t launch_dx_wgrad(TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, const GemmPlan* wg, int n_wg,
+                           int64_t wg_tiles, int accumulate, int option, hipStream_t s) {
+  const int64_t dx_blocks = block_grid(dx_tiles);
+  const dim3 grid((unsigned)(dx_blocks + block_grid(wg_tiles))), block(256);
+#define MODSE_LAUNCH_DX_WGRAD(TILE, EPI)                                                                                          \
+  hipLaunchKernelGGL((gg_f32_dx_wgrad_kernel<TILE, EPI>), grid, block, 0, s, dx, n_dx, (int)dx_blocks, wg, n_wg, accumulate, option)
+  if (dx_tile.bm == 32) MODSE_LAUNCH_DX_WGRAD(32, EPI_STORE_DUALK);  // (never split)
+  else if (dx_split) MODSE_LAUNCH_DX_WGRAD(64, EPI_STORE_F32);
+  else MODSE_LAUNCH_DX_WGRAD(64, EPI_STORE_DUALK);
+#undef MODSE_LAUNCH_DX_WGRAD
+  return hipGetLastError();
 }

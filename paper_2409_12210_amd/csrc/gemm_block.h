@@ -46,8 +46,11 @@ __device__ inline int tile_of_workgroup(int b) {
 
 // BN: columns of C per tile.  NB = 2: two B matrices that share A (the up-projection's W1 and W3), BN columns of each.
 // KG > 1: KG groups of waves share the tile, each takes every KG-th of a step's four K slices, and the sums meet in LDS.
+// block: of the launch's workgroups that work on this plan.  ring: ring_bytes(BM, NB * BN, NSLOT) of LDS.
+constexpr int ring_bytes(int bm, int br, int nslot) { return bm == br ? nslot * bm * 128 : nslot / 2 * (bm + br) * 128; }
 template <typename T, int BM, int BN, int NB, int WAVES_M, int WAVES_N, int NSLOT, int EPI, int LAYOUT, int KG = 1>
-__device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int n_prob, int accumulate, int option) {
+__device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int n_prob, int accumulate, int option, int block,
+                                         char* const ring) {
   constexpr int ES = sizeof(T), CE = 16 / ES, BK = 128 / ES;
   constexpr bool A_T = (LAYOUT & 1) != 0, B_T = (LAYOUT & 2) != 0, F32 = ES == 4;
   constexpr int BR = NB * BN;               // B rows of a stage
@@ -63,14 +66,13 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   static_assert(EQUAL || NSLOT % 2 == 0, "panels of different sizes: whole stages");
   static_assert(KG == 1 || (KG == 4 && MI * NI == 1), "a slice and a block per wave");
   static_assert((NSLOT % 2 == 0 ? STAGE : BM * 128) >= NW / KG * 4096, "epilogue: 4 KiB per wave in the slots of one step");
-  __shared__ __attribute__((aligned(1024))) char ring[EQUAL ? NSLOT * BM * 128 : NSLOT / 2 * STAGE];
   auto slot_byte = [](int slot) { return EQUAL ? slot * (BM * 128) : (slot >> 1) * STAGE + (slot & 1) * (BR * 128); };
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave / (WAVES_M * WAVES_N);
   const int wm = wave % (WAVES_M * WAVES_N) / WAVES_N, wn = wave % WAVES_N;
-  const int tile = tile_of_workgroup(blockIdx.x);
+  const int tile = tile_of_workgroup(block);
   // The tile's problem: the last one that starts at or before it.  Every lane looks at the first tile of up to four problems
   // and touches their entries, all in one round trip: a launch's first workgroups find the lists in no cache, and one load
   // after the other (number of problems, their list, the tile's, its entry) took them about a microsecond more: training pass of
@@ -352,7 +354,7 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   if constexpr (KG > 1) {  // (nothing is on its way into LDS any more, and behind the barrier nobody reads a panel)
     char* const sums = ring + lane * 16;
     auto part = [&](int g, int q, int r) { return reinterpret_cast<f32x4*>(sums + (((g - 1) * NB + q) * 4 + r) * 1024); };
-    static_assert(sizeof(ring) >= (KG - 1) * NB * 4096, "the groups' sums");
+    static_assert(ring_bytes(BM, BR, NSLOT) >= (KG - 1) * NB * 4096, "the groups' sums");
     __syncthreads();
     if (kg > 0) {
 #pragma unroll
@@ -507,17 +509,36 @@ __device__ __forceinline__ void gg_block(const GemmPlan* __restrict__ plan, int 
   }
 }
 
+#define MODSE_RING(BM, BR, NSLOT) __shared__ __attribute__((aligned(1024))) char ring[ring_bytes(BM, BR, NSLOT)]
 template <int BM, int BN, int NB, int EPI, int LAYOUT>
 __global__ __launch_bounds__(256, 2) void gg_f32_kernel(const GemmPlan* __restrict__ plan, int n_prob, int accumulate, int option) {
-  gg_block<float, BM, BN, NB, 2, 2, 4, EPI, LAYOUT>(plan, n_prob, accumulate, option);
+  MODSE_RING(BM, NB * BN, 4);
+  gg_block<float, BM, BN, NB, 2, 2, 4, EPI, LAYOUT>(plan, n_prob, accumulate, option, blockIdx.x, ring);
 }
 // Launches of few tiles.  Bound by latency: of the workgroup's start, of the loads of a K step, of the dependent matrix
 // instructions of a wave.  So the tile is small (32 x 32), its four waves take one K slice of a step each and add up through
 // LDS, and 32 to 36 KiB of ring let four workgroups of a CU wait at a time.  d = 256, 512 tokens: up-projection 14 -> 11 us,
 // dX 19 -> 11; with twice the ring and two workgroups per CU the same there, but up to 6 % slower for whole layers of more tiles.
+constexpr int small_slots(int nb) { return nb == 1 ? 8 : 6; }
 template <int NB, int EPI, int LAYOUT>
 __global__ __launch_bounds__(256, 4) void gg_f32_small_kernel(const GemmPlan* __restrict__ plan, int n_prob, int accumulate, int option) {
-  gg_block<float, 32, 32, NB, 1, 1, NB == 1 ? 8 : 6, EPI, LAYOUT, 4>(plan, n_prob, accumulate, option);
+  MODSE_RING(32, NB * 32, small_slots(NB));
+  gg_block<float, 32, 32, NB, 1, 1, small_slots(NB), EPI, LAYOUT, 4>(plan, n_prob, accumulate, option, blockIdx.x, ring);
+}
+// Both products that follow dH, in one launch: the first `dx_blocks` workgroups take dX (tiles of DX_TILE), the others the weight
+// gradients.  Neither needs the other, and in a layer of few tiles each leaves most of the chip idle and takes as long as its chain of
+// latencies.  FIGURES
+template <int DX_TILE, int DX_EPI>
+__global__ __launch_bounds__(256, 4) void gg_f32_dx_wgrad_kernel(const GemmPlan* __restrict__ dx, int n_dx, int dx_blocks,
+                                                                 const GemmPlan* __restrict__ wg, int n_wg, int accumulate, int option) {
+  static_assert(ring_bytes(32, 32, 8) == ring_bytes(64, 64, 4), "one ring for either tile");
+  MODSE_RING(64, 64, 4);
+  if ((int)blockIdx.x >= dx_blocks)
+    gg_block<float, 64, 64, 1, 2, 2, 4, EPI_STORE_F32, LAYOUT_AB_K>(wg, n_wg, accumulate, option, blockIdx.x - dx_blocks, ring);
+  else if constexpr (DX_TILE == 32)
+    gg_block<float, 32, 32, 1, 1, 1, small_slots(1), DX_EPI, LAYOUT_B_KN, 4>(dx, n_dx, 0, 0, blockIdx.x, ring);
+  else
+    gg_block<float, 64, 64, 1, 2, 2, 4, DX_EPI, LAYOUT_B_KN>(dx, n_dx, 0, 0, blockIdx.x, ring);
 }
 // as many ring slots as leave room for eight waves per CU
 constexpr int ring_slots(int bm, int br, int waves) {
@@ -527,13 +548,18 @@ constexpr int ring_slots(int bm, int br, int waves) {
 template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_block_kernel(const GemmPlan* __restrict__ plan, int n_prob,
                                                                                int accumulate, int option) {
-  gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, ring_slots(BM, NB * BN, WAVES_M * WAVES_N), EPI, LAYOUT>(plan, n_prob, accumulate, option);
+  constexpr int NSLOT = ring_slots(BM, NB * BN, WAVES_M * WAVES_N);
+  MODSE_RING(BM, NB * BN, NSLOT);
+  gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, NSLOT, EPI, LAYOUT>(plan, n_prob, accumulate, option, blockIdx.x, ring);
 }
 // tiles of 32 or 64 rows (decode-sized batches and experts with few tokens), under a name of their own for profiles
 template <int BM, int BN, int NB, int WAVES_M, int WAVES_N, int EPI, int LAYOUT>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_skinny_kernel(const GemmPlan* __restrict__ plan, int n_prob,
                                                                                 int accumulate, int option) {
-  gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, ring_slots(BM, NB * BN, WAVES_M * WAVES_N), EPI, LAYOUT>(plan, n_prob, accumulate, option);
+  constexpr int NSLOT = ring_slots(BM, NB * BN, WAVES_M * WAVES_N);
+  MODSE_RING(BM, NB * BN, NSLOT);
+  gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, NSLOT, EPI, LAYOUT>(plan, n_prob, accumulate, option, blockIdx.x, ring);
 }
+#undef MODSE_RING
 
 }  // namespace modse_gemm
