@@ -16,6 +16,7 @@ typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -180,10 +181,13 @@ struct DxRows {
   const float* slabs;
   int32_t kchunk;
 };
+// neither optional part of the gate takes part in the backward pass: launch_bwd_prep leaves the gradient of the logits
+bool bwd_gate_is_plain(const LayerDims& L, const GateExtPtrs* G, float aux_grad);
+// dwg_done: the shares of the router's weight gradient are there (launch_dx_wgrad)
 hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const DxRows& rows,
                              const float* dg, const RoutingPtrs& R, const GateExtPtrs* G, float aux_grad,
                              const BwdRouterBufs& B, void* dX, float* dW_gate, float* dW_noise, float* dgamma,
-                             int accumulate, hipStream_t s);
+                             int accumulate, bool dwg_done, hipStream_t s);
 
 // gemm.hip
 struct TileShape {
@@ -199,10 +203,11 @@ enum GemmOption {
 hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int n_prob, int accumulate,
                                int option, int64_t max_tiles, hipStream_t s, int layout = -1);
 
-// dX and the weight gradients in one launch, for float32 layers of small tiles
+// dX, the weight gradients and (dwg, may be null) the shares of the router's in one launch, for float32 layers of small tiles
+struct DwgArgs;
 bool dx_wgrad_in_one_launch(modse_dtype dt, TileShape dx_tile, TileShape wg_tile);
 hipError_t launch_dx_wgrad(TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, const GemmPlan* wg, int n_wg,
-                           int64_t wg_tiles, int accumulate, int option, hipStream_t s);
+                           int64_t wg_tiles, int accumulate, int option, const DwgArgs* dwg, hipStream_t s);
 
 struct FwdPlanArgs {
   const void *Xp, *W1, *W3, *W2;

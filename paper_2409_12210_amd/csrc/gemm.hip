@@ -117,11 +117,14 @@ bool dx_wgrad_in_one_launch(modse_dtype dt, TileShape dx_tile, TileShape wg_tile
   return dt == MODSE_F32 && dx_tile.bm <= 64 && wg_tile.bm == 64;
 }
 hipError_t launch_dx_wgrad(TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, const GemmPlan* wg, int n_wg,
-                           int64_t wg_tiles, int accumulate, int option, hipStream_t s) {
+                           int64_t wg_tiles, int accumulate, int option, const DwgArgs* dwg, hipStream_t s) {
   const int64_t dx_blocks = block_grid(dx_tiles);
-  const dim3 grid((unsigned)(dx_blocks + block_grid(wg_tiles))), block(256);
+  const DwgArgs w = dwg ? *dwg : DwgArgs{};
+  const int n_dwg = dwg ? dwg_blocks(w) : 0;
+  const dim3 grid((unsigned)(n_dwg + dx_blocks + block_grid(wg_tiles))), block(256);
 #define MODSE_LAUNCH_DX_WGRAD(TILE, EPI)                                                                                          \
-  hipLaunchKernelGGL((gg_f32_dx_wgrad_kernel<TILE, EPI>), grid, block, 0, s, dx, n_dx, (int)dx_blocks, wg, n_wg, accumulate, option)
+  hipLaunchKernelGGL((gg_f32_dx_wgrad_kernel<TILE, EPI>), grid, block, 0, s, w, n_dwg, dx, n_dx, (int)dx_blocks, wg, n_wg, accumulate, \
+                     option)
   if (dx_tile.bm == 32) MODSE_LAUNCH_DX_WGRAD(32, EPI_STORE_DUALK);  // (never split)
   else if (dx_split) MODSE_LAUNCH_DX_WGRAD(64, EPI_STORE_F32);
   else MODSE_LAUNCH_DX_WGRAD(64, EPI_STORE_DUALK);

@@ -8,6 +8,7 @@
 #include <climits>
 #include <type_traits>
 
+#include "bwd_dwg.h"
 #include "common.h"
 #include "gemm_plan.h"
 
@@ -16,7 +17,6 @@ namespace {
 constexpr int TPB = MODSE_ROUTE_TOKENS_PER_BLOCK;  // tokens per block
 constexpr int ROUTE_THREADS = 256;
 constexpr int ROUTER_TOKEN_MAX_T = 4096;  // plain-gate batches up to this size take a token router (one or four per block)
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 __device__ inline double shfl_xor_f64(double v, int mask) {
@@ -129,28 +129,6 @@ __device__ inline bool write_gate(const TopPick& p, int t, int N, int top_k, int
 }
 
 // ---------------------------------------------------------------- the router's dot products
-
-// eight consecutive elements as loaded, and element i of them as float
-template <typename T>
-struct Raw8;
-template <>
-struct Raw8<bf16_t> {
-  u32x4 v;
-  __device__ void load(const bf16_t* p) { v = *reinterpret_cast<const u32x4*>(p); }
-  __device__ float get(int i) const {
-    const uint32_t w = v[i >> 1];
-    return __uint_as_float((i & 1) ? (w & 0xffff0000u) : (w << 16));
-  }
-};
-template <>
-struct Raw8<float> {
-  f32x4 a, b;
-  __device__ void load(const float* p) {
-    a = *reinterpret_cast<const f32x4*>(p);
-    b = *reinterpret_cast<const f32x4*>(p + 4);
-  }
-  __device__ float get(int i) const { return i < 4 ? a[i] : b[i - 4]; }
-};
 
 // Row r of the LDS copy of W_gate that router_stream_kernel keeps: elements of type W (double when the matrix
 // fits that way, else float), NE per row; the eight rows of one lane and step lie together, followed by 16
@@ -1980,7 +1958,6 @@ __global__ __launch_bounds__(256) void bwd_gate_rows_kernel(const T* __restrict_
   else row(std::false_type{});
 }
 
-constexpr int BR_SLAB = 512, BR_TOK = 32;  // columns of d that a wave (eight per lane) owns; tokens per block and step
 static_assert(BR_TOK == MODSE_ROUTE_TOKENS_PER_BLOCK, "the workspace holds one partial gradient per 32-token block");
 struct BwdRouterArgs {
   const void *Wg, *Wn;        // [d, N]; Wn null: no noise term
@@ -2071,93 +2048,10 @@ __global__ __launch_bounds__(256) void bwd_gate_rows_ext_kernel(BwdRouterArgs a,
   }
 }
 
-// partial[chunk][m][c][e] = sum over the chunk's tokens of x[t][c] dl[t][e] (m = 1: du), reduced over the chunks by
-// dwg_reduce_kernel.  A block owns a slab, eight columns e and `tok` tokens, a quarter of them per wave.  A lane keeps its 8
-// x 8 slice of the sum in registers; one load brings dl of eight tokens, which go to scalar registers; dl and the rows of the
-// next batch of tokens are on their way during the arithmetic of one, without any barrier; at the end the waves' sums
-// meet in LDS in a fixed order.
 template <typename T>
-__global__ __launch_bounds__(256, 3) void bwd_dwg_kernel(BwdRouterArgs a, const T* __restrict__ x, int tok,
-                                                         float* __restrict__ partial) {
-  constexpr int TB = sizeof(T) == 2 ? 8 : 4;
-  __shared__ float s_sum[2][64][64];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int d = a.d, N = a.N, c = blockIdx.y * BR_SLAB + lane * 8, cl = min(c, d - 8);
-  const int groups = (N + 7) / 8, m = blockIdx.z / groups, e0 = blockIdx.z % groups * 8, ne = min(8, N - e0);
-  const float* const dl = (m ? a.du : a.dl) + e0;
-  float acc[8][8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[q][e] = 0.f;
-  const int per = tok / 4, t0 = blockIdx.x * tok + wave * per, t1 = min(t0 + per, a.ntok);
-  Raw8<T> cur[TB], nxt[TB];
-  auto fetch = [&](Raw8<T> (&r)[TB], int t) {  // (tokens beyond the last repeat it; their dl is zero)
-#pragma unroll
-    for (int u = 0; u < TB; ++u) r[u].load(x + (size_t)min(t + u, a.ntok - 1) * d + cl);
-  };
-  auto fetch_dl = [&](int t) -> float {  // lane 8 u + e: token t + u, column e0 + e
-    const int u = lane >> 3, e = lane & 7;
-    const float v = dl[(size_t)min(t + u, a.ntok - 1) * N + min(e, ne - 1)];
-    return e < ne && t + u < t1 ? v : 0.f;
-  };
-  float dcur = 0.f;
-  if (t0 < t1) {
-    fetch(cur, t0);
-    dcur = fetch_dl(t0);
-  }
-#pragma unroll 1
-  for (int t = t0; t < t1; t += TB) {
-    fetch(nxt, t + TB);
-    const float dnxt = fetch_dl(t + TB);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < TB; ++u) {
-      float dv[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dv[e] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(dcur), u * 8 + e));
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const float xv = cur[u].get(q);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[q][e] = fmaf(xv, dv[e], acc[q][e]);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < TB; ++u) cur[u] = nxt[u];
-    dcur = dnxt;
-  }
-  // waves 2 and 3 hand their sums to waves 0 and 1, then wave 1 its own to wave 0
-#pragma unroll
-  for (int half = 2; half >= 1; half >>= 1) {
-    if (wave >= half && wave < 2 * half) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s_sum[wave - half][q * 8 + e][lane] = acc[q][e];
-    }
-    __syncthreads();
-    if (wave < half) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[q][e] += s_sum[wave][q * 8 + e][lane];
-    }
-    __syncthreads();
-  }
-  if (wave != 0 || c >= d) return;
-  float* const out = partial + (((size_t)blockIdx.x * (a.NP / N) + m) * d + c) * N + e0;
-  if (N == 8) {  // the lane's 8 x 8 block is 256 consecutive bytes
-#pragma unroll
-    for (int q = 0; q < 8; ++q) store8(out + q * 8, acc[q]);
-  } else {
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (e < ne) out[(size_t)q * N + e] = acc[q][e];
-  }
+__global__ __launch_bounds__(256, 3) void bwd_dwg_kernel(DwgArgs a) {
+  __shared__ DwgSums s_sum;
+  bwd_dwg_block<T, sizeof(T) == 2 ? 8 : 4>(a, blockIdx.x, s_sum);
 }
 
 // [d, N] -> [d, NE] with zero columns behind the N real ones
@@ -2381,7 +2275,7 @@ hipError_t bwd_prep_typed(const LayerDims& L, const void* dY, const void* O, con
 template <typename T>
 hipError_t bwd_router_typed(const LayerDims& L, const GateExtPtrs& G, float aux_coef, const void* xv, const void* Wv,
                             const DxRows& rows, const float* dg, const RoutingPtrs& R, const BwdRouterBufs& B, void* dXv,
-                            float* dW_gate, float* dW_noise, float* dgamma, int accumulate, hipStream_t s) {
+                            float* dW_gate, float* dW_noise, float* dgamma, int accumulate, bool dwg_done, hipStream_t s) {
   const T *x = static_cast<const T*>(xv), *W = static_cast<const T*>(Wv), *dXp = static_cast<const T*>(rows.dXp);
   T* const dX = static_cast<T*>(dXv);
   const bool noise = G.W_noise != nullptr, sparse = gate_is_plain(G, aux_coef);  // dl is zero but for the chosen experts
@@ -2395,12 +2289,12 @@ hipError_t bwd_router_typed(const LayerDims& L, const GateExtPtrs& G, float aux_
   const int nmat = noise ? 2 : 1, slabs = (L.d + BR_SLAB - 1) / BR_SLAB, nb = (L.T + BR_TOK - 1) / BR_TOK;
   const BwdRouterArgs a = {W, G.W_noise, B.dl, B.du, L.T, L.d, L.N, nmat * L.N, L.k, R.row_of};
   // dX comes last: its buffer may be x's (nothing after the weight gradients reads x).
-  // about 512 blocks: fewer, longer chunks mean fewer partial gradients (two matrices: room for half as many)
-  const int groups = (L.N + 7) / 8 * nmat;
-  const int tok = std::max(nmat, std::min(16, nb * slabs * groups / 512)) * BR_TOK, nchunk = (L.T + tok - 1) / tok;
-  hipLaunchKernelGGL((bwd_dwg_kernel<T>), dim3(nchunk, slabs, groups), dim3(256), 0, s, a, x, tok, B.dW_partial);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const DwgReduceArgs red = {B.dW_partial, nchunk, L.d * L.N, nmat, B.dgamma_part, nbt, accumulate, dW_gate, dW_noise, dgamma};
+  const DwgArgs w = dwg_args(L, x, B, nmat);
+  if (!dwg_done) {
+    hipLaunchKernelGGL((bwd_dwg_kernel<T>), dim3(dwg_blocks(w)), dim3(256), 0, s, w);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  const DwgReduceArgs red = {B.dW_partial, w.nchunk, L.d * L.N, nmat, B.dgamma_part, nbt, accumulate, dW_gate, dW_noise, dgamma};
   const int nred = dwg_reduce_blocks(red);
   if (sparse) {
     const dim3 grid((unsigned)(((long)L.T * (L.d / 8) + 255) / 256 + nred));
@@ -2477,12 +2371,14 @@ hipError_t launch_combine_split(const LayerDims& L, modse_dtype dt, const float*
   return hipGetLastError();
 }
 
+bool bwd_gate_is_plain(const LayerDims& L, const GateExtPtrs* G, float aux_grad) {
+  return !G || gate_is_plain(*G, aux_coefficient(L, *G, aux_grad));
+}
+
 hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, const void* O, const RoutingPtrs& R,
                            void* dO, float* dg, const BwdPlanArgs& plan, const GateExtPtrs* G, float aux_grad,
                            const void* W_gate, const BwdRouterBufs& B, hipStream_t s) {
-  const GateExtPtrs none = {};
-  const GateExtPtrs& g = G ? *G : none;
-  const bool plain = gate_is_plain(g, aux_coefficient(L, g, aux_grad));
+  const bool plain = bwd_gate_is_plain(L, G, aux_grad);
   return dt == MODSE_F32 ? bwd_prep_typed<float>(L, dY, O, R, dO, dg, plan, plain, W_gate, B, s)
                          : bwd_prep_typed<bf16_t>(L, dY, O, R, dO, dg, plan, plain, W_gate, B, s);
 }
@@ -2490,12 +2386,12 @@ hipError_t launch_bwd_prep(const LayerDims& L, modse_dtype dt, const void* dY, c
 hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const DxRows& rows,
                              const float* dg, const RoutingPtrs& R, const GateExtPtrs* G, float aux_grad,
                              const BwdRouterBufs& B, void* dX, float* dW_gate, float* dW_noise, float* dgamma,
-                             int accumulate, hipStream_t s) {
+                             int accumulate, bool dwg_done, hipStream_t s) {
   const GateExtPtrs none = {};
   const GateExtPtrs& g = G ? *G : none;
   const float aux_coef = aux_coefficient(L, g, aux_grad);
   return dt == MODSE_F32 ? bwd_router_typed<float>(L, g, aux_coef, x, W_gate, rows, dg, R, B, dX, dW_gate, dW_noise, dgamma,
-                                                   accumulate, s)
+                                                   accumulate, dwg_done, s)
                          : bwd_router_typed<bf16_t>(L, g, aux_coef, x, W_gate, rows, dg, R, B, dX, dW_gate, dW_noise, dgamma,
-                                                    accumulate, s);
+                                                    accumulate, dwg_done, s);
 }
