@@ -84,9 +84,14 @@ hipError_t launch_block(int epilogue, int layout, TileShape t, const GemmPlan* p
     case EPI_STORE: return run_block_tile<T, EPI_STORE, LAYOUT_TN>(t, plan, n_prob, accumulate, option, max_tiles, s);
     case EPI_SWIGLU: return run_block_tile<T, EPI_SWIGLU, LAYOUT_TN>(t, plan, n_prob, accumulate, option, max_tiles, s);
     case EPI_SWIGLU_BWD: return run_block_tile<T, EPI_SWIGLU_BWD, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
-    case EPI_STORE_DUALK: return run_block_tile<T, EPI_STORE_DUALK, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
+    case EPI_STORE_DUALK:
+      if constexpr (std::is_same_v<T, float>) return run_block_tile<T, EPI_STORE_DUALK, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
+      else return hipErrorInvalidValue;  // (launch_dx_dwg)
     case EPI_STORE_F32:
-      if (layout == LAYOUT_B_KN) return run_block_tile<T, EPI_STORE_F32, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
+      if (layout == LAYOUT_B_KN) {
+        if constexpr (std::is_same_v<T, float>) return run_block_tile<T, EPI_STORE_F32, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
+        else return hipErrorInvalidValue;
+      }
       if (layout == LAYOUT_TN) return run_block_tile<T, EPI_STORE_F32, LAYOUT_TN>(t, plan, n_prob, accumulate, option, max_tiles, s);
       return run_block_tile<T, EPI_STORE_F32, LAYOUT_AB_K>(t, plan, n_prob, accumulate, option, max_tiles, s);
   }
@@ -111,6 +116,21 @@ hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const 
       return run_bf16<256, 256, 1, 4, 2, EPI_STORE_F32, LAYOUT_AB_K>(plan, n_prob, accumulate, option, max_tiles, s);
   }
   return hipErrorInvalidValue;
+}
+
+bool dx_dwg_in_one_launch(modse_dtype dt, TileShape dx_tile) { return dt == MODSE_BF16 && dx_tile.bm <= 128; }
+hipError_t launch_dx_dwg(TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, int option, const DwgArgs* dwg,
+                         hipStream_t s) {
+  const int64_t dx_blocks = block_grid(dx_tiles);
+  const DwgArgs w = dwg ? *dwg : DwgArgs{};
+  const dim3 grid((unsigned)(dx_blocks + (dwg ? dwg_blocks(w) : 0))), block(256);
+#define MODSE_LAUNCH_DX(TILE, EPI) hipLaunchKernelGGL((gg_bf16_dx_kernel<TILE, EPI>), grid, block, 0, s, dx, n_dx, option, (int)dx_blocks, w)
+  if (dx_tile.bm == 128 && dx_split) MODSE_LAUNCH_DX(128, EPI_STORE_F32);
+  else if (dx_tile.bm == 128) MODSE_LAUNCH_DX(128, EPI_STORE_DUALK);
+  else if (dx_split) MODSE_LAUNCH_DX(64, EPI_STORE_F32);
+  else MODSE_LAUNCH_DX(64, EPI_STORE_DUALK);
+#undef MODSE_LAUNCH_DX
+  return hipGetLastError();
 }
 
 bool dx_wgrad_in_one_launch(modse_dtype dt, TileShape dx_tile, TileShape wg_tile) {
