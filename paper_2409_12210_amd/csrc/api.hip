@@ -563,26 +563,24 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   const int n_dx = pa.dx_kchunk ? split_problems(L, pa.dx_kchunk, 2) : L.N, wg_option = stream ? GEMM_STREAM_C : 0;
   const int64_t dx_tiles =
       pa.dx_kchunk ? split_tiles_bound(L, pa.dx_tile, pa.dx_kchunk, 2) : tiles_bound(L, pa.dx_tile, false);
-  // the router's weight gradient of a plain gate goes with one of these launches
-  const bool plain = bwd_gate_is_plain(L, ext ? &G : nullptr, aux_grad);
-  const DwgArgs dwg = dwg_args(L, x, rb, 1);
-  bool dwg_done = false;
-  if (dx_wgrad_in_one_launch(dt, pa.dx_tile, pa.wg_tile)) {
-    stamp.mark(MODSE_STAGE_BWD_DGRAD);  // (dX counts with the weight gradients)
-    HIP_TRY(launch_dx_wgrad(pa.dx_tile, pa.dx_kchunk != 0, pa.dx, n_dx, dx_tiles, pa.wg, 3 * L.N, wgrad_tiles(L, pa.wg_tile), accumulate,
-                            wg_option, plain ? &dwg : nullptr, s));
-    dwg_done = plain;
+  const int64_t wg_tiles = wgrad_tiles(L, pa.wg_tile);
+  const int dx_option = spread(L, dt, pa.dx_tile);
+  const bool wg_beside = wgrad_beside_dx(dt, pa.dx_tile, pa.wg_tile);
+  // (of a plain gate: the gradient of the logits is there)
+  const bool dwg_done = dwg_beside_dx(dt, pa.dx_tile, pa.wg_tile) && bwd_gate_is_plain(L, ext ? &G : nullptr, aux_grad);
+  if (wg_beside) stamp.mark(MODSE_STAGE_BWD_DGRAD);  // (dX counts with the weight gradients)
+  if (dwg_beside_dx(dt, pa.dx_tile, pa.wg_tile)) {
+    const DwgArgs dwg = dwg_args(L, x, rb, 1);
+    HIP_TRY(launch_dx(dt, pa.dx_tile, pa.dx_kchunk != 0, pa.dx, n_dx, dx_tiles, dx_option, wg_beside ? pa.wg : nullptr, 3 * L.N, wg_tiles,
+                      accumulate, wg_option, dwg_done ? &dwg : nullptr, s));
+  } else if (pa.dx_kchunk) {
+    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.dx_tile, pa.dx, n_dx, 0, dx_option, dx_tiles, s, LAYOUT_B_KN));
   } else {
-    if (dx_dwg_in_one_launch(dt, pa.dx_tile)) {
-      HIP_TRY(launch_dx_dwg(pa.dx_tile, pa.dx_kchunk != 0, pa.dx, n_dx, dx_tiles, spread(L, dt, pa.dx_tile), plain ? &dwg : nullptr, s));
-      dwg_done = plain;
-    } else if (pa.dx_kchunk) {
-      HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.dx_tile, pa.dx, n_dx, 0, spread(L, dt, pa.dx_tile), dx_tiles, s, LAYOUT_B_KN));
-    } else {
-      HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, n_dx, 0, spread(L, dt, pa.dx_tile), dx_tiles, s));
-    }
+    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, n_dx, 0, dx_option, dx_tiles, s));
+  }
+  if (!wg_beside) {
     stamp.mark(MODSE_STAGE_BWD_DGRAD);
-    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, 3 * L.N, accumulate, wg_option, wgrad_tiles(L, pa.wg_tile), s));
+    HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, 3 * L.N, accumulate, wg_option, wg_tiles, s));
   }
   stamp.mark(MODSE_STAGE_BWD_WGRAD);
 

@@ -203,15 +203,13 @@ enum GemmOption {
 hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const GemmPlan* plan, int n_prob, int accumulate,
                                int option, int64_t max_tiles, hipStream_t s, int layout = -1);
 
-// dX and (dwg, may be null) the shares of the router's weight gradient in one launch, for bf16 layers of small tiles
+// Layers of small tiles: dX and, in the same launch, the weight gradients (wg, null where wgrad_beside_dx says no) and the shares of the
+// router's (dwg, may be null).  Float32 ones come with the weight gradients or not at all (dwg_beside_dx).
 struct DwgArgs;
-bool dx_dwg_in_one_launch(modse_dtype dt, TileShape dx_tile);
-hipError_t launch_dx_dwg(TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, int option, const DwgArgs* dwg,
-                         hipStream_t s);
-// dX, the weight gradients and (dwg, may be null) the shares of the router's in one launch, for float32 layers of small tiles
-bool dx_wgrad_in_one_launch(modse_dtype dt, TileShape dx_tile, TileShape wg_tile);
-hipError_t launch_dx_wgrad(TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, const GemmPlan* wg, int n_wg,
-                           int64_t wg_tiles, int accumulate, int option, const DwgArgs* dwg, hipStream_t s);
+bool dwg_beside_dx(modse_dtype dt, TileShape dx_tile, TileShape wg_tile);
+bool wgrad_beside_dx(modse_dtype dt, TileShape dx_tile, TileShape wg_tile);
+hipError_t launch_dx(modse_dtype dt, TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, int dx_option,
+                     const GemmPlan* wg, int n_wg, int64_t wg_tiles, int accumulate, int wg_option, const DwgArgs* dwg, hipStream_t s);
 
 struct FwdPlanArgs {
   const void *Xp, *W1, *W3, *W2;

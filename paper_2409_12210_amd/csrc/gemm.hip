@@ -86,14 +86,14 @@ hipError_t launch_block(int epilogue, int layout, TileShape t, const GemmPlan* p
     case EPI_SWIGLU_BWD: return run_block_tile<T, EPI_SWIGLU_BWD, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
     case EPI_STORE_DUALK:
       if constexpr (std::is_same_v<T, float>) return run_block_tile<T, EPI_STORE_DUALK, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
-      else return hipErrorInvalidValue;  // (launch_dx_dwg)
+        else return hipErrorInvalidValue;  // (launch_dx)
     case EPI_STORE_F32:
       if (layout == LAYOUT_B_KN) {
         if constexpr (std::is_same_v<T, float>) return run_block_tile<T, EPI_STORE_F32, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
         else return hipErrorInvalidValue;
       }
       if (layout == LAYOUT_TN) return run_block_tile<T, EPI_STORE_F32, LAYOUT_TN>(t, plan, n_prob, accumulate, option, max_tiles, s);
-      return run_block_tile<T, EPI_STORE_F32, LAYOUT_AB_K>(t, plan, n_prob, accumulate, option, max_tiles, s);
+      return run_block_tile<T, EPI_STORE_F32, LAYOUT_AB_K>(t, plan, n_prob, accumulate, option, max_tiles, s);  // (bf16: where dX has 256-row tiles)
   }
   return hipErrorInvalidValue;
 }
@@ -118,36 +118,35 @@ hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const 
   return hipErrorInvalidValue;
 }
 
-bool dx_dwg_in_one_launch(modse_dtype dt, TileShape dx_tile) { return dt == MODSE_BF16 && dx_tile.bm <= 128; }
-hipError_t launch_dx_dwg(TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, int option, const DwgArgs* dwg,
-                         hipStream_t s) {
-  const int64_t dx_blocks = block_grid(dx_tiles);
-  const DwgArgs w = dwg ? *dwg : DwgArgs{};
-  const dim3 grid((unsigned)(dx_blocks + (dwg ? dwg_blocks(w) : 0))), block(256);
-#define MODSE_LAUNCH_DX(TILE, EPI) hipLaunchKernelGGL((gg_bf16_dx_kernel<TILE, EPI>), grid, block, 0, s, dx, n_dx, option, (int)dx_blocks, w)
-  if (dx_tile.bm == 128 && dx_split) MODSE_LAUNCH_DX(128, EPI_STORE_F32);
-  else if (dx_tile.bm == 128) MODSE_LAUNCH_DX(128, EPI_STORE_DUALK);
-  else if (dx_split) MODSE_LAUNCH_DX(64, EPI_STORE_F32);
-  else MODSE_LAUNCH_DX(64, EPI_STORE_DUALK);
-#undef MODSE_LAUNCH_DX
-  return hipGetLastError();
+bool dwg_beside_dx(modse_dtype dt, TileShape dx_tile, TileShape wg_tile) {
+  return dt == MODSE_F32 ? dx_tile.bm <= 64 && wg_tile.bm == 64 : dx_tile.bm <= 128;
 }
-
-bool dx_wgrad_in_one_launch(modse_dtype dt, TileShape dx_tile, TileShape wg_tile) {
-  return dt == MODSE_F32 && dx_tile.bm <= 64 && wg_tile.bm == 64;
+bool wgrad_beside_dx(modse_dtype dt, TileShape dx_tile, TileShape wg_tile) {
+  return dwg_beside_dx(dt, dx_tile, wg_tile) && wg_tile.bm <= 128;
 }
-hipError_t launch_dx_wgrad(TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, const GemmPlan* wg, int n_wg,
-                           int64_t wg_tiles, int accumulate, int option, const DwgArgs* dwg, hipStream_t s) {
-  const int64_t dx_blocks = block_grid(dx_tiles);
+hipError_t launch_dx(modse_dtype dt, TileShape dx_tile, bool dx_split, const GemmPlan* dx, int n_dx, int64_t dx_tiles, int dx_option,
+                     const GemmPlan* wg, int n_wg, int64_t wg_tiles, int accumulate, int wg_option, const DwgArgs* dwg, hipStream_t s) {
+  const int64_t dx_blocks = block_grid(dx_tiles), wg_blocks = wg ? block_grid(wg_tiles) : 0;
   const DwgArgs w = dwg ? *dwg : DwgArgs{};
   const int n_dwg = dwg ? dwg_blocks(w) : 0;
-  const dim3 grid((unsigned)(n_dwg + dx_blocks + block_grid(wg_tiles))), block(256);
-#define MODSE_LAUNCH_DX_WGRAD(TILE, EPI)                                                                                          \
+  const dim3 grid((unsigned)(n_dwg + dx_blocks + wg_blocks)), block(256);
+#define MODSE_LAUNCH_F32(TILE, EPI)                                                                                               \
   hipLaunchKernelGGL((gg_f32_dx_wgrad_kernel<TILE, EPI>), grid, block, 0, s, w, n_dwg, dx, n_dx, (int)dx_blocks, wg, n_wg, accumulate, \
-                     option)
-  if (dx_tile.bm == 32) MODSE_LAUNCH_DX_WGRAD(32, EPI_STORE_DUALK);  // (never split)
-  else if (dx_split) MODSE_LAUNCH_DX_WGRAD(64, EPI_STORE_F32);
-  else MODSE_LAUNCH_DX_WGRAD(64, EPI_STORE_DUALK);
-#undef MODSE_LAUNCH_DX_WGRAD
+                     wg_option)
+#define MODSE_LAUNCH_BF16(TILE, EPI)                                                                                             \
+  hipLaunchKernelGGL((gg_bf16_dx_kernel<TILE, EPI>), grid, block, 0, s, dx, n_dx, dx_option, (int)dx_blocks, w, n_dwg, wg, n_wg, \
+                     accumulate, wg_option)
+  if (dt == MODSE_F32) {
+    if (dx_tile.bm == 32) MODSE_LAUNCH_F32(32, EPI_STORE_DUALK);  // (never split)
+    else if (dx_split) MODSE_LAUNCH_F32(64, EPI_STORE_F32);
+    else MODSE_LAUNCH_F32(64, EPI_STORE_DUALK);
+  } else {
+    if (dx_tile.bm == 128 && dx_split) MODSE_LAUNCH_BF16(128, EPI_STORE_F32);
+    else if (dx_tile.bm == 128) MODSE_LAUNCH_BF16(128, EPI_STORE_DUALK);
+    else if (dx_split) MODSE_LAUNCH_BF16(64, EPI_STORE_F32);
+    else MODSE_LAUNCH_BF16(64, EPI_STORE_DUALK);
+  }
+#undef MODSE_LAUNCH_F32
+#undef MODSE_LAUNCH_BF16
   return hipGetLastError();
 }

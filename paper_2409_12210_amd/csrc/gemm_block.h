@@ -566,15 +566,24 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_skinny_kerne
   MODSE_RING(BM, NB * BN, NSLOT);
   gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, NSLOT, EPI, LAYOUT>(plan, n_prob, accumulate, option, blockIdx.x, ring);
 }
-// dX in tiles of 64 or 128 rows; the workgroups behind its `dx_blocks` take the router's weight gradient (of a plain gate), which needs
-// nothing from dX: two micro-batches of 1021 tokens, d = 2048, 1861 -> 1846 us.
+// The same for bf16, dX in tiles of 64 or 128 rows: the n_dwg workgroups behind its `dx_blocks` take the router's weight gradient (of a
+// plain gate; two micro-batches of 1021 tokens, d = 2048, 1861 -> 1846 us with that alone), and if the weight gradients have
+// 128-row tiles, too, they follow: training passes at d = 1024, eight experts of mean width 1024, 512 / 2048 tokens 113 -> 108 / 207 ->
+// 191 us; d = 2048, four experts of 1408, 1024 tokens 243 -> 212.
 template <int BM, int EPI>
-__global__ __launch_bounds__(256, 2) void gg_bf16_dx_kernel(const GemmPlan* __restrict__ plan, int n_prob, int option, int dx_blocks, DwgArgs dwg) {
-  constexpr int NSLOT = ring_slots(BM, 128, 4);
-  MODSE_RING(BM, 128, NSLOT);
-  static_assert(sizeof(DwgSums) <= ring_bytes(BM, 128, NSLOT), "one piece of LDS for both");
-  if ((int)blockIdx.x < dx_blocks) gg_block<bf16_t, BM, 128, 1, 2, 2, NSLOT, EPI, LAYOUT_B_KN>(plan, n_prob, 0, option, blockIdx.x, ring);
-  else bwd_dwg_block<bf16_t, 8>(dwg, blockIdx.x - dx_blocks, *reinterpret_cast<DwgSums*>(ring));
+__global__ __launch_bounds__(256, 2) void gg_bf16_dx_kernel(const GemmPlan* __restrict__ dx, int n_dx, int dx_option, int dx_blocks,
+                                                            DwgArgs dwg, int n_dwg, const GemmPlan* __restrict__ wg, int n_wg,
+                                                            int accumulate, int wg_option) {
+  constexpr int NSLOT = ring_slots(BM, 128, 4), WG_SLOTS = ring_slots(128, 128, 4);
+  MODSE_RING(128, 128, WG_SLOTS);
+  static_assert(sizeof(DwgSums) <= sizeof(ring) && ring_bytes(BM, 128, NSLOT) <= sizeof(ring), "one piece of LDS for all");
+  const int block = (int)blockIdx.x - dx_blocks;
+  if (block < 0)
+    gg_block<bf16_t, BM, 128, 1, 2, 2, NSLOT, EPI, LAYOUT_B_KN>(dx, n_dx, 0, dx_option, blockIdx.x, ring);
+  else if (block < n_dwg)
+    bwd_dwg_block<bf16_t, 8>(dwg, block, *reinterpret_cast<DwgSums*>(ring));
+  else
+    gg_block<bf16_t, 128, 128, 1, 2, 2, WG_SLOTS, EPI_STORE_F32, LAYOUT_AB_K>(wg, n_wg, accumulate, wg_option, block - n_dwg, ring);
 }
 #undef MODSE_RING
 
