@@ -880,9 +880,10 @@ __global__ __launch_bounds__(SC_THREADS, 4) void router_screen_kernel(const bf16
     double l = 0.0;
 #pragma unroll
     for (int w = 0; w < SC_WAVES / 2; ++w) l += (double)s.part.l[w][tl][c];
-    if (bias && e < N) l += (double)bias[e];
-    const double err = gamma * ((double)(s.part.x2[0][tl] * s.part.w2[0][c]) + d * 0x1p-32) + 1e-12, lo = e < N ? l - err : -INFINITY;
-    hi[i] = l + err;
+    const double err = gamma * ((double)(s.part.x2[0][tl] * s.part.w2[0][c]) + d * 0x1p-32) + 1e-12;
+    const double b = bias && e < N ? (double)bias[e] : 0.0;
+    const double lo = e < N ? (l - err) + b : -INFINITY;  // (rounded as the exact logit will be: a bias may be so large that this matters)
+    hi[i] = (l + err) + b;
     if (lo > m1) {
       m2 = m1;
       m1 = lo;

@@ -79,3 +79,24 @@ def test_huge_matrix_values():
     scratch = _scratch_bytes(n, d, T)
     want, got = _route(layer, x, W, None, scratch), _route(layer, x, W, None, scratch + n * d * 2)
     assert torch.equal(got.topk_idx, want.topk_idx) and torch.equal(got.near_tie_count, want.near_tie_count)
+
+
+def _both(layer, x, W, bias):
+    n, d, T = len(layer[1]), layer[0], layer[4]
+    scratch = _scratch_bytes(n, d, T)
+    return _route(layer, x, W, bias, scratch), _route(layer, x, W, bias, scratch + n * d * 2)
+
+
+def test_bias_whose_rounding_exceeds_the_error_bound():
+    # beside a bias of 1e14 logits are multiples of 2^-6.  Expert 0's dot product is 2^-7 + 2^-40, which rounds up and so ties with
+    # the others; float32 sums lose the 2^-40, and 2^-7 rounds down
+    d, n, T = 1024, 64, 2050
+    x = torch.zeros((T, d), device="cuda", dtype=torch.bfloat16)
+    x[:, [0, 256, 512, 513]] = 1
+    W = torch.zeros((d, n), device="cuda", dtype=torch.bfloat16)
+    W[513, 1:] = 0.01
+    W[0, 0], W[256, 0], W[512, 0], W[513, 0] = 1, 2.0 ** -40, -1, 2.0 ** -7
+    want, got = _both((d, (32,) * n, 2, "bf16", T), x, W, torch.full((n,), 1e14, device="cuda"))
+    assert (want.topk_idx.view(T, 2) == torch.tensor([0, 1], device="cuda")).all()
+    for f in ("topk_idx", "counts", "offsets", "row_of", "src_of", "near_tie_count"):
+        assert torch.equal(getattr(got, f), getattr(want, f)), f
