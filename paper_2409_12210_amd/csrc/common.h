@@ -153,6 +153,25 @@ struct FwdPlanArgs;
 // MODSE_PERMUTE_FUSED_MAX_T tokens do all of this in one launch)
 hipError_t launch_permute(const LayerDims& L, modse_dtype dt, const void* x, const RoutingPtrs& R, const RouteBufs& B,
                           void* Xp, const GateExtPtrs* G, const FwdPlanArgs* plan, hipStream_t s);
+// Beyond MODSE_PERMUTE_FUSED_MAX_T tokens: the permutation in one launch over the block histograms (permute_hist_kernel), whose cost
+// grows with the square of the batch, or a scan and a scatter.  Routing call, one launch / two, us (d = 256, top 2):
+//   experts    8192 tokens    12288          16128         32768
+//         8    14.1 / 15.2    17.9 / 15.3    19.4 / 15.5   33.0 / 21.1     (116000 tokens 141 / 59)
+//        32    17.8 / 19.5    24.9 / 23.4    25.2 / 24.7   49.8 / 38.5
+//        64    20.0 / 23.8    27.1 / 30.7    28.7 / 32.0
+// Up to 8192 tokens every block has a CU to itself.  Beyond, counting for many experts pays, or work beside it: the rows that a
+// layer call copies.  Layer call with experts of 32 columns, 64 experts, d = 2048, 12000 tokens 167 / 176; 36 experts, d = 256, 12000
+// tokens 52.4 / 53.5, 16384 63 / 62; 8 experts, d = 2048, 16384 tokens 182 / 187, 32768 355 / 367, 49152 527 / 525; 8 experts, d =
+// 256, 16128 tokens 47.3 / 45.2; top 1 of 20, d = 2048, 20000 tokens 174 / 169.
+constexpr int PERMUTE_HIST_MAX = 32768;
+inline bool permute_by_hist(const LayerDims& L, size_t elem_size, bool with_rows) {
+  const int64_t nb = ((int64_t)L.T + MODSE_ROUTE_TOKENS_PER_BLOCK - 1) / MODSE_ROUTE_TOKENS_PER_BLOCK;
+  if (nb * (L.N + 1) > PERMUTE_HIST_MAX) return false;
+  if (nb <= 256) return true;
+  if (!with_rows) return L.N > 48;
+  if (L.k == 2 && L.d * elem_size >= 4096) return nb <= 1024;
+  return L.N > 16 && nb <= (L.N > 36 ? 512 : 384);
+}
 hipError_t launch_route(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const float* bias,
                         const RoutingPtrs& R, const RouteBufs& B, void* Xp, const GateExtPtrs* G, hipStream_t s);
 hipError_t launch_routing_stats(const LayerDims& L, const int32_t* topk_idx, int32_t* slot_counts, float* summary,

@@ -1588,11 +1588,9 @@ __global__ __launch_bounds__(PF_THREADS) void permute_fused_kernel(const T* __re
 
 // Batches beyond that: the same over the router's block histograms, whose rows of W = N + 1 counters every block adds up by itself,
 // those of the blocks before its own apart (PERMUTE_HIST_MAX counters, 128 KiB from the L2, at most), so that no scan has to come
-// before.  The first block writes the totals and makes the plans, block 1 + b ranks and copies the tokens of histogram b.
-// 64 experts, d = 2048: routing call of 8192 tokens 34.5 -> 31.1 us (scan 6.5 and scatter 5 -> 8.3), 5003 tokens with their rows copied 10
-// + 15 -> 15.8; 8 experts 16384 tokens 8 + 33 -> 41, 32768 tokens 10 + 73 -> 85.  Beyond PERMUTE_HIST_MAX a block would read more than
-// the scan costs: route_scan_kernel and scatter_kernel.
-constexpr int PH_THREADS = 1024, PH_RUNS = 32, PERMUTE_HIST_MAX = 32768;
+// before.  The first block writes the totals and makes the plans, block 1 + b ranks and copies the tokens of histogram b.  What
+// that costs grows with the square of the batch: see permute_by_hist for the batches that take it.
+constexpr int PH_THREADS = 1024, PH_RUNS = 32;
 template <typename T>
 __global__ __launch_bounds__(PH_THREADS) void permute_hist_kernel(const T* __restrict__ x, int ntok, int d, int N, int top_k,
                                                                   const int32_t* __restrict__ topk_idx,
@@ -2329,7 +2327,7 @@ hipError_t router_typed(const LayerDims& L, const void* xv, const void* Wgv, con
 
 // The permutation (and the forward tile plans when `plan` is given).  Up to MODSE_PERMUTE_FUSED_MAX_T tokens: one launch for all of it, whose
 // blocks count the choices themselves, which grows with the square of the batch; beyond that one over the router's block
-// histograms, and where those are long (PERMUTE_HIST_MAX) a scan over them, then the scatter.
+// histograms (permute_by_hist), or a scan over them, then the scatter.
 template <typename T>
 hipError_t permute_typed(const LayerDims& L, modse_dtype dt, const void* xv, const RoutingPtrs& R, const RouteBufs& B,
                          void* Xpv, const GateExtPtrs* G, const FwdPlanArgs* plan, hipStream_t s) {
@@ -2349,7 +2347,7 @@ hipError_t permute_typed(const LayerDims& L, modse_dtype dt, const void* xv, con
                        plan ? *plan : FwdPlanArgs{}, plan ? 1 : 0);
     return hipGetLastError();
   }
-  if ((int64_t)nb * (L.N + 1) <= PERMUTE_HIST_MAX) {
+  if (permute_by_hist(L, sizeof(T), Xpv != nullptr)) {
     hipLaunchKernelGGL((permute_hist_kernel<T>), dim3(nb + 1), dim3(PH_THREADS), 0, s, x, L.T, L.d, L.N, L.k, R.topk_idx, B.blockhist, nb,
                        R, static_cast<T*>(Xpv), L, dt == MODSE_F32 ? 4 : 2, plan ? *plan : FwdPlanArgs{}, plan ? 1 : 0);
     return hipGetLastError();

@@ -21,6 +21,12 @@ extern "C" void choice(int d, int N, const int* f, int k, int T, int dtype, int 
   const auto c = modse_gemm::gemm_choice(L, (modse_dtype)dtype, epilogue);
   out[0] = c.tile.bm; out[1] = c.tile.bn; out[2] = c.kchunk;
 }
+extern "C" int by_hist(int d, int N, int k, int T, int elem_size, int with_rows) {
+  LayerDims L;
+  std::memset(&L, 0, sizeof L);
+  L.d = d; L.N = N; L.k = k; L.T = T;
+  return permute_by_hist(L, elem_size, with_rows != 0);
+}
 """
 GEMMS = {"up": 2, "down": 0, "dh": 3, "dx": 4, "wgrad": 1}  # the GemmEpilogue that names each of the five products
 Choice = namedtuple("Choice", "bm bn kchunk")               # kchunk: 0 = K not split
@@ -41,3 +47,7 @@ def choice(gemm, d, d_ff, k, T, dtype):
     out = (ctypes.c_int * 3)()
     _lib().choice(d, len(d_ff), (ctypes.c_int * len(d_ff))(*d_ff), k, T, 0 if dtype == "f32" else 1, GEMMS[gemm], out)
     return Choice(*out)
+
+
+def permute_by_hist(d, n_experts, k, T, dtype, with_rows):
+    return bool(_lib().by_hist(d, n_experts, k, T, 4 if dtype == "f32" else 2, int(with_rows)))
