@@ -687,14 +687,19 @@ __global__ __launch_bounds__(RW_THREADS) void router_kernel(const T* __restrict_
 // accumulator, once per 32), so gamma = 1.1 (d / 8 + 64) 2^-23 times |x| |w| covers it (4e-5 of it at d = 2048, 1.5e-3
 // for logits of deviation 0.9: a few of a hundred tokens get more than k candidates).  What the lengths lose of values
 // below 2^-63, whose squares are subnormal, and the matrix pipe of subnormal inputs is less than d 2^-32 of |x| |w| as
-// long as no length exceeds 2^30; a block that meets a longer row or column, an infinity or no number leaves all experts to
-// the second launch.
+// long as no length exceeds 2^30; of a longer row, of one with an infinity or no number, and of all rows if a column is such,
+// all experts are left to the second launch.  The logits of a row of zeros are the bias: its top k + 1 are found here.
 //
 // 64 experts, d = 2048, 8192 tokens: the launches take 12.7 and 11.5 us, the general router 46.9 (float64 matrix pipe); routing
 // call 55.0 -> 35.1.  The first is a chain of latencies (loads, then the sums and bounds of a token: 8 + 4 us), the second
 // half float64 arithmetic, half the same.  Tried on the first without gain: sixteen waves of half as many steps, blocks
 // that start at different columns, loops that are not unrolled (14.7).
+// The second launch's time depends on the candidates.  Routing call at d = 2048, ordinary values / every tenth row zero / W_gate = 0 (all
+// experts of all tokens, see exact_crowd) / the general router: 64 experts 8192 tokens 33 / 39 / 63 / 56 us, 32768 tokens 86 / 96 /
+// 205 / 187; 32 experts 8192 tokens 29 / 35 / 43 / 36.  (With the candidates two at a time whatever their number and rows of zeros
+// like the others 33 / 151 / 174, 86 / 357 / 612, 29 / 101 / 97.)
 constexpr int SC_THREADS = 512, SC_WAVES = SC_THREADS / 64, SC_TOKENS = 32, SC_TRANSPOSE_ROWS = 64;
+constexpr int SC_CROWD = 12;
 constexpr double SC_NEAR = 1.1e-6;  // (the near-tie distance of write_gate, and some)
 constexpr float SC_LARGE = 0x1p60f;  // square of the largest length
 // Columns of W_gate as rows (the second launch reads them): 64 rows of W_gate per block.
@@ -714,14 +719,16 @@ __device__ inline void transpose_block(const bf16_t* __restrict__ W, int d, int 
   const int e = threadIdx.x >> 3, c = (threadIdx.x & 7) * 8;
   if (e < N && c < rows) *reinterpret_cast<bf16x8*>(Wt + (size_t)e * d + k0 + c) = *reinterpret_cast<const bf16x8*>(&tile[e][c]);
 }
-// cand_lo / cand_hi [t * top_k]: bits of token t's candidates.  The first nscreen blocks take 32 tokens each, the others
-// transpose W (rows of N; Wg: the same in rows of NE).  blockhist (may be null) is cleared for the second launch.
+// cand_lo / cand_hi [t * top_k]: bits of token t's candidates.  crowd: a byte per four tokens, whose lowest bits say which have
+// more than SC_CROWD of them.  The first nscreen blocks take 32 tokens each, the others transpose W (rows of N; Wg: the same in
+// rows of NE).  blockhist (may be null) is cleared for the second launch.
 template <int NE>
 __global__ __launch_bounds__(SC_THREADS, 4) void router_screen_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wg,
                                                                    const bf16_t* __restrict__ W, const float* __restrict__ bias,
                                                                    int ntok, int d, int N, int top_k, int nscreen,
                                                                    uint32_t* __restrict__ cand_lo, uint32_t* __restrict__ cand_hi,
-                                                                   bf16_t* __restrict__ Wt, int32_t* __restrict__ blockhist) {
+                                                                   uint8_t* __restrict__ crowd, bf16_t* __restrict__ Wt,
+                                                                   int32_t* __restrict__ blockhist) {
   // A lane reads EPL neighbouring experts of eight matrix rows; column j of group g is expert EPL j + g.  TRADE: it reads
   // twice as many of four rows and trades half of them with lane j ^ 8, which has the next four rows (half as many loads; 64
   // experts 13.8 -> 12.7 us, but with 32 9.7 -> 11.0); column j of group g is then expert 2 EPL (j & 7) + EPL (j >> 3) + g.
@@ -863,15 +870,30 @@ __global__ __launch_bounds__(SC_THREADS, 4) void router_screen_kernel(const bf16
   if (tid < SC_TOKENS + NE) {
 #pragma unroll
     for (int w = 0; w < SC_WAVES; ++w) len += is_x ? s.part.x2[w][tid] : s.part.w2[w][tid - SC_TOKENS];
-    if (!(len <= SC_LARGE)) s_large = 1;
+    if (!is_x && !(len <= SC_LARGE)) s_large = 1;
   }
   __syncthreads();
-  if (is_x) s.part.x2[0][tid] = sqrtf(len);
+  if (is_x) s.part.x2[0][tid] = len <= SC_LARGE ? sqrtf(len) : INFINITY;
   else if (tid < SC_TOKENS + NE) s.part.w2[0][tid - SC_TOKENS] = sqrtf(len);
   __syncthreads();
   // sixteen threads per token, EPL experts each
   const int tl = tid >> 4, t16 = tid & 15, t = t0 + tl;
   auto expert = [&](int i) { return TRADE ? 2 * EPL * (t16 & 7) + EPL * (t16 >> 3) + i : EPL * t16 + i; };
+  const float xlen = s.part.x2[0][tl];
+  const bool large = s_large || xlen == INFINITY;
+  bool zero = false;  // a row of zeros: its logits are the bias, exactly
+  if (xlen == 0.f && !large) {
+    const bf16_t* const row = x + (size_t)min(t, ntok - 1) * d;
+    uint32_t bits = 0;
+#pragma unroll 4
+    for (int c = t16 * 8; c < d; c += 128) {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(row + c);
+      bits |= v[0] | v[1] | v[2] | v[3];
+    }
+#pragma unroll
+    for (int b = 1; b < 16; b <<= 1) bits |= __shfl_xor(bits, b, 64);
+    zero = (bits & 0x7fff7fffu) == 0;
+  }
   const double gamma = 1.1 * (d / 8 + 64) * 0x1p-23;
   double hi[EPL], m1 = -INFINITY, m2 = -INFINITY;  // m1, m2: the largest lower bounds
 #pragma unroll
@@ -880,7 +902,7 @@ __global__ __launch_bounds__(SC_THREADS, 4) void router_screen_kernel(const bf16
     double l = 0.0;
 #pragma unroll
     for (int w = 0; w < SC_WAVES / 2; ++w) l += (double)s.part.l[w][tl][c];
-    const double err = gamma * ((double)(s.part.x2[0][tl] * s.part.w2[0][c]) + d * 0x1p-32) + 1e-12;
+    const double err = zero ? 0.0 : gamma * ((double)(xlen * s.part.w2[0][c]) + d * 0x1p-32) + 1e-12;
     const double b = bias && e < N ? (double)bias[e] : 0.0;
     const double lo = e < N ? (l - err) + b : -INFINITY;  // (rounded as the exact logit will be: a bias may be so large that this matters)
     hi[i] = (l + err) + b;
@@ -902,7 +924,33 @@ __global__ __launch_bounds__(SC_THREADS, 4) void router_screen_kernel(const bf16
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
     const int e = expert(i);
-    if (e < N && (s_large || hi[i] >= least)) mask |= 1ull << e;
+    if (e < N && (large || hi[i] >= least)) mask |= 1ull << e;
+  }
+  if (zero) {  // (most often all experts tie: of exact logits the first top_k + 1 decide)
+    mask = 0;
+#pragma unroll 1
+    for (int r = 0; r <= top_k; ++r) {
+      double best = -INFINITY;
+      int at = N;
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) {
+        const int e = expert(i);
+        if (e < N && !(mask >> e & 1) && hi[i] > best) {
+          best = hi[i];
+          at = e;
+        }
+      }
+#pragma unroll
+      for (int b = 1; b < 16; b <<= 1) {
+        const double o = shfl_xor_f64(best, b);
+        const int oe = __shfl_xor(at, b, 64);
+        if (o > best || (o == best && oe < at)) {
+          best = o;
+          at = oe;
+        }
+      }
+      if (at < N) mask |= 1ull << at;
+    }
   }
 #pragma unroll
   for (int b = 1; b < 16; b <<= 1) {
@@ -913,26 +961,136 @@ __global__ __launch_bounds__(SC_THREADS, 4) void router_screen_kernel(const bf16
     cand_lo[(size_t)t * top_k] = (uint32_t)mask;
     cand_hi[(size_t)t * top_k] = (uint32_t)(mask >> 32);
   }
+  const uint64_t crowded = __ballot(t16 == 0 && t < ntok && __popcll(mask) > SC_CROWD);  // bits 0, 16, 32 and 48
+  if (lane == 0) crowd[blockIdx.x * SC_WAVES + wave] = (crowded | crowded >> 15 | crowded >> 30 | crowded >> 45) & 15;
 }
 
 // The candidates' dot products in float64, top-k and gate: 32 threads per token, two candidates at a time, in ascending
 // order.  topk_idx and topk_w hold the token's candidates when the launch starts.  A sum runs over a thread's columns and then
-// over a fixed tree: it depends on the token and the expert alone.
-constexpr int EX_LANES = 32, EX_TOKENS = 8, EX_THREADS = EX_LANES * EX_TOKENS;
-__global__ __launch_bounds__(EX_THREADS) void router_exact_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wt,
-                                                                  const float* __restrict__ bias, int ntok, int d, int N,
-                                                                  int top_k, int32_t* topk_idx, float* topk_w,
-                                                                  int32_t* __restrict__ blockhist,
-                                                                  int32_t* __restrict__ near_flag) {
+// over a fixed tree.
+// A round of two takes 4.7 us at 8192 tokens, d = 2048, and a token may have all experts for candidates (columns of W_gate that
+// are equal or zero, rows and columns beyond the error bound).  Tokens of more than SC_CROWD candidates therefore take all logits,
+// from the float64 matrix pipe (exact_crowd), which is as long as six or seven rounds.  Which way a token goes depends on its row,
+// W_gate and the bias alone, and so do the bits of its gate weights.
+constexpr int EX_LANES = 32, EX_TOKENS = 8, EX_THREADS = EX_LANES * EX_TOKENS, EX_CROWD_TOKENS = 2 * EX_TOKENS;
+template <int NE>
+struct CrowdLds {
+  double part[2][EX_CROWD_TOKENS][NE + 1];
+};
+// Decides for those of the sixteen tokens from t0 on that are in `crowd` (a byte per four tokens).  Operand lanes as in
+// router_kernel; a wave takes every fourth step of 32 columns.  (The instruction of router_mfma_kernel would fit a block's eight
+// tokens, but then W_gate is read for every eight: 32768 tokens with W_gate = 0, 64 experts 327 us, this 205.)
+template <int NE>
+__device__ inline void exact_crowd(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wt, const float* __restrict__ bias,
+                                   uint32_t crowd, int t0, int ntok, int d, int N, int top_k, int32_t* topk_idx, float* topk_w,
+                                   int32_t* __restrict__ blockhist, int32_t* __restrict__ near_flag, CrowdLds<NE>& s) {
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  constexpr int NG = NE / 16, WAVES = EX_THREADS / 64;
+  static_assert(EX_CROWD_TOKENS == 16 && EX_THREADS == 16 * 16 && WAVES == 4, "sixteen threads per token, two pairs of waves");
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane >> 4, j = lane & 15, nstep = (d / 32 - wave + WAVES - 1) / WAVES;
+  // (tokens and experts that are not there repeat the last; not used)
+  const bf16_t* const row = x + (size_t)min(t0 + j, ntok - 1) * d + q * 8;
+  const bf16_t* col[NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) col[g] = Wt + (size_t)min(g * 16 + j, N - 1) * d + q * 8;
+  f64x4 acc[NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) acc[g] = f64x4{0.0, 0.0, 0.0, 0.0};
+  struct Step {
+    Raw8<bf16_t> x, w[NG];
+  };
+  auto load = [&](Step& st, int i) {
+    const int c = (wave + min(i, nstep - 1) * WAVES) * 32;
+    st.x.load(row + c);
+#pragma unroll
+    for (int g = 0; g < NG; ++g) st.w[g].load(col[g] + c);
+  };
+  if (nstep > 0) {
+    Step cur, nxt;
+    load(cur, 0);
+#pragma unroll 1
+    for (int i = 0; i < nstep; ++i) {
+      load(nxt, i + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int m = 0; m < 8; ++m) {
+        const double a = (double)cur.x.get(m);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)cur.w[g].get(m), acc[g], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      cur = nxt;
+    }
+  }
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {  // waves 2 and 3 hand their sums to waves 0 and 1
+    if ((wave >= 2) == (half == 0)) {
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          double& v = s.part[wave & 1][4 * r + q][g * 16 + j];
+          v = half == 0 ? acc[g][r] : acc[g][r] + v;
+        }
+    }
+    __syncthreads();
+  }
+  const int tl = tid >> 4, t16 = tid & 15, t = t0 + tl;
+  const bool on = (crowd >> (8 * (tl >> 2) + (tl & 3)) & 1) != 0;
+  double l[NG], u[NG];
+#pragma unroll
+  for (int i = 0; i < NG; ++i) {
+    const int e = t16 * NG + i;
+    l[i] = s.part[0][tl][e] + s.part[1][tl][e] + (bias && e < N ? (double)bias[e] : 0.0);
+    u[i] = 0.0;
+  }
+  bool near;
+  const TopPick p = route_token16<NG, false>(l, u, t16, t, on, N, top_k, GateExtPtrs{}, topk_idx, topk_w, near);
+  if (on && t16 == 0) {
+    if (near_flag) {
+      near_flag[t] = near ? 1 : 0;
+    } else {
+      int32_t* const hist = blockhist + (size_t)(t / TPB) * (N + 1);
+      atomicAdd(&hist[p.i1], 1);
+      if (top_k == 2) atomicAdd(&hist[p.i2], 1);
+      if (near) atomicAdd(&hist[N], 1);
+    }
+  }
+}
+template <int NE>
+__global__ __launch_bounds__(EX_THREADS, 4) void router_exact_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wt,
+                                                                     const float* __restrict__ bias,
+                                                                     const uint32_t* __restrict__ crowd_words, int ntok, int d, int N,
+                                                                     int top_k, int32_t* topk_idx, float* topk_w,
+                                                                     int32_t* __restrict__ blockhist,
+                                                                     int32_t* __restrict__ near_flag) {
   __shared__ int s_hist[MODSE_MAX_EXPERTS + 1];
+  __shared__ CrowdLds<NE> s_crowd;
   const int tid = threadIdx.x, tl = tid / EX_LANES, ln = tid % EX_LANES, t = blockIdx.x * EX_TOKENS + tl;
   if (tid <= MODSE_MAX_EXPERTS) s_hist[tid] = 0;
+  // My own tokens' byte pair, and the sixteen tokens whose crowded ones are mine: those of the first half of the grid, which share
+  // out evenly to the CUs (32768 tokens, W_gate = 0: 204 us, as tasks of every other block 349).
+  const uint32_t crowd = crowd_words[blockIdx.x >> 1] >> (blockIdx.x & 1) * 16;
+  const uint32_t task = blockIdx.x < (gridDim.x + 1) / 2 ? crowd_words[blockIdx.x] : 0;
+  const size_t at = (size_t)min(t, ntok - 1) * top_k;
+  uint64_t mask = ((uint64_t)__float_as_uint(topk_w[at]) << 32) | (uint32_t)topk_idx[at];  // (of a crowded token: anything)
   __syncthreads();
-  if (t < ntok) {
-    const size_t at = (size_t)t * top_k;
-    uint64_t mask = ((uint64_t)__float_as_uint(topk_w[at]) << 32) | (uint32_t)topk_idx[at];
+  if (task)
+    exact_crowd<NE>(x, Wt, bias, task, blockIdx.x * EX_CROWD_TOKENS, ntok, d, N, top_k, topk_idx, topk_w, blockhist, near_flag, s_crowd);
+  if (t < ntok && !(crowd >> (8 * (tl >> 2) + (tl & 3)) & 1)) {
     const bf16_t* const row = x + (size_t)t * d;
     TopPick p = {-INFINITY, -INFINITY, -INFINITY, -1, -1};
+    auto consider = [&](double dot, int e) {
+      const double l = dot + (bias ? (double)bias[e] : 0.0);
+      if (l > p.m1) {
+        p.m3 = p.m2; p.m2 = p.m1; p.i2 = p.i1; p.m1 = l; p.i1 = e;
+      } else if (l > p.m2) {
+        p.m3 = p.m2; p.m2 = l; p.i2 = e;
+      } else if (l > p.m3) {
+        p.m3 = l;
+      }
+    };
     while (mask) {
       int e[2];
       e[0] = __builtin_ctzll(mask);
@@ -972,18 +1130,8 @@ __global__ __launch_bounds__(EX_THREADS) void router_exact_kernel(const bf16_t* 
         sum[0] += shfl_xor_f64(sum[0], b);
         sum[1] += shfl_xor_f64(sum[1], b);
       }
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        if (c == 1 && !two) break;
-        const double l = sum[c] + (bias ? (double)bias[e[c]] : 0.0);
-        if (l > p.m1) {
-          p.m3 = p.m2; p.m2 = p.m1; p.i2 = p.i1; p.m1 = l; p.i1 = e[c];
-        } else if (l > p.m2) {
-          p.m3 = p.m2; p.m2 = l; p.i2 = e[c];
-        } else if (l > p.m3) {
-          p.m3 = l;
-        }
-      }
+      consider(sum[0], e[0]);
+      if (two) consider(sum[1], e[1]);
     }
     if (p.i1 < 0) p.i1 = 0;                                  // every logit is -inf
     if (p.i2 < 0 || p.i2 == p.i1) p.i2 = p.i1 == 0 ? 1 : 0;  // no second one above -inf (see pick_top)
@@ -2262,16 +2410,18 @@ hipError_t router_typed(const LayerDims& L, const void* xv, const void* Wgv, con
       uint32_t* const lo = reinterpret_cast<uint32_t*>(R.topk_idx);
       uint32_t* const hi = reinterpret_cast<uint32_t*>(R.topk_w);
       bf16_t* const wt = static_cast<bf16_t*>(B.wt);
+      uint8_t* const crowd = reinterpret_cast<uint8_t*>(R.src_of);  // (written by the permutation only; T k words for T / 4 bytes)
       int32_t* const hist = router_leaves_flags(L, G) ? nullptr : B.blockhist;
       if (NE == 32)
         hipLaunchKernelGGL((router_screen_kernel<32>), grid, dim3(SC_THREADS), 0, s, x, Wg, static_cast<const T*>(Wgv), bias, L.T, L.d,
-                           L.N, L.k, nscreen, lo, hi, wt, hist);
+                           L.N, L.k, nscreen, lo, hi, crowd, wt, hist);
       else
         hipLaunchKernelGGL((router_screen_kernel<64>), grid, dim3(SC_THREADS), 0, s, x, Wg, static_cast<const T*>(Wgv), bias, L.T, L.d,
-                           L.N, L.k, nscreen, lo, hi, wt, hist);
+                           L.N, L.k, nscreen, lo, hi, crowd, wt, hist);
       if ((e = hipGetLastError()) != hipSuccess) return e;
-      hipLaunchKernelGGL(router_exact_kernel, dim3((L.T + EX_TOKENS - 1) / EX_TOKENS), dim3(EX_THREADS), 0, s, x, wt, bias, L.T, L.d,
-                         L.N, L.k, R.topk_idx, R.topk_w, hist, hist ? nullptr : B.near_flag);
+      hipLaunchKernelGGL((NE == 32 ? router_exact_kernel<32> : router_exact_kernel<64>), dim3((L.T + EX_TOKENS - 1) / EX_TOKENS),
+                         dim3(EX_THREADS), 0, s, x, wt, bias, reinterpret_cast<const uint32_t*>(crowd), L.T, L.d, L.N, L.k, R.topk_idx, R.topk_w, hist,
+                         hist ? nullptr : B.near_flag);
     }
     e = hipGetLastError();
   } else if (kind == ROUTER_STREAM && router_on_mfma(L)) {
