@@ -87,7 +87,10 @@ typedef struct {
  * call's T, so one workspace, sized for a program's largest batch, does for all.
  * A smaller one is refused, unless all that it lacks is room for the partial sums
  * of a product that small batches split: the product is then not split, which
- * is slower and adds in another order. */
+ * is slower and adds in another order.  modse_route refuses only what does not
+ * hold its scratch; a bfloat16 call of more than 16 experts that finds no room
+ * behind it for W_gate's n_experts * d_model elements may take a slower router
+ * that adds in another order, which can change the last bit of a gate weight. */
 #define MODSE_WS_FWD 0
 #define MODSE_WS_BWD 1
 #define MODSE_WS_FWD_SAVED 2
@@ -110,8 +113,9 @@ modse_status modse_route(const modse_desc* desc, int64_t T, const void* x, const
 /* modse_route for callers that cannot allocate or pass a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * The router's scratch (per-block histograms, near-tie flags) is a device
- * array inside the library, MODSE_ROUTE_STATIC_SCRATCH_BYTES per GPU, held
- * until the process ends; the call allocates and frees nothing.  Same
+ * array inside the library, MODSE_ROUTE_STATIC_SCRATCH_BYTES per GPU and 4 MiB
+ * for W_gate's columns, held until the process ends; the call allocates and
+ * frees nothing.  Same
  * arguments, results and checks as modse_route otherwise.  The need is about
  * T * (4 + (n_experts + 1) / 8) bytes, so the array serves 65536 tokens at
  * any expert count that is a power of two (other counts also keep a padded

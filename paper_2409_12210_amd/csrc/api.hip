@@ -368,7 +368,8 @@ modse_status modse_route_ext(const modse_desc* desc, int64_t T, const void* x, c
 // not allocate): the router's scratch -- per-block histograms and near-tie flags -- lives in a device array
 // of this library.  Every GPU holds its own copy at its own address; the name below is only the host-side
 // handle of the symbol, the address comes from hipGetSymbolAddress, once per device.
-static __device__ __align__(256) unsigned char g_route_scratch[MODSE_ROUTE_STATIC_SCRATCH_BYTES];
+// Behind the scratch: W_gate's columns.
+static __device__ __align__(256) unsigned char g_route_scratch[MODSE_ROUTE_STATIC_SCRATCH_BYTES + ROUTE_WT_MAX];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -398,7 +399,7 @@ modse_status modse_route_static(const modse_desc* desc, int64_t T, const void* x
   const RoutingPtrs R = {out->topk_idx, out->topk_w, out->counts, out->offsets, out->row_of, out->src_of, out->near_tie_count};
   // every word of the scratch that a kernel reads has been written by an earlier kernel of this call
   HIP_TRY(launch_route(L, desc->dtype, x, W_gate, logit_bias, R,
-                       route_bufs(scratch, w, wt_behind(scratch, w, MODSE_ROUTE_STATIC_SCRATCH_BYTES, L, desc->dtype)), nullptr, nullptr,
+                       route_bufs(scratch, w, scratch + MODSE_ROUTE_STATIC_SCRATCH_BYTES), nullptr, nullptr,
                        static_cast<hipStream_t>(hip_stream)));
   return MODSE_OK;
 }

@@ -144,6 +144,9 @@ inline size_t route_wpad_bytes(const LayerDims& L, size_t elem_size) {
   return NE == L.N ? 0 : 2 * (size_t)L.d * NE * elem_size;
 }
 inline size_t route_wt_bytes(const LayerDims& L, size_t elem_size) { return (size_t)L.N * L.d * elem_size; }
+// W_gate's columns of a layer that takes such a router are no longer (64 experts: d = 32768): modse_route_static keeps as much
+// room, so that it takes the router of the calls with a workspace
+constexpr size_t ROUTE_WT_MAX = (size_t)4 << 20;
 // launch_route = launch_router (logits, top-k, gate) + launch_permute (histogram, scan, stable scatter; Xp may
 // be null).
 hipError_t launch_router(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const float* bias,

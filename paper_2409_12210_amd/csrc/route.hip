@@ -2344,7 +2344,8 @@ bool router_leaves_flags(const LayerDims& L, const GateExtPtrs* G) { return !G &
 enum RouterKind { ROUTER_TOKEN, ROUTER_STREAM, ROUTER_SCREEN, ROUTER_BLOCK };
 RouterKind router_kind(const LayerDims& L, modse_dtype dt, const GateExtPtrs* G, const RouteBufs& B) {
   if (G) return ROUTER_BLOCK;
-  if (dt == MODSE_BF16 && L.N > 16 && L.T > (L.N > 32 ? 1535 : 2048) && B.wt) return ROUTER_SCREEN;
+  if (dt == MODSE_BF16 && L.N > 16 && L.T > (L.N > 32 ? 1535 : 2048) && B.wt && route_wt_bytes(L, 2) <= ROUTE_WT_MAX)
+    return ROUTER_SCREEN;
   if (L.T <= ROUTER_TOKEN_MAX_T) return ROUTER_TOKEN;
   if (L.N <= 16 && (size_t)(L.d / 8) * rs_group_bytes(padded_experts(L.N), 4) <= (size_t)RS_W_BYTES) return ROUTER_STREAM;
   return ROUTER_BLOCK;
