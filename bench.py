@@ -203,8 +203,10 @@ def gemm_summary(run, st, ms_per_step):
            "fwd_grouped_gemm_tflops": tf(up + down, st["up"] + st["down"])}
     out["fwd_grouped_gemm_frac_of_bf16_peak"] = round(out["fwd_grouped_gemm_tflops"] / PEAK_BF16_TFLOPS, 4)
     if run.bwd:
-        out["bwd_dgrad_tflops"] = tf(up + down, st["bwd_dgrad"])
-        out["bwd_wgrad_tflops"] = tf(up + down, st["bwd_wgrad"])
+        joined = st["bwd_wgrad"] == 0  # layers of small tiles: one launch makes dX and the weight gradients
+        out["bwd_dgrad_tflops"] = None if joined else tf(up + down, st["bwd_dgrad"])
+        out["bwd_wgrad_tflops"] = None if joined else tf(up + down, st["bwd_wgrad"])
+        out["bwd_grouped_gemm_tflops"] = tf(2 * (up + down), st["bwd_dgrad"] + st["bwd_wgrad"])
         gemm_ms = st["up"] + st["down"] + st["bwd_dgrad"] + st["bwd_wgrad"]
         out["all_grouped_gemm_tflops"] = tf(3 * (up + down), gemm_ms)
         out["all_grouped_gemm_frac_of_bf16_peak"] = round(out["all_grouped_gemm_tflops"] / PEAK_BF16_TFLOPS, 4)
@@ -296,6 +298,13 @@ def main():
                     "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(gbs / PEAK_HBM_GBS, 4),
                     "traffic": None, "bytes_per_launch": wbytes, "avg_launch_ms": round(st["up"] + st["down"], 4),
                     "whole_layer_gbs": round(wbytes / (ms_per_step * 1e-3) / 1e9, 1)}
+    elif run.bwd and st["bwd_wgrad"] == 0:
+        fl = 2 * (up_flops + down_flops)
+        tfl = fl / (st["bwd_dgrad"] * 1e-3) / 1e12
+        roofline = {"bound": "mfma", "kernel": "dH, and the launch of dX and the weight gradients (layers of small tiles)",
+                    "achieved": round(tfl, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
+                    "frac": round(tfl / PEAK_BF16_TFLOPS, 4), "traffic": None, "flops_per_launch": fl,
+                    "avg_launch_ms": round(st["bwd_dgrad"], 4)}
     elif run.bwd:
         # the launch that takes the largest share of a training step: dW1, dW3 and dW2 of all experts in one grid
         fl = up_flops + down_flops   # 6 d sum_e n_e f_e: dW1 and dW3 (2 d n f each) and dW2 (2 d n f) per expert

@@ -219,8 +219,9 @@ enum {
   MODSE_STAGE_COMBINE = 4,  /* gate-weighted unpermute */
   MODSE_STAGE_BWD_PREP = 5, /* dO = g dY, d gate = <dY, O>, tile plans */
   MODSE_STAGE_BWD_DGRAD = 6,/* dH (+SwiGLU backward) and dX_permuted GEMMs */
-  MODSE_STAGE_BWD_WGRAD = 7,/* dW1, dW3, dW2 GEMMs; in layers of small tiles, where
-                               one launch makes both, dX_permuted as well */
+  MODSE_STAGE_BWD_WGRAD = 7,/* dW1, dW3, dW2 GEMMs; layers of small tiles, where one
+                               launch makes them and dX_permuted, count them as
+                               BWD_DGRAD, and this stage reads 0 */
   MODSE_STAGE_BWD_ROUTER = 8,/* dX gather, d logits, dW_gate (whose shares may be
                                 made beside dX_permuted) */
   MODSE_N_STAGES = 9

@@ -569,7 +569,6 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   const bool wg_beside = wgrad_beside_dx(dt, pa.dx_tile, pa.wg_tile);
   // (of a plain gate: the gradient of the logits is there)
   const bool dwg_done = dwg_beside_dx(dt, pa.dx_tile, pa.wg_tile) && bwd_gate_is_plain(L, ext ? &G : nullptr, aux_grad);
-  if (wg_beside) stamp.mark(MODSE_STAGE_BWD_DGRAD);  // (dX counts with the weight gradients)
   if (dwg_beside_dx(dt, pa.dx_tile, pa.wg_tile)) {
     const DwgArgs dwg = dwg_args(L, x, rb, 1);
     HIP_TRY(launch_dx(dt, pa.dx_tile, pa.dx_kchunk != 0, pa.dx, n_dx, dx_tiles, dx_option, wg_beside ? pa.wg : nullptr, 3 * L.N, wg_tiles,
@@ -579,11 +578,11 @@ modse_status modse_layer_bwd_ext(const modse_desc* desc, int64_t T, const void* 
   } else {
     HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_DUALK, pa.dx_tile, pa.dx, n_dx, 0, dx_option, dx_tiles, s));
   }
+  stamp.mark(MODSE_STAGE_BWD_DGRAD);  // (and the weight gradients, where they are in that launch)
   if (!wg_beside) {
-    stamp.mark(MODSE_STAGE_BWD_DGRAD);
     HIP_TRY(launch_grouped_gemm(dt, EPI_STORE_F32, pa.wg_tile, pa.wg, 3 * L.N, accumulate, wg_option, wg_tiles, s));
+    stamp.mark(MODSE_STAGE_BWD_WGRAD);
   }
-  stamp.mark(MODSE_STAGE_BWD_WGRAD);
 
   const DxRows rows = {pa.dXp, pa.dXpart, pa.dx_kchunk};
   HIP_TRY(launch_bwd_router(L, dt, x, W_gate, rows, dg, R, ext ? &G : nullptr, aux_grad, rb, dX, dW_gate, dW_noise,
