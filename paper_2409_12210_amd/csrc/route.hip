@@ -881,19 +881,6 @@ __global__ __launch_bounds__(SC_THREADS, 4) void router_screen_kernel(const bf16
   auto expert = [&](int i) { return TRADE ? 2 * EPL * (t16 & 7) + EPL * (t16 >> 3) + i : EPL * t16 + i; };
   const float xlen = s.part.x2[0][tl];
   const bool large = s_large || xlen == INFINITY;
-  bool zero = false;  // a row of zeros: its logits are the bias, exactly
-  if (xlen == 0.f && !large) {
-    const bf16_t* const row = x + (size_t)min(t, ntok - 1) * d;
-    uint32_t bits = 0;
-#pragma unroll 4
-    for (int c = t16 * 8; c < d; c += 128) {
-      const u32x4 v = *reinterpret_cast<const u32x4*>(row + c);
-      bits |= v[0] | v[1] | v[2] | v[3];
-    }
-#pragma unroll
-    for (int b = 1; b < 16; b <<= 1) bits |= __shfl_xor(bits, b, 64);
-    zero = (bits & 0x7fff7fffu) == 0;
-  }
   const double gamma = 1.1 * (d / 8 + 64) * 0x1p-23;
   double hi[EPL], m1 = -INFINITY, m2 = -INFINITY;  // m1, m2: the largest lower bounds
 #pragma unroll
@@ -902,10 +889,15 @@ __global__ __launch_bounds__(SC_THREADS, 4) void router_screen_kernel(const bf16
     double l = 0.0;
 #pragma unroll
     for (int w = 0; w < SC_WAVES / 2; ++w) l += (double)s.part.l[w][tl][c];
-    const double err = zero ? 0.0 : gamma * ((double)(xlen * s.part.w2[0][c]) + d * 0x1p-32) + 1e-12;
-    const double b = bias && e < N ? (double)bias[e] : 0.0;
-    const double lo = e < N ? (l - err) + b : -INFINITY;  // (rounded as the exact logit will be: a bias may be so large that this matters)
-    hi[i] = (l + err) + b;
+    const double err = gamma * ((double)(xlen * s.part.w2[0][c]) + d * 0x1p-32) + 1e-12;
+    double lo = l - err;
+    hi[i] = l + err;
+    if (bias) {  // (rounded as the exact logit will be: a bias may be so large that this matters)
+      const double b = e < N ? (double)bias[e] : 0.0;
+      lo += b;
+      hi[i] += b;
+    }
+    if (e >= N) lo = -INFINITY;
     if (lo > m1) {
       m2 = m1;
       m1 = lo;
@@ -926,30 +918,43 @@ __global__ __launch_bounds__(SC_THREADS, 4) void router_screen_kernel(const bf16
     const int e = expert(i);
     if (e < N && (large || hi[i] >= least)) mask |= 1ull << e;
   }
-  if (zero) {  // (most often all experts tie: of exact logits the first top_k + 1 decide)
-    mask = 0;
+  if (xlen == 0.f && !large) {  // a row of zeros, or of values whose squares are
+    const bf16_t* const row = x + (size_t)min(t, ntok - 1) * d;
+    uint32_t bits = 0;
+#pragma unroll 4
+    for (int c = t16 * 8; c < d; c += 128) {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(row + c);
+      bits |= v[0] | v[1] | v[2] | v[3];
+    }
+#pragma unroll
+    for (int b = 1; b < 16; b <<= 1) bits |= __shfl_xor(bits, b, 64);
+    if ((bits & 0x7fff7fffu) == 0) {  // its logits are the bias: the first top_k + 1 decide (most often all experts tie)
+      mask = 0;
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) hi[i] = bias && expert(i) < N ? (double)bias[expert(i)] : 0.0;
 #pragma unroll 1
-    for (int r = 0; r <= top_k; ++r) {
-      double best = -INFINITY;
-      int at = N;
+      for (int r = 0; r <= top_k; ++r) {
+        double best = -INFINITY;
+        int at = N;
 #pragma unroll
-      for (int i = 0; i < EPL; ++i) {
-        const int e = expert(i);
-        if (e < N && !(mask >> e & 1) && hi[i] > best) {
-          best = hi[i];
-          at = e;
+        for (int i = 0; i < EPL; ++i) {
+          const int e = expert(i);
+          if (e < N && !(mask >> e & 1) && hi[i] > best) {
+            best = hi[i];
+            at = e;
+          }
         }
-      }
 #pragma unroll
-      for (int b = 1; b < 16; b <<= 1) {
-        const double o = shfl_xor_f64(best, b);
-        const int oe = __shfl_xor(at, b, 64);
-        if (o > best || (o == best && oe < at)) {
-          best = o;
-          at = oe;
+        for (int b = 1; b < 16; b <<= 1) {
+          const double o = shfl_xor_f64(best, b);
+          const int oe = __shfl_xor(at, b, 64);
+          if (o > best || (o == best && oe < at)) {
+            best = o;
+            at = oe;
+          }
         }
+        if (at < N) mask |= 1ull << at;
       }
-      if (at < N) mask |= 1ull << at;
     }
   }
 #pragma unroll
