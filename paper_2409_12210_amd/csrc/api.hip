@@ -442,8 +442,9 @@ modse_status modse_layer_fwd_ext(const modse_desc* desc, int64_t T, const void* 
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   char* wsb = static_cast<char*>(ws);
   const RoutingPtrs R = routing_from(routing_out, wsb, w);
-  // (W_gate's columns lie where the experts' outputs will: those are T k rows of d, written long after the routing)
-  void* const wt = (int64_t)L.T * L.k >= L.N ? (saved ? static_cast<char*>(saved) + saved_layout(L, dt).O : wsb + w.O) : nullptr;
+  // (W_gate's N columns lie where the experts' outputs will: those are T k rows of d, more than N where a router wants
+  // the columns, and written long after the routing)
+  void* const wt = saved ? static_cast<char*>(saved) + saved_layout(L, dt).O : wsb + w.O;
   const RouteBufs RB = route_bufs(wsb, w.route, wt);
   Stamp stamp(0, s);
 

@@ -1,5 +1,5 @@
 // Weight gradient of the router, dW_gate = x^T dl (and dW_noise = x^T du): the shares of the chunks of tokens.  A header because
-// float32 layers of small tiles take it in the launch of their weight gradients (gemm_block.h).
+// layers of small tiles take it in the launch of dX (gemm_block.h).
 #pragma once
 #include <algorithm>
 

@@ -205,7 +205,7 @@ struct DxRows {
 };
 // neither optional part of the gate takes part in the backward pass: launch_bwd_prep leaves the gradient of the logits
 bool bwd_gate_is_plain(const LayerDims& L, const GateExtPtrs* G, float aux_grad);
-// dwg_done: the shares of the router's weight gradient are there (launch_dx_wgrad)
+// dwg_done: the shares of the router's weight gradient are there (launch_dx)
 hipError_t launch_bwd_router(const LayerDims& L, modse_dtype dt, const void* x, const void* W_gate, const DxRows& rows,
                              const float* dg, const RoutingPtrs& R, const GateExtPtrs* G, float aux_grad,
                              const BwdRouterBufs& B, void* dX, float* dW_gate, float* dW_noise, float* dgamma,

@@ -86,7 +86,7 @@ hipError_t launch_block(int epilogue, int layout, TileShape t, const GemmPlan* p
     case EPI_SWIGLU_BWD: return run_block_tile<T, EPI_SWIGLU_BWD, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
     case EPI_STORE_DUALK:
       if constexpr (std::is_same_v<T, float>) return run_block_tile<T, EPI_STORE_DUALK, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
-        else return hipErrorInvalidValue;  // (launch_dx)
+      else return hipErrorInvalidValue;  // (launch_dx)
     case EPI_STORE_F32:
       if (layout == LAYOUT_B_KN) {
         if constexpr (std::is_same_v<T, float>) return run_block_tile<T, EPI_STORE_F32, LAYOUT_B_KN>(t, plan, n_prob, accumulate, option, max_tiles, s);
@@ -118,6 +118,8 @@ hipError_t launch_grouped_gemm(modse_dtype dt, int epilogue, TileShape t, const 
   return hipErrorInvalidValue;
 }
 
+// Wherever the tiles allow it: in none of 58 layers drawn over the sizes that have such tiles was one launch slower by more than
+// the runs differ (figures at the kernels, gemm_block.h).
 bool dwg_beside_dx(modse_dtype dt, TileShape dx_tile, TileShape wg_tile) {
   return dt == MODSE_F32 ? dx_tile.bm <= 64 && wg_tile.bm == 64 : dx_tile.bm <= 128;
 }

@@ -7,8 +7,8 @@
 // LDS: five panels of 32 KiB.  A panel holds 64 K-elements of one operand for the whole tile: 256 rows of
 // 128 bytes for a K-contiguous operand (the 16-byte chunk index of a row is XOR-ed with ((row >> 1) & 7):
 // conflict-free ds_read_b128 on the 64 banks of gfx950), or 64 K-rows of 512 bytes for an operand stored
-// [K, X] (16-byte chunk index XOR-ed with 4 * (k & 3), fragments through ds_read_b64_tr_b16).  Step g uses
-// panel 2g (A) and 2g+1 (B); panel i lives in slot i mod 5, so a panel can be refilled as soon as the step
+// [K, X] (16-byte chunk index XOR-ed with 4 * (k & 3) + 2 * ((k >> 3) & 1), fragments through ds_read_b64_tr_b16).
+// Step g uses panel 2g (A) and 2g+1 (B); panel i lives in slot i mod 5, so a panel can be refilled as soon as the step
 // two (B) or three (A) steps back has been read.
 //
 // Ping-pong: the two waves of a SIMD (wave w and w + 4) run one phase apart.  Every step has four phases
@@ -31,9 +31,11 @@
 // first operand.  The B tile is fed as first operand, so those 4 values are consecutive columns of C.
 // The chip is limited by power under these products, and this instruction takes less of it than 32x32x16, which reads
 // and writes an accumulator for every 16 K instead of every 32: with operands in registers 2070 TFLOP/s against 1810 over
-// 6 ms, with all of them read from LDS 1680 against 1535; forward pass of 16384 tokens, d = 2048, eight experts of mean
-// width 5632 1869 -> 1793 us, training step of 32768 tokens 11.23 -> 10.77 ms.  For the same reason the blocks of a wave are
-// walked to and fro, so that from one MFMA to the next only one operand changes: 1793 -> 1731 us and 10.77 -> 10.45 ms.
+// 6 ms, with all of them read from LDS 1680 against 1535.  In the forward pass of 16384 tokens, d = 2048, eight experts of
+// mean width 5632, the matrix pipes are busy for the same 1.53e9 (up) and 0.76e9 (down) cycles with either, at a clock of 1.62 and
+// 1.59 GHz with 32x32x16 and of 1.77 and 1.78 with this: 1838 -> 1760 us, training step of 32768 tokens 11.08 -> 10.63 ms.  For
+// the same reason the blocks of a wave are walked to and fro, so that from one MFMA to the next only one operand changes: 1760 ->
+// 1746 us and 10.63 -> 10.55 ms.
 // (The tiles of gemm_block.h wait for their loads, not for power: the instruction changed nothing there.)
 #pragma once
 #include "gemm_bf16_util.h"

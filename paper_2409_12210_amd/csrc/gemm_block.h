@@ -29,7 +29,8 @@
 //
 // float32 is bound by the matrix pipe (157 TFLOP/s; a library product of 8192^3 reaches 153).  Measured in place of
 // vector-FMA tiles of 64 x 64 x 16: the five GEMMs of a training step at d = 1024, 4096 tokens, 8 experts of mean width
-// 2816 take 3.9 ms instead of 7.0 (60 -> 109 TFLOP/s); at d = 256, 512 tokens 46 us instead of 174.
+// 2816 took 3.9 ms instead of 7.0 (60 -> 109 TFLOP/s; 3.4 by now, 122 over the whole pass); at d = 256, 512 tokens 46 us
+// instead of 174.
 #pragma once
 #include "bwd_dwg.h"
 #include "gemm_bf16.h"
@@ -529,7 +530,8 @@ __global__ __launch_bounds__(256, 4) void gg_f32_small_kernel(const GemmPlan* __
 // What follows dH in one launch: the first n_dwg workgroups take the router's weight gradient (of a plain gate), the next `dx_blocks` dX (tiles
 // of DX_TILE), the others the weight gradients.  None needs another, and in a layer of few tiles each leaves most of the chip
 // idle and takes as long as its chain of latencies: 512 tokens, d = 256 6.8 + 10.9 + 9.6 us in launches of their own, 14.6 in
-// one; training pass 72.3 -> 59.6 us.  (The router's tokens come in batches of two: 128 registers.)
+// one; training pass 72.3 -> 59.6 us.  Backward passes of 24 drawn layers, 38 to 11597 tokens, d = 128 to 1024: 0.996 to 1.47 times
+// as fast, on average 1.21.  (The router's tokens come in batches of two: 128 registers.)
 template <int DX_TILE, int DX_EPI>
 __global__ __launch_bounds__(256, 4) void gg_f32_dx_wgrad_kernel(DwgArgs dwg, int n_dwg, const GemmPlan* __restrict__ dx, int n_dx,
                                                                  int dx_blocks, const GemmPlan* __restrict__ wg, int n_wg,
@@ -567,9 +569,10 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 2) void gg_bf16_skinny_kerne
   gg_block<bf16_t, BM, BN, NB, WAVES_M, WAVES_N, NSLOT, EPI, LAYOUT>(plan, n_prob, accumulate, option, blockIdx.x, ring);
 }
 // The same for bf16, dX in tiles of 64 or 128 rows: the n_dwg workgroups behind its `dx_blocks` take the router's weight gradient (of a
-// plain gate; two micro-batches of 1021 tokens, d = 2048, 1861 -> 1846 us with that alone), and if the weight gradients have
-// 128-row tiles, too, they follow: training passes at d = 1024, eight experts of mean width 1024, 512 / 2048 tokens 113 -> 108 / 207 ->
-// 191 us; d = 2048, four experts of 1408, 1024 tokens 243 -> 212.
+// plain gate; by itself worth a launch, which at two micro-batches of 1021 tokens is less than the runs differ), and if the weight
+// gradients have 128-row tiles, too, they follow: training passes at d = 1024, eight experts of mean width 1024, 512 / 2048 tokens
+// 113 -> 108 / 207 -> 191 us; d = 2048, four experts of 1408, 1024 tokens 243 -> 212.  Backward passes of 34 drawn layers with
+// such tiles, 33 to 14313 tokens, d = 512 to 4096: 1.02 to 1.30 times as fast, on average 1.10.
 template <int BM, int EPI>
 __global__ __launch_bounds__(256, 2) void gg_bf16_dx_kernel(const GemmPlan* __restrict__ dx, int n_dx, int dx_option, int dx_blocks,
                                                             DwgArgs dwg, int n_dwg, const GemmPlan* __restrict__ wg, int n_wg,

@@ -2337,6 +2337,9 @@ hipError_t run_router(const LayerDims& L, const T* x, const T* Wg, const float* 
   return hipGetLastError();
 }
 
+// whether the router (token-wise or screened) leaves flags and no block histograms
+bool router_leaves_flags(const LayerDims& L, const GateExtPtrs* G) { return !G && L.T <= ROUTER_TOKEN_MAX_T; }
+enum RouterKind { ROUTER_TOKEN, ROUTER_STREAM, ROUTER_SCREEN, ROUTER_BLOCK };
 // Which router a layer takes.  Plain gate, small and medium batches: one block per token (or four) keeps the chip busy
 // where 32-token blocks would leave most CUs idle.  Larger plain batches of up to 16 experts: router_stream_kernel (or
 // its matrix-instruction form) when W_gate fits its LDS area.  Otherwise, and with the optional gate parts,
@@ -2344,9 +2347,6 @@ hipError_t run_router(const LayerDims& L, const T* x, const T* Wg, const float* 
 // launches beat the token router's rounds (four tokens per block): routing call at d = 2048, token router / screened, 64
 // experts 1024 tokens 19.9 / 21.4 us, 1536 27.8 / 21.8, 4096 47.6 / 28.1; 32 experts 1536 20.6 / 20.5, 3072 26.4 / 22.3 (d =
 // 1024, 2048 tokens: 19.8 / 20.1 and 15.5 / 18.0).
-// whether the router leaves flags and no block histograms
-bool router_leaves_flags(const LayerDims& L, const GateExtPtrs* G) { return !G && L.T <= ROUTER_TOKEN_MAX_T; }
-enum RouterKind { ROUTER_TOKEN, ROUTER_STREAM, ROUTER_SCREEN, ROUTER_BLOCK };
 RouterKind router_kind(const LayerDims& L, modse_dtype dt, const GateExtPtrs* G, const RouteBufs& B) {
   if (G) return ROUTER_BLOCK;
   if (dt == MODSE_BF16 && L.N > 16 && L.T > (L.N > 32 ? 1535 : 2048) && B.wt && route_wt_bytes(L, 2) <= ROUTE_WT_MAX)
@@ -2362,7 +2362,7 @@ bool router_on_mfma(const LayerDims& L) {
   return L.N <= 16 && L.d % 256 == 0 && (size_t)L.d * NE * 8 <= (size_t)rm_w_bytes(NE);
 }
 
-// logits, top-k, gate (and, except for ROUTER_TOKEN, the block histograms)
+// logits, top-k, gate (and the block histograms, or the flags of router_leaves_flags)
 template <typename T>
 hipError_t router_typed(const LayerDims& L, const void* xv, const void* Wgv, const float* bias, const RoutingPtrs& R,
                         const RouteBufs& B, const GateExtPtrs* G, hipStream_t s) {
